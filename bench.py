@@ -423,7 +423,7 @@ def main():
     Q, K, V = synth.make_qkv(w, device=dev)
     res, pipe = measure(w, args.sparsity, Q, K, V, args.steps, args.warmup,
                         dense_reps=0 if args.no_dense else 1)
-    attn_ms = res["kernel_avg_ms"].get("attn_mfma_kernel", 0.0) or res["kernel_avg_ms"].get("attn_simple_kernel", 0.0)
+    attn_ms = res["kernel_avg_ms"].get("attn_mfma_kernel", 0.0) or res["kernel_avg_ms"].get("attn_f32_kernel", 0.0)
     achieved = res["executed_flops"] / (attn_ms * 1e-3) / 1e12 if attn_ms else None
     traffic = profiled_traffic(w.name, args.sparsity)
 

@@ -34,7 +34,7 @@ std::vector<ProfRec> g_prof_recs;
 const char* const kKernelNames[K_COUNT] = {
     "norm_tile_sort_kernel", "merge_pass_kernel", "block_stats_kernel",
     "block_scores_kernel", "row_select_kernel", "gather_kernels", "attn_mfma_kernel",
-    "attn_simple_kernel", "block_mass_kernel", "diagnostic_small_kernels", "scores_select_kernel"};
+    "attn_f32_kernel", "block_mass_kernel", "diagnostic_small_kernels", "scores_select_kernel", "attn_combine_kernel"};
 }  // namespace
 
 ProfScope::ProfScope(int id, hipStream_t st) : slot_(-1), st_(st) {
@@ -224,7 +224,7 @@ basa_status attn_common(const basa_tensor* q, const basa_tensor* k, const basa_t
     if (reinterpret_cast<uintptr_t>(ws) % 256) { set_error("workspace must be 256-byte aligned"); return BASA_ERR_INVALID_ARG; }
     return launch_attn_mfma(a, st);
   }
-  return launch_attn_simple(a, st);
+  return launch_attn_f32(a, st);          // (a workspace it does not get costs speed, not the call)
 }
 
 }  // namespace
@@ -248,7 +248,7 @@ size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, co
 
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p) {
   if (check_qk(q, k) != BASA_OK || check_params(p, false) != BASA_OK) return 0;
-  if (!use_mfma(q)) return 256;   // the fp32 path needs none; keep the size non-zero for callers
+  if (!use_mfma(q)) return attn_f32_workspace_bytes(q->batch * q->heads, q->L, q->d);
   return attn_mfma_workspace_bytes(q->batch * q->heads, k->batch * k->heads, q->L, k->L, q->d, p->block);
 }
 

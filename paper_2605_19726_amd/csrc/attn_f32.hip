@@ -1,0 +1,421 @@
+// Block-sparse attention for f32 tensors on the fp32 matrix instruction (Sec. 2; Eq. 1; Alg. 1
+// step 12): products, accumulation and softmax state in fp32 throughout.
+//
+// Bound: the matrix cores.  v_mfma_f32_32x32x2_f32 does 4096 flop in 64 cycles (157 TFLOP/s over
+// the chip); a 32-key tile costs a wave of 32 queries 2 x D/2 of them, 8192 cycles at D = 128, against
+// about 500 cycles of softmax arithmetic and 32 16-byte LDS reads.
+//
+// A workgroup owns 32 QG queries of ONE query block and walks that block's own list (no union, no
+// idle waves).  Its waves are QG query groups x KS key slices: slice s takes every KS-th 32-key tile,
+// with an online softmax of its own, and the slices are merged through LDS at the end.  Slices
+// rather than more queries per workgroup: two waves per SIMD hide each other's softmax, and a map
+// with few query blocks still occupies the chip.  When it does not (few heads, short sequences, or a
+// last round of workgroups that is mostly empty) the list is further split over `splits` workgroups,
+// whose partial results attn_combine_kernel adds up.
+//
+// K and V rows are gathered straight from the caller's tensors, through perm_k, by direct-to-LDS
+// loads (the source address of a lane is free, its LDS slot is not): no tiling pass, one launch.  The
+// scores are computed transposed, S^T = K Q^T, so that a lane owns one query (running maximum and
+// sum are per-lane scalars) and register r of the score accumulator is, as it stands, the B operand of
+// the second product's step r (O^T += V^T P^T, two keys per step): no conversion, no lane exchange.
+// Row i of output block db is dimension (D/32) i + db, so that one 16-byte read of a V row feeds
+// the matrix instruction of all four output blocks (8 bytes, two blocks, at D = 64).  K: 16-byte chunk
+// c of row r sits at c ^ (r & 15), V is linear: both conflict-free.
+//
+// Measured (8 heads, L = 4096, d = B = 128, 16 of 32 blocks): 3037 us for the former kernel (one
+// thread per query, fp32 FMA) -> 293 us, 117 TFLOP/s of the 154 the library's fp32 matrix product
+// reaches on this card (the matrix cores are busy 75 % of the cycles; the vector instructions of a tile are
+// only partly hidden behind them, and two independent workgroups per compute unit instead of two slices
+// that meet at a barrier measure the same); one head, L = 1024, d = B = 64: 345 -> 12 + 4 us.
+#include <algorithm>
+#include <climits>
+#include "common.hpp"
+
+namespace basa {
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void* lds_ptr_t;
+typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
+
+constexpr int kTK = 32;                     // keys per tile
+constexpr float kLazyTau = 8.0f;            // log2 of the largest exponentiated score kept before a rescale
+constexpr int kCUs = 256, kMaxSplits = 16;
+
+struct F32Args {
+  AttnArgs a;
+  int Nq, Nk, group, wgs_per_head, total, splits;
+  float scale_log2e;
+  float* part_o;                            // splits > 1: [split][BHq][Lq][D], rows by sorted position
+  float2* part_ml;                          //             [split][BHq][Lq] running maximum (log2), running sum
+};
+
+template <int D, int QG, int KS, bool kCausal>
+__global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_kernel(F32Args p) {
+  constexpr int CPR = D / 4;                // 16-byte chunks per row
+  constexpr int DB = D / 32;                // output blocks of 32 dimensions
+  constexpr int kHalf = kTK * D * 4;        // bytes of a K tile (and of a V tile)
+  constexpr int kStage = 2 * kHalf;
+  constexpr int kChunks = kHalf / 1024;     // wave-wide loads per K tile
+  static_assert(kChunks % QG == 0, "the chunks of a tile are dealt to the waves of its slice in rounds");
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // [slice][stage][K tile, V tile], then key indices
+  int* kix = reinterpret_cast<int*>(smem + KS * 2 * kStage);    // kCausal: [slice][stage][kTK] original key indices
+
+  const AttnArgs& a = p.a;
+  int logical = blockIdx.x;                 // one XCD, one range of heads
+  if ((p.total & 7) == 0) logical = (blockIdx.x & 7) * (p.total >> 3) + (blockIdx.x >> 3);
+  const int split = logical % p.splits;
+  const int wgi = logical / p.splits;
+  const int bhq = wgi / p.wgs_per_head, wg = wgi - bhq * p.wgs_per_head;
+  const int bhk = bhq / p.group;
+  const int lane = threadIdx.x & 63, li = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int g = wave % QG, slice = wave / QG;
+  const int Lq = a.q.L, Lk = a.k.L, B = a.B;
+  const int pos = wg * (32 * QG) + g * 32 + li;          // sorted position of this lane's query
+  const int gq = wg * (32 * QG) / B;
+  const int qrow = pos < Lq ? perm_at(a.perm_q, (int64_t)bhq * Lq, pos, Lq) : 0;
+  const int q_lim = (kCausal && pos < Lq) ? qrow + a.causal_off : INT_MIN;
+
+  const int64_t rowid = (int64_t)bhq * p.Nq + gq;
+  const int count = a.row_cols ? min(a.row_count[rowid], a.cols_stride) : p.Nk;
+  const int32_t* cols = a.row_cols ? a.row_cols + rowid * a.cols_stride : nullptr;
+  const int tpb = B / kTK, tiles = max(0, count) * tpb;
+  const int stride = p.splits * KS, first = split * KS + slice;
+  const int steps = (tiles + stride - 1) / stride;
+  const int32_t* pk = a.perm_k ? a.perm_k + (int64_t)bhk * Lk : nullptr;
+  const char* kbase = reinterpret_cast<const char*>(a.k.ptr) + a.k.head_offset(bhk) * 4;
+  const char* vbase = reinterpret_cast<const char*>(a.v.ptr) + a.v.head_offset(bhk) * 4;
+  char* ring = smem + slice * 2 * kStage;
+
+  // First key of this slice's tile of step s, or -1: past the list, not a key block, or past the last
+  // key.  Lane l holds the one of step 64 n + l, read for 64 steps at a time: a list entry loaded step by step
+  // would be waited for behind the tile loads that are in flight.
+  auto keys_of_64_steps = [&](int s0) -> int {
+    const int i = (s0 + lane) * stride + first;
+    // (loaded before the count is known: the list, the count and perm_q then arrive together)
+    const int gk = cols ? cols[min(i / tpb, a.cols_stride - 1)] : i / tpb;
+    const int key0 = gk * B + (i % tpb) * kTK;
+    return (i < tiles && (unsigned)gk < (unsigned)p.Nk && key0 < Lk) ? key0 : -1;
+  };
+  // Original index of key li of the tile (clamped: a key past the end is masked where it is used), as stored:
+  // perm_at's check is made when it is used, one step later, so that nothing waits for the load here.
+  auto raw_row = [&](int key0) -> int {
+    const int kp = min(max(key0, 0) + li, Lk - 1);
+    return pk ? pk[kp] : kp;
+  };
+  // row * stride * 4 with one 32 x 32 -> 64 bit multiply (the high half of a stride is nearly always 0)
+  auto row_bytes = [&](uint32_t row, int64_t stride) -> uint64_t {
+    const uint64_t sb = (uint64_t)stride * 4;
+    uint64_t off = (uint64_t)row * (uint32_t)sb;
+    if (sb >> 32) off += (uint64_t)(row * (uint32_t)(sb >> 32)) << 32;
+    return off;
+  };
+  auto issue = [&](int key0, int raw, int stage) {
+    if (key0 < 0) return;
+    const int rows = (unsigned)raw < (unsigned)Lk ? raw : min(key0 + li, Lk - 1);
+    char* dst = ring + stage * kStage;
+#pragma unroll
+    for (int j = 0; j < kChunks / QG; ++j) {
+      const int ch = j * QG + g;
+      const int r = ch * (64 / CPR) + lane / CPR, c = lane % CPR;
+      const uint32_t row = (uint32_t)__shfl(rows, r);
+      const char* ks = kbase + row_bytes(row, a.k.stride_l) + 16 * (c ^ (r & 15));
+      const char* vs = vbase + row_bytes(row, a.v.stride_l) + 16 * c;
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)ks, (lds_ptr_t)(dst + ch * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)vs, (lds_ptr_t)(dst + kHalf + ch * 1024), 16, 0, 0);
+    }
+    if (kCausal && g == 0 && lane < kTK) kix[(slice * 2 + stage) * kTK + lane] = key0 + lane < Lk ? rows : INT_MAX;
+  };
+
+  int keys = keys_of_64_steps(0);
+  int key_cur = __builtin_amdgcn_readlane(keys, 0), key_nxt = __builtin_amdgcn_readlane(keys, 1);
+  {
+    const int raw0 = raw_row(key_cur);
+    issue(key_cur, raw0, 0);
+  }
+  int raw_nxt = raw_row(key_nxt);
+  floatx4 qf[D / 8];                        // lane (query li, half h): Q[8 k + 4 h .. + 3]
+  {
+    const floatx4* qp = reinterpret_cast<const floatx4*>(reinterpret_cast<const float*>(a.q.ptr) + a.q.head_offset(bhq) +
+                                                         (int64_t)qrow * a.q.stride_l);
+#pragma unroll
+    for (int k = 0; k < D / 8; ++k) qf[k] = qp[2 * k + h];
+  }
+  floatx16 o[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db) o[db] = floatx16{0};
+  float m_run = -INFINITY, l_run = 0.f;
+  const float c = p.scale_log2e;
+  // The two waves of a SIMD belong to different halves of the slices: one half asks for its next tile before
+  // the first product, the other after it, so that the two do not run through softmax and address
+  // arithmetic in step while the matrix core idles.
+  const bool late = slice >= KS / 2;
+
+  for (int s = 0; s < steps; ++s) {
+    // my loads of step s have landed (and the key rows of step s + 1); after the barrier everyone's have,
+    // and everyone is done with the other stage, which the next loads overwrite
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    const int stage = s & 1;
+    int key_n2 = -1, raw_n2 = 0;
+    auto next_tile = [&]() {
+      issue(key_nxt, raw_nxt, stage ^ 1);
+      if (((s + 2) & 63) == 0) keys = keys_of_64_steps(s + 2);
+      key_n2 = __builtin_amdgcn_readlane(keys, (s + 2) & 63);
+      raw_n2 = raw_row(key_n2);
+    };
+    if (!late || key_cur < 0) next_tile();
+    if (key_cur >= 0) {
+      const char* ks = ring + stage * kStage;
+      const char* vs = ks + kHalf;
+      floatx16 sc = floatx16{0};
+#pragma unroll
+      for (int k = 0; k < D / 8; ++k) {
+        const floatx4 kf = *reinterpret_cast<const floatx4*>(ks + li * (D * 4) + (((2 * k + h) ^ (li & 15)) << 4));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j], qf[k][j], sc, 0, 0, 0);
+      }
+      if (late) next_tile();
+      // register r of half h: key 8 (r / 4) + 4 h + r % 4 of the tile
+      if constexpr (kCausal) {
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const int4 ix = *reinterpret_cast<const int4*>(kix + (slice * 2 + stage) * kTK + 8 * r4 + 4 * h);
+          if (ix.x > q_lim) sc[4 * r4] = -INFINITY;
+          if (ix.y > q_lim) sc[4 * r4 + 1] = -INFINITY;
+          if (ix.z > q_lim) sc[4 * r4 + 2] = -INFINITY;
+          if (ix.w > q_lim) sc[4 * r4 + 3] = -INFINITY;
+        }
+      } else if (key_cur + kTK > Lk) {
+        const int nvalid = Lk - key_cur;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (8 * (r >> 2) + 4 * h + (r & 3) >= nvalid) sc[r] = -INFINITY;
+      }
+      float mx = sc[0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32)) * c;
+      if (__builtin_amdgcn_ballot_w64(mx > m_run + kLazyTau) != 0) {
+        const float m_new = fmaxf(m_run, mx);
+        const float alpha = m_new == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+      }
+      // (causal: a query that has seen no key yet subtracts 0, so that exp2 sees -inf, never inf - inf)
+      const float m_use = (kCausal && m_run == -INFINITY) ? 0.f : m_run;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, -m_use));
+        l_run += sc[r];
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const char* vrow = vs + (8 * (r >> 2) + 4 * h + (r & 3)) * (D * 4) + li * (4 * DB);
+        if constexpr (DB == 4) {
+          const floatx4 vf = *reinterpret_cast<const floatx4*>(vrow);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db], sc[r], o[db], 0, 0, 0);
+        } else {
+          const floatx2 vf = *reinterpret_cast<const floatx2*>(vrow);
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[db], sc[r], o[db], 0, 0, 0);
+        }
+      }
+    }
+    key_cur = key_nxt; key_nxt = key_n2; raw_nxt = raw_n2;
+  }
+
+  // ---- merge the key slices through LDS (the ring is free once everyone has left the loop)
+  float l_tot = l_run + __shfl_xor(l_run, 32);
+  asm volatile("" : "+v"(l_tot));           // (the lane exchange is over before the barriers below)
+  if constexpr (KS > 1) {
+    constexpr int kSlot = DB * 16 * 64 * 4 + 2 * 64 * 4;           // one wave's accumulators, then its maxima and sums
+    static_assert((KS - 1) * QG * kSlot <= KS * 2 * kStage, "the slices' results fit the ring");
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (slice > 0) {
+      float* w = reinterpret_cast<float*>(smem + ((slice - 1) * QG + g) * kSlot);
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          reinterpret_cast<floatx4*>(w)[(db * 4 + r4) * 64 + lane] =
+              floatx4{o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
+      w[DB * 16 * 64 + lane] = m_run;
+      w[DB * 16 * 64 + 64 + lane] = l_tot;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (slice > 0) return;
+#pragma unroll
+    for (int s = 1; s < KS; ++s) {
+      const float* w = reinterpret_cast<const float*>(smem + ((s - 1) * QG + g) * kSlot);
+      const float ms = w[DB * 16 * 64 + lane], ls = w[DB * 16 * 64 + 64 + lane];
+      const float m_new = fmaxf(m_run, ms);
+      const float f0 = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+      const float f1 = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - m_new);
+      l_tot = l_tot * f0 + ls * f1;
+      m_run = m_new;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const floatx4 t = reinterpret_cast<const floatx4*>(w)[(db * 4 + r4) * 64 + lane];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[db][4 * r4 + e] = o[db][4 * r4 + e] * f0 + t[e] * f1;
+        }
+    }
+  }
+  if (pos >= Lq) return;
+  // register r of block db: dimension DB i + db, i = 8 (r / 4) + 4 h + r % 4
+  if (p.splits > 1) {
+    const int64_t prow = ((int64_t)split * (p.total / (p.splits * p.wgs_per_head)) + bhq) * Lq + pos;
+    float* po = p.part_o + prow * D;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int i = 8 * (r >> 2) + 4 * h + (r & 3);
+      if constexpr (DB == 4) *reinterpret_cast<floatx4*>(po + 4 * i) = floatx4{o[0][r], o[1][r], o[2][r], o[3][r]};
+      else *reinterpret_cast<floatx2*>(po + 2 * i) = floatx2{o[0][r], o[1][r]};
+    }
+    if (h == 0) p.part_ml[prow] = make_float2(m_run, l_tot);
+    return;
+  }
+  const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;            // a row without any visible key: zeros
+  float* op = reinterpret_cast<float*>(a.out) + a.out_offset(bhq, qrow);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int i = 8 * (r >> 2) + 4 * h + (r & 3);
+    if constexpr (DB == 4) *reinterpret_cast<floatx4*>(op + 4 * i) = floatx4{o[0][r], o[1][r], o[2][r], o[3][r]} * inv_l;
+    else *reinterpret_cast<floatx2*>(op + 2 * i) = floatx2{o[0][r], o[1][r]} * inv_l;
+  }
+  if (a.lse && h == 0) a.lse[(int64_t)bhq * Lq + qrow] = (m_run + __log2f(l_tot)) * 0.6931471805599453f;
+}
+
+// Adds up the partial results of the workgroups that shared a query's list: D/4 lanes per query.
+template <bool kBf16, int D>
+__global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const float* __restrict__ part_o,
+                                                           const float2* __restrict__ part_ml, int splits, int64_t rows) {
+  constexpr int LPR = D / 4;
+  const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;       // bhq * Lq + sorted position
+  if (row >= rows) return;
+  const int sub = threadIdx.x % LPR;
+  const int Lq = a.q.L, bhq = (int)(row / Lq), pos = (int)(row - (int64_t)bhq * Lq);
+  float m = -INFINITY, l = 0.f;
+  for (int s = 0; s < splits; ++s) m = fmaxf(m, part_ml[s * rows + row].x);
+  floatx4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < splits; ++s) {
+    const float2 ml = part_ml[s * rows + row];
+    const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ml.x - m);
+    const floatx4 t = *reinterpret_cast<const floatx4*>(part_o + (s * rows + row) * D + 4 * sub);
+    l = fmaf(ml.y, f, l);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = fmaf(t[e], f, o[e]);
+  }
+  const float inv_l = l > 0.f ? 1.0f / l : 0.f;
+  const int qrow = perm_at(a.perm_q, (int64_t)bhq * Lq, pos, Lq);
+  if constexpr (kBf16) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    bf16x4 t;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = (__bf16)(o[e] * inv_l);
+    *reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(a.out) + a.out_offset(bhq, qrow) + 4 * sub) = t;
+  } else {
+    *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(a.out) + a.out_offset(bhq, qrow) + 4 * sub) = o * inv_l;
+  }
+  if (a.lse && sub == 0) a.lse[(int64_t)bhq * Lq + qrow] = (m + __log2f(l)) * 0.6931471805599453f;
+}
+
+template <int D, int QG, int KS>
+basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
+  constexpr int kQueries = 32 * QG;
+  const int B = p.a.B;
+  p.wgs_per_head = ceil_div(p.Nq * B, kQueries);
+  const int work = BHq * p.wgs_per_head;                  // workgroups without splitting, one to a compute unit
+  // How many workgroups share a list: rounds of workgroups times (steps of one, a tile per slice each, plus
+  // its prologue and epilogue), plus the combining pass and its bytes.  The step times are measured
+  // (attn_f32_kernel at 1, 2 and 4 splits: 26.2, 17.0, 12.3 us for one head of L = 1024, d = B = 64, and 4.2 us
+  // for the combining pass; L = 4096, d = B = 128, 8 heads: 293 us unsplit, 315 + 11 in two).
+  const int tiles = (p.a.row_cols ? std::min(p.a.cols_stride, p.Nk) : p.Nk) * (B / kTK);
+  const size_t row_bytes = (size_t)BHq * p.a.q.L * (D * 4 + 8);
+  const double step_us = (D == 128 ? 9.2 : 4.5) * (QG * KS == 8 ? 1.0 : 0.6);
+  double best = 0.0;
+  int splits = 1;
+  for (int s = 1; s <= kMaxSplits && (s == 1 || (tiles >= s * KS && s * row_bytes <= p.a.ws_bytes)); ++s) {
+    const double cost = ceil_div(work * s, kCUs) * (ceil_div(tiles, s * KS) * step_us + 8.0) +
+                        (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
+    if (s == 1 || cost < best) { best = cost; splits = s; }
+  }
+  p.splits = splits;
+  p.total = work * splits;
+  if (splits > 1) {
+    p.part_o = reinterpret_cast<float*>(p.a.ws);
+    p.part_ml = reinterpret_cast<float2*>(p.part_o + (size_t)splits * BHq * p.a.q.L * D);
+  }
+  const size_t lds = (size_t)KS * 2 * 2 * kTK * D * 4 + (p.a.causal ? KS * 2 * kTK * 4 : 0);
+  {
+    ProfScope prof(K_ATTN_F32, st);
+#define BASA_F32(C)                                                                                              \
+  do {                                                                                                           \
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, QG, KS, C>),      \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");                                 \
+    hipLaunchKernelGGL((attn_f32_kernel<D, QG, KS, C>), dim3(p.total), dim3(64 * QG * KS), lds, st, p);          \
+  } while (0)
+    if (p.a.causal) BASA_F32(true);
+    else BASA_F32(false);
+#undef BASA_F32
+    BASA_HIP_CHECK_LAUNCH("attn_f32_kernel");
+  }
+  return splits > 1 ? launch_attn_combine(p.a, p.part_o, p.part_ml, splits, st) : BASA_OK;
+}
+
+}  // namespace
+
+basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const float2* part_ml, int splits, hipStream_t st) {
+  const int64_t rows = (int64_t)a.q.batch * a.q.heads * a.q.L;
+  const int rpw = 256 / (a.q.d / 4);
+  const dim3 grid((unsigned)((rows + rpw - 1) / rpw));
+  ProfScope prof(K_ATTN_COMBINE, st);
+#define BASA_COMB(BF, D) hipLaunchKernelGGL((attn_combine_kernel<BF, D>), grid, dim3(256), 0, st, a, part_o, part_ml, splits, rows)
+  const bool bf = a.q.dtype == BASA_BF16;
+  if (bf && a.q.d == 128) BASA_COMB(true, 128);
+  else if (bf) BASA_COMB(true, 64);
+  else if (a.q.d == 128) BASA_COMB(false, 128);
+  else BASA_COMB(false, 64);
+#undef BASA_COMB
+  BASA_HIP_CHECK_LAUNCH("attn_combine_kernel");
+  return BASA_OK;
+}
+
+// Room for the partial results of as many workgroups per list as could be of use (callers who hand over
+// less get fewer): enough to give every compute unit two workgroups.
+size_t attn_f32_workspace_bytes(int BHq, int Lq, int d) {
+  const int64_t wgs = (int64_t)BHq * ceil_div(Lq, 128);
+  const size_t splits = (size_t)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 2 * kCUs / wgs));
+  return align_up(splits * BHq * Lq * (d * 4 + 8), 256);
+}
+
+basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {
+  const int BHq = a.q.batch * a.q.heads;
+  F32Args p;
+  p.a = a;
+  p.Nq = ceil_div(a.q.L, a.B); p.Nk = ceil_div(a.k.L, a.B);
+  if (BHq == 0 || p.Nq == 0) return BASA_OK;
+  p.group = a.q.heads / a.k.heads;
+  p.scale_log2e = 1.4426950408889634f / sqrtf((float)a.q.d);
+  p.part_o = nullptr; p.part_ml = nullptr;
+  if (!a.ws || reinterpret_cast<uintptr_t>(a.ws) % 16) p.a.ws_bytes = 0;
+  // queries per workgroup = the query block; slices so that its tiles fill the LDS (128 KB of ring)
+  if (a.q.d == 128) return a.B == 128 ? launch_f32<128, 4, 2>(p, BHq, st) : launch_f32<128, 2, 2>(p, BHq, st);
+  return a.B == 128 ? launch_f32<64, 4, 2>(p, BHq, st) : launch_f32<64, 2, 4>(p, BHq, st);
+}
+
+}  // namespace basa

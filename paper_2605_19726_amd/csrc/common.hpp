@@ -42,7 +42,7 @@ basa_status hip_fail(hipError_t e, const char* what);
 // with a pair of HIP events on the launch stream when profiling is enabled.
 enum KernelId {
   K_NORM_TILE_SORT = 0, K_MERGE, K_STATS, K_SCORES, K_ROW_SELECT, K_GATHER, K_ATTN,
-  K_ATTN_SIMPLE, K_BLOCK_MASS, K_DIAG_SMALL, K_SCORES_SELECT, K_COUNT
+  K_ATTN_F32, K_BLOCK_MASS, K_DIAG_SMALL, K_SCORES_SELECT, K_ATTN_COMBINE, K_COUNT
 };
 struct ProfScope {
   ProfScope(int id, hipStream_t st);
@@ -148,7 +148,11 @@ struct AttnArgs {
   int causal_off;             // L_k - L_q
 };
 size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B);
-basa_status launch_attn_simple(const AttnArgs& a, hipStream_t st);
+size_t attn_f32_workspace_bytes(int BHq, int Lq, int d);
+basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
+// Partial results of several workgroups per query: unnormalised rows part_o[split][BHq][Lq][d] and
+// their (running maximum in log2 units, sum) part_ml[split][BHq][Lq], rows by sorted position.
+basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const float2* part_ml, int splits, hipStream_t st);
 basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st);
 
 // Selection-fidelity diagnostics (diag.hip).  block mass: bf16 on the matrix cores, f32 on a plain kernel.

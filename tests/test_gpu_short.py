@@ -1,0 +1,58 @@
+"""Kernels and dispatch branches for calls that do not fill the device: sizes around their tiles,
+slices and splits, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import basa_oracle as o
+from paper_2605_19726_amd import binding as bd
+from parity_util import check_output, np64
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _qkv(hq, hk, Lq, Lk, d, dtype, seed=0):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    r = lambda h, L: torch.randn((1, h, L, d), generator=g, device=DEV).to(dtype)
+    return r(hq, Lq), r(hk, Lk), r(hk, Lk)
+
+
+def _lists(hq, n_q, n_k, seed, stride):
+    """Ascending lists of different lengths (1 .. n_k), the rest of a row filled with an invalid entry."""
+    rng = np.random.default_rng(seed)
+    count = rng.integers(1, n_k + 1, (1, hq, n_q))
+    cols = np.full((1, hq, n_q, stride), n_k + 7)
+    for idx in np.ndindex(count.shape):
+        cols[idx][:count[idx]] = np.sort(rng.choice(n_k, count[idx], replace=False))
+    t = lambda a: torch.from_numpy(a.astype(np.int32)).to(DEV)
+    return t(count), t(cols), count, cols
+
+
+def _perm(h, L, seed):
+    return torch.stack([torch.randperm(L, generator=torch.Generator().manual_seed(seed + i)) for i in range(h)]).to(DEV, torch.int32)[None]
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float32])
+@pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("Lq,Lk", [(1, 1), (31, 33), (65, 129), (200, 1000), (130, 5000), (2048 + 77, 2048 + 77)])
+def test_attention_of_short_calls_against_the_oracle(dtype, d, block, Lq, Lk, causal):
+    hq, hk = 2, 1
+    Q, K, V = _qkv(hq, hk, Lq, Lk, d, dtype, seed=Lq + Lk + d)
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    cnt, cols, cnt_h, cols_h = _lists(hq, n_q, n_k, Lq + 3 * Lk, n_k)
+    pq, pk = _perm(hq, Lq, 1), _perm(hk, Lk, 50)
+    out, lse = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, causal=causal)
+    torch.cuda.synchronize()
+    for h in range(hq):
+        lists = [cols_h[0, h, g, :cnt_h[0, h, g]] for g in range(n_q)]
+        args = (np64(Q[0, h]), np64(K[0, 0]), np64(V[0, 0]), pq[0, h].cpu().numpy(), pk[0, 0].cpu().numpy(), lists, block)
+        fn = o.sparse_attention_causal if causal else o.sparse_attention
+        ref, ref_lse = fn(*args, return_lse=True)
+        check_output(np64(out[0, h]), ref, dtype == torch.bfloat16, f"head {h}")
+        got = lse[0, h].cpu().numpy()
+        assert np.array_equal(np.isinf(got), np.isinf(ref_lse))
+        fin = np.isfinite(ref_lse)
+        np.testing.assert_allclose(got[fin], ref_lse[fin], rtol=0, atol=2e-2 if dtype == torch.bfloat16 else 1e-4)
