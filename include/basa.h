@@ -74,8 +74,11 @@ typedef struct {
                                 as a mass budget), at least min_keep and at most kappa    */
   int32_t min_keep;          /* floor on the per-row count when mass_target > 0; 0 means 1 */
   int32_t attn_shape;        /* basa_sparse_attn, bf16 only: shape of the attention workgroup.
-                              * 0 = chosen by the library (on the device, between 3 and 2, from
-                              * how much the lists of neighbouring query blocks overlap),
+                              * 0 = chosen by the library: calls that do not fill the device take
+                              * 2 (with the arithmetic of 3, or, on lists of more than 32 key
+                              * tiles, several workgroups per list whose results are added up);
+                              * the others 3 or 2, chosen on the device from how much the lists of
+                              * neighbouring query blocks overlap,
                               * 1 = 256 queries sharing every K/V tile, 2 = 128 queries,
                               * 3 = 512 queries (64 per wave).  1 and 2 give identical bits;
                               * 3 runs the online softmax against a reference that is raised only
@@ -84,7 +87,8 @@ typedef struct {
                               * range in which that is exact; 4 = shape 3 with running maxima from
                               * the start (for comparison).  3 and 4 agree with 1 and 2 within the
                               * output tolerance.  The causal variant always runs shape 3 (4 if
-                              * asked for); other entry points ignore the field */
+                              * asked for; with 0 also several workgroups per list); other entry
+                              * points ignore the field */
   int32_t n_segments;        /* 0: none.  1..BASA_MAX_SEGMENTS: the sort is segment-aware (the
                                 windowed sort of Alg. 1 step 1 with runs of unequal length, e.g.
                                 one run per modality or frame): tokens segment_starts[j] ..

@@ -248,8 +248,9 @@ size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, co
 
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p) {
   if (check_qk(q, k) != BASA_OK || check_params(p, false) != BASA_OK) return 0;
-  if (!use_mfma(q)) return attn_f32_workspace_bytes(q->batch * q->heads, q->L, q->d);
-  return attn_mfma_workspace_bytes(q->batch * q->heads, k->batch * k->heads, q->L, k->L, q->d, p->block);
+  if (!use_mfma(q)) return attn_f32_workspace_bytes(q->batch, q->heads, q->L, q->d);
+  return attn_mfma_workspace_bytes(q->batch * q->heads, k->batch * k->heads, q->L, k->L, q->d, p->block) +
+         attn_mfma_split_bytes(q->batch, q->heads, q->L, q->d);
 }
 
 basa_status basa_norm_sort(const basa_tensor* x, const basa_params* p, int32_t* perm, float* keys_out,
@@ -396,7 +397,7 @@ basa_status basa_dense_attn(const basa_tensor* q, const basa_tensor* k, const ba
   basa_status s;
   if ((s = check_qkv(q, k, v)) != BASA_OK) return s;
   if ((s = check_params(p, false)) != BASA_OK) return s;
-  return attn_common(q, k, v, nullptr, nullptr, 0, nullptr, nullptr, p->block, 3, p->causal, out, out_strides, lse, ws,
+  return attn_common(q, k, v, nullptr, nullptr, 0, nullptr, nullptr, p->block, 0, p->causal, out, out_strides, lse, ws,
                      ws_bytes, stream);
 }
 

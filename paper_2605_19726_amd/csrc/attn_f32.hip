@@ -179,6 +179,13 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
         for (int j = 0; j < 4; ++j) sc = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j], qf[k][j], sc, 0, 0, 0);
       }
       if (late) next_tile();
+      if (key_cur + kTK > Lk) {
+        // Rows past the end hold copies of the last one; their probabilities are 0, but 0 times an infinity of V
+        // is not.  Every wave clears all of them itself (its own reads come after its own writes).
+        const char* v0 = vs + (Lk - key_cur) * (D * 4);
+        for (int i = lane; i < (key_cur + kTK - Lk) * CPR; i += 64)
+          reinterpret_cast<floatx4*>(const_cast<char*>(v0))[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+      }
       // register r of half h: key 8 (r / 4) + 4 h + r % 4 of the tile
       if constexpr (kCausal) {
 #pragma unroll
@@ -209,8 +216,8 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
 #pragma unroll
           for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
       }
-      // (causal: a query that has seen no key yet subtracts 0, so that exp2 sees -inf, never inf - inf)
-      const float m_use = (kCausal && m_run == -INFINITY) ? 0.f : m_run;
+      // (a query that has seen no finite score yet subtracts 0, so that exp2 sees -inf, never inf - inf)
+      const float m_use = m_run == -INFINITY ? 0.f : m_run;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, -m_use));

@@ -47,6 +47,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTileKeys = 64;
 constexpr int kIxStride = kTileKeys + 4;    // causal: ints per tile of the key-index array (64 indices, min, max, 2 unused)
@@ -181,6 +182,9 @@ struct MfmaArgs {
   int run_if_solo;           // with probe: this launch runs iff (lists overlap little) == run_if_solo
   int32_t* redo;             // nullable, one word per workgroup: written by the pass without running maxima (1 = a row
                              // sum left the safe range), read by the pass with them, which skips workgroups at 0
+  int splits;                // kSplit: workgroups that share a union list, and where they leave their rows:
+  float* part_o;             //   [split][BHq][Lq][D] unnormalised, by sorted position
+  float2* part_ml;           //   [split][BHq][Lq] running maximum (log2), running sum
 };
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -191,6 +195,7 @@ template <int D>
 struct WaveState {
   floatx16 o[Geo<D>::kDBlocks];
   float m_run, l_run;
+  float lt;                  // kFast: the row sum of the half tile before this one
 };
 
 // max of three floats; this file is compiled with -fno-honor-nans (scores are finite or
@@ -199,7 +204,8 @@ __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(
 
 // One 64-key tile: S^T, softmax, O^T update, reading the LDS stage at `stage`.  kMasked:
 // keys at tile positions >= nvalid do not exist (ragged end of the sequence) and get -inf.
-template <bool kMasked, int D>
+// kFast: no maximum is taken, the arithmetic of process_tile2's kFast form step by step (same bits).
+template <bool kMasked, int D, bool kFast>
 __device__ __forceinline__ void process_tile(WaveState<D>& st, const bf16x8 (&qf)[Geo<D>::kKSteps], const char* stage,
                                              int kaddr0, int vaddr0, float c, int nvalid, int h) {
   const char* ks = stage;
@@ -222,6 +228,47 @@ __device__ __forceinline__ void process_tile(WaveState<D>& st, const bf16x8 (&qf
       if (kk >= nvalid) s0[r] = -INFINITY;
       if (32 + kk >= nvalid) s1[r] = -INFINITY;
     }
+  }
+  if constexpr (kFast) {
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (__builtin_amdgcn_ballot_w64(st.lt > kSafeSum) != 0) {
+        const float other = __shfl_xor(st.lt, 32);           // (by every lane, see process_tile2)
+        const bool up = (st.lt > kSafeSum) | (other > kSafeSum);
+        const float alpha = up ? kShiftMul : 1.f;
+        st.m_run += up ? kShiftLog2 : 0.f;
+        st.l_run *= alpha;
+#pragma unroll
+        for (int i = 0; i < Geo<D>::kDBlocks; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) st.o[i][r] *= alpha;
+      }
+      const floatx16& sh = half == 0 ? s0 : s1;
+      bf16x8 pb[2];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) pb[r >> 3][r & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sh[r], c, -st.m_run));
+      float la = 0.f;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        la = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[g], pb[g], 0, 1), ones, la, false);
+        la = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[g], pb[g], 2, 3), ones, la, false);
+        la = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[g], pb[g], 4, 5), ones, la, false);
+        la = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[g], pb[g], 6, 7), ones, la, false);
+      }
+      st.l_run += la;
+      st.lt = la;
+#pragma unroll
+      for (int g = 0; g < 2; ++g) {
+        const int va = vaddr0 ^ ((2 * half + g) << 5);
+#pragma unroll
+        for (int db = 0; db < Geo<D>::kDBlocks; ++db) {
+          const bf16x8 vv = *reinterpret_cast<const bf16x8*>(vs + va + db * 32 * 128);
+          st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, pb[g], st.o[db], 0, 0, 0);
+        }
+      }
+    }
+    return;
   }
   // ---- online softmax in the log2 domain, lazy running max
   float mx = max3(s0[0], s1[0], s0[1]);
@@ -432,11 +479,12 @@ __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&
 template <int D, int NG> struct StateOf { typedef WaveState<D> type; };
 template <int D> struct StateOf<D, 2> { typedef WaveState2<D> type; };
 template <int D>
-__device__ __forceinline__ void init_state(WaveState<D>& st, bool = false) {
+__device__ __forceinline__ void init_state(WaveState<D>& st, bool fast = false) {
 #pragma unroll
   for (int i = 0; i < Geo<D>::kDBlocks; ++i) st.o[i] = floatx16{0};
-  st.m_run = -INFINITY;
+  st.m_run = fast ? 0.f : -INFINITY;
   st.l_run = 0.f;
+  st.lt = 0.f;
 }
 template <int D>
 __device__ __forceinline__ void init_state(WaveState2<D>& st, bool fast = false) {
@@ -456,6 +504,13 @@ template <int D> __device__ __forceinline__ float l_of(const WaveState2<D>& st, 
 template <int D> __device__ __forceinline__ float m_of(const WaveState2<D>& st, int r) { return st.m_run[r]; }
 template <int D> __device__ __forceinline__ const floatx16& o_of(const WaveState2<D>& st, int r, int db) { return st.o[r][db]; }
 
+// kFast: has a final row sum left the range in which that pass is exact?  (On the bit patterns, which order like
+// the values for positive floats and put inf, NaN and anything negative above kMaxSum: this file is compiled
+// without NaN semantics for float comparisons.)
+__device__ __forceinline__ bool sum_is_unsafe(float l) {
+  return __float_as_uint(l) - __float_as_uint(kMinSum) > __float_as_uint(kMaxSum) - __float_as_uint(kMinSum);
+}
+
 __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) {
   const int b = bhq / a.heads_q, hh = bhq - b * a.heads_q;
   return (int64_t)b * a.out_sb + (int64_t)hh * a.out_sh + (int64_t)row * a.out_sl;
@@ -468,11 +523,18 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
 // kCausal (512-query shape only): the ring is followed by the original key indices of each stage's
 // tile (with their minimum), every score is masked by original position, and a wave skips a tile
 // none of whose keys is visible to any of its queries.
-template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false>
+// kSplit: a.splits workgroups share the query blocks and take equal runs of the union list each; their rows
+// stay unnormalised and attn_combine_kernel adds them up.
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
 __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 : 2) void attn_mfma_kernel(MfmaArgs a) {
   using G = Geo<D>;
   static_assert(!kCausal || (kQPW == 64 && kWgQueries == kWideQueries), "the causal path is built on the 512-query shape");
-  static_assert(!kFast || (kQPW == 64 && kWgQueries == kWideQueries), "the pass without running maxima is built on the 512-query shape");
+  static_assert(!kFast || !kSplit, "the safe range of a row's sum is tested on the whole sum");
+  static_assert(!kFast || (kQPW == 64 && kWgQueries == kWideQueries) || (kQPW == 32 && kWgQueries == kSoloQueries),
+                "the pass without running maxima is built on the 512-query and the 128-query shape");
+  // the 128-query shape has the registers to repeat itself with running maxima where that is needed; the
+  // 512-query one leaves it to a second launch
+  constexpr bool kRetry = kFast && kQPW == 32;
   constexpr int kWaves = kWgQueries / kQPW, kThreads = kWaves * 64, kQueriesPerWg = kWgQueries;
   constexpr int kNG = kQPW / 32;             // 32-query groups per wave: 1 or 2
   constexpr int kStages = stages_of(kThreads, kQPW);
@@ -502,6 +564,11 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   // XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
   int logical = blockIdx.x;
   if ((a.total_wgs & 7) == 0) logical = (blockIdx.x & 7) * (a.total_wgs >> 3) + (blockIdx.x >> 3);
+  int split = 0;
+  if constexpr (kSplit) {
+    split = logical % a.splits;
+    logical /= a.splits;
+  }
   // the pass with running maxima, launched behind the one without: only the workgroups that one gave up on
   if (!kFast && a.redo && a.redo[logical] == 0) return;
   const int bhq = logical / a.wgs_per_head, wg = logical - bhq * a.wgs_per_head;
@@ -548,7 +615,21 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   }
   // every thread has passed its last read of flags (the ring area) and seq is complete
 
+  if constexpr (kSplit) {                    // this workgroup's run of the list
+    const int u0 = n_union * split / a.splits;
+    n_union = n_union * (split + 1) / a.splits - u0;
+    seq += u0;
+  }
   if (n_union == 0) {
+    if constexpr (kSplit) {
+      // nothing to add: a maximum of -inf and a sum of 0, whose row the combining pass does not read
+      for (int r = 0; r < kNG; ++r) {
+        const int pos = pos0 + 32 * r;
+        if (pos < a.Lq && h == 0)
+          a.part_ml[((int64_t)split * (a.total_wgs / (a.splits * a.wgs_per_head)) + bhq) * a.Lq + pos] = make_float2(-INFINITY, 0.f);
+      }
+      return;
+    }
     // no valid key block in any list of this workgroup (malformed input): its rows become zeros
     for (int r = 0; r < kNG; ++r) {
       const int pos = pos0 + 32 * r;
@@ -559,7 +640,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
         if (a.lse && h == 0) a.lse[(int64_t)bhq * a.Lq + orow] = -INFINITY;
       }
     }
-    if (kFast && tid == 0) a.redo[logical] = 0;
+    if (kFast && !kRetry && tid == 0) a.redo[logical] = 0;
     return;
   }
   int n_tiles = n_union * TPB;
@@ -602,8 +683,11 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   };
 
   // prologue: the first tile (SHARED: the first pair; past the end: the last tile again, never read)
-  issue_tile(tile_of(0), 0);
-  if (kStages == 4) issue_tile(tile_of(1), 1);
+  auto issue_first = [&]() {
+    issue_tile(tile_of(0), 0);
+    if (kStages == 4) issue_tile(tile_of(1), 1);
+  };
+  issue_first();
 
   // Q^T operand: lane (query li, half h) holds Q[q][16 s + 8 h .. +7] for s = 0..7
   bf16x8 qf[kNG][kQR];
@@ -637,9 +721,9 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   init_state<D>(st, kFast);
   const float c = a.scale_log2e;
   // one 64-key tile of the ring, for the one or two query groups of this wave
-  auto tile = [&](auto masked, int stage_no, int nvalid) {
+  auto tile = [&](auto masked, int stage_no, int nvalid, auto fast) {
     const char* stage = smem + stage_no * kStageBytes;
-    if constexpr (kNG == 1) process_tile<decltype(masked)::value, D>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
+    if constexpr (kNG == 1) process_tile<decltype(masked)::value, D, decltype(fast)::value>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
     else {
       // the lane half is needed by the masking code only (ragged tile, causal mask): taken from the
       // thread index there, it does not occupy a register through the main loop
@@ -667,6 +751,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     if constexpr (!kCausal) return true;
     return __builtin_amdgcn_readfirstlane(kix_lds[stage_no * kIxStride + kTileKeys]) <= wq_max;
   };
+  constexpr std::integral_constant<bool, kFast> kMode{};
   constexpr std::false_type kFull{};
   constexpr std::true_type kRagged{};
   const uint32_t my_bit = 1u << (24 + grp);
@@ -700,7 +785,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
         for (int j = 0; j < R; ++j) issue_tile(tile_of(t + R + j), half_next * R + j);
       }
       const uint32_t raw_n = seq[(t + 1) / TPB];
-      if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kFull, ((t / R) & 1) * R + t % R, kTileKeys);
+      if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kFull, ((t / R) & 1) * R + t % R, kTileKeys, kMode);
       e_cur = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
     }
     if (t % R == 0) {
@@ -708,7 +793,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
       __syncthreads();
     }
     const int nvalid = a.Lk - ((int)(e_cur & 0xffffffu) * TPB + (t % TPB)) * kTileKeys;
-    if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kRagged, ((t / R) & 1) * R + t % R, nvalid);
+    if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kRagged, ((t / R) & 1) * R + t % R, nvalid, kMode);
   } else if constexpr (kStages == 4) {
   uint32_t e_a = entry_of(0);
   uint32_t e_b = entry_of(min(1, n_tiles - 1));
@@ -726,8 +811,8 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
       issue_tile(b1 * TPB + (tf1 % TPB), 2 * slot_next + 1);
     }
     const int slot = ((t >> 1) & 1) * 2;            // first ring stage of the pair
-    if (e_a & my_bit) tile(kFull, slot, kTileKeys);
-    if (e_b & my_bit) tile(kFull, slot + 1, kTileKeys);
+    if (e_a & my_bit) tile(kFull, slot, kTileKeys, kMode);
+    if (e_b & my_bit) tile(kFull, slot + 1, kTileKeys, kMode);
     e_a = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_f0);
     e_b = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_f1);
   }
@@ -737,31 +822,43 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     __syncthreads();
     const int slot = ((t >> 1) & 1) * 2;
     if (t + 1 < n_tiles) {
-      if (e_a & my_bit) tile(kFull, slot, kTileKeys);
+      if (e_a & my_bit) tile(kFull, slot, kTileKeys, kMode);
       const int nvalid = a.Lk - ((int)(e_b & 0xffffffu) * TPB + ((t + 1) % TPB)) * kTileKeys;
-      if (e_b & my_bit) tile(kRagged, slot + 1, nvalid);
+      if (e_b & my_bit) tile(kRagged, slot + 1, nvalid, kMode);
     } else {
       const int nvalid = a.Lk - ((int)(e_a & 0xffffffu) * TPB + (t % TPB)) * kTileKeys;
-      if (e_a & my_bit) tile(kRagged, slot, nvalid);
+      if (e_a & my_bit) tile(kRagged, slot, nvalid, kMode);
     }
   }
   } else {
     // SOLO: two stages, one tile per barrier; tile t+1 lands while tile t is computed
-    uint32_t e_cur = entry_of(0);
-    int t = 0;
-    for (; t + 1 < n_tiles; ++t) {
+    auto walk = [&](auto fast) {
+      uint32_t e_cur = entry_of(0);
+      int t = 0;
+      for (; t + 1 < n_tiles; ++t) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const uint32_t raw_n = seq[(t + 1) / TPB];
+        const uint32_t e_nxt = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
+        issue_tile((int)(e_nxt & 0xffffffu) * TPB + ((t + 1) % TPB), (t + 1) & 1);
+        if (e_cur & my_bit) tile(kFull, t & 1, kTileKeys, fast);
+        e_cur = e_nxt;
+      }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
-      const uint32_t raw_n = seq[(t + 1) / TPB];
-      const uint32_t e_nxt = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
-      issue_tile((int)(e_nxt & 0xffffffu) * TPB + ((t + 1) % TPB), (t + 1) & 1);
-      if (e_cur & my_bit) tile(kFull, t & 1, kTileKeys);
-      e_cur = e_nxt;
+      const int nvalid = a.Lk - ((int)(e_cur & 0xffffffu) * TPB + (t % TPB)) * kTileKeys;
+      if (e_cur & my_bit) tile(kRagged, t & 1, nvalid, fast);
+    };
+    walk(kMode);
+    if constexpr (kRetry) {
+      const float l_all = l_of(st, 0) + __shfl_xor(l_of(st, 0), 32);
+      // (the barrier inside also says that every wave is done with the ring)
+      if (__syncthreads_or(pos0 < a.Lq && sum_is_unsafe(l_all))) {
+        init_state<D>(st, false);
+        issue_first();
+        walk(std::false_type{});
+      }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    const int nvalid = a.Lk - ((int)(e_cur & 0xffffffu) * TPB + (t % TPB)) * kTileKeys;
-    if (e_cur & my_bit) tile(kRagged, t & 1, nvalid);
   }
 
   // ---- epilogue: normalise, scatter rows to their original positions
@@ -778,12 +875,24 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     const float l_tot = l_part + __shfl_xor(l_part, 32);
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;    // a query block without any valid key block: zeros
     const int pos = pos_e + 32 * r;
-    // (on the bit patterns, which order like the values for positive floats and put inf, NaN and anything
-    //  negative above kMaxSum: this file is compiled without NaN semantics for float comparisons)
-    if (kFast && pos < a.Lq && __float_as_uint(l_tot) - __float_as_uint(kMinSum) > __float_as_uint(kMaxSum) - __float_as_uint(kMinSum))
-      unsafe = 1;
+    if (kFast && !kRetry && pos < a.Lq && sum_is_unsafe(l_tot)) unsafe = 1;
     const int h = h_e;
-    if (pos < a.Lq) {
+    if constexpr (kSplit) {
+      if (pos < a.Lq) {
+        const int64_t prow = ((int64_t)split * (a.total_wgs / (a.splits * a.wgs_per_head)) + bhq) * a.Lq + pos;
+        float* po = a.part_o + prow * D;
+#pragma unroll
+        for (int db = 0; db < G::kDBlocks; ++db)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            floatx4 t;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) t[e] = o_of(st, r, db)[4 * r4 + e];
+            *reinterpret_cast<floatx4*>(po + 32 * db + 8 * r4 + 4 * h) = t;
+          }
+        if (h == 0) a.part_ml[prow] = make_float2(m_fin, l_tot);
+      }
+    } else if (pos < a.Lq) {
       const int orow = perm_at(a.perm_q, (int64_t)bhq * a.Lq, pos, a.Lq);
       __bf16* op = a.out + out_off(a, bhq, orow);
 #pragma unroll
@@ -799,7 +908,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
         a.lse[(int64_t)bhq * a.Lq + orow] = (m_fin + __log2f(l_tot)) * 0.6931471805599453f;
     }
   }
-  if constexpr (kFast) {
+  if constexpr (kFast && !kRetry) {
     // (a row without any visible key has the sum 0 as well and is sent round again: it comes out as zeros both times)
     const int any = __syncthreads_or(unsafe);
     if (threadIdx.x == 0) a.redo[logical] = any;
@@ -816,7 +925,7 @@ size_t lds_bytes(int threads, int qpw, int Nk, bool causal = false, bool fast = 
   return causal ? ((base + 15) & ~(size_t)15) + (size_t)stages_of(threads, qpw) * kIxStride * 4 : base;
 }
 
-template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false>
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit>
 basa_status launch_main(MfmaArgs m, int BHq, hipStream_t st) {
   constexpr int kThreads = kWgQueries / kQPW * 64;
   const size_t lds = lds_bytes<D>(kThreads, kQPW, m.Nk, kCausal, kFast);
@@ -827,21 +936,21 @@ basa_status launch_main(MfmaArgs m, int BHq, hipStream_t st) {
     return BASA_ERR_UNSUPPORTED;
   }
   m.wgs_per_head = ceil_div(m.Nq * kB, kWgQueries);
-  m.total_wgs = BHq * m.wgs_per_head;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mfma_kernel<kB, D, kWgQueries, kQPW, kCausal, kFast>),
+  m.total_wgs = BHq * m.wgs_per_head * (kSplit ? m.splits : 1);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mfma_kernel<kB, D, kWgQueries, kQPW, kCausal, kFast, kSplit>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
-  hipLaunchKernelGGL((attn_mfma_kernel<kB, D, kWgQueries, kQPW, kCausal, kFast>), dim3(m.total_wgs), dim3(kThreads), lds, st, m);
+  hipLaunchKernelGGL((attn_mfma_kernel<kB, D, kWgQueries, kQPW, kCausal, kFast, kSplit>), dim3(m.total_wgs), dim3(kThreads), lds, st, m);
   BASA_HIP_CHECK_LAUNCH("attn_mfma_kernel");
   return BASA_OK;
 }
 // dispatch on block size and head dimension
-template <int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false>
+template <int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
 basa_status launch_shape(const MfmaArgs& m, int B, int d, int BHq, hipStream_t st) {
-  if (d == 128) return B == 128 ? launch_main<128, 128, kWgQueries, kQPW, kCausal, kFast>(m, BHq, st)
-                                : launch_main<64, 128, kWgQueries, kQPW, kCausal, kFast>(m, BHq, st);
-  return B == 128 ? launch_main<128, 64, kWgQueries, kQPW, kCausal, kFast>(m, BHq, st)
-                  : launch_main<64, 64, kWgQueries, kQPW, kCausal, kFast>(m, BHq, st);
+  if (d == 128) return B == 128 ? launch_main<128, 128, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st)
+                                : launch_main<64, 128, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st);
+  return B == 128 ? launch_main<128, 64, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st)
+                  : launch_main<64, 64, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st);
 }
 // The 512-query shape in two passes: without running maxima, then, for the workgroups whose row sums
 // left the safe range (none on ordinary inputs: that launch returns at once), with them.
@@ -855,6 +964,51 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
     m.redo = nullptr;
   }
   return launch_shape<kWideQueries, 64, kCausal, false>(m, B, d, BHq, st);
+}
+
+// Calls whose workgroups do not fill the device (fewer than two of 512 queries per compute unit): the shape
+// (512 or 128 queries per workgroup) and the number of workgroups that share a list, from an estimate of the
+// time.  Lists are split on the 128-query shape (split 512-query workgroups measure no better: 75 against 72 us,
+// dense, 8 heads, L = 4100, d = 64), on the 512-query one only for the causal kernel, which has no
+// other.  The rule sees the heads of one batch entry, so that an entry's result does not depend on the others.
+// One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries, 1.95 us for
+// two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; about 8 us of prologue and
+// epilogue per round of workgroups, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
+// Attention call (tiling of K and V included), one workgroup of 512 queries per list -> this rule:
+// 256 queries against 32K keys, 32 heads on 8, keep 25 %: 351 -> 104 us (128 queries, 8 workgroups per list);
+// 8 heads, L = 2472, d = 64: 63 -> 31 us; 16 heads, L = 1977: 81 -> 38 us; dense, 8 heads, L = 12000, d = 128: 571 us,
+// unchanged (the 128-query shape would take 624).
+// Lists of up to 32 tiles stay whole: splitting them never paid (16 heads, L = 1977, 16 tiles: 39 us whole, 47 in two;
+// 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36), and a whole list on the 128-query shape gives the same bits as on the
+// 512-query one.
+constexpr int kCUs = 256, kMaxSplits = 32, kMinSplitTiles = 32;
+struct Plan { bool solo; int splits; };
+Plan plan_small(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, size_t part_bytes) {
+  const size_t row_bytes = (size_t)heads * Lq * (d * 4 + 8);
+  const double dead = 1.0 - (double)list_len / Nk, scale = d == 128 ? 1.0 : 0.63;
+  Plan best{false, 1};
+  double best_cost = 0.0;
+  for (int solo = 0; solo <= (causal ? 0 : 1); ++solo) {
+    const int queries = solo ? kSoloQueries : kWideQueries;
+    const int blocks = std::min(queries / B, Nq);
+    const int64_t wgs = (int64_t)heads * ceil_div(Nq * B, queries);
+    // blocks in the union of a workgroup's lists: 1.13 lists for four at 50 %, 1.29 at 90 % (full method, measured)
+    const double uni = std::min((double)Nk, list_len * (1.0 + 0.1 * (blocks - 1) * dead));
+    for (int s = 1; s <= kMaxSplits && (s == 1 || ((solo != 0) != causal && list_len * (B / kTileKeys) > kMinSplitTiles && s * row_bytes <= part_bytes)); ++s) {
+      const int64_t per_cu = (wgs * s + kCUs - 1) / kCUs;
+      const double rounds = solo ? (double)((per_cu + 1) / 2) : (double)per_cu;
+      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25 : (double)per_cu * 2.95;
+      const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + 8.0 * rounds +
+                          (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
+      if ((!solo && s == 1) || cost < best_cost) { best_cost = cost; best = Plan{solo != 0, s}; }
+    }
+  }
+  return best;
+}
+// Room for the partial rows of a batch entry, of as many workgroups per list as could be of use: two rounds of workgroups.
+size_t part_bytes_of(int heads, int Lq, int d) {
+  const int64_t splits = std::min<int64_t>(kMaxSplits, 8 * kCUs / ((int64_t)heads * ceil_div(Lq, kSoloQueries)));
+  return splits < 2 ? 0 : (size_t)splits * heads * Lq * (d * 4 + 8);
 }
 
 // Causal variant: per 64-key tile of the ordered keys, the original index of every key (INT_MAX past
@@ -949,6 +1103,9 @@ size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B
   // + one word per 512-query workgroup (which of them the pass with running maxima has to repeat)
   return 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B) + align_up((size_t)BHq * ceil_div(Nq * B, kWideQueries) * 4, 256);
 }
+size_t attn_mfma_split_bytes(int batch, int heads, int Lq, int d) {
+  return align_up((size_t)batch * part_bytes_of(heads, Lq, d), 256);
+}
 
 basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   const int BHq = a.q.batch * a.q.heads, BHkv = a.k.batch * a.k.heads;
@@ -1003,6 +1160,19 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   m.scale_log2e = 1.4426950408889634f / sqrtf((float)d);
   m.probe = nullptr; m.run_if_solo = 0; m.redo = nullptr;
   m.kix = nullptr; m.causal_off = a.causal_off;
+  const int gsz = kWideQueries / B;
+  Plan plan{false, 1};
+  m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
+  if (a.variant == 0 && (int64_t)a.q.heads * Nq * B < 2 * kCUs * kWideQueries) {
+    const size_t base = attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B);
+    plan = plan_small(a.q.heads, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0,
+                      (a.ws_bytes - base) / a.q.batch);
+    if (plan.splits > 1) {
+      m.splits = plan.splits;
+      m.part_o = reinterpret_cast<float*>(ws + base);
+      m.part_ml = reinterpret_cast<float2*>(m.part_o + (size_t)plan.splits * BHq * a.q.L * d);
+    }
+  }
   if (a.causal) {
     int32_t* kix = reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256);
     const int tiles_per_head = Nk * B / kTileKeys;
@@ -1012,14 +1182,29 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
       BASA_HIP_CHECK_LAUNCH("key_index_kernel");
     }
     m.kix = kix;
-    ProfScope prof(K_ATTN, st);
-    return launch_wide<true>(m, B, d, BHq, redo, a.variant != 4, st);
+    if (plan.splits > 1) {
+      ProfScope prof(K_ATTN, st);
+      const basa_status s = launch_shape<kWideQueries, 64, true, false, true>(m, B, d, BHq, st);
+      if (s != BASA_OK) return s;
+    } else {
+      ProfScope prof(K_ATTN, st);
+      return launch_wide<true>(m, B, d, BHq, redo, a.variant != 4, st);
+    }
+    return launch_attn_combine(a, m.part_o, m.part_ml, m.splits, st);
+  }
+  if (plan.solo) {
+    {
+      ProfScope prof(K_ATTN, st);
+      const basa_status s = plan.splits == 1 ? launch_shape<kSoloQueries, 32, false, true>(m, B, d, BHq, st)
+                                             : launch_shape<kSoloQueries, 32, false, false, true>(m, B, d, BHq, st);
+      if (s != BASA_OK || plan.splits == 1) return s;
+    }
+    return launch_attn_combine(a, m.part_o, m.part_ml, m.splits, st);
   }
 
   // Which shape of workgroup: asked for, or (B = d = 128, block lists given, enough work to pay for
   // three tiny launches) decided on the device from how much neighbouring lists overlap.
   int variant = a.variant;
-  const int gsz = kWideQueries / B;
   const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
   if (variant == 0 && !can_probe) variant = a.row_cols ? BASA_ATTN_DEFAULT_LISTS : 3;   // no lists: every block shares every tile
   if (variant == 0) {

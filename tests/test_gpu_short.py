@@ -56,3 +56,20 @@ def test_attention_of_short_calls_against_the_oracle(dtype, d, block, Lq, Lk, ca
         assert np.array_equal(np.isinf(got), np.isinf(ref_lse))
         fin = np.isfinite(ref_lse)
         np.testing.assert_allclose(got[fin], ref_lse[fin], rtol=0, atol=2e-2 if dtype == torch.bfloat16 else 1e-4)
+
+
+@pytest.mark.parametrize("d,block", [(64, 64), (128, 128)])
+@pytest.mark.parametrize("Lk", [33, 64 + 1, 300])
+def test_f32_infinite_scores_and_an_infinite_last_value_row(d, block, Lk):
+    """Keys whose scores are -inf carry no weight, also when a whole tile is made of them, and an infinity in
+    the last V row (what the positions past the end are clamped to) comes out as that infinity."""
+    Q, K, V = _qkv(1, 1, 40, Lk, d, torch.float32, seed=Lk)
+    Q[..., 0] = 1e20
+    K[..., 0] = 0.0
+    K[..., :32, 0] = -1e20                       # score -1e40: below the smallest float
+    V[0, 0, -1, 5] = float("inf")
+    out = bd.basa_dense_attn(Q, K, V, block)
+    torch.cuda.synchronize()
+    q, k, v = Q[0, 0].cpu().double(), K[0, 0].cpu().double(), V[0, 0].cpu().double()
+    ref = torch.softmax(q[:, 1:] @ k[32:, 1:].T / d ** 0.5, -1) @ v[32:]
+    np.testing.assert_allclose(out[0, 0].cpu().double().numpy(), ref.numpy(), rtol=1e-4, atol=1e-4)
