@@ -35,7 +35,7 @@ def _perm(h, L, seed):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("dtype", [torch.float32])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("Lq,Lk", [(1, 1), (31, 33), (65, 129), (200, 1000), (130, 5000), (2048 + 77, 2048 + 77)])
 def test_attention_of_short_calls_against_the_oracle(dtype, d, block, Lq, Lk, causal):
@@ -73,3 +73,26 @@ def test_f32_infinite_scores_and_an_infinite_last_value_row(d, block, Lk):
     q, k, v = Q[0, 0].cpu().double(), K[0, 0].cpu().double(), V[0, 0].cpu().double()
     ref = torch.softmax(q[:, 1:] @ k[32:, 1:].T / d ** 0.5, -1) @ v[32:]
     np.testing.assert_allclose(out[0, 0].cpu().double().numpy(), ref.numpy(), rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("d,block,L", [(64, 64, 300), (128, 128, 200), (128, 64, 4000)])
+def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_maxima(d, block, L):
+    """Scores near +300 and near -300 (log2 units): the 128-query shape has to repeat itself with running maxima
+    (L = 4000 instead splits its lists, which always carry maxima)."""
+    g = torch.Generator().manual_seed(d + L)
+    u = torch.randn(d, generator=g)
+    u /= u.norm()
+    amp = (300.0 * d ** 0.5 / 1.4426950408889634) ** 0.5
+    Q, K, V = (torch.randn(1, 3, L, d, generator=g) * 0.5 for _ in range(3))
+    Q[0, :2] += amp * u
+    K[0, 0] += amp * u
+    K[0, 1] -= amp * u
+    Q, K, V = (t.to(torch.bfloat16).to(DEV) for t in (Q, K, V))
+    out, lse = bd.basa_dense_attn(Q, K, V, block, want_lse=True)
+    torch.cuda.synchronize()
+    for h in range(3):
+        s = np64(Q[0, h]) @ np64(K[0, h]).T / d ** 0.5
+        m = s.max(1, keepdims=True)
+        p = np.exp(s - m)
+        check_output(np64(out[0, h]), p @ np64(V[0, h]) / p.sum(1, keepdims=True), True, f"head {h}")
+        np.testing.assert_allclose(lse[0, h].cpu().numpy(), m[:, 0] + np.log(p.sum(1)), rtol=1e-4, atol=3e-2)
