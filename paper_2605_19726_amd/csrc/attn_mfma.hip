@@ -747,9 +747,12 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     for (int off = 32; off > 0; off >>= 1) wq_max = max(wq_max, __shfl_xor(wq_max, off));
     wq_max = __builtin_amdgcn_readfirstlane(wq_max);
   }
+  int wk_min = INT_MAX;         // kCausal: the smallest original key index in the wave's own list
   auto tile_has_visible_keys = [&](int stage_no) -> bool {
     if constexpr (!kCausal) return true;
-    return __builtin_amdgcn_readfirstlane(kix_lds[stage_no * kIxStride + kTileKeys]) <= wq_max;
+    const int kmin = __builtin_amdgcn_readfirstlane(kix_lds[stage_no * kIxStride + kTileKeys]);
+    wk_min = min(wk_min, kmin);
+    return kmin <= wq_max;
   };
   constexpr std::integral_constant<bool, kFast> kMode{};
   constexpr std::false_type kFull{};
@@ -875,7 +878,9 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     const float l_tot = l_part + __shfl_xor(l_part, 32);
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;    // a query block without any valid key block: zeros
     const int pos = pos_e + 32 * r;
-    if (kFast && !kRetry && pos < a.Lq && sum_is_unsafe(l_tot)) unsafe = 1;
+    // (causal: a query that sees no key of its list has the sum 0 and is done; there are one or two such queries
+    //  per head, and repeating their workgroups took 1210 us after the 8579 of this pass at 32 heads, L = 32768)
+    if (kFast && !kRetry && pos < a.Lq && (!kCausal || q_lim[r] >= wk_min) && sum_is_unsafe(l_tot)) unsafe = 1;
     const int h = h_e;
     if constexpr (kSplit) {
       if (pos < a.Lq) {
@@ -909,7 +914,6 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     }
   }
   if constexpr (kFast && !kRetry) {
-    // (a row without any visible key has the sum 0 as well and is sent round again: it comes out as zeros both times)
     const int any = __syncthreads_or(unsafe);
     if (threadIdx.x == 0) a.redo[logical] = any;
   }
@@ -971,7 +975,7 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // time.  Lists are split on the 128-query shape (split 512-query workgroups measure no better: 75 against 72 us,
 // dense, 8 heads, L = 4100, d = 64), on the 512-query one only for the causal kernel, which has no
 // other.  The rule sees the heads of one batch entry, so that an entry's result does not depend on the others.
-// One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries, 1.95 us for
+// One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries (causal: 3.4), 1.95 us for
 // two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; about 8 us of prologue and
 // epilogue per round of workgroups, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
 // Attention call (tiling of K and V included), one workgroup of 512 queries per list -> this rule:
@@ -979,8 +983,8 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // 8 heads, L = 2472, d = 64: 63 -> 31 us; 16 heads, L = 1977: 81 -> 38 us; dense, 8 heads, L = 12000, d = 128: 571 us,
 // unchanged (the 128-query shape would take 624).
 // Lists of up to 32 tiles stay whole: splitting them never paid (16 heads, L = 1977, 16 tiles: 39 us whole, 47 in two;
-// 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36), and a whole list on the 128-query shape gives the same bits as on the
-// 512-query one.
+// 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36; not so the causal kernel, 8 heads, L = 2100: 94 and 59 in six), and a
+// whole list on the 128-query shape gives the same bits as on the 512-query one.
 constexpr int kCUs = 256, kMaxSplits = 32, kMinSplitTiles = 32;
 struct Plan { bool solo; int splits; };
 Plan plan_small(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, size_t part_bytes) {
@@ -994,10 +998,10 @@ Plan plan_small(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, b
     const int64_t wgs = (int64_t)heads * ceil_div(Nq * B, queries);
     // blocks in the union of a workgroup's lists: 1.13 lists for four at 50 %, 1.29 at 90 % (full method, measured)
     const double uni = std::min((double)Nk, list_len * (1.0 + 0.1 * (blocks - 1) * dead));
-    for (int s = 1; s <= kMaxSplits && (s == 1 || ((solo != 0) != causal && list_len * (B / kTileKeys) > kMinSplitTiles && s * row_bytes <= part_bytes)); ++s) {
+    for (int s = 1; s <= kMaxSplits && (s == 1 || ((solo != 0) != causal && (causal || list_len * (B / kTileKeys) > kMinSplitTiles) && s * row_bytes <= part_bytes)); ++s) {
       const int64_t per_cu = (wgs * s + kCUs - 1) / kCUs;
       const double rounds = solo ? (double)((per_cu + 1) / 2) : (double)per_cu;
-      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25 : (double)per_cu * 2.95;
+      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25 : (double)per_cu * (causal ? 3.4 : 2.95);
       const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + 8.0 * rounds +
                           (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
       if ((!solo && s == 1) || cost < best_cost) { best_cost = cost; best = Plan{solo != 0, s}; }

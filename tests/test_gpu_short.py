@@ -35,16 +35,16 @@ def _perm(h, L, seed):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("dtype,shape", [(torch.float32, 0), (torch.bfloat16, 0), (torch.bfloat16, 3)])
 @pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
 @pytest.mark.parametrize("Lq,Lk", [(1, 1), (31, 33), (65, 129), (200, 1000), (130, 5000), (2048 + 77, 2048 + 77)])
-def test_attention_of_short_calls_against_the_oracle(dtype, d, block, Lq, Lk, causal):
+def test_attention_of_short_calls_against_the_oracle(dtype, shape, d, block, Lq, Lk, causal):
     hq, hk = 2, 1
     Q, K, V = _qkv(hq, hk, Lq, Lk, d, dtype, seed=Lq + Lk + d)
     n_q, n_k = -(-Lq // block), -(-Lk // block)
     cnt, cols, cnt_h, cols_h = _lists(hq, n_q, n_k, Lq + 3 * Lk, n_k)
     pq, pk = _perm(hq, Lq, 1), _perm(hk, Lk, 50)
-    out, lse = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, causal=causal)
+    out, lse = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, attn_shape=shape, causal=causal)
     torch.cuda.synchronize()
     for h in range(hq):
         lists = [cols_h[0, h, g, :cnt_h[0, h, g]] for g in range(n_q)]
