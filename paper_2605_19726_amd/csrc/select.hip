@@ -150,6 +150,73 @@ __global__ __launch_bounds__(256, 2) void block_scores_kernel(const uint4* __res
 }
 
 // ---------------------------------------------------------------------------------
+// The same map for calls whose 128 x 256 tiles would leave most of the device idle.  Such a tile takes a
+// workgroup 1.4-1.6 us per k-step however few of them there are; here a wave owns one 32 x 32 tile (six matrix
+// instructions per k-step, about 0.3 us, a chain on one accumulator) and takes its operands straight from global
+// memory into registers, four k-steps ahead; four waves (2 x 2) to a workgroup, so that each operand is
+// fetched by two of them through the same L1.  No LDS, no barrier.  The accumulator receives the same products in
+// the same order as in block_scores_kernel: same bits.
+// Measured: 1 head, 16 x 16 blocks, d = 64: 22.8 -> 7.6 us; 8 heads, 32 x 32, d = 128: 41.4 -> 11.3; 32 heads,
+// 128 x 128: 46.4 -> 14.1; 32 heads, 2 x 256: 45.2 -> 11.1.
+// ---------------------------------------------------------------------------------
+constexpr int kSmallTile = 64;              // rows and columns of the map per workgroup
+__global__ __launch_bounds__(256) void block_scores_small_kernel(const uint4* __restrict__ featQ,
+                                                                 const uint4* __restrict__ featK,
+                                                                 float* __restrict__ scores, int group, int Nq,
+                                                                 int Nk, int K, int S) {
+  constexpr int kDepth = 4;
+  const int tiles_x = (Nk + kSmallTile - 1) / kSmallTile, tiles_y = (Nq + kSmallTile - 1) / kSmallTile, total = gridDim.x;
+  int logical = blockIdx.x;                     // one XCD, one range of heads
+  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  const int bhq = logical / (tiles_x * tiles_y);
+  const int rem = logical - bhq * (tiles_x * tiles_y);
+  const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
+  const int bhk = bhq / group;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int li = lane & 31, h = lane >> 5;
+  const int row_base = ty * kSmallTile + (wave >> 1) * 32, col_base = tx * kSmallTile + (wave & 1) * 32;
+  if (row_base >= Nq || col_base >= Nk) return;
+  const int n_steps = K >> 4, groups = S >> 3;
+  // (rows and columns past the end read the last one; their results are never stored)
+  const uint4* fq = featQ + ((int64_t)bhq * 3 * groups + h) * Nq + min(row_base + li, Nq - 1);
+  const uint4* fk = featK + ((int64_t)bhk * 3 * groups + h) * Nk + min(col_base + li, Nk - 1);
+  uint4 a[kDepth][3], b[kDepth][3];
+  auto load = [&](int s, uint4 (&ra)[3], uint4 (&rb)[3]) {
+    const int64_t st = 2 * min(s, n_steps - 1);
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      ra[part] = fq[(part * groups + st) * Nq];
+      rb[part] = fk[(part * groups + st) * Nk];
+    }
+  };
+  floatx16 acc = floatx16{0};
+#pragma unroll
+  for (int i = 0; i < kDepth; ++i) load(i, a[i], b[i]);
+  for (int s0 = 0; s0 < n_steps; s0 += kDepth) {
+#pragma unroll
+    for (int i = 0; i < kDepth; ++i) {
+      if (s0 + i < n_steps) {                   // uniform
+        constexpr int PQ[6] = {0, 1, 0, 2, 1, 0};
+        constexpr int PK[6] = {2, 1, 1, 0, 0, 0};
+#pragma unroll
+        for (int pr = 0; pr < 6; ++pr)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[i][PQ[pr]]),
+                                                        __builtin_bit_cast(bf16x8, b[i][PK[pr]]), acc, 0, 0, 0);
+      }
+      load(s0 + i + kDepth, a[i], b[i]);
+    }
+  }
+  float* out = scores + (int64_t)bhq * Nq * Nk;
+  const int col = col_base + li;
+  if (col >= Nk) return;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = row_base + 8 * (r >> 2) + 4 * h + (r & 3);
+    if (row < Nq) out[(int64_t)row * Nk + col] = acc[r];
+  }
+}
+
+// ---------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t ordered_bits(float f) {
   uint32_t u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -646,6 +713,18 @@ basa_status launch_block_scores(const void* featQ, const void* featK, float* sco
   if (kdim_used % 16 != 0 || feat_stride % 8 != 0) {        // whole k-steps of 16
     set_error("score map: contraction length %d is not a multiple of 16", kdim_used);
     return BASA_ERR_UNSUPPORTED;
+  }
+  // Up to 1280 tiles of 64 x 64 (five workgroups per compute unit) the small tiles are faster: at 784 of them (16 heads,
+  // 391 x 391 blocks, d = 64) 19 against 28 us, at 512 (32 heads, 256 x 256, d = 128) 22 against 50; at 2048 (32 heads,
+  // 512 x 512) 70 against 55.
+  const int64_t small_tiles = (int64_t)ceil_div(Nk, kSmallTile) * ceil_div(Nq, kSmallTile) * BHq;
+  if (small_tiles <= 1280) {
+    ProfScope prof(K_SCORES, st);
+    hipLaunchKernelGGL(block_scores_small_kernel, dim3((unsigned)small_tiles), dim3(256), 0, st,
+                       reinterpret_cast<const uint4*>(featQ), reinterpret_cast<const uint4*>(featK), scores, group, Nq, Nk,
+                       kdim_used, feat_stride);
+    BASA_HIP_CHECK_LAUNCH("block_scores_small_kernel");
+    return BASA_OK;
   }
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&block_scores_kernel),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, kScoresLdsBytes);

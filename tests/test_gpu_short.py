@@ -96,3 +96,20 @@ def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_m
         p = np.exp(s - m)
         check_output(np64(out[0, h]), p @ np64(V[0, h]) / p.sum(1, keepdims=True), True, f"head {h}")
         np.testing.assert_allclose(lse[0, h].cpu().numpy(), m[:, 0] + np.log(p.sum(1)), rtol=1e-4, atol=3e-2)
+
+
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+@pytest.mark.parametrize("d,block", [(64, 64), (128, 128)])
+@pytest.mark.parametrize("hq,Lq,Lk", [(2, 1, 1), (2, 64 * 33 - 5, 64 * 65 + 1), (4, 300, 20000), (90, 64 * 64 * 2, 64 * 129)])
+def test_block_scores_of_small_maps(hq, Lq, Lk, d, block, beta):
+    """The 32 x 32 tiles of small maps (the last sizes lie around the largest number of tiles that takes them)."""
+    Q, K, _ = _qkv(hq, 2, Lq, Lk, d, torch.bfloat16, seed=Lq + d)
+    sel = bd.basa_select(Q, K, block, 0.5, beta, bd.SORT_NONE, want_scores=True)
+    torch.cuda.synchronize()
+    for h in (0, hq - 1):
+        mq, vq = o.block_stats(np64(Q[0, h]), block)
+        mk, vk = o.block_stats(np64(K[0, h // (hq // 2)]), block)
+        ref = o.baseline_logits(mq, mk)
+        if beta:
+            ref = ref + beta * o.diag_compensation(mq, vq, mk, vk)
+        np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
