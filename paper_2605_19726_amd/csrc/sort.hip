@@ -8,13 +8,15 @@
 // index, which also makes every word distinct (no stability concerns in the sort).  The
 // segment field is 0 unless the caller gave a list of segments of unequal length; those are
 // sorted as ONE sequence per head, and the segment field keeps every segment in its range.
+#include <algorithm>
+#include <type_traits>
 #include "common.hpp"
 
 namespace basa {
 namespace {
 
 constexpr int kSortThreads = 256;
-constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB)
+constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB); kSmallTile for calls of few words
 constexpr int kMergeItems = 8;       // outputs per thread in a merge pass
 constexpr int kMergeChunk = kSortThreads * kMergeItems;   // 2048 outputs per workgroup
 constexpr int kIdxBits = 27;
@@ -43,7 +45,6 @@ struct SegGeom {
 // ---- the tile's bitonic network, 16 words per thread in registers ------------------------
 // Word i of the tile lives at LDS slot i + i/16 (one pad word per 16: a thread's 16 consecutive
 // words, and the other two ownership patterns below, then hit distinct banks).
-constexpr int kTileSlots = kTile + kTile / 16;
 __device__ __forceinline__ int tile_slot(int i) { return i + (i >> 4); }
 
 // Three ways of dealing the 4096 = 2^12 words to 256 threads x 16 registers; in layout G the
@@ -126,7 +127,88 @@ __device__ __forceinline__ void sort_tile_in_lds(uint64_t* buf, int t) {
   __syncthreads();
 }
 
-template <bool kBf16, int kD>
+// ---- the network of a small tile: 1024 words, 256 threads, 4 words per thread ------------------
+// Wave w sorts words 256 w .. 256 w + 255 by itself (index = 4 lane + register: two index bits in registers, six
+// exchanged between lanes, no barrier); the four runs are then ranked against each other in LDS.  Returns in
+// rank[r] the place of v[r] in the tile (padding words, all alike, get places past the last real word).
+constexpr int kSmallTile = 1024;
+__device__ __forceinline__ void sort_256_in_wave(uint64_t (&v)[4], int lane) {
+#pragma unroll
+  for (int m = 1; m <= 8; ++m) {
+    const int k = 1 << m;              // k = 256: beyond the indices of a wave, everything ascending
+#pragma unroll
+    for (int b = m - 1; b >= 0; --b) {
+      if (b < 2) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if (r & (1 << b)) continue;
+          const int r2 = r | (1 << b);
+          const bool up = ((4 * lane + r) & k) == 0;
+          const uint64_t a = v[r], c = v[r2];
+          const bool swap = (a > c) == up;
+          v[r] = swap ? c : a;
+          v[r2] = swap ? a : c;
+        }
+      } else {
+        const bool up = ((4 * lane) & k) == 0, lower = (lane & (1 << (b - 2))) == 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const uint64_t o = __shfl_xor((unsigned long long)v[r], 1 << (b - 2));
+          const bool take = (o < v[r]) == (lower == up);
+          v[r] = take ? o : v[r];
+        }
+      }
+    }
+  }
+}
+__device__ __forceinline__ void rank_small_tile(uint64_t (&v)[4], int (&rank)[4], uint64_t* buf, int t) {
+  const int lane = t & 63, wave = t >> 6;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = buf[tile_slot(4 * t + r)];
+  sort_256_in_wave(v, lane);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    buf[tile_slot(4 * t + r)] = v[r];          // (each wave rewrites the words it read)
+    rank[r] = 4 * lane + r;
+  }
+  __syncthreads();
+  // Words below v[r] in the other three runs: twelve binary searches side by side.  A position P in a run is kept as
+  // its slot P + P/16, which a step moves by a constant: every probe is one LDS read at an immediate offset, one
+  // compare and one conditional add.
+  int pos[3][4];
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) pos[j][r] = tile_slot(((wave + 1 + j) & 3) * 256);
+  auto probe = [&](auto step, auto move) {       // is word P + step - 1 below v[r]?  Then P moves on by `step`
+    constexpr int kStep = decltype(step)::value, kMove = decltype(move)::value;
+    constexpr int kOff = kStep >= 16 ? kMove - 2 : kStep - 1;
+    uint64_t w[3][4];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[j][r] = buf[pos[j][r] + kOff];
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) pos[j][r] = w[j][r] < v[r] ? pos[j][r] + kMove : pos[j][r];
+  };
+#define BASA_PROBE(S) probe(std::integral_constant<int, S>{}, std::integral_constant<int, S >= 16 ? S + S / 16 : S>{})
+  BASA_PROBE(128); BASA_PROBE(64); BASA_PROBE(32); BASA_PROBE(16); BASA_PROBE(8); BASA_PROBE(4); BASA_PROBE(2); BASA_PROBE(1);
+#undef BASA_PROBE
+  // P <= 255 now; word P itself decides between P and P + 1
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int run0 = tile_slot(((wave + 1 + j) & 3) * 256);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int slot = pos[j][r] - run0;         // P + P/16
+      rank[r] += slot - slot / 17 + (buf[pos[j][r]] < v[r] ? 1 : 0);
+    }
+  }
+}
+
+template <bool kBf16, int kD, int kTileT>
 __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
                                                                       uint64_t* __restrict__ out,
                                                                       int32_t* __restrict__ perm0,
@@ -138,16 +220,16 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
   constexpr int kRowsPerIter = kSortThreads / LPR;
   constexpr int kIters = 8;
   constexpr int kRowsPerPass = kRowsPerIter * kIters;
-  static_assert(kTile % kRowsPerPass == 0, "a tile is a whole number of passes");
-  __shared__ uint64_t buf[kTileSlots];
+  static_assert(kTileT % kRowsPerPass == 0, "a tile is a whole number of passes");
+  __shared__ uint64_t buf[kTileT + kTileT / 16];
 
   const int bh = blockIdx.y;
   const int seg = blockIdx.x / g.tiles_per_seg;
   const int tile = blockIdx.x - seg * g.tiles_per_seg;
   const int seg_end = min((seg + 1) * g.W, g.L);
-  const int start = seg * g.W + tile * kTile;
+  const int start = seg * g.W + tile * kTileT;
   if (start >= seg_end) return;
-  const int n = min(kTile, seg_end - start);
+  const int n = min(kTileT, seg_end - start);
   const int64_t hb = (int64_t)bh * g.L;
   const bool second = bh >= BH0;
   const TensorView& x = second ? x1 : x0;
@@ -267,11 +349,23 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
       }
     }
   }
-  for (int i = n + threadIdx.x; i < kTile; i += kSortThreads) buf[tile_slot(i)] = ~0ull;
+  for (int i = n + threadIdx.x; i < kTileT; i += kSortThreads) buf[tile_slot(i)] = ~0ull;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();
 
-  // ---- phase 2: bitonic network over the kTile words
+  // ---- phase 2: the words of the tile into order
+  if constexpr (kTileT == kSmallTile) {
+    uint64_t v[4];
+    int rank[4];
+    rank_small_tile(v, rank, buf, threadIdx.x);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (v[r] == ~0ull) continue;             // padding
+      if (perm_out) perm_out[hb + start + rank[r]] = idx_of_word(v[r]);
+      else out[hb + start + rank[r]] = v[r];
+    }
+    return;
+  }
   sort_tile_in_lds(buf, threadIdx.x);
   if (perm_out) {
     for (int i = threadIdx.x; i < n; i += kSortThreads) perm_out[hb + start + i] = idx_of_word(buf[tile_slot(i)]);
@@ -390,7 +484,7 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
                                                                    int quads_per_seg, int quads_total) {
   extern __shared__ __attribute__((aligned(16))) uint64_t quad[];       // kQuadWords
   const int t = threadIdx.x;
-  // A workgroup takes quads blockIdx.x, blockIdx.x + gridDim.x, ... (two of them as launched): the words
+  // A workgroup takes quads blockIdx.x, blockIdx.x + gridDim.x, ... (one or two of them as launched): the words
   // of the next one are requested into registers before this one is merged, so the memory system is
   // not idle while the workgroup works in LDS.
   struct Where { const uint64_t* src; int64_t obase; int n; int32_t* perm_out; };
@@ -462,6 +556,54 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
   }
 }
 
+// ---------------------------------------------------------------------------------
+// kG neighbouring runs into one by ranking: the place of a word is its place in its own run plus the number of
+// smaller words in each of the others (no two words are equal), found by kG binary searches side by side.  One
+// word per thread, so that a call of few words is spread over the whole device, where merging kernels have a
+// workgroup walk thousands of words in LDS; the searches of a wave (neighbouring words) touch the same lines.
+// ---------------------------------------------------------------------------------
+// Bound by the probes (kG log2(run) per word, through L1); 32 rows of 7627 words, 8 runs each: 15.6 us against
+// 40 us for the LDS merge of a few workgroups; 2 x 10^6 words in 32 runs: 193 us against 39.
+template <int kG>
+__global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
+                                                                 int32_t* __restrict__ perm0, int32_t* __restrict__ perm1,
+                                                                 int BH0, SegGeom g, int run, int chunks_per_bh) {
+  const int total = gridDim.x;
+  int logical = blockIdx.x;                // a head's words on one XCD: their scattered stores meet in its L2
+  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  const int bh = logical / chunks_per_bh, i = (logical - bh * chunks_per_bh) * kSortThreads + threadIdx.x;
+  if (i >= g.L) return;
+  const int64_t hb = (int64_t)bh * g.L;
+  const int seg = i / g.W, seg0 = seg * g.W, seg_end = min(seg0 + g.W, g.L);
+  const int mine = (i - seg0) / run;
+  const int base = seg0 + mine / kG * kG * run;          // first word of the group of runs
+  const uint64_t v = in[hb + i];
+  int n[kG], pos[kG];
+#pragma unroll
+  for (int j = 0; j < kG; ++j) {
+    n[j] = max(0, min(run, seg_end - (base + j * run)));
+    if (base + j * run == seg0 + mine * run) n[j] = 0;
+    pos[j] = 0;
+  }
+  for (int step = run; step > 0; step >>= 1) {           // (run is a power of two)
+    uint64_t w[kG];
+#pragma unroll
+    for (int j = 0; j < kG; ++j) {
+      const int p = min(pos[j] + step, n[j]);
+      w[j] = in[hb + (p > 0 ? base + j * run + p - 1 : i)];
+    }
+#pragma unroll
+    for (int j = 0; j < kG; ++j)
+      if (pos[j] + step <= n[j] && w[j] < v) pos[j] += step;
+  }
+  int rank = (i - seg0) - mine * run;
+#pragma unroll
+  for (int j = 0; j < kG; ++j) rank += pos[j];
+  int32_t* perm_out = bh < BH0 ? perm0 : (perm1 ? perm1 - (int64_t)BH0 * g.L : nullptr);
+  if (perm_out) perm_out[hb + base + rank] = idx_of_word(v);
+  else out[hb + base + rank] = v;
+}
+
 __global__ void iota_kernel(int32_t* perm, int L, int64_t total) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < total) perm[i] = (int32_t)(i % L);
@@ -498,25 +640,61 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   g.L = L;
   g.W = (window > 0 && window < L) ? window : L;      // a segment list is sorted as one run of L
   g.segs = ceil_div(L, g.W);
-  g.tiles_per_seg = ceil_div(g.W, kTile);
+  // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
+  // merges over the device; many words: tiles of 4096 and the merging kernels, which move each word once or
+  // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
+  // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
+  const bool few = (int64_t)BH * L <= (1 << 19);
+  const int tile = few ? kSmallTile : kTile;
+  g.tiles_per_seg = ceil_div(g.W, tile);
   const bool single = g.tiles_per_seg == 1;
   {
   ProfScope prof(K_NORM_TILE_SORT, st);
   const dim3 grid(g.segs * g.tiles_per_seg, BH);
-#define BASA_KEYS(BF, D)                                                                              \
-  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
+#define BASA_KEYS_T(BF, D, T)                                                                            \
+  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
                      single ? perm0 : nullptr, single ? perm1 : nullptr, keys_out, g, segs)
+#define BASA_KEYS(BF, D)                          \
+  do {                                            \
+    if (few) BASA_KEYS_T(BF, D, kSmallTile);      \
+    else BASA_KEYS_T(BF, D, kTile);               \
+  } while (0)
   if (bf16 && x0.d == 128) BASA_KEYS(true, 128);
   else if (bf16 && x0.d == 64) BASA_KEYS(true, 64);
   else if (!bf16 && x0.d == 128) BASA_KEYS(false, 128);
   else BASA_KEYS(false, 64);
 #undef BASA_KEYS
+#undef BASA_KEYS_T
   BASA_HIP_CHECK_LAUNCH("norm_tile_sort_kernel");
   }
   if (single) return BASA_OK;
 
   uint64_t* src = buf1;
   uint64_t* dst = buf0;
+  if (few) {
+    // as few passes as groups of up to eight runs allow, each with the smallest group that keeps to that number
+    const int chunks = ceil_div(L, kSortThreads);
+    int passes = 0;
+    for (int64_t r = 1; r < ceil_div(g.W, tile); r *= 8) ++passes;
+    for (int64_t run = tile; run < g.W; --passes) {
+      const int64_t runs = (g.W + run - 1) / run;
+      int G = 2;
+      while (G < 8 && (passes == 1 ? G : passes == 2 ? G * G : (int64_t)G * G * G) < runs) G *= 2;
+      const bool last = run * G >= g.W;
+      ProfScope prof(K_MERGE, st);
+#define BASA_RANK(N)                                                                                             \
+  hipLaunchKernelGGL(rank_runs_kernel<N>, dim3((unsigned)chunks * BH), dim3(kSortThreads), 0, st, src, dst,      \
+                     last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, (int)run, chunks)
+      if (G == 2) BASA_RANK(2);
+      else if (G == 4) BASA_RANK(4);
+      else BASA_RANK(8);
+#undef BASA_RANK
+      BASA_HIP_CHECK_LAUNCH("rank_runs_kernel");
+      uint64_t* t = src; src = dst; dst = t;
+      run *= G;
+    }
+    return BASA_OK;
+  }
   int run0 = kTile;
   if (g.W > 2 * kTile) {
     // more than two tiles per segment: the first two passes in one launch
@@ -527,7 +705,9 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
     ProfScope prof(K_MERGE, st);
     const int quads_total = BH * g.segs * quads_per_seg;
-    hipLaunchKernelGGL(merge_quads_kernel, dim3(ceil_div(quads_total, 2)), dim3(kQuadThreads), kQuadWords * 8, st,
+    // one quad per workgroup while there are compute units for all (64 quads: 21.7 us, two per workgroup 37)
+    const int quad_wgs = quads_total <= 512 ? std::min(quads_total, 256) : ceil_div(quads_total, 2);
+    hipLaunchKernelGGL(merge_quads_kernel, dim3(quad_wgs), dim3(kQuadThreads), kQuadWords * 8, st,
                        src, dst, last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, quads_per_seg, quads_total);
     BASA_HIP_CHECK_LAUNCH("merge_quads_kernel");
     uint64_t* t = src; src = dst; dst = t;

@@ -113,3 +113,18 @@ def test_block_scores_of_small_maps(hq, Lq, Lk, d, block, beta):
         if beta:
             ref = ref + beta * o.diag_compensation(mq, vq, mk, vk)
         np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
+
+
+@pytest.mark.parametrize("window", [0, 128, 1024, 9 * 128, 5120])
+@pytest.mark.parametrize("heads,L", [(2, 1), (3, 255), (2, 257), (2, 1024), (2, 1025), (1, 4097), (2, 16385), (1, 70001),
+                                     (8, 65536), (8, 65537)])
+def test_norm_sort_around_the_tile_and_pass_sizes(heads, L, window):
+    """Small tiles and ranked runs (2 to 69 of them, one to three passes), and past 2^19 words the large tiles."""
+    g = torch.Generator(device=DEV).manual_seed(L)
+    x = torch.randn((1, heads, L, 64), generator=g, device=DEV).to(torch.bfloat16)
+    if L > 300:
+        x[0, 0, 100:140] = x[0, 0, 200:240]              # exact ties
+    perm = bd.basa_norm_sort(x, 64 if window % 128 else 128, window=window)
+    torch.cuda.synchronize()
+    for h in {0, heads - 1}:
+        assert np.array_equal(perm[0, h].cpu().numpy(), o.norm_sort(np64(x[0, h]), window)), h
