@@ -1010,8 +1010,9 @@ Plan plan_small(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, b
   return best;
 }
 // Room for the partial rows of a batch entry, of as many workgroups per list as could be of use: two rounds of workgroups.
-size_t part_bytes_of(int heads, int Lq, int d) {
-  const int64_t splits = std::min<int64_t>(kMaxSplits, 8 * kCUs / ((int64_t)heads * ceil_div(Lq, kSoloQueries)));
+size_t part_bytes_of(int heads, int Lq, int Nk, int B, int d, bool causal) {
+  if (!causal && Nk * (B / kTileKeys) <= kMinSplitTiles) return 0;
+  const int64_t splits = std::min<int64_t>(std::min(kMaxSplits, Nk), 8 * kCUs / ((int64_t)heads * ceil_div(Lq, kSoloQueries)));
   return splits < 2 ? 0 : (size_t)splits * heads * Lq * (d * 4 + 8);
 }
 
@@ -1107,8 +1108,8 @@ size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B
   // + one word per 512-query workgroup (which of them the pass with running maxima has to repeat)
   return 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B) + align_up((size_t)BHq * ceil_div(Nq * B, kWideQueries) * 4, 256);
 }
-size_t attn_mfma_split_bytes(int batch, int heads, int Lq, int d) {
-  return align_up((size_t)batch * part_bytes_of(heads, Lq, d), 256);
+size_t attn_mfma_split_bytes(int batch, int heads, int Lq, int Lk, int d, int B, bool causal) {
+  return align_up((size_t)batch * part_bytes_of(heads, Lq, ceil_div(Lk, B), B, d, causal), 256);
 }
 
 basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
