@@ -322,8 +322,7 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
 
   const bool sort_q = p->sort == BASA_SORT_Q || p->sort == BASA_SORT_QK;
   const bool sort_k = p->sort == BASA_SORT_K || p->sort == BASA_SORT_QK;
-  const bool same_len = q->L == k->L;       // then Q and K share every launch
-  if (sort_q && sort_k && same_len) {
+  if (sort_q && sort_k) {                   // Q and K share the launches
     s = launch_norm_sort2(qv, kv, p->window, segs, perm_q, perm_k, sort_ws, st);
     if (s != BASA_OK) return s;
   } else {
@@ -336,12 +335,7 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
   }
   const int32_t* pq = sort_q ? perm_q : nullptr;
   const int32_t* pk = sort_k ? perm_k : nullptr;
-  if (same_len) {
-    if ((s = launch_select_features(qv, pq, featq, kv, pk, featk, B, p->beta, st)) != BASA_OK) return s;
-  } else {
-    if ((s = launch_block_stats(qv, pq, B, nullptr, nullptr, featq, 1, p->beta, nullptr, st)) != BASA_OK) return s;
-    if ((s = launch_block_stats(kv, pk, B, nullptr, nullptr, featk, 0, p->beta, nullptr, st)) != BASA_OK) return s;
-  }
+  if ((s = launch_select_features(qv, pq, featq, kv, pk, featk, B, p->beta, st)) != BASA_OK) return s;
   const int kdim = (p->beta == 0.f) ? q->d : 3 * q->d;
   // fixed count per row, nobody asks for the map, no second pass over it: the map stays on chip
   const bool fusable = !scores && !p->causal && p->mass_target == 0.0 && p->budget_total == 0 &&

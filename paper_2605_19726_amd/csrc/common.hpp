@@ -64,7 +64,7 @@ struct SegList {
 };
 basa_status launch_norm_sort(const TensorView& x, int window, const SegList& segs, int32_t* perm, float* keys_out,
                              void* ws, hipStream_t st);
-// Two tensors of identical L, d and dtype through the same launches (ws sized for both).
+// Two tensors of identical d and dtype through the same launches (ws sized for both at the larger L).
 basa_status launch_norm_sort2(const TensorView& q, const TensorView& k, int window, const SegList& segs, int32_t* perm_q,
                               int32_t* perm_k, void* ws, hipStream_t st);
 basa_status launch_iota_perm(int32_t* perm, int BH, int L, hipStream_t st);
@@ -83,7 +83,7 @@ basa_status launch_block_stats(const TensorView& x, const int32_t* perm, int B, 
                                float* var, void* feat, int feat_is_query, float beta, void* x_sorted,
                                hipStream_t st);
 
-// Selection features of Q (query side) and K (key side), identical L / d / dtype, in one launch.
+// Selection features of Q (query side) and K (key side), identical d / dtype, in one launch.
 basa_status launch_select_features(const TensorView& q, const int32_t* perm_q, void* feat_q,
                                    const TensorView& k, const int32_t* perm_k, void* feat_k, int B,
                                    float beta, hipStream_t st);

@@ -35,8 +35,8 @@ __device__ __forceinline__ int32_t idx_of_word(uint64_t w) { return (int32_t)((u
 // are in different phases, so the LDS-bound sort of one hides under the HBM-bound key pass of
 // the others.
 // Segment s of a head covers [s*W, min((s+1)*W, L)); tiles never straddle segments.
-// Up to two tensors of the same L, d and dtype are handled by one launch: rows blockIdx.y <
-// BH0 belong to x0, the rest to x1; packed words and permutations of x1 follow those of x0.
+// Up to two tensors of the same d and dtype are handled by one launch: rows blockIdx.y < BH0 belong
+// to x0 (geometry g0), the rest to x1 (g1); packed words of x1 follow those of x0.
 // ---------------------------------------------------------------------------------
 struct SegGeom {
   int L, W, segs, tiles_per_seg;
@@ -213,8 +213,8 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
                                                                       uint64_t* __restrict__ out,
                                                                       int32_t* __restrict__ perm0,
                                                                       int32_t* __restrict__ perm1,
-                                                                      float* __restrict__ keys_out, SegGeom g,
-                                                                      SegList sl) {
+                                                                      float* __restrict__ keys_out, SegGeom g0,
+                                                                      SegGeom g1, SegList sl) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;          // lanes per row: 8, 16 or 32
   constexpr int kRowsPerIter = kSortThreads / LPR;
@@ -223,7 +223,9 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
   static_assert(kTileT % kRowsPerPass == 0, "a tile is a whole number of passes");
   __shared__ uint64_t buf[kTileT + kTileT / 16];
 
-  const int bh = blockIdx.y;
+  const bool second = (int)blockIdx.y >= BH0;
+  const SegGeom& g = second ? g1 : g0;
+  const int bh = second ? blockIdx.y - BH0 : blockIdx.y;
   const int seg = blockIdx.x / g.tiles_per_seg;
   const int tile = blockIdx.x - seg * g.tiles_per_seg;
   const int seg_end = min((seg + 1) * g.W, g.L);
@@ -231,10 +233,10 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
   if (start >= seg_end) return;
   const int n = min(kTileT, seg_end - start);
   const int64_t hb = (int64_t)bh * g.L;
-  const bool second = bh >= BH0;
   const TensorView& x = second ? x1 : x0;
-  int32_t* perm_out = second ? (perm1 ? perm1 - (int64_t)BH0 * g.L : nullptr) : perm0;
-  const char* base = reinterpret_cast<const char*>(x.ptr) + x.head_offset(second ? bh - BH0 : bh) * kElem;
+  if (second) out += (int64_t)BH0 * g0.L;
+  int32_t* perm_out = second ? perm1 : perm0;
+  const char* base = reinterpret_cast<const char*>(x.ptr) + x.head_offset(bh) * kElem;
   const int sub = threadIdx.x % LPR;
   const int rig = threadIdx.x / LPR;
   // segment of the tile's first token; nearly every tile lies inside one segment
@@ -623,54 +625,19 @@ basa_status launch_iota_perm(int32_t* perm, int BH, int L, hipStream_t st) {
   return BASA_OK;
 }
 
-// Sort one tensor (x1 == nullptr) or two tensors of identical L, d and dtype in the same launches.
-static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, int window, const SegList& segs, int32_t* perm0,
-                                  int32_t* perm1, float* keys_out, void* ws, hipStream_t st) {
-  const int BH0 = x0.batch * x0.heads, BH1 = x1 ? x1->batch * x1->heads : 0, L = x0.L;
-  const int BH = BH0 + BH1;
-  if (BH == 0 || L == 0) return BASA_OK;
-  uint64_t* buf0 = reinterpret_cast<uint64_t*>(ws);
-  uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) +
-                                               align_up((size_t)BH * L * sizeof(uint64_t), 256));
-  const TensorView& xb = x1 ? *x1 : x0;
-  const bool bf16 = x0.dtype == BASA_BF16;
-  (void)buf0;
-
+static SegGeom geom_of(int L, int window, int tile) {
   SegGeom g;
   g.L = L;
   g.W = (window > 0 && window < L) ? window : L;      // a segment list is sorted as one run of L
   g.segs = ceil_div(L, g.W);
-  // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
-  // merges over the device; many words: tiles of 4096 and the merging kernels, which move each word once or
-  // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
-  // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
-  const bool few = (int64_t)BH * L <= (1 << 19);
-  const int tile = few ? kSmallTile : kTile;
   g.tiles_per_seg = ceil_div(g.W, tile);
-  const bool single = g.tiles_per_seg == 1;
-  {
-  ProfScope prof(K_NORM_TILE_SORT, st);
-  const dim3 grid(g.segs * g.tiles_per_seg, BH);
-#define BASA_KEYS_T(BF, D, T)                                                                            \
-  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
-                     single ? perm0 : nullptr, single ? perm1 : nullptr, keys_out, g, segs)
-#define BASA_KEYS(BF, D)                          \
-  do {                                            \
-    if (few) BASA_KEYS_T(BF, D, kSmallTile);      \
-    else BASA_KEYS_T(BF, D, kTile);               \
-  } while (0)
-  if (bf16 && x0.d == 128) BASA_KEYS(true, 128);
-  else if (bf16 && x0.d == 64) BASA_KEYS(true, 64);
-  else if (!bf16 && x0.d == 128) BASA_KEYS(false, 128);
-  else BASA_KEYS(false, 64);
-#undef BASA_KEYS
-#undef BASA_KEYS_T
-  BASA_HIP_CHECK_LAUNCH("norm_tile_sort_kernel");
-  }
-  if (single) return BASA_OK;
+  return g;
+}
 
-  uint64_t* src = buf1;
-  uint64_t* dst = buf0;
+// Sorted tiles in src merged into whole segments: BH rows (the first BH0 go to perm0, the rest to perm1).
+static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, const SegGeom& g, int tile, bool few,
+                               int32_t* perm0, int32_t* perm1, hipStream_t st) {
+  const int L = g.L;
   if (few) {
     // as few passes as groups of up to eight runs allow, each with the smallest group that keeps to that number
     const int chunks = ceil_div(L, kSortThreads);
@@ -725,6 +692,54 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
     uint64_t* t = src; src = dst; dst = t;
   }
   return BASA_OK;
+}
+
+// Sort one tensor (x1 == nullptr) or two tensors of identical d and dtype in the same launches.
+static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, int window, const SegList& segs, int32_t* perm0,
+                                  int32_t* perm1, float* keys_out, void* ws, hipStream_t st) {
+  const int BH0 = x0.batch * x0.heads, BH1 = x1 ? x1->batch * x1->heads : 0, L0 = x0.L, L1 = x1 ? x1->L : x0.L;
+  const int64_t words0 = (int64_t)BH0 * L0, words = words0 + (int64_t)BH1 * L1;
+  if (words == 0) return BASA_OK;
+  // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
+  // merges over the device; many words: tiles of 4096 and the merging kernels, which move each word once or
+  // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
+  // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
+  const bool few = words <= (1 << 19);
+  if (x1 && ((L0 != L1 && !few) || BH0 + BH1 > 65535)) {       // (65535: the grid's second dimension)
+    const basa_status s = norm_sort_impl(x0, nullptr, window, segs, perm0, nullptr, keys_out, ws, st);
+    return s != BASA_OK ? s : norm_sort_impl(*x1, nullptr, window, segs, perm1, nullptr, nullptr, ws, st);
+  }
+  uint64_t* buf0 = reinterpret_cast<uint64_t*>(ws);
+  uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + align_up((size_t)words * sizeof(uint64_t), 256));
+  const TensorView& xb = x1 ? *x1 : x0;
+  const bool bf16 = x0.dtype == BASA_BF16;
+  const int tile = few ? kSmallTile : kTile;
+  const SegGeom g0 = geom_of(L0, window, tile), g1 = geom_of(L1, window, tile);
+  const bool single0 = g0.tiles_per_seg == 1, single1 = g1.tiles_per_seg == 1;
+  {
+  ProfScope prof(K_NORM_TILE_SORT, st);
+  const dim3 grid(std::max(g0.segs * g0.tiles_per_seg, x1 ? g1.segs * g1.tiles_per_seg : 0), BH0 + BH1);
+#define BASA_KEYS_T(BF, D, T)                                                                            \
+  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
+                     single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs)
+#define BASA_KEYS(BF, D)                          \
+  do {                                            \
+    if (few) BASA_KEYS_T(BF, D, kSmallTile);      \
+    else BASA_KEYS_T(BF, D, kTile);               \
+  } while (0)
+  if (bf16 && x0.d == 128) BASA_KEYS(true, 128);
+  else if (bf16 && x0.d == 64) BASA_KEYS(true, 64);
+  else if (!bf16 && x0.d == 128) BASA_KEYS(false, 128);
+  else BASA_KEYS(false, 64);
+#undef BASA_KEYS
+#undef BASA_KEYS_T
+  BASA_HIP_CHECK_LAUNCH("norm_tile_sort_kernel");
+  }
+  if (L0 == L1) return single0 ? BASA_OK : merge_tiles(buf1, buf0, BH0 + BH1, BH0, g0, tile, few, perm0, perm1, st);
+  basa_status s = BASA_OK;
+  if (!single0) s = merge_tiles(buf1, buf0, BH0, BH0, g0, tile, few, perm0, nullptr, st);
+  if (s == BASA_OK && !single1) s = merge_tiles(buf1 + words0, buf0 + words0, BH1, BH1, g1, tile, few, perm1, nullptr, st);
+  return s;
 }
 
 basa_status launch_norm_sort(const TensorView& x, int window, const SegList& segs, int32_t* perm, float* keys_out,

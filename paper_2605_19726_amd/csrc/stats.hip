@@ -6,13 +6,14 @@
 // Besides mean/var it can emit the block's selection features, with which the
 // compensated logit of Eq. 2 + Eq. 14 is ONE dot product of length 3d:
 //   l' = [Qbar/sqrt(d), beta*VarQ/d, beta*Qbar^2/d] . [Kbar, Kbar^2 + VarK, VarK]
+#include <algorithm>
 #include "common.hpp"
 
 namespace basa {
 namespace {
 
-// One tensor's share of a launch.  Up to two tensors of identical L, d and dtype go through the
-// same launch: rows blockIdx.y < BH0 belong to job 0, the rest to job 1.
+// One tensor's share of a launch.  Up to two tensors of identical d and dtype go through the same
+// launch: rows blockIdx.y < BH0 belong to job 0, the rest to job 1.
 struct StatsJob {
   TensorView x;
   const int32_t* perm;
@@ -23,7 +24,7 @@ struct StatsJob {
   void* sorted_out;          // nullable: the ordered sequence x[perm], contiguous [BH][L][d], dtype of x
 };
 
-constexpr int kGroup = 8;      // consecutive blocks per workgroup
+constexpr int kGroup = 8;      // consecutive blocks per workgroup, at most
 
 // Element e of a 16-byte chunk as a float.
 template <bool kBf16>
@@ -33,17 +34,17 @@ __device__ __forceinline__ float chunk_elem(const uint4& r, int e) {
   else return __uint_as_float(w[e]);
 }
 
-// A workgroup pools kGroup consecutive blocks of the ordered sequence, one after the other.  A row
+// A workgroup pools per_wg <= kGroup consecutive blocks of the ordered sequence, one after the other.  A row
 // is 16-byte chunks spread over LPR adjacent lanes; a thread holds chunk `sub` of ITERS rows.  The
 // rows of block b+1 (and the permutation entries of block b+2) are requested before block b is
 // reduced, so the workgroup has loads in flight all the time: the gather is bound by the number of
 // bytes in flight, and a kernel that loads, reduces and retires one block at a time has none in
 // flight for half of its life.  Sums over the rows held by a wave are taken with lane exchanges,
-// over the four waves through LDS.  The features of the kGroup blocks are collected in LDS and
+// over the four waves through LDS.  The features of its blocks are collected in LDS and
 // written at the end as 128-byte runs (in the [part][k/8][g][k%8] layout one block's features are
 // 16-byte pieces 16 KB apart, which cost a fifth of the kernel when every block wrote its own).
 template <bool kBf16, int kD, int kB>
-__global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob j1, int BH0, float beta) {
+__global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob j1, int BH0, float beta, int per_wg) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;       // lanes per row
   constexpr int RPI = 256 / LPR;             // rows per iteration
@@ -64,8 +65,9 @@ __global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob 
   const int bh = second ? blockIdx.y - BH0 : blockIdx.y;
   const int L = x.L;
   const int N = (L + kB - 1) / kB;
-  const int g0 = blockIdx.x * kGroup;
-  const int nb = min(kGroup, N - g0);        // blocks of this workgroup that exist (>= 1 by the grid)
+  const int g0 = blockIdx.x * per_wg;
+  const int nb = min(per_wg, N - g0);        // blocks of this workgroup that exist
+  if (nb <= 0) return;                       // (the other tensor of the launch is the longer one)
   const int sub = threadIdx.x % LPR, rig = threadIdx.x / LPR;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const char* base = reinterpret_cast<const char*>(x.ptr) + x.head_offset(bh) * kElem;
@@ -272,14 +274,24 @@ static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int 
   const TensorView& x = j0.x;
   const int BH0 = x.batch * x.heads;
   const int BH1 = j1 ? j1->x.batch * j1->x.heads : 0;
-  const int N = ceil_div(x.L, B);
-  if (BH0 + BH1 == 0 || N == 0) return BASA_OK;
-  dim3 grid(ceil_div(N, kGroup), BH0 + BH1);
+  if (BH0 + BH1 == 0 || x.L == 0) return BASA_OK;
+  if (j1 && BH0 + BH1 > 65535) {               // the grid's second dimension
+    const basa_status s = block_stats_impl(j0, nullptr, B, beta, st);
+    return s != BASA_OK ? s : block_stats_impl(*j1, nullptr, B, beta, st);
+  }
+  const int N = std::max(ceil_div(x.L, B), j1 ? ceil_div(j1->x.L, B) : 0);
+  // Blocks per workgroup: a workgroup takes its blocks one after the other, so calls of few blocks get as many
+  // workgroups as there are (16 + 16 heads of 16 blocks: 11.0 us against 28.7 with 8 to a workgroup; 1920 blocks: 20.0
+  // with 2, 29.0 with 8; 5120: 24.3 with 4, 28.3 with 8), large ones the full runs of features (8192: 57.5 with 8,
+  // 63 with 2, 73 with 1).
+  const int64_t blocks = (int64_t)BH0 * ceil_div(x.L, B) + (int64_t)BH1 * (j1 ? ceil_div(j1->x.L, B) : 0);
+  const int per_wg = blocks <= 1024 ? 1 : blocks <= 2048 ? 2 : blocks <= 6144 ? 4 : kGroup;
+  dim3 grid(ceil_div(N, per_wg), BH0 + BH1);
   ProfScope prof(K_STATS, st);
   const bool bf = x.dtype == BASA_BF16;
   const StatsJob& jb = j1 ? *j1 : j0;
 #define BASA_STATS(BF, D, BB) \
-  hipLaunchKernelGGL((block_stats_kernel<BF, D, BB>), grid, dim3(256), 0, st, j0, jb, BH0, beta)
+  hipLaunchKernelGGL((block_stats_kernel<BF, D, BB>), grid, dim3(256), 0, st, j0, jb, BH0, beta, per_wg)
   if (bf && x.d == 128 && B == 128) BASA_STATS(true, 128, 128);
   else if (bf && x.d == 128 && B == 64) BASA_STATS(true, 128, 64);
   else if (bf && x.d == 64 && B == 128) BASA_STATS(true, 64, 128);

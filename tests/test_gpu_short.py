@@ -128,3 +128,18 @@ def test_norm_sort_around_the_tile_and_pass_sizes(heads, L, window):
     torch.cuda.synchronize()
     for h in {0, heads - 1}:
         assert np.array_equal(perm[0, h].cpu().numpy(), o.norm_sort(np64(x[0, h]), window)), h
+
+
+@pytest.mark.parametrize("dtype,d,block", [(torch.bfloat16, 128, 128), (torch.float32, 64, 64)])
+@pytest.mark.parametrize("hq,hk,Lq,Lk", [(4, 2, 1, 9000), (4, 2, 2000, 70), (2, 2, 5000, 3000), (8, 4, 500, 131072)])
+def test_sort_and_features_of_sequences_of_different_lengths(hq, hk, Lq, Lk, dtype, d, block):
+    """Q and K share the launches although their tiles, passes and block counts differ (the last: too many words)."""
+    Q, K, _ = _qkv(hq, hk, Lq, Lk, d, dtype, seed=Lq)
+    sel = bd.basa_select(Q, K, block, 0.5, want_scores=True)
+    torch.cuda.synchronize()
+    for h in (0, hq - 1):
+        q, k = np64(Q[0, h]), np64(K[0, h // (hq // hk)])
+        ref = o.select(q, k, block, 0.5, 1.0)
+        assert np.array_equal(sel.perm_q[0, h].cpu().numpy(), ref["perm_q"])
+        assert np.array_equal(sel.perm_k[0, h // (hq // hk)].cpu().numpy(), ref["perm_k"])
+        np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref["logits"], rtol=2e-5, atol=2e-5)
