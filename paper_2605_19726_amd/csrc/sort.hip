@@ -560,11 +560,11 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
 
 // ---------------------------------------------------------------------------------
 // kG neighbouring runs into one by ranking: the place of a word is its place in its own run plus the number of
-// smaller words in each of the others (no two words are equal), found by kG binary searches side by side.  One
+// smaller words in each of the others (no two words are equal), found by kG - 1 binary searches side by side.  One
 // word per thread, so that a call of few words is spread over the whole device, where merging kernels have a
 // workgroup walk thousands of words in LDS; the searches of a wave (neighbouring words) touch the same lines.
 // ---------------------------------------------------------------------------------
-// Bound by the probes (kG log2(run) per word, through L1); 32 rows of 7627 words, 8 runs each: 15.6 us against
+// Bound by the probes ((kG - 1) log2(run) per word, through L1); 32 rows of 7627 words, 8 runs each: 15.6 us against
 // 40 us for the LDS merge of a few workgroups; 2 x 10^6 words in 32 runs: 193 us against 39.
 template <int kG>
 __global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
@@ -580,27 +580,29 @@ __global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t*
   const int mine = (i - seg0) / run;
   const int base = seg0 + mine / kG * kG * run;          // first word of the group of runs
   const uint64_t v = in[hb + i];
-  int n[kG], pos[kG];
+  constexpr int kOthers = kG - 1;
+  const int mine_g = mine % kG;
+  int start[kOthers], n[kOthers], pos[kOthers];
 #pragma unroll
-  for (int j = 0; j < kG; ++j) {
-    n[j] = max(0, min(run, seg_end - (base + j * run)));
-    if (base + j * run == seg0 + mine * run) n[j] = 0;
+  for (int j = 0; j < kOthers; ++j) {
+    start[j] = base + (j < mine_g ? j : j + 1) * run;
+    n[j] = max(0, min(run, seg_end - start[j]));
     pos[j] = 0;
   }
   for (int step = run; step > 0; step >>= 1) {           // (run is a power of two)
-    uint64_t w[kG];
+    uint64_t w[kOthers];
 #pragma unroll
-    for (int j = 0; j < kG; ++j) {
+    for (int j = 0; j < kOthers; ++j) {
       const int p = min(pos[j] + step, n[j]);
-      w[j] = in[hb + (p > 0 ? base + j * run + p - 1 : i)];
+      w[j] = in[hb + (p > 0 ? start[j] + p - 1 : i)];
     }
 #pragma unroll
-    for (int j = 0; j < kG; ++j)
+    for (int j = 0; j < kOthers; ++j)
       if (pos[j] + step <= n[j] && w[j] < v) pos[j] += step;
   }
   int rank = (i - seg0) - mine * run;
 #pragma unroll
-  for (int j = 0; j < kG; ++j) rank += pos[j];
+  for (int j = 0; j < kOthers; ++j) rank += pos[j];
   int32_t* perm_out = bh < BH0 ? perm0 : (perm1 ? perm1 - (int64_t)BH0 * g.L : nullptr);
   if (perm_out) perm_out[hb + base + rank] = idx_of_word(v);
   else out[hb + base + rank] = v;
