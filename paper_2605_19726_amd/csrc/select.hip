@@ -827,6 +827,8 @@ basa_status launch_row_select(const float* scores, int rows_total, int Nk, int k
                          kappa, mass_target, min_keep, keep_in, live, mask_bits, row_count, row_cols, row_mass); \
   } while (0)
   if (Nk <= 256) BASA_SEL(4);
+  else if (Nk <= 512) BASA_SEL(8);
+  else if (Nk <= 768) BASA_SEL(12);
   else if (Nk <= 1024) BASA_SEL(16);
   else if (Nk <= 2048) BASA_SEL(32);
   else if (Nk <= 4096) BASA_SEL(64);
