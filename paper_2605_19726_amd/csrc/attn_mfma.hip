@@ -108,36 +108,30 @@ constexpr int q_reg_steps(int d, int qpw, bool causal = false, bool fast = false
 // ---------------------------------------------------------------------------------
 // Gather kernels
 // ---------------------------------------------------------------------------------
-// Rows of a bf16 tensor in sorted order, zero-padded; swizzle = 1 writes K-tile order.
+// 64 rows of K in sorted order, zero-padded, in K-tile order.
 template <int D>
-__global__ __launch_bounds__(256) void gather_rows_kernel(TensorView x, const int32_t* __restrict__ perm,
-                                                          uint4* __restrict__ dst, int rows_padded,
-                                                          int swizzle) {
+__device__ __forceinline__ void gather_k_tile(const TensorView& x, const int32_t* __restrict__ pm, uint4* __restrict__ dst,
+                                              int bh, int tile, int tiles_per_head) {
   constexpr int CPR = Geo<D>::kChunksPerRow, RPI = 256 / CPR, ITERS = 64 / RPI;
-  const int bh = blockIdx.y;
   const int sub = threadIdx.x % CPR, rig = threadIdx.x / CPR;
-  const int32_t* pm = perm ? perm + (int64_t)bh * x.L : nullptr;
   const char* base = reinterpret_cast<const char*>(x.ptr) + x.head_offset(bh) * 2;
   uint4 v[ITERS];
-  gather_chunks<ITERS>(v, pm, base, x.L, (int64_t)x.stride_l * 2, blockIdx.x * 64 + rig, RPI, sub);
+  gather_chunks<ITERS>(v, pm, base, x.L, (int64_t)x.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
-    const int pos = blockIdx.x * 64 + it * RPI + rig;
-    const int c = swizzle ? (sub ^ (pos & (CPR - 1))) : sub;
-    if (pos < rows_padded) dst[((int64_t)bh * rows_padded + pos) * CPR + c] = v[it];
+    const int pos = tile * kTileKeys + it * RPI + rig;
+    dst[((int64_t)bh * tiles_per_head * kTileKeys + pos) * CPR + (sub ^ (pos & (CPR - 1)))] = v[it];
   }
 }
 
 // V: gather 64 sorted rows, transpose through LDS, write the swizzled [D][64] tile.
 template <int D>
-__global__ __launch_bounds__(256) void gather_vt_kernel(TensorView v, const int32_t* __restrict__ perm,
-                                                        uint4* __restrict__ dst, int tiles_per_head) {
+__device__ __forceinline__ void gather_vt_tile(const TensorView& v, const int32_t* __restrict__ pm, uint4* __restrict__ dst,
+                                               int bh, int tile, int tiles_per_head) {
   constexpr int CPR = Geo<D>::kChunksPerRow, RPI = 256 / CPR, ITERS = 64 / RPI;
   constexpr int kRowStride = D + 8;   // one row + 16 B pad
   __shared__ __attribute__((aligned(16))) uint16_t rows[kTileKeys][kRowStride];
-  const int bh = blockIdx.y, tile = blockIdx.x;
   const int sub = threadIdx.x % CPR, rig = threadIdx.x / CPR;
-  const int32_t* pm = perm ? perm + (int64_t)bh * v.L : nullptr;
   const char* base = reinterpret_cast<const char*>(v.ptr) + v.head_offset(bh) * 2;
   uint4 val[ITERS];
   gather_chunks<ITERS>(val, pm, base, v.L, (int64_t)v.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
@@ -161,6 +155,43 @@ __global__ __launch_bounds__(256) void gather_vt_kernel(TensorView v, const int3
     o.x = e[0] | ((uint32_t)e[1] << 16); o.y = e[2] | ((uint32_t)e[3] << 16);
     o.z = e[4] | ((uint32_t)e[5] << 16); o.w = e[6] | ((uint32_t)e[7] << 16);
     dst[(((int64_t)bh * tiles_per_head + tile) * D + dd) * 8 + (s8 ^ ((dd >> 1) & 7))] = o;
+  }
+}
+
+// Causal variant: the original index of every key of a tile (INT_MAX past the end of the sequence), then the smallest
+// and the largest of the 64.
+__device__ __forceinline__ void key_index_tile(const int32_t* __restrict__ pm, int Lk, int32_t* __restrict__ out, int bh, int tile,
+                                               int tiles_per_head) {
+  const int lane = threadIdx.x;
+  if (lane >= 64) return;
+  const int pos = tile * kTileKeys + lane;
+  const int idx = pos < Lk ? perm_at(pm, 0, pos, Lk) : INT_MAX;
+  int lo = idx, hi = idx;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off));
+    hi = max(hi, __shfl_xor(hi, off));
+  }
+  int32_t* o = out + ((int64_t)bh * tiles_per_head + tile) * kIxStride;
+  o[lane] = idx;
+  if (lane < 4) o[kTileKeys + lane] = lane == 0 ? lo : (lane == 1 ? hi : 0);
+}
+
+// Everything the main kernel reads besides Q, in one launch (small calls pay about 4 us for each): blockIdx.z = 0 the
+// K tiles, 1 the V^T tiles, 2 (causal) the key indices; the counters of the overlap probe start at zero.
+template <int D>
+__global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v, const int32_t* __restrict__ perm,
+                                                      uint4* __restrict__ Kt, uint4* __restrict__ Vt, int32_t* __restrict__ kix,
+                                                      int32_t* __restrict__ probe) {
+  const int tile = blockIdx.x, bh = blockIdx.y, tiles_per_head = gridDim.x;
+  const int32_t* pm = perm ? perm + (int64_t)bh * k.L : nullptr;
+  if (blockIdx.z == 0) {
+    gather_k_tile<D>(k, pm, Kt, bh, tile, tiles_per_head);
+    if (tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
+  } else if (blockIdx.z == 1) {
+    gather_vt_tile<D>(v, pm, Vt, bh, tile, tiles_per_head);
+  } else {
+    key_index_tile(pm, k.L, kix, bh, tile, tiles_per_head);
   }
 }
 
@@ -1016,24 +1047,6 @@ size_t part_bytes_of(int heads, int Lq, int Nk, int B, int d, bool causal) {
   return splits < 2 ? 0 : (size_t)splits * heads * Lq * (d * 4 + 8);
 }
 
-// Causal variant: per 64-key tile of the ordered keys, the original index of every key (INT_MAX past
-// the end of the sequence), then the smallest and the largest of the 64.
-__global__ __launch_bounds__(64) void key_index_kernel(const int32_t* __restrict__ perm, int Lk, int tiles_per_head,
-                                                       int32_t* __restrict__ out) {
-  const int tile = blockIdx.x, bh = blockIdx.y, lane = threadIdx.x;
-  const int pos = tile * kTileKeys + lane;
-  const int idx = pos < Lk ? perm_at(perm, (int64_t)bh * Lk, pos, Lk) : INT_MAX;
-  int lo = idx, hi = idx;
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    lo = min(lo, __shfl_xor(lo, off));
-    hi = max(hi, __shfl_xor(hi, off));
-  }
-  int32_t* o = out + ((int64_t)bh * tiles_per_head + tile) * kIxStride;
-  o[lane] = idx;
-  if (lane < 4) o[kTileKeys + lane] = lane == 0 ? lo : (lane == 1 ? hi : 0);
-}
-
 // How much the lists of the query blocks that would share a 512-query workgroup have in common, on
 // every kProbeStride-th such group of gsz = 512 / B neighbouring blocks: probe[0] += blocks in the
 // union of the group's lists (what a 512-query workgroup walks), probe[1] += the same for each of
@@ -1086,20 +1099,6 @@ __global__ __launch_bounds__(256) void list_overlap_kernel(const int32_t* __rest
     atomicAdd(&probe[1], uni_sub);
   }
 }
-__global__ void zero_probe_kernel(int32_t* probe) {
-  if (threadIdx.x < 2) probe[threadIdx.x] = 0;
-}
-
-template <int D>
-basa_status launch_gathers(const AttnArgs& a, uint4* Kt, uint4* Vt, int BHkv, int Nk, hipStream_t st) {
-  const int B = a.B;
-  hipLaunchKernelGGL(gather_rows_kernel<D>, dim3(Nk * B / 64, BHkv), dim3(256), 0, st, a.k, a.perm_k, Kt, Nk * B, 1);
-  BASA_HIP_CHECK_LAUNCH("gather_rows_kernel(K)");
-  hipLaunchKernelGGL(gather_vt_kernel<D>, dim3(Nk * B / 64, BHkv), dim3(256), 0, st, a.v, a.perm_k, Vt, Nk * B / 64);
-  BASA_HIP_CHECK_LAUNCH("gather_vt_kernel");
-  return BASA_OK;
-}
-
 }  // namespace
 
 size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B) {
@@ -1146,11 +1145,13 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   int32_t* probe = reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d));
   int32_t* redo = reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B));
 
+  int32_t* kix = a.causal ? reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256) : nullptr;
   {
     ProfScope prof(K_GATHER, st);
-    const basa_status s = d == 128 ? launch_gathers<128>(a, Kt, Vt, BHkv, Nk, st)
-                                   : launch_gathers<64>(a, Kt, Vt, BHkv, Nk, st);
-    if (s != BASA_OK) return s;
+    const dim3 grid(Nk * B / kTileKeys, BHkv, a.causal ? 3 : 2);
+    if (d == 128) hipLaunchKernelGGL(tile_kv_kernel<128>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe);
+    else hipLaunchKernelGGL(tile_kv_kernel<64>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe);
+    BASA_HIP_CHECK_LAUNCH("tile_kv_kernel");
   }
 
   MfmaArgs m;
@@ -1164,7 +1165,7 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   m.wgs_per_head = 0; m.total_wgs = 0;
   m.scale_log2e = 1.4426950408889634f / sqrtf((float)d);
   m.probe = nullptr; m.run_if_solo = 0; m.redo = nullptr;
-  m.kix = nullptr; m.causal_off = a.causal_off;
+  m.kix = kix; m.causal_off = a.causal_off;
   const int gsz = kWideQueries / B;
   Plan plan{false, 1};
   m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
@@ -1179,14 +1180,6 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     }
   }
   if (a.causal) {
-    int32_t* kix = reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256);
-    const int tiles_per_head = Nk * B / kTileKeys;
-    {
-      ProfScope prof(K_GATHER, st);
-      hipLaunchKernelGGL(key_index_kernel, dim3(tiles_per_head, BHkv), dim3(64), 0, st, a.perm_k, a.k.L, tiles_per_head, kix);
-      BASA_HIP_CHECK_LAUNCH("key_index_kernel");
-    }
-    m.kix = kix;
     if (plan.splits > 1) {
       ProfScope prof(K_ATTN, st);
       const basa_status s = launch_shape<kWideQueries, 64, true, false, true>(m, B, d, BHq, st);
@@ -1214,8 +1207,6 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   if (variant == 0 && !can_probe) variant = a.row_cols ? BASA_ATTN_DEFAULT_LISTS : 3;   // no lists: every block shares every tile
   if (variant == 0) {
     const int groups_total = BHq * (Nq / gsz);
-    hipLaunchKernelGGL(zero_probe_kernel, dim3(1), dim3(64), 0, st, probe);
-    BASA_HIP_CHECK_LAUNCH("zero_probe_kernel");
     hipLaunchKernelGGL(list_overlap_kernel, dim3(ceil_div(ceil_div(groups_total, kProbeStride), 4)), dim3(256), 0, st,
                        a.row_count, a.row_cols, a.cols_stride, Nq, Nk, gsz, groups_total, probe);
     BASA_HIP_CHECK_LAUNCH("list_overlap_kernel");
