@@ -22,6 +22,12 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
+typedef const __attribute__((address_space(3))) bf16x8* lds_frag_ptr_t;
+// LDS byte address of a pointer into the workgroup's shared memory, and a 16-byte fragment read at one.
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)p;
+}
+__device__ __forceinline__ bf16x8 lds_frag(uint32_t addr) { return *(lds_frag_ptr_t)(uintptr_t)addr; }
 
 // ---------------------------------------------------------------------------------
 // scores[bhq][gq][gk] = sum_k featQ[bhq][gq][k] * featK[bhq/group][gk][k], k < K
@@ -73,23 +79,25 @@ __global__ __launch_bounds__(256, 2) void block_scores_kernel(const uint4* __res
   const uint4* fk = featK + (int64_t)bhk * 3 * groups * Nk;
 
   // step s into buffer buf: chunk c = 64 consecutive blocks of one group of one part; blocks
-  // past the end of the map read the last block (their outputs are never stored)
+  // past the end of the map read the last block (their outputs are never stored).  A wave always fetches
+  // the same 64 rows and the same 64 columns: the lane's part of the address is the same in every step, the
+  // rest is uniform.
+  const uint32_t q_lane = (uint32_t)min(row_base + (wave & 1) * 64 + lane, Nq - 1) * 16u;
+  const uint32_t k_lane = (uint32_t)min(col_base + wave * 64 + lane, Nk - 1) * 16u;
   auto issue_step = [&](int s, int buf) {
     uint4* dst = stage_buf + buf * kStage;
 #pragma unroll
     for (int i = 0; i < kChunks / 4; ++i) {
-      const int c = i * 4 + wave;                 // wave-uniform
-      const uint4* src;
+      const char* src;
       int off;
-      if (i < kQStage / 256) {                    // c = part*4 + khalf*2 + which 64 of the 128 rows
-        const int part = c >> 2, kh = (c >> 1) & 1, sub = c & 1;
-        src = fq + ((int64_t)part * groups + 2 * s + kh) * Nq + min(row_base + sub * 64 + lane, Nq - 1);
-        off = (part * 2 + kh) * kTQ + sub * 64;
-      } else {                                    // cc = part*8 + khalf*4 + which 64 of the 256 columns
-        const int cc = c - kQStage / 64;
-        const int part = cc >> 3, kh = (cc >> 2) & 1, sub = cc & 3;
-        src = fk + ((int64_t)part * groups + 2 * s + kh) * Nk + min(col_base + sub * 64 + lane, Nk - 1);
-        off = kQStage + (part * 2 + kh) * kTK + sub * 64;
+      if (i < kQStage / 256) {                    // chunk i*4 + wave = part*4 + khalf*2 + which 64 of the 128 rows
+        const int part = i, kh = wave >> 1;
+        src = reinterpret_cast<const char*>(fq + ((int64_t)part * groups + 2 * s + kh) * Nq) + q_lane;
+        off = (part * 2 + kh) * kTQ + (wave & 1) * 64;
+      } else {                                    // part*8 + khalf*4 + which 64 of the 256 columns
+        const int ii = i - kQStage / 256, part = ii >> 1, kh = ii & 1;
+        src = reinterpret_cast<const char*>(fk + ((int64_t)part * groups + 2 * s + kh) * Nk) + k_lane;
+        off = kQStage + (part * 2 + kh) * kTK + wave * 64;
       }
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)src, (lds_ptr_t)(dst + off), 16, 0, 0);
     }
@@ -105,21 +113,18 @@ __global__ __launch_bounds__(256, 2) void block_scores_kernel(const uint4* __res
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (s + 1 < n_steps) issue_step(s + 1, (s + 1) & 1);
-    const uint4* Qs = stage_buf + (s & 1) * kStage;
-    const uint4* Ks = Qs + kQStage;
+    // (through opaque LDS addresses: a read that the compiler can trace to stage_buf makes it wait for the loads
+    //  just issued as well, whose destination it cannot tell from this one, and nothing is prefetched any more)
+    uint32_t qs = lds_addr(stage_buf + (s & 1) * kStage + h * kTQ + wq * 64 + li);
+    uint32_t ks = lds_addr(stage_buf + (s & 1) * kStage + kQStage + h * kTK + wk * 128 + li);
+    asm volatile("" : "+v"(qs), "+v"(ks));
     bf16x8 a[3][2], b[3][4];
 #pragma unroll
     for (int part = 0; part < 3; ++part) {
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const uint4 v = Qs[(part * 2 + h) * kTQ + wq * 64 + 32 * u + li];
-        a[part][u] = __builtin_bit_cast(bf16x8, v);
-      }
+      for (int u = 0; u < 2; ++u) a[part][u] = lds_frag(qs + (part * 2 * kTQ + 32 * u) * 16);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const uint4 v = Ks[(part * 2 + h) * kTK + wk * 128 + 32 * t + li];
-        b[part][t] = __builtin_bit_cast(bf16x8, v);
-      }
+      for (int t = 0; t < 4; ++t) b[part][t] = lds_frag(ks + (part * 2 * kTK + 32 * t) * 16);
     }
     // by key part, the smallest first (the order in which the fused kernel below receives them)
     constexpr int PQ[6] = {0, 1, 0, 2, 1, 0};
@@ -715,8 +720,8 @@ basa_status launch_block_scores(const void* featQ, const void* featK, float* sco
     return BASA_ERR_UNSUPPORTED;
   }
   // Up to 1280 tiles of 64 x 64 (five workgroups per compute unit) the small tiles are faster: at 784 of them (16 heads,
-  // 391 x 391 blocks, d = 64) 19 against 28 us, at 512 (32 heads, 256 x 256, d = 128) 22 against 50; at 2048 (32 heads,
-  // 512 x 512) 70 against 55.
+  // 391 x 391 blocks, d = 64) 19 against 24 us, at 512 (32 heads, 256 x 256, d = 128) 22 against 37; at 2048 (32 heads,
+  // 512 x 512) 70 against 41.
   const int64_t small_tiles = (int64_t)ceil_div(Nk, kSmallTile) * ceil_div(Nq, kSmallTile) * BHq;
   if (small_tiles <= 1280) {
     ProfScope prof(K_SCORES, st);
