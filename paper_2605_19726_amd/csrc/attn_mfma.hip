@@ -626,6 +626,33 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     }
     __syncthreads();
   }
+  // Q^T operand: lane (query li, half h) holds Q[q][16 s + 8 h .. +7] for s = 0..7
+  bf16x8 qf[kNG][kQR];
+  int q_lim[kNG];               // kCausal: the largest original key index the lane's query of each group may see
+#pragma unroll
+  for (int r = 0; r < kNG; ++r) q_lim[r] = INT_MIN;
+  char* qpark = smem + kRingBytes + (wave * kNG * kQL) * 1024 + lane * 16;    // this lane's parked fragments
+  auto load_q = [&]() {
+#pragma unroll
+    for (int r = 0; r < kNG; ++r) {
+      // the query of sorted position qpos, read from the caller's tensor; positions past L_q
+      // (padding of the last block, or a query block that does not exist) read row 0 and are never stored
+      const int qpos = pos0 + 32 * r;
+      const int qrow = qpos < a.Lq ? perm_at(a.perm_q, (int64_t)bhq * a.Lq, qpos, a.Lq) : 0;
+      if (kCausal && qpos < a.Lq) q_lim[r] = qrow + a.causal_off;
+      const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q.ptr) +
+                                                       (a.q.head_offset(bhq) + (int64_t)qrow * a.q.stride_l) * 2);
+#pragma unroll
+      for (int s = 0; s < G::kKSteps; ++s) {
+        uint4 t = qp[2 * s + h];
+        if (s < kQR) qf[r][s < kQR ? s : 0] = *reinterpret_cast<bf16x8*>(&t);
+        else *reinterpret_cast<uint4*>(qpark + (r * kQL + s - kQR) * 1024) = t;    // read back by this lane only
+      }
+    }
+  };
+  // One query group per wave: requested here, the rows arrive while the union is built.  (Two groups: below; held
+  // across the union they cost the register allocator its footing: 15 spills instead of 4, 10 % of the kernel.)
+  if constexpr (kNG == 1) load_q();
   int n_union = 0;
   for (int base = 0; base < a.Nk; base += kThreads) {
     const int cidx = base + tid;
@@ -720,28 +747,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   };
   issue_first();
 
-  // Q^T operand: lane (query li, half h) holds Q[q][16 s + 8 h .. +7] for s = 0..7
-  bf16x8 qf[kNG][kQR];
-  int q_lim[kNG];               // kCausal: the largest original key index the lane's query of each group may see
-#pragma unroll
-  for (int r = 0; r < kNG; ++r) q_lim[r] = INT_MIN;
-  char* qpark = smem + kRingBytes + (wave * kNG * kQL) * 1024 + lane * 16;    // this lane's parked fragments
-#pragma unroll
-  for (int r = 0; r < kNG; ++r) {
-    // the query of sorted position qpos, read from the caller's tensor; positions past L_q
-    // (padding of the last block, or a query block that does not exist) read row 0 and are never stored
-    const int qpos = pos0 + 32 * r;
-    const int qrow = qpos < a.Lq ? perm_at(a.perm_q, (int64_t)bhq * a.Lq, qpos, a.Lq) : 0;
-    if (kCausal && qpos < a.Lq) q_lim[r] = qrow + a.causal_off;
-    const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q.ptr) +
-                                                     (a.q.head_offset(bhq) + (int64_t)qrow * a.q.stride_l) * 2);
-#pragma unroll
-    for (int s = 0; s < G::kKSteps; ++s) {
-      uint4 t = qp[2 * s + h];
-      if (s < kQR) qf[r][s < kQR ? s : 0] = *reinterpret_cast<bf16x8*>(&t);
-      else *reinterpret_cast<uint4*>(qpark + (r * kQL + s - kQR) * 1024) = t;    // read back by this lane only
-    }
-  }
+  if constexpr (kNG == 2) load_q();
   // LDS byte offsets inside a stage.  K: row li (+32 for the second block), chunk 2s+h at
   // position (2s+h) ^ (li & 15).  V^T: d-row li (+32 db), chunk 2g+h at (2g+h) ^ ((li>>1)&7).
   // (step s / group g are folded in by xor with s<<5 / g<<5 at the point of use)
