@@ -50,7 +50,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTileKeys = 64;
-constexpr int kIxStride = kTileKeys + 4;    // causal: ints per tile of the key-index array (64 indices, min, max, 2 unused)
+constexpr int kIxStride = kTileKeys + 4;    // causal: ints per tile of the key-index array (64 indices and 4 bounds, key_index_tile)
 #ifndef BASA_ATTN_QR
 #define BASA_ATTN_QR 7
 #endif
@@ -108,15 +108,31 @@ constexpr int q_reg_steps(int d, int qpw, bool causal = false, bool fast = false
 // ---------------------------------------------------------------------------------
 // Gather kernels
 // ---------------------------------------------------------------------------------
-// 64 rows of K in sorted order, zero-padded, in K-tile order.
+// Rows of a tile given by a table of row indices (INT_MAX: no row, zeros).  As in gather_chunks, all loads are
+// unconditional and in flight together.
+template <int ITERS>
+__device__ __forceinline__ void gather_listed(uint4 (&v)[ITERS], const int* rows, const char* base, int L, int64_t row_bytes,
+                                              int first, int step, int sub) {
+  int row[ITERS];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) row[it] = rows[first + it * step];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it) v[it] = reinterpret_cast<const uint4*>(base + min(row[it], L - 1) * row_bytes)[sub];
+#pragma unroll
+  for (int it = 0; it < ITERS; ++it)
+    if (row[it] == INT_MAX) v[it] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// 64 rows of K in sorted order, zero-padded, in K-tile order (rows: the rows of the tile, or null for perm's order).
 template <int D>
-__device__ __forceinline__ void gather_k_tile(const TensorView& x, const int32_t* __restrict__ pm, uint4* __restrict__ dst,
-                                              int bh, int tile, int tiles_per_head) {
+__device__ __forceinline__ void gather_k_tile(const TensorView& x, const int32_t* __restrict__ pm, const int* rows,
+                                              uint4* __restrict__ dst, int bh, int tile, int tiles_per_head) {
   constexpr int CPR = Geo<D>::kChunksPerRow, RPI = 256 / CPR, ITERS = 64 / RPI;
   const int sub = threadIdx.x % CPR, rig = threadIdx.x / CPR;
   const char* base = reinterpret_cast<const char*>(x.ptr) + x.head_offset(bh) * 2;
   uint4 v[ITERS];
-  gather_chunks<ITERS>(v, pm, base, x.L, (int64_t)x.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
+  if (rows) gather_listed<ITERS>(v, rows, base, x.L, (int64_t)x.stride_l * 2, rig, RPI, sub);
+  else gather_chunks<ITERS>(v, pm, base, x.L, (int64_t)x.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int pos = tile * kTileKeys + it * RPI + rig;
@@ -126,15 +142,16 @@ __device__ __forceinline__ void gather_k_tile(const TensorView& x, const int32_t
 
 // V: gather 64 sorted rows, transpose through LDS, write the swizzled [D][64] tile.
 template <int D>
-__device__ __forceinline__ void gather_vt_tile(const TensorView& v, const int32_t* __restrict__ pm, uint4* __restrict__ dst,
-                                               int bh, int tile, int tiles_per_head) {
+__device__ __forceinline__ void gather_vt_tile(const TensorView& v, const int32_t* __restrict__ pm, const int* listed,
+                                               uint4* __restrict__ dst, int bh, int tile, int tiles_per_head) {
   constexpr int CPR = Geo<D>::kChunksPerRow, RPI = 256 / CPR, ITERS = 64 / RPI;
   constexpr int kRowStride = D + 8;   // one row + 16 B pad
   __shared__ __attribute__((aligned(16))) uint16_t rows[kTileKeys][kRowStride];
   const int sub = threadIdx.x % CPR, rig = threadIdx.x / CPR;
   const char* base = reinterpret_cast<const char*>(v.ptr) + v.head_offset(bh) * 2;
   uint4 val[ITERS];
-  gather_chunks<ITERS>(val, pm, base, v.L, (int64_t)v.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
+  if (listed) gather_listed<ITERS>(val, listed, base, v.L, (int64_t)v.stride_l * 2, rig, RPI, sub);
+  else gather_chunks<ITERS>(val, pm, base, v.L, (int64_t)v.stride_l * 2, tile * kTileKeys + rig, RPI, sub);
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) *reinterpret_cast<uint4*>(&rows[it * RPI + rig][sub * 8]) = val[it];
   __syncthreads();
@@ -159,39 +176,83 @@ __device__ __forceinline__ void gather_vt_tile(const TensorView& v, const int32_
 }
 
 // Causal variant: the original index of every key of a tile (INT_MAX past the end of the sequence), then the smallest
-// and the largest of the 64.
-__device__ __forceinline__ void key_index_tile(const int32_t* __restrict__ pm, int Lk, int32_t* __restrict__ out, int bh, int tile,
-                                               int tiles_per_head) {
+// of all, the smallest of the second 32, the largest of the first 32 and of the second 32.
+__device__ __forceinline__ void key_index_tile(const int32_t* __restrict__ pm, const int* rows, int Lk, int32_t* __restrict__ out,
+                                               int bh, int tile, int tiles_per_head) {
   const int lane = threadIdx.x;
   if (lane >= 64) return;
   const int pos = tile * kTileKeys + lane;
-  const int idx = pos < Lk ? perm_at(pm, 0, pos, Lk) : INT_MAX;
+  const int idx = rows ? rows[lane] : pos < Lk ? perm_at(pm, 0, pos, Lk) : INT_MAX;
   int lo = idx, hi = idx;
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
+  for (int off = 16; off > 0; off >>= 1) {
     lo = min(lo, __shfl_xor(lo, off));
     hi = max(hi, __shfl_xor(hi, off));
   }
+  const int lo_other = __shfl_xor(lo, 32);
   int32_t* o = out + ((int64_t)bh * tiles_per_head + tile) * kIxStride;
   o[lane] = idx;
-  if (lane < 4) o[kTileKeys + lane] = lane == 0 ? lo : (lane == 1 ? hi : 0);
+  if (lane == 0) { o[kTileKeys] = min(lo, lo_other); o[kTileKeys + 1] = lo_other; o[kTileKeys + 2] = hi; }
+  if (lane == 32) o[kTileKeys + 3] = hi;
+}
+
+// The entries of `raw` (128 of them, a block's original indices; INT_MAX where there is none) by increasing value, entry
+// t placed by thread t: its place is the number of entries before it.
+__device__ __forceinline__ int place_in_block(const int* raw, int t) {
+  const int mine = raw[t];
+  int place = 0;
+#pragma unroll 8
+  for (int j = 0; j < 128; j += 4) {
+    const int4 x = *reinterpret_cast<const int4*>(raw + j);
+    place += (x.x < mine || (x.x == mine && j < t)) + (x.y < mine || (x.y == mine && j + 1 < t)) +
+             (x.z < mine || (x.z == mine && j + 2 < t)) + (x.w < mine || (x.w == mine && j + 3 < t));
+  }
+  return place;
 }
 
 // Everything the main kernel reads besides Q, in one launch (small calls pay about 4 us for each): blockIdx.z = 0 the
-// K tiles, 1 the V^T tiles, 2 (causal) the key indices; the counters of the overlap probe start at zero.
+// K tiles and (causal) the key indices, 1 the V^T tiles; the counters of the overlap probe start at zero.
+// by_index (causal, blocks of 128): the keys of a block in the order of their original indices instead of perm's.  A
+// list names whole blocks, so the order inside one is free, and this one lets the main kernel leave out the half
+// tiles whose keys all come after a wave's queries.
 template <int D>
 __global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v, const int32_t* __restrict__ perm,
                                                       uint4* __restrict__ Kt, uint4* __restrict__ Vt, int32_t* __restrict__ kix,
-                                                      int32_t* __restrict__ probe) {
+                                                      int32_t* __restrict__ probe, int by_index) {
+  __shared__ __attribute__((aligned(16))) int raw[128], ordered[128], place[128];
   const int tile = blockIdx.x, bh = blockIdx.y, tiles_per_head = gridDim.x;
   const int32_t* pm = perm ? perm + (int64_t)bh * k.L : nullptr;
+  const int* rows = nullptr;
+  if (by_index) {
+    // ranked by counting, two threads to an entry (places past the keys, and those a malformed perm leaves open, stay
+    // without a row)
+    constexpr int kNone = INT_MAX - 127;
+    const int t = threadIdx.x, e = t & 127, pos = (tile >> 1) * 128 + e;
+    if (t < 128) {
+      raw[t] = pos < k.L ? perm_at(pm, 0, pos, k.L) : kNone + t;
+      ordered[t] = INT_MAX;
+      place[t] = 0;
+    }
+    __syncthreads();
+    const int mine = raw[e];
+    int before = 0;
+#pragma unroll
+    for (int j = 0; j < 64; j += 4) {
+      const int4 x = *reinterpret_cast<const int4*>(raw + (t >> 7) * 64 + j);
+      before += (x.x < mine) + (x.y < mine) + (x.z < mine) + (x.w < mine);
+    }
+    atomicAdd(&place[e], before);
+    __syncthreads();
+    if (t < 128 && mine < kNone) ordered[place[t]] = mine;
+    __syncthreads();
+    rows = ordered + (tile & 1) * kTileKeys;
+  }
   if (blockIdx.z == 0) {
-    gather_k_tile<D>(k, pm, Kt, bh, tile, tiles_per_head);
+    gather_k_tile<D>(k, pm, rows, Kt, bh, tile, tiles_per_head);
     if (tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
-  } else if (blockIdx.z == 1) {
-    gather_vt_tile<D>(v, pm, Vt, bh, tile, tiles_per_head);
+    if (kix) key_index_tile(pm, rows, k.L, kix, bh, tile, tiles_per_head);
   } else {
-    key_index_tile(pm, k.L, kix, bh, tile, tiles_per_head);
+    gather_vt_tile<D>(v, pm, rows, Vt, bh, tile, tiles_per_head);
   }
 }
 
@@ -380,7 +441,8 @@ struct WaveState2 {
 template <bool kMasked, int D, int kQR, bool kCausal = false, bool kFast = false>
 __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&qa)[kQR], const bf16x8 (&qb)[kQR],
                                               const char* qs, const char* stage, int kaddr0, int vaddr0, float c,
-                                              int nvalid, int h, const int* kix4 = nullptr, int qla = 0, int qlb = 0) {
+                                              int nvalid, int h, const int* kix4 = nullptr, int qla = 0, int qlb = 0,
+                                              int seen = 0) {
   constexpr int kQL = Geo<D>::kKSteps - kQR;               // k-steps whose Q^T fragments live in LDS
   // One LDS address per operand and tile; the k-step (group) is folded in by an xor at the point of
   // use (ring stages start at multiples of 32 KB, so the xor of bits 5-8 commutes with adding the
@@ -392,6 +454,7 @@ __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     if (kMasked && half == 1 && nvalid <= 32) break;        // wave-uniform: no key in the second half
+    if (kCausal && half == 1 && (seen & 1)) break;          // wave-uniform: none that a query of the wave sees
     // the parked fragments are read again in every half: kept in registers across the halves they
     // would cost the 16 registers that parking them is meant to free
     asm volatile("" ::: "memory");
@@ -416,7 +479,7 @@ __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&
         if (kk >= nvalid) { sa[r] = -INFINITY; sb[r] = -INFINITY; }
       }
     }
-    if constexpr (kCausal) {
+    if (kCausal && !(seen & (2 << half))) {                 // wave-uniform: not every query sees all of the half
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         const int4 ix = *reinterpret_cast<const int4*>(kix4 + 32 * half + 8 * g4);
@@ -552,8 +615,11 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
 // this workgroup lists it).  While seq is being built the ring area holds the per-key-block
 // membership flags.
 // kCausal (512-query shape only): the ring is followed by the original key indices of each stage's
-// tile (with their minimum), every score is masked by original position, and a wave skips a tile
-// none of whose keys is visible to any of its queries.
+// tile (with their bounds), scores are masked by original position, and a wave skips a tile or its second half if
+// none of its keys is visible to any of the wave's queries, and the mask if all are to all.  With sorted sequences a
+// block's indices are spread over the whole sequence; blocks of 128 are therefore walked by original index inside
+// (tile_kv_kernel, positions_by_index): 32 heads, L = 32768, s = 0.5: 8579 us in perm's order, 7910 with hidden halves
+// left out, 7209 without the masks that mask nothing.
 // kSplit: a.splits workgroups share the query blocks and take equal runs of the union list each; their rows
 // stay unnormalised and attn_combine_kernel adds them up.
 template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
@@ -609,7 +675,30 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   const int li = lane & 31, h = lane >> 5;
   const int grp = wave * kQPW / kB;                    // query block of this wave inside the wg
   const int nqb = min(NQB, a.Nq - wg * NQB);           // query blocks that exist
+  // Sorted positions of the queries of thread t.  Causal with blocks of 128: the queries of a block are dealt to its
+  // two waves by original index, the lower half to one and the upper half to the other (the order inside a block is
+  // free), so that the wave of the lower half can leave out what lies beyond all its queries; of the two waves of
+  // a SIMD, numbers w and w + 4, one has a lower and one an upper half.
+  constexpr bool kByIndex = kCausal && kB == 128;
+  auto positions_by_index = [&](int t, int (&pos)[2]) {
+    int* raw = reinterpret_cast<int*>(smem);
+    int* ordered = raw + kQueriesPerWg;
+    const int p = wg * kQueriesPerWg + t, w = t >> 6;
+    raw[t] = p < a.Lq ? perm_at(a.perm_q, (int64_t)bhq * a.Lq, p, a.Lq) : INT_MAX;
+    __syncthreads();
+    ordered[(t & ~127) + place_in_block(raw + (t & ~127), t & 127)] = p;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 2; ++r) pos[r] = ordered[(w >> 1) * 128 + ((w ^ (w >> 2)) & 1) * 64 + 32 * r + (t & 31)];
+    __syncthreads();
+  };
   const int pos0 = wg * kQueriesPerWg + wave * kQPW + li;   // sorted position of this lane's first query (next: +32)
+  int qpos[2];                                              // kByIndex: of both
+  if constexpr (kByIndex) positions_by_index(tid, qpos);
+  auto position = [&](int r) -> int {
+    if constexpr (kByIndex) return qpos[r];
+    return pos0 + 32 * r;
+  };
 
   // ---- union of the block lists of this workgroup's query blocks ------------------------
   for (int c = tid; c < a.Nk; c += kThreads) flags[c] = a.row_cols ? 0u : ((1u << nqb) - 1u);
@@ -637,7 +726,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     for (int r = 0; r < kNG; ++r) {
       // the query of sorted position qpos, read from the caller's tensor; positions past L_q
       // (padding of the last block, or a query block that does not exist) read row 0 and are never stored
-      const int qpos = pos0 + 32 * r;
+      const int qpos = position(r);
       const int qrow = qpos < a.Lq ? perm_at(a.perm_q, (int64_t)bhq * a.Lq, qpos, a.Lq) : 0;
       if (kCausal && qpos < a.Lq) q_lim[r] = qrow + a.causal_off;
       const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q.ptr) +
@@ -682,7 +771,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     if constexpr (kSplit) {
       // nothing to add: a maximum of -inf and a sum of 0, whose row the combining pass does not read
       for (int r = 0; r < kNG; ++r) {
-        const int pos = pos0 + 32 * r;
+        const int pos = position(r);
         if (pos < a.Lq && h == 0)
           a.part_ml[((int64_t)split * (a.total_wgs / (a.splits * a.wgs_per_head)) + bhq) * a.Lq + pos] = make_float2(-INFINITY, 0.f);
       }
@@ -690,7 +779,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     }
     // no valid key block in any list of this workgroup (malformed input): its rows become zeros
     for (int r = 0; r < kNG; ++r) {
-      const int pos = pos0 + 32 * r;
+      const int pos = position(r);
       if (pos < a.Lq) {
         const int orow = perm_at(a.perm_q, (int64_t)bhq * a.Lq, pos, a.Lq);
         uint4* op = reinterpret_cast<uint4*>(a.out + out_off(a, bhq, orow));
@@ -758,6 +847,30 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   init_state<D>(st, kFast);
   const float c = a.scale_log2e;
   // one 64-key tile of the ring, for the one or two query groups of this wave
+  // causal: the largest limit among this wave's queries (lanes without a query ask for nothing); a tile
+  // whose smallest key index lies beyond it has nothing for the wave, and neither has such a second half
+  int wq_max = INT_MIN;
+  if constexpr (kCausal) {
+    wq_max = max(q_lim[0], q_lim[kNG - 1]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wq_max = max(wq_max, __shfl_xor(wq_max, off));
+    wq_max = __builtin_amdgcn_readfirstlane(wq_max);
+  }
+  // ... and the smallest: a half whose largest index does not exceed it needs no mask
+  int wq_min = INT_MAX;
+  if constexpr (kCausal) {
+    wq_min = min(q_lim[0] == INT_MIN ? INT_MAX : q_lim[0], q_lim[kNG - 1] == INT_MIN ? INT_MAX : q_lim[kNG - 1]);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) wq_min = min(wq_min, __shfl_xor(wq_min, off));
+    wq_min = __builtin_amdgcn_readfirstlane(wq_min);
+  }
+  // bit 0: the second half has nothing for the wave; bits 1, 2: the first / second half needs no mask
+  auto seen_of = [&](int stage_no) -> int {
+    if constexpr (!kCausal) return 0;
+    const int* bound = kix_lds + stage_no * kIxStride + kTileKeys;
+    return (__builtin_amdgcn_readfirstlane(bound[1]) > wq_max ? 1 : 0) | (__builtin_amdgcn_readfirstlane(bound[2]) <= wq_min ? 2 : 0) |
+           (__builtin_amdgcn_readfirstlane(bound[3]) <= wq_min ? 4 : 0);
+  };
   auto tile = [&](auto masked, int stage_no, int nvalid, auto fast) {
     const char* stage = smem + stage_no * kStageBytes;
     if constexpr (kNG == 1) process_tile<decltype(masked)::value, D, decltype(fast)::value>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
@@ -772,18 +885,9 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
       }
       process_tile2<decltype(masked)::value, D, kQR, kCausal, kFast>(st, qf[0], qf[kNG - 1], qpark, stage, kaddr, vaddr, c, nvalid,
                                                                      h2, kix_lds + stage_no * kIxStride + 4 * h2, q_lim[0],
-                                                                     q_lim[kNG - 1]);
+                                                                     q_lim[kNG - 1], seen_of(stage_no));
     }
   };
-  // causal: the largest limit among this wave's queries (lanes without a query ask for nothing); a tile
-  // whose smallest key index lies beyond it has nothing for the wave
-  int wq_max = INT_MIN;
-  if constexpr (kCausal) {
-    wq_max = max(q_lim[0], q_lim[kNG - 1]);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) wq_max = max(wq_max, __shfl_xor(wq_max, off));
-    wq_max = __builtin_amdgcn_readfirstlane(wq_max);
-  }
   int wk_min = INT_MAX;         // kCausal: the smallest original key index in the wave's own list
   auto tile_has_visible_keys = [&](int stage_no) -> bool {
     if constexpr (!kCausal) return true;
@@ -908,13 +1012,19 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   asm volatile("" : "+v"(tid_e));
   const int h_e = (tid_e >> 5) & 1;
   const int pos_e = wg * kQueriesPerWg + (tid_e >> 6) * kQPW + (tid_e & 31);
+  int qpos_e[2];
+  if constexpr (kByIndex) {
+    __syncthreads();                           // (the positions are worked out in the ring, which others may still read)
+    positions_by_index(tid_e, qpos_e);
+  }
   int unsafe = 0;                // kFast: some row of this lane has a sum outside the safe range
 #pragma unroll
   for (int r = 0; r < kNG; ++r) {
     const float l_part = l_of(st, r), m_fin = m_of(st, r);
     const float l_tot = l_part + __shfl_xor(l_part, 32);
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;    // a query block without any valid key block: zeros
-    const int pos = pos_e + 32 * r;
+    int pos = pos_e + 32 * r;
+    if constexpr (kByIndex) pos = qpos_e[r];
     // (causal: a query that sees no key of its list has the sum 0 and is done; there are one or two such queries
     //  per head, and repeating their workgroups took 1210 us after the 8579 of this pass at 32 heads, L = 32768)
     if (kFast && !kRetry && pos < a.Lq && (!kCausal || q_lim[r] >= wk_min) && sum_is_unsafe(l_tot)) unsafe = 1;
@@ -1154,9 +1264,10 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   int32_t* kix = a.causal ? reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256) : nullptr;
   {
     ProfScope prof(K_GATHER, st);
-    const dim3 grid(Nk * B / kTileKeys, BHkv, a.causal ? 3 : 2);
-    if (d == 128) hipLaunchKernelGGL(tile_kv_kernel<128>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe);
-    else hipLaunchKernelGGL(tile_kv_kernel<64>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe);
+    const dim3 grid(Nk * B / kTileKeys, BHkv, 2);
+    const int by_index = a.causal && B == 128 && a.perm_k;
+    if (d == 128) hipLaunchKernelGGL(tile_kv_kernel<128>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index);
+    else hipLaunchKernelGGL(tile_kv_kernel<64>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index);
     BASA_HIP_CHECK_LAUNCH("tile_kv_kernel");
   }
 

@@ -143,3 +143,20 @@ def test_sort_and_features_of_sequences_of_different_lengths(hq, hk, Lq, Lk, dty
         assert np.array_equal(sel.perm_q[0, h].cpu().numpy(), ref["perm_q"])
         assert np.array_equal(sel.perm_k[0, h // (hq // hk)].cpu().numpy(), ref["perm_k"])
         np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref["logits"], rtol=2e-5, atol=2e-5)
+
+
+def test_causal_blocks_ordered_by_index_with_a_malformed_permutation():
+    """Entries that are no index fall back to their position, repeated ones leave places of the block without a row:
+    wrong rows, but nothing outside the tensors, and the other blocks come out right."""
+    L, d, block = 700, 128, 128
+    Q, K, V = _qkv(1, 1, L, L, d, torch.bfloat16, seed=9)
+    pk = torch.arange(L, dtype=torch.int32)
+    pk[:100] = torch.tensor([-7, 10 ** 6, 5, 5] * 25, dtype=torch.int32)
+    cnt = torch.full((1, 1, 6), 1, dtype=torch.int32, device=DEV)
+    cols = torch.tensor([0, 0, 0, 1, 1, 2], dtype=torch.int32, device=DEV).reshape(1, 1, 6, 1)
+    for shape in (0, 3):
+        out = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, None, pk.reshape(1, 1, L).to(DEV), attn_shape=shape, causal=True)
+        torch.cuda.synchronize()
+        ref, _ = o.sparse_attention_causal(np64(Q[0, 0]), np64(K[0, 0]), np64(V[0, 0]), np.arange(L), np.arange(L),
+                                           [[0], [0], [0], [1], [1], [2]], block, return_lse=True)
+        check_output(np64(out[0, 0, 384:]), ref[384:], True, "blocks without a malformed entry")
