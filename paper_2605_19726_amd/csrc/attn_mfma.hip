@@ -647,7 +647,11 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     // ratio of 1.29, 157.7 against 143.6 ms at 1.64): the narrow shape wins once the wide union
     // exceeds about 1.35 times the average narrow one.
     const int uni = a.probe[0], uni_sub = a.probe[1];
-    const bool little_overlap = 100 * (int64_t)uni * 4 > 135 * (int64_t)uni_sub;
+    // At D = 64 a tile is half the bytes and the matrix work, and the narrow shape (half the registers, twice the
+    // waves) hides its softmax better: level at ratios of 1.11 to 1.17 (2 % either way), ahead at 1.22 (1133 / 1003 us,
+    // 32 heads, L = 32768; 3180 / 2895 us, 24 heads, L = 65536).
+    constexpr int kBreakEven = D == 64 ? 119 : 135;
+    const bool little_overlap = 100 * (int64_t)uni * 4 > kBreakEven * (int64_t)uni_sub;
     if ((int)little_overlap != a.run_if_solo) return;
   }
   constexpr int TPB = kB / kTileKeys;        // key tiles per key block: 2 or 1
@@ -1117,41 +1121,51 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
   return launch_shape<kWideQueries, 64, kCausal, false>(m, B, d, BHq, st);
 }
 
-// Calls whose workgroups do not fill the device (fewer than two of 512 queries per compute unit): the shape
+// Calls whose workgroups do not fill the device (fewer than two of 512 queries per compute unit, `small`): the shape
 // (512 or 128 queries per workgroup) and the number of workgroups that share a list, from an estimate of the
 // time.  Lists are split on the 128-query shape (split 512-query workgroups measure no better: 75 against 72 us,
 // dense, 8 heads, L = 4100, d = 64), on the 512-query one only for the causal kernel, which has no
 // other.  The rule sees the heads of one batch entry, so that an entry's result does not depend on the others.
 // One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries (causal: 3.4), 1.95 us for
-// two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; about 8 us of prologue and
-// epilogue per round of workgroups, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
+// two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; 20 us of prologue and epilogue per
+// round of workgroups of 512 queries, 10 us of 128, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
 // Attention call (tiling of K and V included), one workgroup of 512 queries per list -> this rule:
-// 256 queries against 32K keys, 32 heads on 8, keep 25 %: 351 -> 104 us (128 queries, 8 workgroups per list);
-// 8 heads, L = 2472, d = 64: 63 -> 31 us; 16 heads, L = 1977: 81 -> 38 us; dense, 8 heads, L = 12000, d = 128: 571 us,
+// 256 queries against 32K keys, 32 heads on 8, keep 25 %: 351 -> 98 us (128 queries, 8 workgroups per list);
+// 8 heads, L = 2472, d = 64: 63 -> 28 us; 16 heads, L = 1977: 81 -> 36 us; dense, 8 heads, L = 12000, d = 128: 560 us,
 // unchanged (the 128-query shape would take 624).
 // Lists of up to 32 tiles stay whole: splitting them never paid (16 heads, L = 1977, 16 tiles: 39 us whole, 47 in two;
 // 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36; not so the causal kernel, 8 heads, L = 2100: 94 and 59 in six), and a
 // whole list on the 128-query shape gives the same bits as on the 512-query one.
 constexpr int kCUs = 256, kMaxSplits = 32, kMinSplitTiles = 32;
 struct Plan { bool solo; int splits; };
-Plan plan_small(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, size_t part_bytes) {
+// Up to six of 512 queries per compute unit, whole lists only: there a last round that is mostly empty decides, and the
+// 128-query shape has to be 5 % ahead by the estimate.  512-query -> chosen shape: 16 heads, L = 20000, keep 10 %
+// (2.5 rounds): 388 -> 338 us; 24 heads, L = 12500, B = 64, keep 25 %: 644 -> 547; 32 heads, L = 9000, B = d = 64, keep
+// 10 %: 145 -> 104; kept at 512 queries: 32 heads, L = 16384, keep 10 % (four full rounds, 461 either way).
+constexpr int kSmallRounds = 2, kPlannedRounds = 6;
+Plan plan_call(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, bool small, size_t part_bytes) {
   const size_t row_bytes = (size_t)heads * Lq * (d * 4 + 8);
   const double dead = 1.0 - (double)list_len / Nk, scale = d == 128 ? 1.0 : 0.63;
   Plan best{false, 1};
   double best_cost = 0.0;
   for (int solo = 0; solo <= (causal ? 0 : 1); ++solo) {
     const int queries = solo ? kSoloQueries : kWideQueries;
-    const int blocks = std::min(queries / B, Nq);
     const int64_t wgs = (int64_t)heads * ceil_div(Nq * B, queries);
-    // blocks in the union of a workgroup's lists: 1.13 lists for four at 50 %, 1.29 at 90 % (full method, measured)
-    const double uni = std::min((double)Nk, list_len * (1.0 + 0.1 * (blocks - 1) * dead));
-    for (int s = 1; s <= kMaxSplits && (s == 1 || ((solo != 0) != causal && (causal || list_len * (B / kTileKeys) > kMinSplitTiles) && s * row_bytes <= part_bytes)); ++s) {
+    // blocks in the union of a workgroup's lists, measured (full method): the union over 512 queries is 1.14 times that
+    // over 128 at 50 %, 1.22 at 75 %, 1.29 at 90 %; two lists of 64 queries make about 1.05 to 1.1
+    const int groups = solo ? 1 : std::min(4, ceil_div(Nq * B, kSoloQueries));
+    const double uni = std::min((double)Nk, list_len * (1.0 + (B == 64 && Nq > 1 ? 0.1 : 0.0) * dead) *
+                                                (1.0 + 0.1 * (groups - 1) * dead));
+    const bool may_split = small && (solo != 0) != causal && (causal || list_len * (B / kTileKeys) > kMinSplitTiles);
+    for (int s = 1; s == 1 || (may_split && s <= kMaxSplits && uni >= s && s * row_bytes <= part_bytes); ++s) {
       const int64_t per_cu = (wgs * s + kCUs - 1) / kCUs;
       const double rounds = solo ? (double)((per_cu + 1) / 2) : (double)per_cu;
-      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25 : (double)per_cu * (causal ? 3.4 : 2.95);
-      const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + 8.0 * rounds +
+      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25
+                                  : (double)per_cu * (causal ? 3.4 : 2.95);
+      const double round_us = solo ? 10.0 : causal ? 8.0 : 20.0;
+      const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + round_us * rounds +
                           (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
-      if ((!solo && s == 1) || cost < best_cost) { best_cost = cost; best = Plan{solo != 0, s}; }
+      if ((!solo && s == 1) || cost < best_cost * (small ? 1.0 : 0.95)) { best_cost = cost; best = Plan{solo != 0, s}; }
     }
   }
   return best;
@@ -1286,10 +1300,12 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   const int gsz = kWideQueries / B;
   Plan plan{false, 1};
   m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
-  if (a.variant == 0 && (int64_t)a.q.heads * Nq * B < 2 * kCUs * kWideQueries) {
+  const int64_t rows = (int64_t)a.q.heads * Nq * B;
+  const bool small = rows < (int64_t)kSmallRounds * kCUs * kWideQueries;
+  if (a.variant == 0 && rows < (int64_t)kPlannedRounds * kCUs * kWideQueries) {
     const size_t base = attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B);
-    plan = plan_small(a.q.heads, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0,
-                      (a.ws_bytes - base) / a.q.batch);
+    plan = plan_call(a.q.heads, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0, small,
+                     (a.ws_bytes - base) / a.q.batch);
     if (plan.splits > 1) {
       m.splits = plan.splits;
       m.part_o = reinterpret_cast<float*>(ws + base);
@@ -1307,7 +1323,8 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     }
     return launch_attn_combine(a, m.part_o, m.part_ml, m.splits, st);
   }
-  if (plan.solo) {
+  const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
+  if (plan.solo && (small || !can_probe)) {
     {
       ProfScope prof(K_ATTN, st);
       const basa_status s = plan.splits == 1 ? launch_shape<kSoloQueries, 32, false, true>(m, B, d, BHq, st)
@@ -1317,10 +1334,10 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     return launch_attn_combine(a, m.part_o, m.part_ml, m.splits, st);
   }
 
-  // Which shape of workgroup: asked for, or (B = d = 128, block lists given, enough work to pay for
-  // three tiny launches) decided on the device from how much neighbouring lists overlap.
+  // Which shape of workgroup: asked for, or (block lists given, enough work to pay for three tiny launches) decided on
+  // the device from how much neighbouring lists overlap (plan.solo: between the two arithmetics of the 128-query shape,
+  // so that the bits do not depend on which shape the plan takes for lists that overlap).
   int variant = a.variant;
-  const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
   if (variant == 0 && !can_probe) variant = a.row_cols ? BASA_ATTN_DEFAULT_LISTS : 3;   // no lists: every block shares every tile
   if (variant == 0) {
     const int groups_total = BHq * (Nq / gsz);
@@ -1334,7 +1351,9 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   if (variant == 1) return launch_shape<kSharedQueries, 32>(m, B, d, BHq, st);
   if (variant == 0 || variant == 3 || variant == 4) {
     m.run_if_solo = 0;
-    if ((s = launch_wide<false>(m, B, d, BHq, redo, variant != 4, st)) != BASA_OK) return s;
+    s = plan.solo ? launch_shape<kSoloQueries, 32, false, true>(m, B, d, BHq, st)
+                  : launch_wide<false>(m, B, d, BHq, redo, variant != 4, st);
+    if (s != BASA_OK) return s;
   }
   if (variant == 0 || variant == 2) {
     m.run_if_solo = 1;
