@@ -210,6 +210,39 @@ __device__ __forceinline__ int place_in_block(const int* raw, int t) {
   return place;
 }
 
+// Which key blocks the lists of a KV head name, as bitmaps [BHkv][parts][ceil(Nk / 32)], one workgroup to a part (a run
+// of the rows of the `rows` lists of the KV head's query heads, which are neighbours): the blocks that nobody lists
+// need no tiles.  The rows agree in much of what they keep: 19 % of the blocks are listed by any of 128 rows that keep
+// 10 % each, 40 % at 25 %, 68 % at 50 % (L = 16384).  An entry is one independent load per thread, four in flight.
+constexpr int kMaxListedWords = 512;         // 16384 key blocks: more than the main kernel lists
+constexpr int kListedParts = 16;
+__global__ __launch_bounds__(1024) void listed_blocks_kernel(const int32_t* __restrict__ row_count,
+                                                             const int32_t* __restrict__ row_cols, int cols_stride, int rows,
+                                                             int Nk, uint32_t* __restrict__ listed) {
+  __shared__ uint32_t bits[kMaxListedWords];
+  const int words = (Nk + 31) >> 5, parts = gridDim.y, part = blockIdx.y;
+  for (int w = threadIdx.x; w < words; w += 1024) bits[w] = 0u;
+  __syncthreads();
+  const int r0 = (int)((int64_t)rows * part / parts), r1 = (int)((int64_t)rows * (part + 1) / parts);
+  const int64_t row0 = (int64_t)blockIdx.x * rows + r0, entries = (int64_t)(r1 - r0) * cols_stride;
+  for (int64_t e0 = threadIdx.x; e0 < entries; e0 += 4 * 1024) {
+    unsigned col[4];
+    int left[4];                             // entries of the row from this one on
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t e = min(e0 + u * 1024, entries - 1);       // (past the end: the last one again)
+      const int r = (int)((uint32_t)e / (uint32_t)cols_stride), i = (int)e - r * cols_stride;
+      left[u] = row_count[row0 + r] - i;
+      col[u] = (unsigned)row_cols[row0 * cols_stride + e];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (left[u] > 0 && col[u] < (unsigned)Nk) atomicOr(&bits[col[u] >> 5], 1u << (col[u] & 31));
+  }
+  __syncthreads();
+  for (int w = threadIdx.x; w < words; w += 1024) listed[((int64_t)blockIdx.x * parts + part) * words + w] = bits[w];
+}
+
 // Everything the main kernel reads besides Q, in one launch (small calls pay about 4 us for each): blockIdx.z = 0 the
 // K tiles and (causal) the key indices, 1 the V^T tiles; the counters of the overlap probe start at zero.
 // by_index (causal, blocks of 128): the keys of a block in the order of their original indices instead of perm's.  A
@@ -218,11 +251,19 @@ __device__ __forceinline__ int place_in_block(const int* raw, int t) {
 template <int D>
 __global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v, const int32_t* __restrict__ perm,
                                                       uint4* __restrict__ Kt, uint4* __restrict__ Vt, int32_t* __restrict__ kix,
-                                                      int32_t* __restrict__ probe, int by_index) {
+                                                      int32_t* __restrict__ probe, int by_index,
+                                                      const uint32_t* __restrict__ listed, int parts, int tiles_per_block) {
   __shared__ __attribute__((aligned(16))) int raw[128], ordered[128], place[128];
   const int tile = blockIdx.x, bh = blockIdx.y, tiles_per_head = gridDim.x;
   const int32_t* pm = perm ? perm + (int64_t)bh * k.L : nullptr;
   const int* rows = nullptr;
+  if (probe && blockIdx.z == 0 && tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
+  if (listed) {                                      // uniform: nobody reads the tiles of a block in no list
+    const int block = tile / tiles_per_block, words = (tiles_per_head / tiles_per_block + 31) >> 5;
+    uint32_t any = 0u;
+    for (int p = 0; p < parts; ++p) any |= listed[((int64_t)bh * parts + p) * words + (block >> 5)];
+    if (!((any >> (block & 31)) & 1u)) return;
+  }
   if (by_index) {
     // ranked by counting, two threads to an entry (places past the keys, and those a malformed perm leaves open, stay
     // without a row)
@@ -249,7 +290,6 @@ __global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v
   }
   if (blockIdx.z == 0) {
     gather_k_tile<D>(k, pm, rows, Kt, bh, tile, tiles_per_head);
-    if (tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
     if (kix) key_index_tile(pm, rows, k.L, kix, bh, tile, tiles_per_head);
   } else {
     gather_vt_tile<D>(v, pm, rows, Vt, bh, tile, tiles_per_head);
@@ -1073,6 +1113,8 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
 size_t sz_kv(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 2, 256); }
 size_t sz_kix(int BHkv, int Nk, int B) { return align_up((size_t)BHkv * (Nk * B / kTileKeys) * kIxStride * 4, 256); }
 
+size_t sz_listed(int BHkv, int Nk) { return align_up((size_t)BHkv * kListedParts * ceil_div(Nk, 32) * 4, 256); }
+
 template <int D>
 size_t lds_bytes(int threads, int qpw, int Nk, bool causal = false, bool fast = false) {
   const size_t park = (size_t)(threads / 64) * (qpw / 32) * (D / 16 - q_reg_steps(D, qpw, causal, fast)) * 1024;
@@ -1235,7 +1277,9 @@ size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B
   const int Nq = ceil_div(Lq, B), Nk = ceil_div(Lk, B);
   // + the two counters of the list-overlap probe + the key-index tiles of the causal variant
   // + one word per 512-query workgroup (which of them the pass with running maxima has to repeat)
-  return 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B) + align_up((size_t)BHq * ceil_div(Nq * B, kWideQueries) * 4, 256);
+  // + the bitmaps of the listed blocks
+  return 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B) + align_up((size_t)BHq * ceil_div(Nq * B, kWideQueries) * 4, 256) +
+         sz_listed(BHkv, Nk);
 }
 size_t attn_mfma_split_bytes(int batch, int heads, int Lq, int Lk, int d, int B, bool causal) {
   return align_up((size_t)batch * part_bytes_of(heads, Lq, ceil_div(Lk, B), B, d, causal), 256);
@@ -1280,8 +1324,25 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     ProfScope prof(K_GATHER, st);
     const dim3 grid(Nk * B / kTileKeys, BHkv, 2);
     const int by_index = a.causal && B == 128 && a.perm_k;
-    if (d == 128) hipLaunchKernelGGL(tile_kv_kernel<128>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index);
-    else hipLaunchKernelGGL(tile_kv_kernel<64>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index);
+    // Worth a launch of its own (about 5 us) once the tiles take longer than twice that (32 MB read, as much written:
+    // 10 us) and the lists leave something out: 32 heads, L = 16384, keep 10 % / 25 % / 50 %: 90 / 88 / 88 us of tiling ->
+    // 32 / 51 / 73; 500 queries against 60000 keys, 32 heads, keep 10 %: 351 -> 50.
+    const int rows = a.q.heads / a.k.heads * Nq;
+    const int64_t entries = (int64_t)rows * a.cols_stride;
+    uint32_t* listed = nullptr;
+    int parts = 1;
+    if (a.row_cols && (int64_t)a.cols_stride * 10 <= (int64_t)Nk * 9 && entries < ((int64_t)1 << 31) && Nk <= 32 * kMaxListedWords &&
+        sz_kv(BHkv, Nk, B, d) >= ((size_t)16 << 20)) {
+      parts = (int)std::min<int64_t>(std::min(rows, kListedParts), (entries + 4095) / 4096);
+      listed = reinterpret_cast<uint32_t*>(ws + attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B) - sz_listed(BHkv, Nk));
+      hipLaunchKernelGGL(listed_blocks_kernel, dim3(BHkv, parts), dim3(1024), 0, st, a.row_count, a.row_cols, a.cols_stride, rows,
+                         Nk, listed);
+      BASA_HIP_CHECK_LAUNCH("listed_blocks_kernel");
+    }
+    if (d == 128) hipLaunchKernelGGL(tile_kv_kernel<128>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index,
+                                    listed, parts, B / kTileKeys);
+    else hipLaunchKernelGGL(tile_kv_kernel<64>, grid, dim3(256), 0, st, a.k, a.v, a.perm_k, Kt, Vt, kix, probe, by_index,
+                                    listed, parts, B / kTileKeys);
     BASA_HIP_CHECK_LAUNCH("tile_kv_kernel");
   }
 

@@ -160,3 +160,39 @@ def test_causal_blocks_ordered_by_index_with_a_malformed_permutation():
         ref, _ = o.sparse_attention_causal(np64(Q[0, 0]), np64(K[0, 0]), np64(V[0, 0]), np.arange(L), np.arange(L),
                                            [[0], [0], [0], [1], [1], [2]], block, return_lse=True)
         check_output(np64(out[0, 0, 384:]), ref[384:], True, "blocks without a malformed entry")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("hq,hk,Lq,Lk,d,block", [(4, 2, 300, 140000, 64, 128), (2, 1, 1030, 70000, 128, 64), (16, 8, 8200, 8200, 128, 128)])
+def test_tiles_of_listed_blocks_only(hq, hk, Lq, Lk, d, block, causal):
+    """K and V large enough for the bitmaps of listed blocks: rows of different lengths, with invalid entries behind and
+    among them, the last block listed by some; unlisted tiles of the workspace hold NaN."""
+    Q, K, V = _qkv(hq, hk, Lq, Lk, d, torch.bfloat16, seed=Lk)
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    stride = max(2, n_k // 12)
+    rng = np.random.default_rng(Lk)
+    cols = np.full((1, hq, n_q, stride), n_k + 3)
+    cnt = rng.integers(1, stride + 1, (1, hq, n_q))
+    for idx in np.ndindex(cnt.shape):
+        own = rng.choice(n_k, cnt[idx], replace=False)
+        own[0] = n_k - 1 if idx[2] % 2 else own[0]
+        own = np.unique(own)
+        cols[idx][:cnt[idx]] = np.append(own, [n_k + 9] * (cnt[idx] - len(own)))
+    t = lambda a: torch.from_numpy(a.astype(np.int32)).to(DEV)
+    ws = torch.full((bd.attn_workspace_size(Q, K, bd.params(block, 0.5, causal=causal)),), 0xFF, dtype=torch.uint8, device=DEV)
+    out = bd.basa_sparse_attn(Q, K, V, t(cnt), t(cols), block, ws=ws, causal=causal)
+    torch.cuda.synchronize()
+    ident_q, ident_k = np.arange(Lq), np.arange(Lk)
+    for h in (0, hq - 1):
+        kh = h // (hq // hk)
+        k, v = np64(K[0, kh]), np64(V[0, kh])
+        for g in (0, n_q // 2, n_q - 1):
+            rows = ident_q[g * block:(g + 1) * block]
+            keys = np.concatenate([ident_k[c * block:(c + 1) * block] for c in cols[0, h, g, :cnt[0, h, g]] if c < n_k])
+            s = np64(Q[0, h])[rows] @ k[keys].T / d ** 0.5
+            if causal:
+                s = np.where(keys[None] <= rows[:, None] + (Lk - Lq), s, -np.inf)
+            m = s.max(1, keepdims=True)
+            p = np.exp(s - np.where(np.isinf(m), 0.0, m))
+            ref = p @ v[keys] / np.maximum(p.sum(1, keepdims=True), 1e-300)
+            check_output(np64(out[0, h])[rows], ref, True, f"head {h} block {g}")
