@@ -346,25 +346,23 @@ basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
   constexpr int kQueries = 32 * QG;
   const int B = p.a.B;
   p.wgs_per_head = ceil_div(p.Nq * B, kQueries);
-  // workgroups without splitting, one to a compute unit (of one batch entry, so that an entry's result does not
-  // depend on the others)
-  const int work = p.a.q.heads * p.wgs_per_head;
+  const int work = BHq * p.wgs_per_head;                  // workgroups without splitting, one to a compute unit
   // How many workgroups share a list: rounds of workgroups times (steps of one, a tile per slice each, plus
   // its prologue and epilogue), plus the combining pass and its bytes.  The step times are measured
   // (attn_f32_kernel at 1, 2 and 4 splits: 26.2, 17.0, 12.3 us for one head of L = 1024, d = B = 64, and 4.2 us
   // for the combining pass; L = 4096, d = B = 128, 8 heads: 293 us unsplit, 315 + 11 in two).
   const int tiles = (p.a.row_cols ? std::min(p.a.cols_stride, p.Nk) : p.Nk) * (B / kTK);
-  const size_t row_bytes = (size_t)p.a.q.heads * p.a.q.L * (D * 4 + 8);
+  const size_t row_bytes = (size_t)BHq * p.a.q.L * (D * 4 + 8);
   const double step_us = (D == 128 ? 9.2 : 4.5) * (QG * KS == 8 ? 1.0 : 0.6);
   double best = 0.0;
   int splits = 1;
-  for (int s = 1; s <= kMaxSplits && (s == 1 || (tiles >= s * KS && s * row_bytes * p.a.q.batch <= p.a.ws_bytes)); ++s) {
+  for (int s = 1; s <= kMaxSplits && (s == 1 || (tiles >= s * KS && s * row_bytes <= p.a.ws_bytes)); ++s) {
     const double cost = ceil_div(work * s, kCUs) * (ceil_div(tiles, s * KS) * step_us + 8.0) +
                         (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
     if (s == 1 || cost < best) { best = cost; splits = s; }
   }
   p.splits = splits;
-  p.total = BHq * p.wgs_per_head * splits;
+  p.total = work * splits;
   if (splits > 1) {
     p.part_o = reinterpret_cast<float*>(p.a.ws);
     p.part_ml = reinterpret_cast<float2*>(p.part_o + (size_t)splits * BHq * p.a.q.L * D);
@@ -407,10 +405,10 @@ basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const fl
 
 // Room for the partial results of as many workgroups per list as could be of use (callers who hand over
 // less get fewer): enough to give every compute unit two workgroups.
-size_t attn_f32_workspace_bytes(int batch, int heads, int Lq, int d) {
-  const int64_t wgs = (int64_t)heads * ceil_div(Lq, 128);
+size_t attn_f32_workspace_bytes(int BHq, int Lq, int d) {
+  const int64_t wgs = (int64_t)BHq * ceil_div(Lq, 128);
   const size_t splits = (size_t)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 2 * kCUs / wgs));
-  return align_up(splits * batch * heads * Lq * (d * 4 + 8), 256);
+  return align_up(splits * BHq * Lq * (d * 4 + 8), 256);
 }
 
 basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {

@@ -1167,7 +1167,7 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // (512 or 128 queries per workgroup) and the number of workgroups that share a list, from an estimate of the
 // time.  Lists are split on the 128-query shape (split 512-query workgroups measure no better: 75 against 72 us,
 // dense, 8 heads, L = 4100, d = 64), on the 512-query one only for the causal kernel, which has no
-// other.  The rule sees the heads of one batch entry, so that an entry's result does not depend on the others.
+// other.
 // One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries (causal: 3.4), 1.95 us for
 // two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; 20 us of prologue and epilogue per
 // round of workgroups of 512 queries, 10 us of 128, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
@@ -1185,14 +1185,14 @@ struct Plan { bool solo; int splits; };
 // (2.5 rounds): 388 -> 338 us; 24 heads, L = 12500, B = 64, keep 25 %: 644 -> 547; 32 heads, L = 9000, B = d = 64, keep
 // 10 %: 145 -> 104; kept at 512 queries: 32 heads, L = 16384, keep 10 % (four full rounds, 461 either way).
 constexpr int kSmallRounds = 2, kPlannedRounds = 6;
-Plan plan_call(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, bool small, size_t part_bytes) {
-  const size_t row_bytes = (size_t)heads * Lq * (d * 4 + 8);
+Plan plan_call(int BHq, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, bool small, size_t part_bytes) {
+  const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
   const double dead = 1.0 - (double)list_len / Nk, scale = d == 128 ? 1.0 : 0.63;
   Plan best{false, 1};
   double best_cost = 0.0;
   for (int solo = 0; solo <= (causal ? 0 : 1); ++solo) {
     const int queries = solo ? kSoloQueries : kWideQueries;
-    const int64_t wgs = (int64_t)heads * ceil_div(Nq * B, queries);
+    const int64_t wgs = (int64_t)BHq * ceil_div(Nq * B, queries);
     // blocks in the union of a workgroup's lists, measured (full method): the union over 512 queries is 1.14 times that
     // over 128 at 50 %, 1.22 at 75 %, 1.29 at 90 %; two lists of 64 queries make about 1.05 to 1.1
     const int groups = solo ? 1 : std::min(4, ceil_div(Nq * B, kSoloQueries));
@@ -1212,11 +1212,11 @@ Plan plan_call(int heads, int Nq, int Nk, int Lq, int B, int d, int list_len, bo
   }
   return best;
 }
-// Room for the partial rows of a batch entry, of as many workgroups per list as could be of use: two rounds of workgroups.
-size_t part_bytes_of(int heads, int Lq, int Nk, int B, int d, bool causal) {
+// Room for the partial rows of as many workgroups per list as could be of use: two rounds of workgroups.
+size_t part_bytes_of(int BHq, int Lq, int Nk, int B, int d, bool causal) {
   if (!causal && Nk * (B / kTileKeys) <= kMinSplitTiles) return 0;
-  const int64_t splits = std::min<int64_t>(std::min(kMaxSplits, Nk), 8 * kCUs / ((int64_t)heads * ceil_div(Lq, kSoloQueries)));
-  return splits < 2 ? 0 : (size_t)splits * heads * Lq * (d * 4 + 8);
+  const int64_t splits = std::min<int64_t>(std::min(kMaxSplits, Nk), 8 * kCUs / ((int64_t)BHq * ceil_div(Lq, kSoloQueries)));
+  return splits < 2 ? 0 : (size_t)splits * BHq * Lq * (d * 4 + 8);
 }
 
 // How much the lists of the query blocks that would share a 512-query workgroup have in common, on
@@ -1281,8 +1281,8 @@ size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B
   return 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B) + align_up((size_t)BHq * ceil_div(Nq * B, kWideQueries) * 4, 256) +
          sz_listed(BHkv, Nk);
 }
-size_t attn_mfma_split_bytes(int batch, int heads, int Lq, int Lk, int d, int B, bool causal) {
-  return align_up((size_t)batch * part_bytes_of(heads, Lq, ceil_div(Lk, B), B, d, causal), 256);
+size_t attn_mfma_split_bytes(int BHq, int Lq, int Lk, int d, int B, bool causal) {
+  return align_up(part_bytes_of(BHq, Lq, ceil_div(Lk, B), B, d, causal), 256);
 }
 
 basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
@@ -1361,12 +1361,12 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   const int gsz = kWideQueries / B;
   Plan plan{false, 1};
   m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
-  const int64_t rows = (int64_t)a.q.heads * Nq * B;
+  const int64_t rows = (int64_t)BHq * Nq * B;
   const bool small = rows < (int64_t)kSmallRounds * kCUs * kWideQueries;
   if (a.variant == 0 && rows < (int64_t)kPlannedRounds * kCUs * kWideQueries) {
     const size_t base = attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B);
-    plan = plan_call(a.q.heads, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0, small,
-                     (a.ws_bytes - base) / a.q.batch);
+    plan = plan_call(BHq, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0, small,
+                     a.ws_bytes - base);
     if (plan.splits > 1) {
       m.splits = plan.splits;
       m.part_o = reinterpret_cast<float*>(ws + base);
