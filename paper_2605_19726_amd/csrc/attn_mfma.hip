@@ -55,6 +55,10 @@ constexpr int kIxStride = kTileKeys + 4;    // causal: ints per tile of the key-
 #define BASA_ATTN_QR 7
 #endif
 constexpr float kLazyTau = 8.0f;            // log2 of the largest exponentiated score kept
+// Running maximum (log2 units) of a query that has met no score above -inf yet: below every finite one (a float times
+// log2(e) / 8 at most), and itself finite, so that its scores of -inf exponentiate to 0 and rescaling it by itself is 1;
+// from -inf both would be exp2(inf - inf).
+constexpr float kNoMax = -1e38f;
 // The pass without running maxima (64 queries per wave): a query's reference moves up by kShiftLog2
 // once the probabilities of half a tile add up to more than kSafeSum; a row whose final sum lies
 // outside [kMinSum, kMaxSum] (or is not a number) has left the range in which that pass is exact.
@@ -557,9 +561,7 @@ __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&
       const float mca = mxa * c, mcb = mxb * c;
       if (__builtin_amdgcn_ballot_w64(mca > st.m_run[0] + kLazyTau || mcb > st.m_run[1] + kLazyTau) != 0) {
         const float na = fmaxf(st.m_run[0], mca), nb = fmaxf(st.m_run[1], mcb);
-        // (causal: a query that still sees nothing has -inf on both sides; its state stays as it is)
-        const float aa = (kCausal && na == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(st.m_run[0] - na);
-        const float ab = (kCausal && nb == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(st.m_run[1] - nb);
+        const float aa = __builtin_amdgcn_exp2f(st.m_run[0] - na), ab = __builtin_amdgcn_exp2f(st.m_run[1] - nb);
         st.m_run[0] = na; st.m_run[1] = nb;
         st.l_run[0] *= aa; st.l_run[1] *= ab;
 #pragma unroll
@@ -568,9 +570,7 @@ __device__ __forceinline__ void process_tile2(WaveState2<D>& st, const bf16x8 (&
           for (int r = 0; r < 16; ++r) { st.o[0][i][r] *= aa; st.o[1][i][r] *= ab; }
       }
     }
-    // (causal: a query that has seen no key yet subtracts 0, so that exp2 sees -inf, never inf - inf)
-    const float ma = (!kFast && kCausal && st.m_run[0] == -INFINITY) ? 0.f : st.m_run[0];
-    const float mb = (!kFast && kCausal && st.m_run[1] == -INFINITY) ? 0.f : st.m_run[1];
+    const float ma = st.m_run[0], mb = st.m_run[1];
     bf16x8 pa[2], pb[2];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -616,7 +616,7 @@ template <int D>
 __device__ __forceinline__ void init_state(WaveState<D>& st, bool fast = false) {
 #pragma unroll
   for (int i = 0; i < Geo<D>::kDBlocks; ++i) st.o[i] = floatx16{0};
-  st.m_run = fast ? 0.f : -INFINITY;
+  st.m_run = fast ? 0.f : kNoMax;
   st.l_run = 0.f;
   st.lt = 0.f;
 }
@@ -626,7 +626,7 @@ __device__ __forceinline__ void init_state(WaveState2<D>& st, bool fast = false)
   for (int r = 0; r < 2; ++r) {
 #pragma unroll
     for (int i = 0; i < Geo<D>::kDBlocks; ++i) st.o[r][i] = floatx16{0};
-    st.m_run[r] = fast ? 0.f : -INFINITY;
+    st.m_run[r] = fast ? 0.f : kNoMax;
     st.l_run[r] = 0.f;
     st.lt[r] = 0.f;
   }

@@ -75,6 +75,39 @@ def test_f32_infinite_scores_and_an_infinite_last_value_row(d, block, Lk):
     np.testing.assert_allclose(out[0, 0].cpu().double().numpy(), ref.numpy(), rtol=1e-4, atol=1e-4)
 
 
+@pytest.mark.parametrize("shape", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("hq,d,block,Lk,hidden", [(2, 64, 64, 300, 64), (3, 128, 128, 1000, 128), (2, 128, 128, 4096, 64),
+                                                  (2, 64, 128, 4096 + 33, 1500), (1, 128, 64, 8200, 8000)])
+def test_bf16_keys_whose_scores_are_minus_infinity(hq, d, block, Lk, hidden, shape):
+    """As above in bf16, on whole lists and (shape 0, above 32 tiles) on split ones: the hidden keys fill the first tile of a
+    list, of a part of it, or whole parts.  Every other query sees all keys, so that within a wave some have a maximum
+    and some do not; queries 4 to 7 have scores shifted by +-300 (log2 units), which the pass without running maxima
+    hands on to the one with them; query 8 sees no key at all and comes out as zeros."""
+    Lq = 200
+    Q, K, V = _qkv(hq, 1, Lq, Lk, d, torch.bfloat16, seed=Lk + d)
+    Q[:, :, 0::2, 0], Q[:, :, 1::2, 0] = 1e20, 0.0
+    K[..., 0] = 0.0
+    K[..., :hidden, 0] = -1e20                   # times 1e20: below the smallest float
+    K[..., 1], Q[..., 1], Q[..., 8, 1] = 1e20, 0.0, -1e20
+    K[..., 2], Q[..., 2] = 16.0, 0.0             # the same for every key: shifts all scores of a query
+    shift = 300.0 / 1.4426950408889634 * d ** 0.5 / 16.0
+    Q[:, :, 4:6, 2], Q[:, :, 6:8, 2] = shift, -shift
+    out, lse = bd.basa_sparse_attn(Q, K, V, None, None, block, want_lse=True, attn_shape=shape)
+    torch.cuda.synchronize()
+    for h in range(hq):
+        q, k, v = np64(Q[0, h]), np64(K[0, 0]), np64(V[0, 0])
+        with np.errstate(over="ignore"):
+            s = (q @ k.T / d ** 0.5).astype(np.float32).astype(np.float64)
+        m = s.max(1, keepdims=True)
+        p = np.exp(s - np.where(np.isinf(m), 0.0, m))
+        l = p.sum(1, keepdims=True)
+        check_output(np64(out[0, h]), p @ v / np.maximum(l, 1e-300), True, f"head {h}")
+        got = lse[0, h].cpu().numpy()
+        assert got[8] == -np.inf
+        rest = np.arange(Lq) != 8
+        np.testing.assert_allclose(got[rest], (m + np.log(np.maximum(l, 1e-300)))[rest, 0], rtol=1e-4, atol=3e-2)
+
+
 @pytest.mark.parametrize("d,block,L", [(64, 64, 300), (128, 128, 200), (128, 64, 4000)])
 def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_maxima(d, block, L):
     """Scores near +300 and near -300 (log2 units): the 128-query shape has to repeat itself with running maxima
