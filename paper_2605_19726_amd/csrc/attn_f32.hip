@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const flo
   floatx4 o = {0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < splits; ++s) {
     const float2 ml = part_ml[s * rows + row];
-    if (ml.x == -INFINITY) continue;                     // nothing was seen there (and perhaps nothing written)
+    if (ml.y == 0.f) continue;                           // nothing was seen there (and perhaps nothing written); not so a NaN
     const float f = __builtin_amdgcn_exp2f(ml.x - m);
     const floatx4 t = *reinterpret_cast<const floatx4*>(part_o + (s * rows + row) * D + 4 * sub);
     l = fmaf(ml.y, f, l);

@@ -108,6 +108,21 @@ def test_bf16_keys_whose_scores_are_minus_infinity(hq, d, block, Lk, hidden, sha
         np.testing.assert_allclose(got[rest], (m + np.log(np.maximum(l, 1e-300)))[rest, 0], rtol=1e-4, atol=3e-2)
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,Lk,causal", [(64, 300, False), (128, 4096, False), (128, 4096, True)])
+def test_nan_of_a_query_reaches_its_output_row(dtype, d, Lk, causal):
+    """Also where the list is split over workgroups that each saw no number (above 32 tiles in bf16, all sizes in f32)."""
+    Lq = 200
+    Q, K, V = _qkv(2, 1, Lq, Lk, d, dtype, seed=Lk)
+    Q[0, 1, 77] = float("nan")
+    out, lse = bd.basa_dense_attn(Q, K, V, 128, want_lse=True, causal=causal)
+    torch.cuda.synchronize()
+    nan = torch.zeros(2, Lq, dtype=torch.bool)
+    nan[1, 77] = True
+    assert torch.equal(torch.isnan(lse[0]).cpu(), nan)
+    assert torch.equal(torch.isnan(out[0]).all(-1).cpu(), nan) and torch.equal(torch.isnan(out[0]).any(-1).cpu(), nan)
+
+
 @pytest.mark.parametrize("d,block,L", [(64, 64, 300), (128, 128, 200), (128, 64, 4000)])
 def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_maxima(d, block, L):
     """Scores near +300 and near -300 (log2 units): the 128-query shape has to repeat itself with running maxima
