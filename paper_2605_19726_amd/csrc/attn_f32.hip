@@ -44,10 +44,26 @@ constexpr int kTK = 32;                     // keys per tile
 constexpr float kLazyTau = 8.0f;            // log2 of the largest exponentiated score kept before a rescale
 constexpr int kCUs = 256, kMaxSplits = 16;
 
+// Log-sum-exp from a running maximum in log2 units and its sum.  The unit is the rounded scale_log2e times a score, so
+// the factor back to natural units is computed from it in double and kept in two parts, and the sum m + log2(l), whose
+// last place is twice that of the result, is not formed: scores near 1000 (lse 2000, d = 64): off by 8.7e-5 at
+// most, 1.8e-4 as (m + log2(l)) ln 2; half a unit in the last place is 6.1e-5.
+struct LseFactor { float hi, lo; };
+LseFactor lse_factor(int d) {
+  const double f = 1.0 / (sqrt((double)d) * (double)(1.4426950408889634f / sqrtf((float)d)));
+  LseFactor k;
+  k.hi = (float)f; k.lo = (float)(f - (double)k.hi);
+  return k;
+}
+__device__ __forceinline__ float lse_of(float m, float l, LseFactor k) {
+  return l == 0.f ? -INFINITY : fmaf(m, k.hi, fmaf(m, k.lo, __log2f(l) * 0.6931471805599453f));
+}
+
 struct F32Args {
   AttnArgs a;
   int Nq, Nk, group, wgs_per_head, total, splits;
   float scale_log2e;
+  LseFactor lse_k;
   float* part_o;                            // splits > 1: [split][BHq][Lq][D], rows by sorted position
   float2* part_ml;                          //             [split][BHq][Lq] running maximum (log2), running sum
 };
@@ -303,13 +319,14 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
     if constexpr (DB == 4) *reinterpret_cast<floatx4*>(op + 4 * i) = floatx4{o[0][r], o[1][r], o[2][r], o[3][r]} * inv_l;
     else *reinterpret_cast<floatx2*>(op + 2 * i) = floatx2{o[0][r], o[1][r]} * inv_l;
   }
-  if (a.lse && h == 0) a.lse[(int64_t)bhq * Lq + qrow] = (m_run + __log2f(l_tot)) * 0.6931471805599453f;
+  if (a.lse && h == 0) a.lse[(int64_t)bhq * Lq + qrow] = lse_of(m_run, l_tot, p.lse_k);
 }
 
 // Adds up the partial results of the workgroups that shared a query's list: D/4 lanes per query.
 template <bool kBf16, int D>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const float* __restrict__ part_o,
-                                                           const float2* __restrict__ part_ml, int splits, int64_t rows) {
+                                                           const float2* __restrict__ part_ml, int splits, int64_t rows,
+                                                           LseFactor lse_k) {
   constexpr int LPR = D / 4;
   const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;       // bhq * Lq + sorted position
   if (row >= rows) return;
@@ -338,7 +355,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const flo
   } else {
     *reinterpret_cast<floatx4*>(reinterpret_cast<float*>(a.out) + a.out_offset(bhq, qrow) + 4 * sub) = o * inv_l;
   }
-  if (a.lse && sub == 0) a.lse[(int64_t)bhq * Lq + qrow] = (m + __log2f(l)) * 0.6931471805599453f;
+  if (a.lse && sub == 0) a.lse[(int64_t)bhq * Lq + qrow] = lse_of(m, l, lse_k);
 }
 
 template <int D, int QG, int KS>
@@ -392,7 +409,8 @@ basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const fl
   const int rpw = 256 / (a.q.d / 4);
   const dim3 grid((unsigned)((rows + rpw - 1) / rpw));
   ProfScope prof(K_ATTN_COMBINE, st);
-#define BASA_COMB(BF, D) hipLaunchKernelGGL((attn_combine_kernel<BF, D>), grid, dim3(256), 0, st, a, part_o, part_ml, splits, rows)
+#define BASA_COMB(BF, D) hipLaunchKernelGGL((attn_combine_kernel<BF, D>), grid, dim3(256), 0, st, a, part_o, part_ml, splits, rows, \
+                                               lse_factor(D))
   const bool bf = a.q.dtype == BASA_BF16;
   if (bf && a.q.d == 128) BASA_COMB(true, 128);
   else if (bf) BASA_COMB(true, 64);
@@ -419,6 +437,7 @@ basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {
   if (BHq == 0 || p.Nq == 0) return BASA_OK;
   p.group = a.q.heads / a.k.heads;
   p.scale_log2e = 1.4426950408889634f / sqrtf((float)a.q.d);
+  p.lse_k = lse_factor(a.q.d);
   p.part_o = nullptr; p.part_ml = nullptr;
   if (!a.ws || reinterpret_cast<uintptr_t>(a.ws) % 16) p.a.ws_bytes = 0;
   // queries per workgroup = the query block; slices so that its tiles fill the LDS (128 KB of ring)

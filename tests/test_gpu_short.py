@@ -123,6 +123,25 @@ def test_nan_of_a_query_reaches_its_output_row(dtype, d, Lk, causal):
     assert torch.equal(torch.isnan(out[0]).all(-1).cpu(), nan) and torch.equal(torch.isnan(out[0]).any(-1).cpu(), nan)
 
 
+@pytest.mark.parametrize("d,L", [(64, 300), (64, 3000), (128, 700), (128, 5000)])
+def test_f32_lse_of_large_scores(d, L):
+    """Scores near 500 to 2000.  The result is a rounded fp32 number: half a unit in its last place (0.55 with the small
+    terms).  The d additions behind the large product of a score round to its place, ulp / sqrt(12) each, sqrt(d) together,
+    and 1 / sqrt(d) scales them; averaging over the L / e keys that count (scores of unit variance) leaves the standard
+    deviation below, of which four cover 200 queries."""
+    Q, K, V = _qkv(3, 1, 200, L, d, torch.float32, seed=d + L)
+    K[..., 2], Q[..., 2] = 16.0, torch.tensor([300.0, -300.0, 1000.0], device=DEV)[None, :, None]
+    _, lse = bd.basa_dense_attn(Q, K, V, 128, want_lse=True)
+    torch.cuda.synchronize()
+    for h in range(3):
+        s = np64(Q[0, h]) @ np64(K[0, 0]).T / d ** 0.5
+        m = s.max(1)
+        ref = m + np.log(np.exp(s - m[:, None]).sum(1))
+        ulp = lambda x: np.spacing(np.abs(x).astype(np.float32)).astype(np.float64)
+        bound = 0.55 * ulp(ref) + 4.0 * ulp(ref * d ** 0.5) / 12 ** 0.5 / (L / np.e) ** 0.5
+        assert (np.abs(lse[0, h].cpu().numpy() - ref) <= bound).all(), h
+
+
 @pytest.mark.parametrize("d,block,L", [(64, 64, 300), (128, 128, 200), (128, 64, 4000)])
 def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_maxima(d, block, L):
     """Scores near +300 and near -300 (log2 units): the 128-query shape has to repeat itself with running maxima
