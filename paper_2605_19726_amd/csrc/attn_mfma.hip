@@ -37,6 +37,7 @@
 // two tiles: one pair is computed while the next pair lands; one workgroup barrier per pair.
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <type_traits>
 #include "common.hpp"
 
@@ -1113,6 +1114,16 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
 size_t sz_kv(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 2, 256); }
 size_t sz_kix(int BHkv, int Nk, int B) { return align_up((size_t)BHkv * (Nk * B / kTileKeys) * kIxStride * 4, 256); }
 
+// Do the bitmaps of the listed blocks cost less than the tiles they save?  They take 5 us and 5 us per million list
+// entries (the atomics of a row meet in the same words); the tiles move kv_bytes four times at 5.6 TB/s, and with lists
+// of a share f of the blocks about (1 - f)^1.5 / 2 of that time is saved: rows of a KV head add up to much more than one
+// of them.  Tiling, all blocks -> listed ones by the bitmaps: 32 heads, L = 16384, keep 10 / 25 / 50 %: 90 -> 32, 87 -> 46,
+// 85 -> 68 us; 32 heads, 256 queries of 32768, 25 %: 188 -> 55; 32 heads on 8, L = 100000, B = 64 (6252 rows per KV head), 10 %:
+// 139 -> 105; against, same sizes, 25 / 50 / 75 %: 138 -> 188, 137 -> 313, 137 -> 428; 8 heads, L = 24000, B = 64, 50 %: 35 -> 40.
+bool bitmaps_pay(size_t kv_bytes, double f, double entries) {
+  const double tiling_us = 4.0 * (double)kv_bytes / 5.6e6;
+  return tiling_us * 0.5 * (1.0 - f) * std::sqrt(1.0 - f) > 5.0 + 5e-6 * entries;
+}
 size_t sz_listed(int BHkv, int Nk) { return align_up((size_t)BHkv * kListedParts * ceil_div(Nk, 32) * 4, 256); }
 
 template <int D>
@@ -1324,15 +1335,12 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     ProfScope prof(K_GATHER, st);
     const dim3 grid(Nk * B / kTileKeys, BHkv, 2);
     const int by_index = a.causal && B == 128 && a.perm_k;
-    // Worth a launch of its own (about 5 us) once the tiles take longer than twice that (32 MB read, as much written:
-    // 10 us) and the lists leave something out: 32 heads, L = 16384, keep 10 % / 25 % / 50 %: 90 / 88 / 88 us of tiling ->
-    // 32 / 51 / 73; 500 queries against 60000 keys, 32 heads, keep 10 %: 351 -> 50.
     const int rows = a.q.heads / a.k.heads * Nq;
     const int64_t entries = (int64_t)rows * a.cols_stride;
     uint32_t* listed = nullptr;
     int parts = 1;
-    if (a.row_cols && (int64_t)a.cols_stride * 10 <= (int64_t)Nk * 9 && entries < ((int64_t)1 << 31) && Nk <= 32 * kMaxListedWords &&
-        sz_kv(BHkv, Nk, B, d) >= ((size_t)16 << 20)) {
+    if (a.row_cols && entries < ((int64_t)1 << 31) && Nk <= 32 * kMaxListedWords &&
+        bitmaps_pay(sz_kv(BHkv, Nk, B, d), std::min(1.0, (double)a.cols_stride / Nk), (double)entries * BHkv)) {
       parts = (int)std::min<int64_t>(std::min(rows, kListedParts), (entries + 4095) / 4096);
       listed = reinterpret_cast<uint32_t*>(ws + attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B) - sz_listed(BHkv, Nk));
       hipLaunchKernelGGL(listed_blocks_kernel, dim3(BHkv, parts), dim3(1024), 0, st, a.row_count, a.row_cols, a.cols_stride, rows,
