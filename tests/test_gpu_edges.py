@@ -77,7 +77,8 @@ def test_inputs_that_tie_everywhere():
 
 def test_batch_two_with_strided_batches():
     """Two batches living in one buffer with a gap between them: each batch must come out exactly
-    as it does when passed alone, and batch 1 must match the oracle."""
+    as it does when passed alone (lists of up to 32 key tiles are never split, and whole lists give the same
+    bits on either shape; longer ones of small calls agree within rounding), and batch 1 must match the oracle."""
     w = C[4].scaled("batch2", heads_q=2, heads_kv=2, L=1024 + 128 + 9)
     parts = [synth.make_qkv(w.scaled(f"b{i}", index=40 + i), device=DEV) for i in range(2)]
     def pack(i):
@@ -333,7 +334,8 @@ def test_every_workgroup_shape_against_the_oracle(L, block, d):
             np.testing.assert_allclose(lse[0, h].cpu().numpy(), lse_ref, rtol=0, atol=3e-2)
     # 32 queries per wave: every wave walks its own tiles in the same order in both shapes: identical bits
     assert torch.equal(outs[0][0], outs[1][0])
-    # too small for the overlap probe: the library takes the 512-query shape
+    # too small for the overlap probe, lists too short to be split: the library takes 128 or 512 queries per workgroup, whose
+    # passes without running maxima give the same bits
     assert torch.equal(outs[3][0], outs[2][0]) and torch.equal(outs[3][1], outs[2][1])
 
 

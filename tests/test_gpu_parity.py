@@ -60,9 +60,9 @@ def test_norm_sort_windowed_and_ties():
 
 
 def test_norm_sort_with_runs_of_three_to_eighteen_tiles():
-    """Segments longer than two sort tiles go through the kernel that merges four tiles in LDS: a ragged
-    quad that is also the last pass (window of 3.03 tiles), whole quads followed by ordinary passes
-    (10 tiles per window, the last window cut short), one run of 17.1 tiles, and a segment list."""
+    """Windows of 3.03, 10 (the last one cut short) and 4 large sort tiles, one run of 17.1, and a segment list.  These calls
+    are few enough words for tiles of 1024 and ranking; test_norm_sort_of_many_words_... in test_gpu_short.py has the same
+    runs on tiles of 4096 and the kernel that merges four of them in LDS."""
     w = C[1].scaled("quads", heads_q=2, heads_kv=2, L=70000 + 64)
     Q, _, _ = gen(w)
     for window in (12416, 40960, 16384, 0):

@@ -1,5 +1,7 @@
 """Kernels and dispatch branches for calls that do not fill the device: sizes around their tiles,
 slices and splits, against the oracle."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -169,7 +171,7 @@ def test_small_calls_with_scores_outside_the_range_of_the_pass_without_running_m
 @pytest.mark.parametrize("d,block", [(64, 64), (128, 128)])
 @pytest.mark.parametrize("hq,Lq,Lk", [(2, 1, 1), (2, 64 * 33 - 5, 64 * 65 + 1), (4, 300, 20000), (90, 64 * 64 * 2, 64 * 129)])
 def test_block_scores_of_small_maps(hq, Lq, Lk, d, block, beta):
-    """The 32 x 32 tiles of small maps (the last sizes lie around the largest number of tiles that takes them)."""
+    """The 32 x 32 tiles of small maps (2 to 540 tiles of 64 x 64)."""
     Q, K, _ = _qkv(hq, 2, Lq, Lk, d, torch.bfloat16, seed=Lq + d)
     sel = bd.basa_select(Q, K, block, 0.5, beta, bd.SORT_NONE, want_scores=True)
     torch.cuda.synchronize()
@@ -263,3 +265,81 @@ def test_tiles_of_listed_blocks_only(hq, hk, Lq, Lk, d, block, causal):
             p = np.exp(s - np.where(np.isinf(m), 0.0, m))
             ref = p @ v[keys] / np.maximum(p.sum(1, keepdims=True), 1e-300)
             check_output(np64(out[0, h])[rows], ref, True, f"head {h} block {g}")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype,d,block", [(torch.bfloat16, 128, 128), (torch.bfloat16, 64, 64), (torch.float32, 128, 128)])
+def test_split_lists_with_several_batch_entries_and_less_workspace(dtype, d, block, causal):
+    """Three entries in a token-major buffer, lists of up to 80 tiles: split as far as the workspace has room for partial
+    rows (all of it, two parts per list, none).  Every entry against the oracle each time.  In bf16 the workspace shows
+    in the bits: without room the lists stay whole, as those of attn_shape 3 are."""
+    b, hq, hk, Lq, Lk = 3, 4, 2, 300, 5000
+    g = torch.Generator(device=DEV).manual_seed(d + block)
+    r = lambda h, L: torch.randn((b, L, h, d), generator=g, device=DEV).to(dtype).permute(0, 2, 1, 3)
+    Q, K, V = r(hq, Lq), r(hk, Lk), r(hk, Lk)
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    lists = [_lists(hq, n_q, n_k, 70 + i, n_k) for i in range(b)]
+    cnt, cols = torch.cat([x[0] for x in lists]), torch.cat([x[1] for x in lists])
+    pq, pk = torch.cat([_perm(hq, Lq, 10 * i) for i in range(b)]), torch.cat([_perm(hk, Lk, 500 + 10 * i) for i in range(b)])
+    call = lambda **kw: bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, causal=causal, **kw)
+    room = lambda n: torch.full((n,), 0xFF, dtype=torch.uint8, device=DEV)
+    full = bd.attn_workspace_size(Q, K, bd.params(block, causal=causal))
+    least = 256
+    if dtype == torch.bfloat16:
+        with pytest.raises(bd.BasaError, match="too small: need") as e:
+            call(ws=room(256))
+        least = int(re.search(r"need (\d+) bytes", str(e.value)).group(1))
+    two = least + 2 * b * hq * Lq * (4 * d + 8)
+    assert least < two < full
+    got = [call(ws=room(n)) for n in (full, two, least)]
+    torch.cuda.synchronize()
+    if dtype == torch.bfloat16:
+        whole = call(attn_shape=3)
+        assert torch.equal(got[2][0], whole[0]) and torch.equal(got[2][1], whole[1])
+        assert not torch.equal(got[0][0], whole[0]) and not torch.equal(got[1][0], whole[0]) and not torch.equal(got[0][0], got[1][0])
+    fn = o.sparse_attention_causal if causal else o.sparse_attention
+    for i in range(b):
+        for h in range(hq):
+            args = (np64(Q[i, h]), np64(K[i, h // 2]), np64(V[i, h // 2]), pq[i, h].cpu().numpy(), pk[i, h // 2].cpu().numpy(),
+                    [lists[i][3][0, h, j, :lists[i][2][0, h, j]] for j in range(n_q)], block)
+            ref, ref_lse = fn(*args, return_lse=True)
+            fin = np.isfinite(ref_lse)
+            for out, lse in got:
+                check_output(np64(out[i, h]), ref, dtype == torch.bfloat16, f"entry {i} head {h}")
+                have = lse[i, h].cpu().numpy()
+                assert np.array_equal(np.isfinite(have), fin)
+                np.testing.assert_allclose(have[fin], ref_lse[fin], rtol=0, atol=2e-2 if dtype == torch.bfloat16 else 1e-4)
+
+
+@pytest.mark.parametrize("dtype,d,windows", [(torch.bfloat16, 128, (12416, 40960, 16384, 0)), (torch.float32, 64, (12416, 0))])
+def test_norm_sort_of_many_words_with_runs_of_three_to_eighteen_tiles(dtype, d, windows):
+    """Past 2^19 words: tiles of 4096, and the kernel that merges four of them in LDS (a ragged quad that is also the last
+    pass, whole quads followed by ordinary passes, one run of 17.1 tiles), then segments that straddle tiles."""
+    heads, L = 8, 70000 + 64
+    g = torch.Generator(device=DEV).manual_seed(d)
+    x = torch.randn((1, heads, L, d), generator=g, device=DEV).to(dtype)
+    x[0, 0, 9000:9064] = x[0, 0, 100:164]                # exact ties across tiles
+    x[0, 7, 4090:4100] = x[0, 7, 4080:4090]              # and around a tile edge
+    assert heads * L > 1 << 19
+    for kw in [dict(window=w) for w in windows] + [dict(segments=[0, 4095, 4097, 9000, 30001, 50000])]:
+        perm = bd.basa_norm_sort(x, 128, **kw)
+        torch.cuda.synchronize()
+        for h in (0, 3, heads - 1):
+            assert np.array_equal(perm[0, h].cpu().numpy(), o.norm_sort(np64(x[0, h]), **kw)), (kw, h)
+
+
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("hq,n_q,n_k", [(20, 500, 507), (20, 500, 513), (4, 130, 4000)])
+def test_block_scores_on_both_sides_of_the_line_between_the_tile_sizes(hq, n_q, n_k, d, beta):
+    """Ragged rows and columns: 1280 tiles of 64 x 64 (the small kernel's last), 1440, and 756 of few rows and many columns."""
+    Q, K, _ = _qkv(hq, 2, 64 * n_q - 5, 64 * n_k - 9, d, torch.bfloat16, seed=n_k + d)
+    sel = bd.basa_select(Q, K, 64, 0.5, beta, bd.SORT_NONE, want_scores=True)
+    torch.cuda.synchronize()
+    for h in (0, hq - 1):
+        mq, vq = o.block_stats(np64(Q[0, h]), 64)
+        mk, vk = o.block_stats(np64(K[0, h // (hq // 2)]), 64)
+        ref = o.baseline_logits(mq, mk)
+        if beta:
+            ref = ref + beta * o.diag_compensation(mq, vq, mk, vk)
+        np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
