@@ -74,11 +74,12 @@ typedef struct {
                                 as a mass budget), at least min_keep and at most kappa    */
   int32_t min_keep;          /* floor on the per-row count when mass_target > 0; 0 means 1 */
   int32_t attn_shape;        /* basa_sparse_attn, bf16 only: shape of the attention workgroup.
-                              * 0 = chosen by the library: calls that do not fill the device take
-                              * 2 (with the arithmetic of 3, or, on lists of more than 32 key
-                              * tiles, several workgroups per list whose results are added up);
-                              * the others 3 or 2, chosen on the device from how much the lists of
-                              * neighbouring query blocks overlap,
+                              * 0 = chosen by the library: 3, or, in calls of up to six workgroups of
+                              * 512 queries per compute unit and where an estimate of the time says so,
+                              * 2 with the arithmetic of 3.  Below two, lists of more than 32 key tiles
+                              * may be split over several workgroups whose results are added up; from
+                              * two on, block lists that overlap little between neighbouring query
+                              * blocks (found out on the device) send the call to 2,
                               * 1 = 256 queries sharing every K/V tile, 2 = 128 queries,
                               * 3 = 512 queries (64 per wave).  1 and 2 give identical bits;
                               * 3 runs the online softmax against a reference that is raised only
@@ -135,7 +136,10 @@ int32_t basa_kappa(int32_t n_k, double sparsity);
 /* Bytes of workspace basa_select needs for these shapes (0 on invalid arguments).  Each stage has
  * its own size call, so that a caller who runs one stage does not reserve the others' scratch. */
 size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
-/* Bytes of workspace basa_sparse_attn / basa_dense_attn need (0 on invalid arguments). */
+/* Bytes of workspace basa_sparse_attn / basa_dense_attn make use of (0 on invalid arguments).  bf16: the
+ * tiled K and V are required (BASA_ERR_WORKSPACE names the bytes), the rest is room for partial results of
+ * lists that are split over workgroups; f32: all of it is.  With less room lists are split less, or not at
+ * all, which costs time and never the call. */
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
 /* Bytes of workspace basa_norm_sort needs for x. */
 size_t basa_sort_workspace_size(const basa_tensor* x, const basa_params* p);
@@ -221,6 +225,12 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
  * tokens; the row of sorted position i is written to out row perm_q[i].
  * bf16 tensors: bf16 MFMA with fp32 accumulation and fp32 softmax state (d = 64 or 128);
  * f32 tensors: fp32 throughout.
+ * A key whose score is -inf (and whose V row is finite) carries no weight; a query that has no other gets
+ * a zero row and lse = -inf.
+ * Repeating a call gives the same bits.  How far lists are split (f32 tensors; bf16 with attn_shape = 0)
+ * depends on batch * heads_q * L_q of the whole call and on ws_bytes, so that a batch entry agrees with
+ * the same entry passed alone, or with another workspace, within rounding only.  Lists are never split
+ * with attn_shape 1 to 4, nor for f32 tensors with ws_bytes below 2 * batch * heads_q * L_q * (4 d + 8).
  *   row_count    [batch, heads_q, N_q] int32, each in [1, N_k].
  *   row_cols     [batch, heads_q, N_q, cols_stride] int32, ascending, each in [0, N_k).
  *                NULL means every key block for every row (dense).  The lists are device
@@ -236,8 +246,8 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
  *                Rows of out must not alias each other or the inputs.
  *   lse          out, nullable, [batch, heads_q, L_q] float: log-sum-exp of the kept
  *                logits of every query (original order).
- *   ws           workspace of basa_attn_workspace_size() bytes.
- *   p            block and attn_shape are read.
+ *   ws           workspace of basa_attn_workspace_size() bytes, or fewer (see there).
+ *   p            block, attn_shape and causal are read.
  */
 basa_status basa_sparse_attn(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v,
                              const int32_t* row_count, const int32_t* row_cols,
@@ -248,7 +258,7 @@ basa_status basa_sparse_attn(const basa_tensor* q, const basa_tensor* k, const b
 /*
  * Dense bidirectional attention (Eq. 1) through the same kernels with every key
  * block listed and no permutation: the baseline sparse runs are compared with.
- * Only p->block is read.
+ * p->block and p->causal are read; workgroups are chosen, and lists split, as with attn_shape 0.
  */
 basa_status basa_dense_attn(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v,
                             const basa_params* p, void* out, const int64_t* out_strides,

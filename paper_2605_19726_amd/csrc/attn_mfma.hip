@@ -14,16 +14,13 @@
 // The swizzles make every ds_read_b128 of 16 consecutive lanes hit 16 distinct 16-byte
 // bank groups.
 //
-// Main kernel: one workgroup of 8 waves owns 256 consecutive sorted queries, i.e. 2 query
-// blocks of 128 (4 of 64), one wave per 32 queries.  Streaming K/V tiles from L2 into LDS is
-// the costly part beside the MFMAs themselves (with 128 queries per tile fetch the kernel was
-// 12 % slower: 8 TB/s of L2 -> LDS traffic), so the query blocks of a workgroup share every tile,
-// and 256 queries are what the register file holds (64 accumulator registers per 32 queries,
-// two waves per SIMD): the workgroup walks the UNION
-// of their block lists in ascending order, each tile is fetched once, and only the waves
-// whose query block lists the tile's key block compute on it.  Scores are computed
-// TRANSPOSED, S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (A = K tile rows from
-// LDS, B = Q^T held in registers), so that every lane owns ONE query: the running max,
+// Main kernel: a workgroup owns 512, 256 or 128 consecutive sorted queries, i.e. 4, 2 or 1 query blocks of 128
+// (twice as many of 64); a wave owns 64 queries in the first shape, which large calls run on, and 32 in the
+// others (see kWideQueries below).  Streaming K/V tiles from L2 into LDS is the costly part beside the MFMAs
+// themselves, so the query blocks of a workgroup share every tile: it walks the UNION of their block lists in
+// ascending order, each tile is fetched once, and only the waves whose query block lists the tile's key block
+// compute on it.  Scores are computed TRANSPOSED, S^T = K Q^T with
+// v_mfma_f32_32x32x16_bf16 (A = K tile rows from LDS, B = Q^T held in registers), so that every lane owns ONE query: the running max,
 // running sum and the rescale factor of the online softmax are per-lane scalars, the
 // row max needs a single exchange between lanes l and l+32, and the exponentiated
 // accumulator registers are, after packing to bf16, already the B operand of the
@@ -33,8 +30,9 @@
 // 8*(e/4) + 4h + e%4 of the group, which is the key order inside a Vt chunk pair.
 // The running max is refreshed lazily: the accumulators are rescaled only when some
 // query's tile max exceeds its running max by more than 2^8, so the common iteration
-// touches O only through MFMA.  K/V tiles go through a 4-stage LDS ring used as two slots of
-// two tiles: one pair is computed while the next pair lands; one workgroup barrier per pair.
+// touches O only through MFMA (or there is no running max at all, see process_tile2).  K/V tiles go
+// through an LDS ring of two stages, one tile computed while the next one lands, a workgroup barrier
+// per tile; the 256-query shape has four, two slots of two tiles.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -1181,7 +1179,8 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // other.
 // One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries (causal: 3.4), 1.95 us for
 // two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; 20 us of prologue and epilogue per
-// round of workgroups of 512 queries, 10 us of 128, 4 us for the combining pass, and the partial rows at 2 TB/s written and read.
+// round of workgroups of 512 queries (25 us of lists of one block, where nothing overlaps them), 10 us of 128, 4 us for the
+// combining pass, and the partial rows at 2 TB/s written and read.
 // Attention call (tiling of K and V included), one workgroup of 512 queries per list -> this rule:
 // 256 queries against 32K keys, 32 heads on 8, keep 25 %: 351 -> 98 us (128 queries, 8 workgroups per list);
 // 8 heads, L = 2472, d = 64: 63 -> 28 us; 16 heads, L = 1977: 81 -> 36 us; dense, 8 heads, L = 12000, d = 128: 560 us,
