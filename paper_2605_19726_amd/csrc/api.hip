@@ -248,7 +248,7 @@ size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, co
 
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p) {
   if (check_qk(q, k) != BASA_OK || check_params(p, false) != BASA_OK) return 0;
-  if (!use_mfma(q)) return attn_f32_workspace_bytes(q->batch * q->heads, q->L, q->d);
+  if (!use_mfma(q)) return attn_f32_workspace_bytes(q->batch * q->heads, q->L, k->L, q->d, p->block);
   return attn_mfma_workspace_bytes(q->batch * q->heads, k->batch * k->heads, q->L, k->L, q->d, p->block) +
          attn_mfma_split_bytes(q->batch * q->heads, q->L, k->L, q->d, p->block, p->causal != 0);
 }

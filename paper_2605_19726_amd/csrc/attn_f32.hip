@@ -358,26 +358,34 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const flo
   if (a.lse && sub == 0) a.lse[(int64_t)bhq * Lq + qrow] = lse_of(m, l, lse_k);
 }
 
-template <int D, int QG, int KS>
-basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
-  constexpr int kQueries = 32 * QG;
-  const int B = p.a.B;
-  p.wgs_per_head = ceil_div(p.Nq * B, kQueries);
-  const int work = BHq * p.wgs_per_head;                  // workgroups without splitting, one to a compute unit
-  // How many workgroups share a list: rounds of workgroups times (steps of one, a tile per slice each, plus
-  // its prologue and epilogue), plus the combining pass and its bytes.  The step times are measured
-  // (attn_f32_kernel at 1, 2 and 4 splits: 26.2, 17.0, 12.3 us for one head of L = 1024, d = B = 64, and 4.2 us
-  // for the combining pass; L = 4096, d = B = 128, 8 heads: 293 us unsplit, 315 + 11 in two).
-  const int tiles = (p.a.row_cols ? std::min(p.a.cols_stride, p.Nk) : p.Nk) * (B / kTK);
-  const size_t row_bytes = (size_t)BHq * p.a.q.L * (D * 4 + 8);
-  const double step_us = (D == 128 ? 9.2 : 4.5) * (QG * KS == 8 ? 1.0 : 0.6);
+// How many workgroups share a list (`work` workgroups without splitting, QG x KS waves each): rounds of workgroups
+// times (steps of one, a tile per slice each, plus its prologue and epilogue), plus the combining pass and its
+// bytes.  The step times are measured (attn_f32_kernel at 1, 2 and 4 splits: 26.2, 17.0, 12.3 us for one head of
+// L = 1024, d = B = 64, and 4.2 us for the combining pass; L = 4096, d = B = 128, 8 heads: 293 us unsplit, 315 + 11 in
+// two).
+int plan_splits(int64_t work, int tiles, int KS, int waves, int D, size_t row_bytes, size_t ws_bytes) {
+  const double step_us = (D == 128 ? 9.2 : 4.5) * (waves == 8 ? 1.0 : 0.6);
   double best = 0.0;
   int splits = 1;
-  for (int s = 1; s <= kMaxSplits && (s == 1 || (tiles >= s * KS && s * row_bytes <= p.a.ws_bytes)); ++s) {
-    const double cost = ceil_div(work * s, kCUs) * (ceil_div(tiles, s * KS) * step_us + 8.0) +
+  for (int s = 1; s <= kMaxSplits && (s == 1 || (tiles >= s * KS && s * row_bytes <= ws_bytes)); ++s) {
+    const double cost = (double)((work * s + kCUs - 1) / kCUs) * (ceil_div(tiles, s * KS) * step_us + 8.0) +
                         (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
     if (s == 1 || cost < best) { best = cost; splits = s; }
   }
+  return splits;
+}
+// Query groups and key slices of a workgroup: queries = the query block; slices so that its tiles fill the LDS (128 KB
+// of ring).
+struct F32Shape { int QG, KS; };
+constexpr F32Shape shape_of(int d, int B) { return F32Shape{B / 32, d == 64 && B == 64 ? 4 : 2}; }
+
+template <int D, int B>
+basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
+  constexpr int QG = shape_of(D, B).QG, KS = shape_of(D, B).KS;
+  p.wgs_per_head = ceil_div(p.Nq * B, 32 * QG);
+  const int work = BHq * p.wgs_per_head;                  // workgroups without splitting, one to a compute unit
+  const int tiles = (p.a.row_cols ? std::min(p.a.cols_stride, p.Nk) : p.Nk) * (B / kTK);
+  const int splits = plan_splits(work, tiles, KS, QG * KS, D, (size_t)BHq * p.a.q.L * (D * 4 + 8), p.a.ws_bytes);
   p.splits = splits;
   p.total = work * splits;
   if (splits > 1) {
@@ -422,11 +430,23 @@ basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const fl
 }
 
 // Room for the partial results of as many workgroups per list as could be of use (callers who hand over
-// less get fewer): enough to give every compute unit two workgroups.
-size_t attn_f32_workspace_bytes(int BHq, int Lq, int d) {
+// less get fewer): enough to give every compute unit two workgroups.  From two rounds of workgroups on, two parts per list
+// help only where the last round is at most half full, and no room is asked for where they would not help lists of
+// every block (or one less: an odd number splits worse); 32 heads of L = 131072 would ask for 4.4 GB.
+size_t attn_f32_workspace_bytes(int BHq, int Lq, int Lk, int d, int B) {
   const int64_t wgs = (int64_t)BHq * ceil_div(Lq, 128);
   const size_t splits = (size_t)std::max<int64_t>(2, std::min<int64_t>(kMaxSplits, 2 * kCUs / wgs));
-  return align_up(splits * BHq * Lq * (d * 4 + 8), 256);
+  const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
+  if (splits == 2) {
+    const F32Shape f = shape_of(d, B);
+    const int64_t work = (int64_t)BHq * ceil_div(Lq, 32 * f.QG);
+    const int Nk = ceil_div(Lk, B);
+    bool use = false;
+    for (int n = std::max(1, Nk - 1); n <= Nk; ++n)
+      use |= plan_splits(work, n * (B / kTK), f.KS, f.QG * f.KS, d, row_bytes, 2 * row_bytes) > 1;
+    if (!use) return 256;                                 // (non-zero for callers)
+  }
+  return align_up(splits * row_bytes, 256);
 }
 
 basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {
@@ -440,9 +460,8 @@ basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {
   p.lse_k = lse_factor(a.q.d);
   p.part_o = nullptr; p.part_ml = nullptr;
   if (!a.ws || reinterpret_cast<uintptr_t>(a.ws) % 16) p.a.ws_bytes = 0;
-  // queries per workgroup = the query block; slices so that its tiles fill the LDS (128 KB of ring)
-  if (a.q.d == 128) return a.B == 128 ? launch_f32<128, 4, 2>(p, BHq, st) : launch_f32<128, 2, 2>(p, BHq, st);
-  return a.B == 128 ? launch_f32<64, 4, 2>(p, BHq, st) : launch_f32<64, 2, 4>(p, BHq, st);
+  if (a.q.d == 128) return a.B == 128 ? launch_f32<128, 128>(p, BHq, st) : launch_f32<128, 64>(p, BHq, st);
+  return a.B == 128 ? launch_f32<64, 128>(p, BHq, st) : launch_f32<64, 64>(p, BHq, st);
 }
 
 }  // namespace basa

@@ -144,6 +144,16 @@ def test_workspace_sizes(lib):
     assert lib.basa_select_workspace_size(C.byref(fake_tensor(d=96)), C.byref(k), C.byref(p)) == 0
 
 
+@pytest.mark.parametrize("heads,L,d,parts", [(1, 1024, 64, 16), (2, 10000, 128, 3), (17, 4096, 128, 2), (8, 4096, 128, 0),
+                                             (32, 16384, 128, 0), (32, 131072, 128, 0), (40, 75600, 64, 0)])
+def test_f32_attention_asks_for_partial_rows_only_where_lists_are_split(lib, heads, L, d, parts):
+    """Few workgroups: as many parts as fill the device twice; 544 of them: two, for the last round; whole rounds: none."""
+    q = fake_tensor(dtype=bd.F32, heads=heads, L=L, d=d)
+    size = lib.basa_attn_workspace_size(C.byref(q), C.byref(q), C.byref(bd.params(64 if d == 64 else 128)))
+    rows = parts * heads * L * (4 * d + 8)
+    assert max(rows, 1) <= size <= rows + 256
+
+
 def test_struct_layouts_match_the_c_header(tmp_path):
     """The ctypes structures of the binding against the header as a C compiler lays it out."""
     import shutil
