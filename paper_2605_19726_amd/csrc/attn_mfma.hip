@@ -31,8 +31,8 @@
 // The running max is refreshed lazily: the accumulators are rescaled only when some
 // query's tile max exceeds its running max by more than 2^8, so the common iteration
 // touches O only through MFMA (or there is no running max at all, see process_tile2).  K/V tiles go
-// through an LDS ring of two stages, one tile computed while the next one lands, a workgroup barrier
-// per tile; the 256-query shape has four, two slots of two tiles.
+// through an LDS ring: two stages and a workgroup barrier per tile in the 128-query shape, two slots of two
+// tiles in the 256-query one, up to four stages in the 512-query one, whose query blocks may be at different tiles.
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -89,12 +89,12 @@ struct Geo {
 };
 // Ring stages of a workgroup: one of 512 threads has the compute unit to itself and walks tiles in
 // pairs (two slots of two); two workgroups of 256 threads share a compute unit and walk one by one.
-// With 64 queries per wave a tile keeps the workgroup busy twice as long, and one tile of prefetch
-// distance (two stages) covers the load.
-#ifndef BASA_ATTN_ST64
-#define BASA_ATTN_ST64 2
-#endif
-constexpr int stages_of(int threads, int qpw) { return threads == 512 ? (qpw == 32 ? 4 : BASA_ATTN_ST64) : 2; }
+// With 64 queries per wave: two, or, where the waves walk in spans (wide_spans), up to four (wide_stages).
+// (Not with d = 64 or the causal mask, whose tiles are too short to hide the choice of the next one: 4527 -> 4721 us at
+//  32 heads, L = 32768, d = 64; 2116 -> 2206 causal, L = 16384.  Nor with running maxima, where the compiler then sends the
+//  accumulators through scratch.)
+constexpr bool wide_spans(int d, bool causal, bool fast) { return d == 128 && !causal && fast; }
+constexpr int stages_of(int threads, int qpw) { return threads == 512 && qpw == 32 ? 4 : 2; }
 // k-steps of Q^T a wave of 64 queries keeps in registers (the rest is parked in LDS): all for D = 64
 // (the causal variant of the 64-queries-per-wave kernel carries the two visibility limits and the
 //  key indices of the half-tile on top: one more k-step of Q^T is parked)
@@ -317,6 +317,7 @@ struct MfmaArgs {
   int run_if_solo;           // with probe: this launch runs iff (lists overlap little) == run_if_solo
   int32_t* redo;             // nullable, one word per workgroup: written by the pass without running maxima (1 = a row
                              // sum left the safe range), read by the pass with them, which skips workgroups at 0
+  int stages;                // 512-query shape: tiles the LDS ring holds
   int splits;                // kSplit: workgroups that share a union list, and where they leave their rows:
   float* part_o;             //   [split][BHq][Lq][D] unnormalised, by sorted position
   float2* part_ml;           //   [split][BHq][Lq] running maximum (log2), running sum
@@ -324,6 +325,13 @@ struct MfmaArgs {
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
+
+// The lane number made anew, opaque to the compiler, which would keep it (and what follows from it) in registers.
+__device__ __forceinline__ int fresh_lane() {
+  int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  asm volatile("" : "+v"(l));
+  return l;
+}
 
 // Per-wave state of the online softmax and the output accumulator.
 template <int D>
@@ -649,7 +657,7 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
   return (int64_t)b * a.out_sb + (int64_t)hh * a.out_sh + (int64_t)row * a.out_sl;
 }
 
-// Dynamic LDS: [ring: kStages x 32 KB][parked Q^T fragments][seq: Nk words][wave_counts: kWaves words].
+// Dynamic LDS: [ring: stages x 32 KB][parked Q^T fragments][seq: Nk words][wave_counts: kWaves words].
 // seq[i] = key block of the i-th entry of the union list | (bit 24+g set iff query block g of
 // this workgroup lists it).  While seq is being built the ring area holds the per-key-block
 // membership flags.
@@ -674,9 +682,12 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   constexpr int kWaves = kWgQueries / kQPW, kThreads = kWaves * 64, kQueriesPerWg = kWgQueries;
   constexpr int kNG = kQPW / 32;             // 32-query groups per wave: 1 or 2
   constexpr int kStages = stages_of(kThreads, kQPW);
+  constexpr bool kSpans = kNG == 2 && wide_spans(D, kCausal, kFast);
+  const int stages = kSpans ? a.stages : kStages;
   constexpr int kQR = q_reg_steps(D, kQPW, kCausal, kFast), kQL = G::kKSteps - kQR;
   constexpr int kQParkBytes = kWaves * kNG * kQL * 1024;
-  constexpr int kTileBytes = G::kTileBytes, kStageBytes = G::kStageBytes, kRingBytes = kStages * kStageBytes;
+  constexpr int kTileBytes = G::kTileBytes, kStageBytes = G::kStageBytes;
+  const int ring_bytes = stages * kStageBytes;
   constexpr int kLoadsPerWave = 2 * G::kChunksPerTile / kWaves;
   constexpr int NQB = kQueriesPerWg / kB;    // query blocks per workgroup: 2 or 4 (SOLO: 1 or 2)
   if (a.probe) {
@@ -696,9 +707,9 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   constexpr int TPB = kB / kTileKeys;        // key tiles per key block: 2 or 1
   extern __shared__ __attribute__((aligned(16))) char smem[];
   uint32_t* flags = reinterpret_cast<uint32_t*>(smem);
-  uint32_t* seq = reinterpret_cast<uint32_t*>(smem + kRingBytes + kQParkBytes);
+  uint32_t* seq = reinterpret_cast<uint32_t*>(smem + ring_bytes + kQParkBytes);
   uint32_t* wave_counts = seq + a.Nk;
-  int* kix_lds = reinterpret_cast<int*>(smem + ((kRingBytes + kQParkBytes + a.Nk * 4 + kWaves * 4 + 15) & ~15));   // kCausal
+  int* kix_lds = reinterpret_cast<int*>(smem + ((ring_bytes + kQParkBytes + a.Nk * 4 + kWaves * 4 + 15) & ~15));   // kCausal
 
   // XCD-aware order: consecutive workgroup ids go round-robin over the 8 XCDs; give each
   // XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
@@ -763,7 +774,7 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   int q_lim[kNG];               // kCausal: the largest original key index the lane's query of each group may see
 #pragma unroll
   for (int r = 0; r < kNG; ++r) q_lim[r] = INT_MIN;
-  char* qpark = smem + kRingBytes + (wave * kNG * kQL) * 1024 + lane * 16;    // this lane's parked fragments
+  char* qpark = smem + ring_bytes + (wave * kNG * kQL) * 1024 + lane * 16;    // this lane's parked fragments
   auto load_q = [&]() {
 #pragma unroll
     for (int r = 0; r < kNG; ++r) {
@@ -850,19 +861,20 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   // direct-to-LDS copy of tile `tile` into ring stage `stage`: 32 chunks of 1 KB, chunk
   // j*kWaves+wave by this wave (16 K chunks, then 16 V chunks)
   auto issue_tile = [&](int tile, int stage) {
+    const int lane_i = kSpans ? fresh_lane() : lane;
     const char* kp = Kh + (int64_t)tile * kTileBytes;      // wave-uniform bases
     const char* vp = Vh + (int64_t)tile * kTileBytes;
 #pragma unroll
     for (int j = 0; j < kLoadsPerWave; ++j) {
       const int cb = j * kWaves + wave;                   // wave-uniform: K chunks first, then V^T chunks
-      const char* src = (cb < G::kChunksPerTile ? kp : vp) + (cb % G::kChunksPerTile) * 1024 + (uint32_t)(lane * 16);
+      const char* src = (cb < G::kChunksPerTile ? kp : vp) + (cb % G::kChunksPerTile) * 1024 + (uint32_t)(lane_i * 16);
       char* dst = smem + stage * kStageBytes + cb * 1024;
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)src, (lds_ptr_t)dst, 16, 0, 0);
     }
     if constexpr (kCausal) {
       // the tile's key indices, minimum and maximum: kIxStride ints = 17 lanes of 16 bytes
-      if (wave == 0 && lane < kIxStride / 4) {
-        const int32_t* src = a.kix + ((int64_t)bhk * tiles_per_head + tile) * kIxStride + lane * 4;
+      if (wave == 0 && lane_i < kIxStride / 4) {
+        const int32_t* src = a.kix + ((int64_t)bhk * tiles_per_head + tile) * kIxStride + lane_i * 4;
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)src, (lds_ptr_t)(kix_lds + stage * kIxStride), 16, 0, 0);
       }
     }
@@ -919,13 +931,8 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
     if constexpr (kNG == 1) process_tile<decltype(masked)::value, D, decltype(fast)::value>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
     else {
       // the lane half is needed by the masking code only (ragged tile, causal mask): taken from the
-      // thread index there, it does not occupy a register through the main loop
-      int h2 = 0;
-      if (decltype(masked)::value || kCausal) {
-        int t2 = threadIdx.x;
-        asm volatile("" : "+v"(t2));
-        h2 = (t2 >> 5) & 1;
-      }
+      // lane number there, it does not occupy a register through the main loop
+      const int h2 = decltype(masked)::value || kCausal ? fresh_lane() >> 5 : 0;
       process_tile2<decltype(masked)::value, D, kQR, kCausal, kFast>(st, qf[0], qf[kNG - 1], qpark, stage, kaddr, vaddr, c, nvalid,
                                                                      h2, kix_lds + stage_no * kIxStride + 4 * h2, q_lim[0],
                                                                      q_lim[kNG - 1], seen_of(stage_no));
@@ -954,33 +961,73 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   // slot; their loads are issued right after the barrier, which also says that every wave is
   // done with that other slot (pair p-1).  The union entries of later tiles are read from LDS
   // early and turned into scalars late, so their latency hides behind the arithmetic.
-  if constexpr (kNG == 2) {
+  if constexpr (kNG == 2 && !kSpans) {
     // 64 queries per wave: ONE call site for full tiles (a second inlined copy of the tile code
-    // costs the register allocator its footing).  Tiles travel in rounds of R = kStages / 2; the
-    // workgroup meets once per round, and round p + 1 lands in the other half of the ring while
-    // round p is computed.
-    constexpr int R = kStages / 2;
+    // costs the register allocator its footing).  Tile t + 1 lands while tile t is computed.
     uint32_t e_cur = entry_of(0);
     int t = 0;
 #pragma nounroll
     for (; t + 1 < n_tiles; ++t) {
-      if (t % R == 0) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        const int half_next = ((t / R) + 1) & 1;
-#pragma unroll
-        for (int j = 0; j < R; ++j) issue_tile(tile_of(t + R + j), half_next * R + j);
-      }
-      const uint32_t raw_n = seq[(t + 1) / TPB];
-      if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kFull, ((t / R) & 1) * R + t % R, kTileKeys, kMode);
-      e_cur = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
-    }
-    if (t % R == 0) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
+      issue_tile(tile_of(t + 1), (t + 1) & 1);
+      const uint32_t raw_n = seq[(t + 1) / TPB];
+      if ((e_cur & my_bit) && tile_has_visible_keys(t & 1)) tile(kFull, t & 1, kTileKeys, kMode);
+      e_cur = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
     const int nvalid = a.Lk - ((int)(e_cur & 0xffffffu) * TPB + (t % TPB)) * kTileKeys;
-    if ((e_cur & my_bit) && tile_has_visible_keys(((t / R) & 1) * R + t % R)) tile(kRagged, ((t / R) & 1) * R + t % R, nvalid, kMode);
+    if ((e_cur & my_bit) && tile_has_visible_keys(t & 1)) tile(kRagged, t & 1, nvalid, kMode);
+  } else if constexpr (kNG == 2) {
+    // The same in spans (wide_spans).  `win` holds, for the tiles lo, lo + 1, ... that have landed, one byte each: the
+    // query blocks that list the tile and have yet to compute it.  Between two barriers every query block computes the
+    // first of these tiles that is left to it; tile lo is then finished by all, and so are those after it that nobody
+    // waits for, whose stages the next tiles take.  A block that does not list a tile works on a later one instead of
+    // sitting it out, and computes its own tiles in the same order as before (same bits).  All waves work this out by
+    // themselves in scalar registers, before the barrier: after it, or without barriers by progress words in LDS, the
+    // chain of instructions and LDS round trips was exposed in every tile (3 to 6 % of the kernel).
+    // Spans, in lists: 1.06 where the union is 1.135 (L = 131072, keep 50 %), 1.13 where it is 1.29 (L = 16384, 10 %).
+    // Tile by tile -> spans: 32 heads, L = 131072: 119.5 -> 117.3 ms; L = 16384, keep 10 %: 667 -> 653 us (whole
+    // operator); L = 32768, B = 64 (eight lists to a workgroup): 8350 -> 7960 us; dense: level.
+    const uint32_t last = (uint32_t)n_tiles - 1, ring = (uint32_t)stages;
+    auto wrap = [&](uint32_t i) { return i >= ring ? i - ring : i; };
+    auto listed_by = [&](uint32_t e, uint32_t i) { return i < last ? e >> 24 : 0u; };      // (the last tile: below)
+    auto entry_at = [&](uint32_t i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)seq[min(i, last) / (uint32_t)TPB]); };
+    uint32_t lo = 0, issued = 1, slot = 0, issue_slot = 1, stage_no = 0;
+    uint32_t e0 = entry_at(1), e1 = entry_at(2);       // of the next two tiles to request
+    uint32_t win = listed_by(entry_at(0), 0), mine = win >> grp & 0x01010101u;
+#pragma nounroll
+    while (lo < last || issued <= last) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      const uint32_t here = issued - lo, want = min(min(last + 1 - issued, ring - here), 2u);
+      if (want > 0) issue_tile((int)((e0 & 0xffffffu) * TPB + issued % TPB), (int)issue_slot);
+      if (want > 1) issue_tile((int)((e1 & 0xffffffu) * TPB + (issued + 1) % TPB), (int)wrap(issue_slot + 1));
+      if (mine != 0u && tile_has_visible_keys((int)stage_no)) tile(kFull, (int)stage_no, kTileKeys, kMode);
+      // what the next span does
+      uint32_t before = win | win << 8;                // byte j: who had one of the tiles 0 .. j to do
+      before |= before << 16;
+      const uint32_t rest = win & before << 8;
+      const uint32_t done = rest ? (uint32_t)__builtin_ctz(rest) >> 3 : min(here, last - lo);
+      const uint32_t fresh = (want > 0 ? listed_by(e0, issued) : 0u) | (want > 1 ? listed_by(e1, issued + 1) << 8 : 0u);
+      win = (uint32_t)((rest | (uint64_t)fresh << 8 * here) >> 8 * done);
+      lo += done;
+      slot = wrap(slot + done);
+      issued += want;
+      issue_slot = wrap(issue_slot + want);
+      mine = win >> grp & 0x01010101u;
+      stage_no = wrap(slot + (mine ? (uint32_t)__builtin_ctz(mine) >> 3 : 0u));
+      e0 = entry_at(issued);
+      e1 = entry_at(issued + 1);
+    }
+    // the last tile, which may be ragged: the masks stay out of the loop
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    const uint32_t e_last = entry_of(n_tiles - 1);
+    const int nvalid = a.Lk - ((int)(e_last & 0xffffffu) * TPB + ((n_tiles - 1) % TPB)) * kTileKeys;
+    const int last_stage = (int)(issue_slot == 0 ? ring - 1 : issue_slot - 1);
+    if ((e_last & my_bit) && tile_has_visible_keys(last_stage)) tile(kRagged, last_stage, nvalid, kMode);
   } else if constexpr (kStages == 4) {
   uint32_t e_a = entry_of(0);
   uint32_t e_b = entry_of(min(1, n_tiles - 1));
@@ -1125,16 +1172,27 @@ bool bitmaps_pay(size_t kv_bytes, double f, double entries) {
 size_t sz_listed(int BHkv, int Nk) { return align_up((size_t)BHkv * kListedParts * ceil_div(Nk, 32) * 4, 256); }
 
 template <int D>
-size_t lds_bytes(int threads, int qpw, int Nk, bool causal = false, bool fast = false) {
+size_t lds_bytes(int threads, int qpw, int Nk, bool causal = false, bool fast = false, int stages = 0) {
   const size_t park = (size_t)(threads / 64) * (qpw / 32) * (D / 16 - q_reg_steps(D, qpw, causal, fast)) * 1024;
-  const size_t base = (size_t)stages_of(threads, qpw) * Geo<D>::kStageBytes + park + (size_t)Nk * 4 + (threads / 64) * 4;
-  return causal ? ((base + 15) & ~(size_t)15) + (size_t)stages_of(threads, qpw) * kIxStride * 4 : base;
+  if (stages == 0) stages = stages_of(threads, qpw);
+  const size_t base = (size_t)stages * Geo<D>::kStageBytes + park + (size_t)Nk * 4 + (threads / 64) * 4;
+  return causal ? ((base + 15) & ~(size_t)15) + (size_t)stages * kIxStride * 4 : base;
+}
+// Ring stages of a 512-query workgroup that walks in spans and has its compute unit to itself: four, or what the list
+// leaves room for.
+constexpr size_t kLdsBytes = 160 * 1024;
+template <int D>
+int wide_stages(int Nk) {
+  int s = 4;
+  while (s > 2 && lds_bytes<D>(512, 64, Nk, false, true, s) > kLdsBytes) --s;
+  return s;
 }
 
 template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit>
 basa_status launch_main(MfmaArgs m, int BHq, hipStream_t st) {
   constexpr int kThreads = kWgQueries / kQPW * 64;
-  const size_t lds = lds_bytes<D>(kThreads, kQPW, m.Nk, kCausal, kFast);
+  if (kQPW == 64) m.stages = wide_spans(D, kCausal, kFast) ? wide_stages<D>(m.Nk) : 2;
+  const size_t lds = lds_bytes<D>(kThreads, kQPW, m.Nk, kCausal, kFast, kQPW == 64 ? m.stages : 0);
   // while the union list is built, the per-key-block membership flags live in the ring area
   if ((size_t)m.Nk * 4 > (size_t)stages_of(kThreads, kQPW) * Geo<D>::kStageBytes) {
     set_error("attention: %d key blocks exceed the %zu this workgroup shape can list", m.Nk,
@@ -1367,7 +1425,7 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   m.kix = kix; m.causal_off = a.causal_off;
   const int gsz = kWideQueries / B;
   Plan plan{false, 1};
-  m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
+  m.stages = 0; m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
   const int64_t rows = (int64_t)BHq * Nq * B;
   const bool small = rows < (int64_t)kSmallRounds * kCUs * kWideQueries;
   if (a.variant == 0 && rows < (int64_t)kPlannedRounds * kCUs * kWideQueries) {

@@ -343,3 +343,28 @@ def test_block_scores_on_both_sides_of_the_line_between_the_tile_sizes(hq, n_q, 
         if beta:
             ref = ref + beta * o.diag_compensation(mq, vq, mk, vk)
         np.testing.assert_allclose(sel.scores[0, h].cpu().numpy(), ref, rtol=2e-5, atol=2e-5)
+
+
+@pytest.mark.parametrize("block,Lq,Lk", [(128, 512, 2048), (128, 1100, 1920 + 70), (64, 600, 1000), (64, 512, 64), (128, 513, 129)])
+@pytest.mark.parametrize("kind", ["disjoint", "one_has_all", "staggered", "single"])
+def test_query_blocks_of_a_workgroup_at_different_tiles(kind, block, Lq, Lk):
+    # 512-query workgroups, whose query blocks walk the tiles of the union at their own pace, against the 128-query ones,
+    # which have no neighbours to wait for: every query takes the same tiles in the same order, so the bits agree
+    Q, K, V = _qkv(2, 1, Lq, Lk, 128, torch.bfloat16, seed=Lq + Lk)
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    rows = {"disjoint": lambda g: [c for c in range(n_k) if c % 4 == g % 4] or [0],
+            "one_has_all": lambda g: list(range(n_k)) if g % 4 == 2 else [n_k - 1 if g % 2 else 0],
+            "staggered": lambda g: list(range(min(2 * (g % 4), n_k - 1), n_k)),
+            "single": lambda g: [(5 * g) % n_k]}[kind]
+    cnt_h = np.array([[[len(rows(g)) for g in range(n_q)]] * 2])
+    cols_h = np.full((1, 2, n_q, n_k), -1)
+    for g in range(n_q):
+        cols_h[:, :, g, :len(rows(g))] = rows(g)
+    t = lambda a: torch.from_numpy(a.astype(np.int32)).to(DEV)
+    pq, pk = _perm(2, Lq, 3), _perm(1, Lk, 9)
+    wide, lse_w = bd.basa_sparse_attn(Q, K, V, t(cnt_h), t(cols_h), block, pq, pk, want_lse=True, attn_shape=3)
+    solo, lse_s = bd.basa_sparse_attn(Q, K, V, t(cnt_h), t(cols_h), block, pq, pk, want_lse=True)
+    assert torch.equal(wide, solo) and torch.equal(lse_w, lse_s)
+    ref = o.sparse_attention(np64(Q[0, 1]), np64(K[0, 0]), np64(V[0, 0]), pq[0, 1].cpu().numpy(), pk[0, 0].cpu().numpy(),
+                             [rows(g) for g in range(n_q)], block)
+    check_output(np64(wide[0, 1]), ref, True, kind)
