@@ -141,6 +141,9 @@ size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, co
  * lists that are split over workgroups; f32: all of it is.  With less room lists are split less, or not at
  * all, which costs time and never the call. */
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
+/* The same, and for f32 tensors the room with which large calls run fastest: K and V cut into bf16 parts (12
+ * bytes per element of K, 1.5 times K and V) and the partial results that go with them. */
+size_t basa_attn_best_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
 /* Bytes of workspace basa_norm_sort needs for x. */
 size_t basa_sort_workspace_size(const basa_tensor* x, const basa_params* p);
 
@@ -224,13 +227,15 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
  * of the listed key blocks of K' = K[perm_k], V' = V[perm_k], normalised over those
  * tokens; the row of sorted position i is written to out row perm_q[i].
  * bf16 tensors: bf16 MFMA with fp32 accumulation and fp32 softmax state (d = 64 or 128);
- * f32 tensors: fp32 throughout.
+ * f32 tensors: inputs, accumulation and softmax state in fp32 throughout (given room, see
+ * basa_attn_best_workspace_size, the products of large calls are formed on the bf16 matrix instruction from
+ * numbers cut into three bf16 parts without loss).
  * A key whose score is -inf (and whose V row is finite) carries no weight; a query that has no other gets
  * a zero row and lse = -inf.
- * Repeating a call gives the same bits.  How far lists are split (f32 tensors; bf16 with attn_shape = 0)
- * depends on batch * heads_q * L_q of the whole call and on ws_bytes, so that a batch entry agrees with
- * the same entry passed alone, or with another workspace, within rounding only.  Lists are never split
- * with attn_shape 1 to 4, nor for f32 tensors with ws_bytes below 2 * batch * heads_q * L_q * (4 d + 8).
+ * Repeating a call gives the same bits.  How far lists are split (f32 tensors; bf16 with attn_shape = 0), and which
+ * of the two products f32 tensors take, depends on batch * heads_q * L_q of the whole call and on ws_bytes, so that
+ * a batch entry agrees with the same entry passed alone, or with another workspace, within rounding only.  Lists
+ * are never split with attn_shape 1 to 4, nor for f32 tensors with ws_bytes below 2 * batch * heads_q * L_q * (4 d + 8).
  *   row_count    [batch, heads_q, N_q] int32, each in [1, N_k].
  *   row_cols     [batch, heads_q, N_q, cols_stride] int32, ascending, each in [0, N_k).
  *                NULL means every key block for every row (dense).  The lists are device

@@ -28,7 +28,7 @@ EXPORTS = (
     "basa_version", "basa_profile_enable", "basa_profile_kernel_count", "basa_profile_kernel_name",
     "basa_profile_read", "basa_calibrate_mfma", "basa_calibrate_read", "basa_block_mass_workspace_size", "basa_block_mass",
     "basa_block_radius", "basa_deviation_bound", "basa_selection_fidelity", "basa_pearson_sums",
-    "basa_static_scratch_size", "basa_static_init", "basa_norm_sort_static",
+    "basa_attn_best_workspace_size", "basa_static_scratch_size", "basa_static_init", "basa_norm_sort_static",
 )
 
 
@@ -70,7 +70,7 @@ def load():
     T, P, V = C.POINTER(BasaTensor), C.POINTER(BasaParams), C.c_void_p
     lib.basa_kappa.restype = C.c_int32
     lib.basa_kappa.argtypes = [C.c_int32, C.c_double]
-    for n in ("basa_select_workspace_size", "basa_attn_workspace_size"):
+    for n in ("basa_select_workspace_size", "basa_attn_workspace_size", "basa_attn_best_workspace_size"):
         getattr(lib, n).restype = C.c_size_t
         getattr(lib, n).argtypes = [T, T, P]
     lib.basa_sort_workspace_size.restype = C.c_size_t
@@ -306,7 +306,7 @@ def basa_sparse_attn(q, k, v, row_count, row_cols, block: int, perm_q=None, perm
     ostr = _out_strides(out, q)
     lse = torch.empty((b, hq, Lq), dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
-        ws = _ws(lib.basa_attn_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
+        ws = _ws(lib.basa_attn_best_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
     stride = 0 if row_cols is None else int(row_cols.shape[-1])
     _check(lib.basa_sparse_attn(C.byref(qd), C.byref(kd), C.byref(vd), _ptr(row_count), _ptr(row_cols),
                                 stride, _ptr(perm_q), _ptr(perm_k), C.byref(p), _ptr(out), ostr, _ptr(lse),
@@ -324,7 +324,7 @@ def basa_dense_attn(q, k, v, block: int = 128, want_lse: bool = False, ws=None, 
     ostr = _out_strides(out, q)
     lse = torch.empty((b, hq, Lq), dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
-        ws = _ws(lib.basa_attn_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
+        ws = _ws(lib.basa_attn_best_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
     _check(lib.basa_dense_attn(C.byref(qd), C.byref(kd), C.byref(vd), C.byref(p), _ptr(out), ostr, _ptr(lse),
                                _ptr(ws), ws.numel(), _stream(q)))
     return (out, lse) if want_lse else out

@@ -253,6 +253,12 @@ size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, cons
          attn_mfma_split_bytes(q->batch * q->heads, q->L, k->L, q->d, p->block, p->causal != 0);
 }
 
+size_t basa_attn_best_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p) {
+  const size_t base = basa_attn_workspace_size(q, k, p);
+  if (base == 0 || use_mfma(q)) return base;
+  return attn_f32_best_workspace_bytes(q->batch * q->heads, k->batch * k->heads, q->L, k->L, q->d, p->block, p->causal != 0);
+}
+
 basa_status basa_norm_sort(const basa_tensor* x, const basa_params* p, int32_t* perm, float* keys_out,
                            void* ws, size_t ws_bytes, void* stream) {
   basa_status s;

@@ -150,6 +150,7 @@ struct AttnArgs {
 size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B);
 size_t attn_mfma_split_bytes(int BHq, int Lq, int Lk, int d, int B, bool causal);   // what a workspace may hold beyond that, for partial results
 size_t attn_f32_workspace_bytes(int BHq, int Lq, int Lk, int d, int B);
+size_t attn_f32_best_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B, bool causal);
 basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st);
 // Partial results of several workgroups per query: unnormalised rows part_o[split][BHq][Lq][d] and
 // their (running maximum in log2 units, sum) part_ml[split][BHq][Lq], rows by sorted position.

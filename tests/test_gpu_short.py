@@ -368,3 +368,67 @@ def test_query_blocks_of_a_workgroup_at_different_tiles(kind, block, Lq, Lk):
     ref = o.sparse_attention(np64(Q[0, 1]), np64(K[0, 0]), np64(V[0, 0]), pq[0, 1].cpu().numpy(), pk[0, 0].cpu().numpy(),
                              [rows(g) for g in range(n_q)], block)
     check_output(np64(wide[0, 1]), ref, True, kind)
+
+
+def _three_part_call(Q, K, V, cnt, cols, block, pq, pk, **kw):
+    """The call, and that it went to the kernel of three-part products (which alone lays out K and V for f32)."""
+    bd.basa_profile_enable(True)
+    try:
+        out = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, **kw)
+        launches = bd.basa_profile_read()
+    finally:
+        bd.basa_profile_enable(False)
+    assert any("gather" in n and c for n, (_, c) in launches.items()), launches
+    return out
+
+
+@pytest.mark.parametrize("d,block", [(64, 64), (64, 128), (128, 64), (128, 128)])
+@pytest.mark.parametrize("Lq,Lk", [(4096, 4096), (4096 + 33, 2944 + 1), (3000, 4001), (8000, 97 * 32)])
+def test_f32_attention_on_three_part_products(d, block, Lq, Lk):
+    # Bound: the six part products leave 2^-25 of |q||k|, sums of up to Lk terms in fp32 (1e-5 with room), as for the
+    # fp32 instruction; and no further from 64 bits than that kernel, whose result the small workspace gives, by half again.
+    hq, hk = 8, 4
+    Q, K, V = _qkv(hq, hk, Lq, Lk, d, torch.float32, seed=Lq + Lk + d)
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    cnt, cols, cnt_h, cols_h = _lists(hq, n_q, n_k, Lq + 3 * Lk, n_k)
+    cnt[0, 5, 1] = 0                                      # a query block without a list: zero rows
+    pq, pk = _perm(hq, Lq, 1), _perm(hk, Lk, 50)
+    out, lse = _three_part_call(Q, K, V, cnt, cols, block, pq, pk, want_lse=True)
+    small = torch.empty(256, dtype=torch.uint8, device=DEV)
+    plain = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, ws=small)
+    none = pq[0, 5, block:2 * block].long()
+    assert not out[0, 5, none].any() and torch.all(lse[0, 5, none] == -float("inf"))
+    for h in (0, 3):
+        lists = [cols_h[0, h, g, :cnt_h[0, h, g]] for g in range(n_q)]
+        ref, ref_lse = o.sparse_attention(np64(Q[0, h]), np64(K[0, h // 2]), np64(V[0, h // 2]), pq[0, h].cpu().numpy(),
+                                          pk[0, h // 2].cpu().numpy(), lists, block, return_lse=True)
+        check_output(np64(out[0, h]), ref, False, f"head {h}")
+        err = lambda x: np.linalg.norm(np64(x[0, h]) - ref) / np.linalg.norm(ref)
+        assert err(out) <= max(1.5 * err(plain), 3e-7)
+        got, fin = lse[0, h].cpu().numpy(), np.isfinite(ref_lse)
+        assert np.array_equal(np.isfinite(got), fin)
+        np.testing.assert_allclose(got[fin], ref_lse[fin], rtol=0, atol=1e-5)
+
+
+@pytest.mark.parametrize("where", ["k_minus", "k_plus", "v", "q_nan", "huge"])
+@pytest.mark.parametrize("block", [64, 128])
+def test_f32_three_part_products_leave_infinities_to_the_fp32_instruction(where, block):
+    L, d, h = 4096, 128, 8
+    Q, K, V = _qkv(h, h, L, L, d, torch.float32, seed=7)
+    if where == "k_minus":                                # scores of -inf or NaN by the sign of one number of the query
+        K[0, 1, 70, 5] = -float("inf")
+    elif where == "k_plus":
+        K[0, 1, 70] = float("inf")
+    elif where == "v":
+        V[0, 2, 4095, 3] = float("inf")
+    elif where == "q_nan":
+        Q[0, 3, 1000, 7] = float("nan")
+    else:                                                 # rounds up past the largest bf16; finite in fp32
+        V[0, 4, 17, 9] = 3.4e38
+    out, lse = _three_part_call(Q, K, V, None, None, block, None, None, want_lse=True)
+    small = torch.empty(256, dtype=torch.uint8, device=DEV)
+    ref, ref_lse = bd.basa_sparse_attn(Q, K, V, None, None, block, want_lse=True, ws=small)
+    for a, b in ((out, ref), (lse, ref_lse)):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isinf(a), torch.isinf(b))
+        fin = torch.isfinite(a) & torch.isfinite(b)
+        assert torch.allclose(a[fin], b[fin], rtol=1e-4, atol=1e-4)
