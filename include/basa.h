@@ -270,6 +270,17 @@ basa_status basa_dense_attn(const basa_tensor* q, const basa_tensor* k, const ba
                             float* lse, void* ws, size_t ws_bytes, void* stream);
 
 const char* basa_status_string(basa_status s);
+/* The whole operator over a packed batch: sequences of different lengths, tokens cu_seqlens[i] ..
+ * cu_seqlens[i + 1] - 1 (host array of n_seq + 1 ascending entries; empty sequences are skipped) of q, k and v
+ * (batch 1, as many queries as keys), each a problem of its own: basa_select, then basa_sparse_attn on its lists.
+ * Rows go to the same tokens of out (out_strides as above, required).  Short bf16 sequences under the default sort
+ * share their launches; a sequence agrees with itself called alone within rounding.  p->n_segments must be 0. */
+size_t basa_varlen_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v,
+                                  const int32_t* cu_seqlens, int32_t n_seq, const basa_params* p);
+basa_status basa_varlen_attn(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v,
+                             const int32_t* cu_seqlens, int32_t n_seq, const basa_params* p, void* out,
+                             const int64_t* out_strides, void* ws, size_t ws_bytes, void* stream);
+
 /* Reason of the last non-OK status returned on this thread (host string, owned by the
  * library, valid until the next failing call on the thread). */
 const char* basa_last_error(void);

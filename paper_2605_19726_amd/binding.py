@@ -28,7 +28,7 @@ EXPORTS = (
     "basa_version", "basa_profile_enable", "basa_profile_kernel_count", "basa_profile_kernel_name",
     "basa_profile_read", "basa_calibrate_mfma", "basa_calibrate_read", "basa_block_mass_workspace_size", "basa_block_mass",
     "basa_block_radius", "basa_deviation_bound", "basa_selection_fidelity", "basa_pearson_sums",
-    "basa_attn_best_workspace_size", "basa_static_scratch_size", "basa_static_init", "basa_norm_sort_static",
+    "basa_attn_best_workspace_size", "basa_varlen_workspace_size", "basa_varlen_attn", "basa_static_scratch_size", "basa_static_init", "basa_norm_sort_static",
 )
 
 
@@ -90,6 +90,11 @@ def load():
     lib.basa_sparse_attn.restype = C.c_int
     S3 = C.POINTER(C.c_int64)
     lib.basa_sparse_attn.argtypes = [T, T, T, V, V, C.c_int32, V, V, P, V, S3, V, V, C.c_size_t, V]
+    I = C.POINTER(C.c_int32)
+    lib.basa_varlen_workspace_size.restype = C.c_size_t
+    lib.basa_varlen_workspace_size.argtypes = [T, T, T, I, C.c_int32, P]
+    lib.basa_varlen_attn.restype = C.c_int
+    lib.basa_varlen_attn.argtypes = [T, T, T, I, C.c_int32, P, V, S3, V, C.c_size_t, V]
     lib.basa_dense_attn.restype = C.c_int
     lib.basa_dense_attn.argtypes = [T, T, T, P, V, S3, V, V, C.c_size_t, V]
     lib.basa_status_string.restype = C.c_char_p
@@ -343,16 +348,29 @@ def ba_att(q, k, v, block: int = 128, sparsity: float = 0.5, beta: float = 1.0, 
 def ba_att_varlen(q, k, v, cu_seqlens, block: int = 128, sparsity: float = 0.5, **kw):
     """Sequences of different lengths packed token-major: q [T, heads_q, d], k and v [T, heads_kv, d],
     cu_seqlens the host list [0, t_1, ..., T] of sequence boundaries.  Every sequence is its own
-    problem (its own sort, block map and kappa) and runs as one pair of library calls on strided
-    views of the packed buffers, reading and writing them in place; the long sequences this method
-    is for each fill the device on their own.  Returns the packed output [T, heads_q, d]."""
+    problem (its own sort, block map and kappa), read and written in place; short sequences share
+    their launches (basa_varlen_attn).  Returns the packed output [T, heads_q, d]."""
     out = torch.empty_like(q)
     view = lambda x, a, b: x[a:b].permute(1, 0, 2).unsqueeze(0)          # [1, heads, L, d], no copy
-    for a, b in zip(cu_seqlens[:-1], cu_seqlens[1:]):
-        a, b = int(a), int(b)
-        if b > a:
-            ba_att(view(q, a, b), view(k, a, b), view(v, a, b), block, sparsity, out=view(out, a, b), **kw)
+    cu = [int(t) for t in cu_seqlens]
+    seqs = [(a, b) for a, b in zip(cu[:-1], cu[1:]) if b > a]
+    if len(seqs) > 1 and kw.get("segments") is None and cu[0] >= 0 and all(a <= b for a, b in zip(cu[:-1], cu[1:])) and \
+            cu[-1] <= min(q.shape[0], k.shape[0], v.shape[0]):
+        T, lib = cu[-1], load()
+        qv, ov = view(q, 0, T), view(out, 0, T)
+        qd, kd, vd, p = tensor_desc(qv), tensor_desc(view(k, 0, T)), tensor_desc(view(v, 0, T)), _varlen_params(block, sparsity, **kw)
+        args = C.byref(qd), C.byref(kd), C.byref(vd), (C.c_int32 * len(cu))(*cu), len(cu) - 1, C.byref(p)
+        ws = _ws(lib.basa_varlen_workspace_size(*args), q.device)
+        _check(lib.basa_varlen_attn(*args, _ptr(out), _out_strides(ov, qv), _ptr(ws), ws.numel(), _stream(q)))
+        return out
+    for a, b in seqs:
+        ba_att(view(q, a, b), view(k, a, b), view(v, a, b), block, sparsity, out=view(out, a, b), **kw)
     return out
+
+
+def _varlen_params(block, sparsity, beta: float = 1.0, sort: int = SORT_QK, window: int = 0, mass_target: float = 0.0,
+                   min_keep: int = 0, segments=None, causal: bool = False):
+    return params(block, sparsity, beta, sort, window, mass_target, min_keep, causal=causal)
 
 
 def basa_profile_enable(on: bool):

@@ -1,6 +1,7 @@
 // extern "C" boundary of the basa library: host-side validation, workspace carving and
 // the order in which the stage kernels are enqueued.  Nothing here allocates device
 // memory or synchronises.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -227,6 +228,119 @@ basa_status attn_common(const basa_tensor* q, const basa_tensor* k, const basa_t
   return launch_attn_f32(a, st);          // (a workspace it does not get costs speed, not the call)
 }
 
+// ---- packed batches: the whole operator over sequences of different lengths -----------------
+// Sequences that leave most of the device idle on their own go through the stages together, up to kMaxJobs of them in
+// a launch; the others one after the other (which also takes what the shared launches do not: f32, windows, segments,
+// the causal variant, a total budget, other sorts).
+basa_tensor rows_of(const basa_tensor& t, int first, int L) {
+  basa_tensor v = t;
+  v.ptr = const_cast<char*>(static_cast<const char*>(t.ptr)) + (int64_t)first * t.stride_l * (t.dtype == BASA_BF16 ? 2 : 4);
+  v.L = L;
+  return v;
+}
+bool batch_takes_params(const basa_tensor* q, const basa_params* p) {
+  return use_mfma(q) && p->sort == BASA_SORT_QK && p->window == 0 && p->n_segments == 0 && p->causal == 0 && p->budget_total == 0 &&
+         p->attn_shape == 0 && p->select_path != 2;
+}
+// One call after the other -> together, whole batch: 6 sequences of 565 to 7627 tokens, 16 heads: 1053 -> 760 us (43
+// launches of 4 to 23 us, and attention at 0.8 PFLOP/s in rounds that are not full -> 7); 10 of 53 to 1171, 8 heads: 602 -> 87 (the
+// host was the bound); 5 of L = 20000 in all, 16 heads on 4, d = B = 64, keep 10 %: 340 -> 162; 8 of 40000, 32 on 8: 1873 -> 1593.
+// One sequence among others: few enough words for the small sort tiles, a map for the small score kernel, and less than two
+// rounds of 512-query workgroups.
+bool batch_takes(const basa_tensor* q, const basa_tensor* k, int L, int B) {
+  const int N = ceil_div(L, B);
+  return (int64_t)(q->heads + k->heads) * L <= (1 << 19) && (int64_t)q->heads * ceil_div(N, 64) * ceil_div(N, 64) <= 1280 &&
+         (int64_t)q->heads * N * B < 2 * 256 * 512 && N <= 4096 && attn_many_takes(N, q->d);
+}
+// Lists of more than 32 tiles are split over workgroups when a sequence is alone; together the sequences have to fill
+// the device instead (one workgroup of 128 queries per compute unit at least).
+bool batch_fills(const basa_tensor* q, const int* cu, const int* seqs, int n, int B) {
+  int64_t wgs = 0;
+  bool long_lists = false;
+  for (int i = 0; i < n; ++i) {
+    const int L = cu[seqs[i] + 1] - cu[seqs[i]];
+    wgs += (int64_t)q->heads * ceil_div(L, 128);
+    long_lists |= L > 32 * 64;
+  }
+  return !long_lists || wgs >= 256;
+}
+// Buffers of one sequence from offset `o` of the workspace on; returns the offset behind them.
+size_t carve_seq(SeqJob* s, const basa_tensor* q, const basa_tensor* k, int L, const basa_params* p, char* ws, size_t o) {
+  const int B = p->block, N = ceil_div(L, B), kappa = kappa_of(N, p->sparsity);
+  auto take = [&](size_t bytes) { char* at = ws ? ws + o : nullptr; o += align_up(bytes, 256); return at; };
+  s->Nq = s->Nk = N;
+  s->kappa = kappa;
+  s->sort_ws = take(sort_workspace_bytes(q->heads + k->heads, L));
+  s->feat_q = take((size_t)q->heads * N * feat_bytes_per_block(q->d));
+  s->feat_k = take((size_t)k->heads * N * feat_bytes_per_block(q->d));
+  s->scores = reinterpret_cast<float*>(take((size_t)q->heads * N * N * 4));
+  s->perm_q = reinterpret_cast<int32_t*>(take((size_t)q->heads * L * 4));
+  s->perm_k = reinterpret_cast<int32_t*>(take((size_t)k->heads * L * 4));
+  s->row_count = reinterpret_cast<int32_t*>(take((size_t)q->heads * N * 4));
+  s->row_cols = reinterpret_cast<int32_t*>(take((size_t)q->heads * N * kappa * 4));
+  s->tiles = take(attn_many_tile_bytes(k->heads, L, q->d, B));
+  return o;
+}
+// What one sequence needs by itself: its lists and permutations, then the workspaces of the two calls.
+struct SingleWs { size_t perm_q, perm_k, count, cols, select, attn, total; };
+SingleWs carve_single(const basa_tensor* q, const basa_tensor* k, const basa_params* p) {
+  SingleWs w;
+  const int Nq = ceil_div(q->L, p->block), Nk = ceil_div(k->L, p->block);
+  size_t o = 0;
+  w.perm_q = o; o += align_up((size_t)q->heads * q->L * 4, 256);
+  w.perm_k = o; o += align_up((size_t)k->heads * k->L * 4, 256);
+  w.count = o; o += align_up((size_t)q->heads * Nq * 4, 256);
+  w.cols = o; o += align_up((size_t)q->heads * Nq * std::max(1, kappa_of(Nk, p->sparsity)) * 4, 256);
+  w.select = o; o += carve_select(q, k, p).total;
+  w.attn = o; o += align_up(basa_attn_best_workspace_size(q, k, p), 256);
+  w.total = o;
+  return w;
+}
+// The sequences in groups: up to kMaxJobs together (together = true) or one by one.  Calls f(seqs, n, together).
+template <class Fn>
+basa_status for_groups(const basa_tensor* q, const basa_tensor* k, const int* cu, int n_seq, const basa_params* p, Fn&& f) {
+  int group[kMaxJobs], n = 0;
+  auto flush = [&]() -> basa_status {
+    basa_status s = BASA_OK;
+    // longest first: the last workgroups of a launch are short ones
+    std::sort(group, group + n, [&](int a, int b) { return cu[a + 1] - cu[a] > cu[b + 1] - cu[b]; });
+    if (n > 1 && batch_fills(q, cu, group, n, p->block)) s = f(group, n, true);
+    else
+      for (int i = 0; i < n && s == BASA_OK; ++i) s = f(group + i, 1, false);
+    n = 0;
+    return s;
+  };
+  const bool together = batch_takes_params(q, p);
+  for (int i = 0; i < n_seq; ++i) {
+    const int L = cu[i + 1] - cu[i];
+    if (L == 0) continue;
+    basa_status s = BASA_OK;
+    if (together && batch_takes(q, k, L, p->block)) {
+      group[n++] = i;
+      if (n == kMaxJobs) s = flush();
+    } else {
+      s = f(&i, 1, false);
+    }
+    if (s != BASA_OK) return s;
+  }
+  return n > 0 ? flush() : BASA_OK;
+}
+basa_status check_varlen(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v, const int32_t* cu, int n_seq,
+                         const basa_params* p) {
+  basa_status s;
+  if ((s = check_qkv(q, k, v)) != BASA_OK) return s;
+  if ((s = check_params(p, true)) != BASA_OK) return s;
+  if (q->batch != 1 || q->L != k->L) { set_error("a packed batch has batch 1 and as many queries as keys"); return BASA_ERR_INVALID_ARG; }
+  if (p->n_segments > 0) { set_error("segments of a packed batch are its sequences"); return BASA_ERR_INVALID_ARG; }
+  if (n_seq < 0 || (n_seq > 0 && !cu)) { set_error("null cu_seqlens"); return BASA_ERR_INVALID_ARG; }
+  for (int i = 0; i < n_seq; ++i)
+    if (cu[i] < 0 || cu[i + 1] < cu[i] || cu[i + 1] > q->L) {
+      set_error("cu_seqlens must ascend within [0, %d] (entry %d)", q->L, i + 1);
+      return BASA_ERR_INVALID_ARG;
+    }
+  return BASA_OK;
+}
+
 }  // namespace
 }  // namespace basa
 
@@ -401,6 +515,87 @@ basa_status basa_dense_attn(const basa_tensor* q, const basa_tensor* k, const ba
                      ws_bytes, stream);
 }
 
+
+size_t basa_varlen_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v, const int32_t* cu_seqlens,
+                                  int32_t n_seq, const basa_params* p) {
+  if (check_varlen(q, k, v, cu_seqlens, n_seq, p) != BASA_OK) return 0;
+  size_t need = 256;
+  for_groups(q, k, cu_seqlens, n_seq, p, [&](const int* seqs, int n, bool together) {
+    size_t o = 0;
+    for (int i = 0; i < n; ++i) {
+      const int first = cu_seqlens[seqs[i]], L = cu_seqlens[seqs[i] + 1] - first;
+      SeqJob s;
+      if (together) {
+        o = carve_seq(&s, q, k, L, p, nullptr, o);
+      } else {
+        const basa_tensor qs = rows_of(*q, first, L), ks = rows_of(*k, first, L);
+        o = carve_single(&qs, &ks, p).total;
+      }
+    }
+    need = std::max(need, o);
+    return BASA_OK;
+  });
+  return need;
+}
+
+basa_status basa_varlen_attn(const basa_tensor* q, const basa_tensor* k, const basa_tensor* v, const int32_t* cu_seqlens,
+                             int32_t n_seq, const basa_params* p, void* out, const int64_t* out_strides, void* ws,
+                             size_t ws_bytes, void* stream) {
+  basa_status s;
+  if ((s = check_varlen(q, k, v, cu_seqlens, n_seq, p)) != BASA_OK) return s;
+  if (!out || !out_strides) { set_error("null output pointer or strides"); return BASA_ERR_INVALID_ARG; }
+  if (reinterpret_cast<uintptr_t>(out) % 16) { set_error("out must be 16-byte aligned"); return BASA_ERR_INVALID_ARG; }
+  const int64_t per16 = q->dtype == BASA_BF16 ? 8 : 4;
+  if (out_strides[2] < q->d || out_strides[0] % per16 || out_strides[1] % per16 || out_strides[2] % per16 || out_strides[0] < 0 ||
+      out_strides[1] < 0) {
+    set_error("out_strides must be non-negative multiples of 16 bytes with the token stride >= d");
+    return BASA_ERR_INVALID_ARG;
+  }
+  for (int i = 0; i < n_seq; ++i)
+    if (ceil_div(cu_seqlens[i + 1] - cu_seqlens[i], p->block) > 4096) {
+      set_error("sequence %d has more than 4096 key blocks", i); return BASA_ERR_UNSUPPORTED;
+    }
+  const size_t need = basa_varlen_workspace_size(q, k, v, cu_seqlens, n_seq, p);
+  if (!ws || ws_bytes < need) {
+    set_error("workspace too small: need %zu bytes, got %zu", need, ws ? ws_bytes : (size_t)0);
+    return BASA_ERR_WORKSPACE;
+  }
+  if (reinterpret_cast<uintptr_t>(ws) % 256) { set_error("workspace must be 256-byte aligned"); return BASA_ERR_INVALID_ARG; }
+  hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+  char* base = reinterpret_cast<char*>(ws);
+  const int elem = q->dtype == BASA_BF16 ? 2 : 4;
+  return for_groups(q, k, cu_seqlens, n_seq, p, [&](const int* seqs, int n, bool together) -> basa_status {
+    basa_status e;
+    if (!together) {
+      const int first = cu_seqlens[seqs[0]], L = cu_seqlens[seqs[0] + 1] - first;
+      const basa_tensor qs = rows_of(*q, first, L), ks = rows_of(*k, first, L), vs = rows_of(*v, first, L);
+      const SingleWs w = carve_single(&qs, &ks, p);
+      int32_t *pq = reinterpret_cast<int32_t*>(base + w.perm_q), *pk = reinterpret_cast<int32_t*>(base + w.perm_k);
+      int32_t *count = reinterpret_cast<int32_t*>(base + w.count), *cols = reinterpret_cast<int32_t*>(base + w.cols);
+      if ((e = basa_select(&qs, &ks, p, nullptr, count, cols, pq, pk, nullptr, nullptr, base + w.select, w.attn - w.select, stream)) != BASA_OK)
+        return e;
+      return basa_sparse_attn(&qs, &ks, &vs, count, cols, kappa_of(ceil_div(L, p->block), p->sparsity), pq, pk, p,
+                              static_cast<char*>(out) + (int64_t)first * out_strides[2] * elem, out_strides, nullptr, base + w.attn,
+                              w.total - w.attn, stream);
+    }
+    SeqJob job[kMaxJobs];
+    size_t o = 0;
+    for (int i = 0; i < n; ++i) {
+      const int first = cu_seqlens[seqs[i]], L = cu_seqlens[seqs[i] + 1] - first;
+      job[i].q = view_of(rows_of(*q, first, L));
+      job[i].k = view_of(rows_of(*k, first, L));
+      job[i].v = view_of(rows_of(*v, first, L));
+      job[i].out = static_cast<char*>(out) + (int64_t)first * out_strides[2] * elem;
+      o = carve_seq(&job[i], q, k, L, p, base, o);
+    }
+    const int kdim = (p->beta == 0.f) ? q->d : 3 * q->d;
+    if ((e = launch_norm_sort_many(job, n, st)) != BASA_OK) return e;
+    if ((e = launch_select_features_many(job, n, p->block, p->beta, st)) != BASA_OK) return e;
+    if ((e = launch_block_scores_many(job, n, kdim, 3 * q->d, st)) != BASA_OK) return e;
+    if ((e = launch_row_select_many(job, n, (float)p->mass_target, p->min_keep, st)) != BASA_OK) return e;
+    return launch_attn_many(job, n, p->block, out_strides, st);
+  });
+}
 
 }  // extern "C"
 

@@ -252,15 +252,14 @@ __global__ __launch_bounds__(1024) void listed_blocks_kernel(const int32_t* __re
 // list names whole blocks, so the order inside one is free, and this one lets the main kernel leave out the half
 // tiles whose keys all come after a wave's queries.
 template <int D>
-__global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v, const int32_t* __restrict__ perm,
-                                                      uint4* __restrict__ Kt, uint4* __restrict__ Vt, int32_t* __restrict__ kix,
-                                                      int32_t* __restrict__ probe, int by_index,
-                                                      const uint32_t* __restrict__ listed, int parts, int tiles_per_block) {
+__device__ __forceinline__ void tile_kv(int tile, int bh, bool is_v, int tiles_per_head, const TensorView& k, const TensorView& v,
+                                        const int32_t* __restrict__ perm, uint4* __restrict__ Kt, uint4* __restrict__ Vt,
+                                        int32_t* __restrict__ kix, int32_t* __restrict__ probe, int by_index,
+                                        const uint32_t* __restrict__ listed, int parts, int tiles_per_block) {
   __shared__ __attribute__((aligned(16))) int raw[128], ordered[128], place[128];
-  const int tile = blockIdx.x, bh = blockIdx.y, tiles_per_head = gridDim.x;
   const int32_t* pm = perm ? perm + (int64_t)bh * k.L : nullptr;
   const int* rows = nullptr;
-  if (probe && blockIdx.z == 0 && tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
+  if (probe && !is_v && tile == 0 && bh == 0 && threadIdx.x < 2) probe[threadIdx.x] = 0;
   if (listed) {                                      // uniform: nobody reads the tiles of a block in no list
     const int block = tile / tiles_per_block, words = (tiles_per_head / tiles_per_block + 31) >> 5;
     uint32_t any = 0u;
@@ -291,13 +290,34 @@ __global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v
     __syncthreads();
     rows = ordered + (tile & 1) * kTileKeys;
   }
-  if (blockIdx.z == 0) {
+  if (!is_v) {
     gather_k_tile<D>(k, pm, rows, Kt, bh, tile, tiles_per_head);
     if (kix) key_index_tile(pm, rows, k.L, kix, bh, tile, tiles_per_head);
   } else {
     gather_vt_tile<D>(v, pm, rows, Vt, bh, tile, tiles_per_head);
   }
 }
+
+template <int D>
+__global__ __launch_bounds__(256) void tile_kv_kernel(TensorView k, TensorView v, const int32_t* __restrict__ perm,
+                                                      uint4* __restrict__ Kt, uint4* __restrict__ Vt, int32_t* __restrict__ kix,
+                                                      int32_t* __restrict__ probe, int by_index,
+                                                      const uint32_t* __restrict__ listed, int parts, int tiles_per_block) {
+  tile_kv<D>(blockIdx.x, blockIdx.y, blockIdx.z != 0, gridDim.x, k, v, perm, Kt, Vt, kix, probe, by_index, listed, parts,
+             tiles_per_block);
+}
+template <int D>
+struct TileJob {
+  TensorView k, v;
+  const int32_t* perm;
+  uint4 *Kt, *Vt;
+  int tiles;
+  __device__ __forceinline__ void run(int block) const {
+    const int row = block / tiles, tile = block - row * tiles, heads = k.heads;
+    const bool is_v = row >= heads;
+    tile_kv<D>(tile, is_v ? row - heads : row, is_v, tiles, k, v, perm, Kt, Vt, nullptr, nullptr, 0, nullptr, 0, 1);
+  }
+};
 
 // ---------------------------------------------------------------------------------
 // Main kernel
@@ -669,8 +689,8 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
 // left out, 7209 without the masks that mask nothing.
 // kSplit: a.splits workgroups share the query blocks and take equal runs of the union list each; their rows
 // stay unnormalised and attn_combine_kernel adds them up.
-template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
-__global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 : 2) void attn_mfma_kernel(MfmaArgs a) {
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit>
+__device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   using G = Geo<D>;
   static_assert(!kCausal || (kQPW == 64 && kWgQueries == kWideQueries), "the causal path is built on the 512-query shape");
   static_assert(!kFast || !kSplit, "the safe range of a row's sum is tested on the whole sum");
@@ -711,10 +731,6 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   uint32_t* wave_counts = seq + a.Nk;
   int* kix_lds = reinterpret_cast<int*>(smem + ((ring_bytes + kQParkBytes + a.Nk * 4 + kWaves * 4 + 15) & ~15));   // kCausal
 
-  // XCD-aware order: consecutive workgroup ids go round-robin over the 8 XCDs; give each
-  // XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
-  int logical = blockIdx.x;
-  if ((a.total_wgs & 7) == 0) logical = (blockIdx.x & 7) * (a.total_wgs >> 3) + (blockIdx.x >> 3);
   int split = 0;
   if constexpr (kSplit) {
     split = logical % a.splits;
@@ -1156,6 +1172,20 @@ __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 
   }
 }
 
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
+__global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 : 2) void attn_mfma_kernel(MfmaArgs a) {
+  // XCD-aware order: consecutive workgroup ids go round-robin over the 8 XCDs; give each
+  // XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
+  int logical = blockIdx.x;
+  if ((a.total_wgs & 7) == 0) logical = (blockIdx.x & 7) * (a.total_wgs >> 3) + (blockIdx.x >> 3);
+  attn_mfma<kB, D, kWgQueries, kQPW, kCausal, kFast, kSplit>(a, logical);
+}
+template <int kB, int D>
+struct AttnJob {
+  MfmaArgs a;
+  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kSoloQueries, 32, false, true, false>(a, block); }
+};
+
 size_t sz_kv(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 2, 256); }
 size_t sz_kix(int BHkv, int Nk, int B) { return align_up((size_t)BHkv * (Nk * B / kTileKeys) * kIxStride * 4, 256); }
 
@@ -1339,7 +1369,60 @@ __global__ __launch_bounds__(256) void list_overlap_kernel(const int32_t* __rest
     atomicAdd(&probe[1], uni_sub);
   }
 }
+template <int kB, int D>
+basa_status attn_many(const SeqJob* seq, int n, const int64_t* out_strides, hipStream_t st) {
+  {
+    Jobs<TileJob<D>> jobs;
+    for (int i = 0; i < n; ++i) {
+      const SeqJob& s = seq[i];
+      const int tiles = s.Nk * (kB / kTileKeys);
+      jobs.add(TileJob<D>{s.k, s.v, s.perm_k, reinterpret_cast<uint4*>(s.tiles),
+                          reinterpret_cast<uint4*>(s.tiles + sz_kv(s.k.heads, s.Nk, kB, D)), tiles},
+               (int64_t)tiles * s.k.heads * 2);
+    }
+    ProfScope prof(K_GATHER, st);
+    hipLaunchKernelGGL(many_kernel<TileJob<D>>, dim3(jobs.first[n]), dim3(256), 0, st, jobs);
+    BASA_HIP_CHECK_LAUNCH("tile_kv");
+  }
+  Jobs<AttnJob<kB, D>> jobs;
+  size_t lds = 0;
+  for (int i = 0; i < n; ++i) {
+    const SeqJob& s = seq[i];
+    MfmaArgs m = {};
+    m.q = s.q; m.Kt = s.tiles; m.Vt = s.tiles + sz_kv(s.k.heads, s.Nk, kB, D);
+    m.row_count = s.row_count; m.row_cols = s.row_cols; m.cols_stride = s.kappa;
+    m.perm_q = s.perm_q;
+    m.out = reinterpret_cast<__bf16*>(s.out);
+    m.out_sb = out_strides[0]; m.out_sh = out_strides[1]; m.out_sl = out_strides[2]; m.heads_q = s.q.heads;
+    m.Nq = s.Nq; m.Nk = s.Nk; m.Lq = s.q.L; m.Lk = s.k.L;
+    m.group = s.q.heads / s.k.heads;
+    m.wgs_per_head = ceil_div(s.Nq * kB, kSoloQueries);
+    m.total_wgs = s.q.heads * m.wgs_per_head;
+    m.scale_log2e = 1.4426950408889634f / sqrtf((float)D);
+    m.splits = 1;
+    jobs.add(AttnJob<kB, D>{m}, m.total_wgs);
+    lds = std::max(lds, lds_bytes<D>(kSoloQueries / 32 * 64, 32, s.Nk, false, true));
+  }
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&many_kernel<AttnJob<kB, D>, 2>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
+  ProfScope prof(K_ATTN, st);
+  hipLaunchKernelGGL((many_kernel<AttnJob<kB, D>, 2>), dim3(jobs.first[n]), dim3(256), lds, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("attn_mfma");
+  return BASA_OK;
+}
 }  // namespace
+
+size_t attn_many_tile_bytes(int heads_kv, int Lk, int d, int B) { return 2 * sz_kv(heads_kv, ceil_div(Lk, B), B, d); }
+bool attn_many_takes(int Nk, int d) {
+  // (the membership words of the key blocks live in the ring while the list is built; two workgroups per compute unit)
+  return d == 128 ? (size_t)Nk * 4 <= 2 * Geo<128>::kStageBytes && lds_bytes<128>(256, 32, Nk, false, true) <= kLdsBytes / 2
+                  : (size_t)Nk * 4 <= 2 * Geo<64>::kStageBytes && lds_bytes<64>(256, 32, Nk, false, true) <= kLdsBytes / 2;
+}
+basa_status launch_attn_many(const SeqJob* seq, int n, int B, const int64_t* out_strides, hipStream_t st) {
+  if (seq[0].q.d == 128) return B == 128 ? attn_many<128, 128>(seq, n, out_strides, st) : attn_many<64, 128>(seq, n, out_strides, st);
+  return B == 128 ? attn_many<128, 64>(seq, n, out_strides, st) : attn_many<64, 64>(seq, n, out_strides, st);
+}
 
 size_t attn_mfma_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B) {
   const int Nq = ceil_div(Lq, B), Nk = ceil_div(Lk, B);

@@ -176,8 +176,55 @@ double calib_mfma_flops(int iters);
 hipError_t launch_calib_mfma(bool random_operands, int iters, float* out, hipStream_t stream);
 hipError_t launch_calib_read(const void* buf, size_t bytes, uint32_t* out, hipStream_t stream);
 
+// ---- several problems in one launch --------------------------------------------
+// A packed batch of short sequences is bound by its launches (about 4 us each, seven to a sequence): the same kernel
+// for all of them goes out once, with the arguments of every sequence.  Job: `Args` of one problem, and
+// `__device__ void run(int block) const` of one of its workgroups.
+constexpr int kMaxJobs = 12;               // as many as the 4 KB of kernel arguments hold
+template <class Job>
+struct Jobs {
+  int n = 0;
+  int first[kMaxJobs + 1] = {0};           // first workgroup of a job: a multiple of 8, so that a run of its workgroups stays
+  int blocks[kMaxJobs];                    //   on one XCD as in a launch of its own
+  Job job[kMaxJobs];
+  void add(const Job& j, int64_t count) {
+    job[n] = j;
+    blocks[n] = (int)count;
+    first[n + 1] = first[n] + (int)((count + 7) / 8 * 8);
+    ++n;
+  }
+};
+// One sequence of a packed batch, [1, heads, L, d] views into the packed tensors, and its buffers.
+struct SeqJob {
+  TensorView q, k, v;
+  int Nq, Nk, kappa;
+  void* sort_ws;
+  void* feat_q;
+  void* feat_k;
+  float* scores;
+  int32_t *perm_q, *perm_k, *row_count, *row_cols;
+  char* tiles;               // K tiles, then V^T tiles
+  void* out;
+};
+// The stages for up to kMaxJobs sequences of bf16, sorted Q and K.
+basa_status launch_norm_sort_many(const SeqJob* seq, int n, hipStream_t st);
+basa_status launch_select_features_many(const SeqJob* seq, int n, int B, float beta, hipStream_t st);
+basa_status launch_block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st);
+basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st);
+size_t attn_many_tile_bytes(int heads_kv, int Lk, int d, int B);
+bool attn_many_takes(int Nk, int d);       // the list fits the kernel's LDS
+basa_status launch_attn_many(const SeqJob* seq, int n, int B, const int64_t* out_strides, hipStream_t st);
+
 // ---- device helpers ------------------------------------------------------------
 #if defined(__HIPCC__)
+template <class Job, int kWavesPerSimd = 1>
+__global__ __launch_bounds__(256, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
+  int i = 0;
+  while (i + 1 < jobs.n && (int)blockIdx.x >= jobs.first[i + 1]) ++i;
+  const int b = blockIdx.x - jobs.first[i], per = (jobs.first[i + 1] - jobs.first[i]) >> 3;
+  const int logical = (b & 7) * per + (b >> 3);
+  if (logical < jobs.blocks[i]) jobs.job[i].run(logical);
+}
 // Entry `pos` of a permutation of 0..L-1 (null = identity).  Permutations are device data the
 // host cannot check: a value that is no index falls back to `pos`, so that a malformed
 // permutation gives wrong rows, never an access outside the tensor.

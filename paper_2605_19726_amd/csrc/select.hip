@@ -165,14 +165,11 @@ __global__ __launch_bounds__(256, 2) void block_scores_kernel(const uint4* __res
 // 128 x 128: 46.4 -> 14.1; 32 heads, 2 x 256: 45.2 -> 11.1.
 // ---------------------------------------------------------------------------------
 constexpr int kSmallTile = 64;              // rows and columns of the map per workgroup
-__global__ __launch_bounds__(256) void block_scores_small_kernel(const uint4* __restrict__ featQ,
-                                                                 const uint4* __restrict__ featK,
-                                                                 float* __restrict__ scores, int group, int Nq,
-                                                                 int Nk, int K, int S) {
+__device__ __forceinline__ void block_scores_small(int logical, const uint4* __restrict__ featQ,
+                                                   const uint4* __restrict__ featK, float* __restrict__ scores, int group,
+                                                   int Nq, int Nk, int K, int S) {
   constexpr int kDepth = 4;
-  const int tiles_x = (Nk + kSmallTile - 1) / kSmallTile, tiles_y = (Nq + kSmallTile - 1) / kSmallTile, total = gridDim.x;
-  int logical = blockIdx.x;                     // one XCD, one range of heads
-  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  const int tiles_x = (Nk + kSmallTile - 1) / kSmallTile, tiles_y = (Nq + kSmallTile - 1) / kSmallTile;
   const int bhq = logical / (tiles_x * tiles_y);
   const int rem = logical - bhq * (tiles_x * tiles_y);
   const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
@@ -221,6 +218,22 @@ __global__ __launch_bounds__(256) void block_scores_small_kernel(const uint4* __
   }
 }
 
+__global__ __launch_bounds__(256) void block_scores_small_kernel(const uint4* __restrict__ featQ,
+                                                                 const uint4* __restrict__ featK,
+                                                                 float* __restrict__ scores, int group, int Nq,
+                                                                 int Nk, int K, int S) {
+  const int total = gridDim.x;
+  int logical = blockIdx.x;                     // one XCD, one range of heads
+  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  block_scores_small(logical, featQ, featK, scores, group, Nq, Nk, K, S);
+}
+struct ScoresJob {
+  const uint4 *fq, *fk;
+  float* scores;
+  int group, Nq, Nk, K, S;
+  __device__ __forceinline__ void run(int block) const { block_scores_small(block, fq, fk, scores, group, Nq, Nk, K, S); }
+};
+
 // ---------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t ordered_bits(float f) {
   uint32_t u = __float_as_uint(f);
@@ -242,16 +255,13 @@ __device__ __forceinline__ float float_of_ordered(uint32_t u) {
 // count is found first (a second bisection, on "mass of the logits >= T"), then the same
 // top-count machinery runs with the row's own count.
 template <int MAXI, bool kLive>
-__global__ __launch_bounds__(256) void row_select_kernel(const float* __restrict__ scores,
-                                                         int rows_total, int Nk, int kappa,
-                                                         float mass_target, int min_keep,
-                                                         const int32_t* __restrict__ keep_in, LiveBlocks live,
-                                                         uint32_t* __restrict__ mask_bits,
-                                                         int32_t* __restrict__ row_count,
-                                                         int32_t* __restrict__ row_cols,
-                                                         float* __restrict__ row_mass) {
+__device__ __forceinline__ void row_select(int block, const float* __restrict__ scores, int rows_total, int Nk, int kappa,
+                                           float mass_target, int min_keep, const int32_t* __restrict__ keep_in,
+                                           const LiveBlocks& live, uint32_t* __restrict__ mask_bits,
+                                           int32_t* __restrict__ row_count, int32_t* __restrict__ row_cols,
+                                           float* __restrict__ row_mass) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + wave;
+  const int row = block * 4 + wave;
   if (row >= rows_total) return;
   const float* src = scores + (int64_t)row * Nk;
   // causal variant: a key block is live for this row iff its smallest original key index does not
@@ -383,6 +393,30 @@ __global__ __launch_bounds__(256) void row_select_kernel(const float* __restrict
     if (row_mass) row_mass[row] = sum_sel / sum_all;
   }
 }
+
+template <int MAXI, bool kLive>
+__global__ __launch_bounds__(256) void row_select_kernel(const float* __restrict__ scores,
+                                                         int rows_total, int Nk, int kappa,
+                                                         float mass_target, int min_keep,
+                                                         const int32_t* __restrict__ keep_in, LiveBlocks live,
+                                                         uint32_t* __restrict__ mask_bits,
+                                                         int32_t* __restrict__ row_count,
+                                                         int32_t* __restrict__ row_cols,
+                                                         float* __restrict__ row_mass) {
+  row_select<MAXI, kLive>(blockIdx.x, scores, rows_total, Nk, kappa, mass_target, min_keep, keep_in, live, mask_bits, row_count,
+                          row_cols, row_mass);
+}
+template <int MAXI>
+struct RowSelectJob {
+  const float* scores;
+  int rows, Nk, kappa, min_keep;
+  float mass_target;
+  int32_t *row_count, *row_cols;
+  __device__ __forceinline__ void run(int block) const {
+    row_select<MAXI, false>(block, scores, rows, Nk, kappa, mass_target, min_keep, nullptr, LiveBlocks{}, nullptr, row_count, row_cols,
+                            nullptr);
+  }
+};
 
 // ---------------------------------------------------------------------------------
 // Score map and fixed-count row selection in ONE kernel: the map never leaves the chip
@@ -740,6 +774,43 @@ basa_status launch_block_scores(const void* featQ, const void* featK, float* sco
                      reinterpret_cast<const uint4*>(featK), scores, group, Nq, Nk, kdim_used, feat_stride);
   BASA_HIP_CHECK_LAUNCH("block_scores_kernel");
   return BASA_OK;
+}
+
+basa_status launch_block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st) {
+  Jobs<ScoresJob> jobs;
+  for (int i = 0; i < n; ++i) {
+    const SeqJob& s = seq[i];
+    jobs.add(ScoresJob{reinterpret_cast<const uint4*>(s.feat_q), reinterpret_cast<const uint4*>(s.feat_k), s.scores,
+                       s.q.heads / s.k.heads, s.Nq, s.Nk, kdim_used, feat_stride},
+             (int64_t)ceil_div(s.Nk, kSmallTile) * ceil_div(s.Nq, kSmallTile) * s.q.heads);
+  }
+  ProfScope prof(K_SCORES, st);
+  hipLaunchKernelGGL(many_kernel<ScoresJob>, dim3(jobs.first[n]), dim3(256), 0, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("block_scores_small");
+  return BASA_OK;
+}
+
+template <int MAXI>
+static basa_status select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st) {
+  Jobs<RowSelectJob<MAXI>> jobs;
+  for (int i = 0; i < n; ++i) {
+    const int rows = seq[i].q.heads * seq[i].Nq;
+    jobs.add(RowSelectJob<MAXI>{seq[i].scores, rows, seq[i].Nk, seq[i].kappa, min_keep, mass_target, seq[i].row_count, seq[i].row_cols},
+             ceil_div(rows, 4));
+  }
+  ProfScope prof(K_ROW_SELECT, st);
+  hipLaunchKernelGGL(many_kernel<RowSelectJob<MAXI>>, dim3(jobs.first[n]), dim3(256), 0, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("row_select");
+  return BASA_OK;
+}
+basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st) {
+  int widest = 0;
+  for (int i = 0; i < n; ++i) widest = std::max(widest, seq[i].Nk);
+  if (widest <= 256) return select_many<4>(seq, n, mass_target, min_keep, st);
+  if (widest <= 512) return select_many<8>(seq, n, mass_target, min_keep, st);
+  if (widest <= 1024) return select_many<16>(seq, n, mass_target, min_keep, st);
+  if (widest <= 2048) return select_many<32>(seq, n, mass_target, min_keep, st);
+  return select_many<64>(seq, n, mass_target, min_keep, st);
 }
 
 bool scores_select_supported(int Nk, int kdim_used, int feat_stride) {

@@ -209,12 +209,10 @@ __device__ __forceinline__ void rank_small_tile(uint64_t (&v)[4], int (&rank)[4]
 }
 
 template <bool kBf16, int kD, int kTileT>
-__global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
-                                                                      uint64_t* __restrict__ out,
-                                                                      int32_t* __restrict__ perm0,
-                                                                      int32_t* __restrict__ perm1,
-                                                                      float* __restrict__ keys_out, SegGeom g0,
-                                                                      SegGeom g1, SegList sl) {
+__device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView& x0, const TensorView& x1, int BH0,
+                                               uint64_t* __restrict__ out, int32_t* __restrict__ perm0,
+                                               int32_t* __restrict__ perm1, float* __restrict__ keys_out, const SegGeom& g0,
+                                               const SegGeom& g1, const SegList& sl) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;          // lanes per row: 8, 16 or 32
   constexpr int kRowsPerIter = kSortThreads / LPR;
@@ -223,11 +221,11 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
   static_assert(kTileT % kRowsPerPass == 0, "a tile is a whole number of passes");
   __shared__ uint64_t buf[kTileT + kTileT / 16];
 
-  const bool second = (int)blockIdx.y >= BH0;
+  const bool second = by >= BH0;
   const SegGeom& g = second ? g1 : g0;
-  const int bh = second ? blockIdx.y - BH0 : blockIdx.y;
-  const int seg = blockIdx.x / g.tiles_per_seg;
-  const int tile = blockIdx.x - seg * g.tiles_per_seg;
+  const int bh = second ? by - BH0 : by;
+  const int seg = bx / g.tiles_per_seg;
+  const int tile = bx - seg * g.tiles_per_seg;
   const int seg_end = min((seg + 1) * g.W, g.L);
   const int start = seg * g.W + tile * kTileT;
   if (start >= seg_end) return;
@@ -376,6 +374,29 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
     for (int i = threadIdx.x; i < n; i += kSortThreads) __builtin_nontemporal_store(buf[tile_slot(i)], &out[hb + start + i]);
   }
 }
+
+template <bool kBf16, int kD, int kTileT>
+__global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
+                                                                      uint64_t* __restrict__ out,
+                                                                      int32_t* __restrict__ perm0,
+                                                                      int32_t* __restrict__ perm1,
+                                                                      float* __restrict__ keys_out, SegGeom g0,
+                                                                      SegGeom g1, SegList sl) {
+  norm_tile_sort<kBf16, kD, kTileT>(blockIdx.x, blockIdx.y, x0, x1, BH0, out, perm0, perm1, keys_out, g0, g1, sl);
+}
+template <int kD>
+struct SmallSortJob {
+  TensorView q, k;
+  uint64_t* out;
+  int32_t *perm_q, *perm_k;                // null: more than one tile
+  SegGeom g;
+  __device__ __forceinline__ void run(int block) const {
+    SegList whole;
+    whole.n = 0;
+    const int by = block / g.tiles_per_seg;
+    norm_tile_sort<true, kD, kSmallTile>(block - by * g.tiles_per_seg, by, q, k, q.heads, out, perm_q, perm_k, nullptr, g, g, whole);
+  }
+};
 
 // ---------------------------------------------------------------------------------
 // Merge pass: sorted runs of `run` elements are merged pairwise inside each segment.
@@ -567,12 +588,9 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
 // Bound by the probes ((kG - 1) log2(run) per word, through L1); 32 rows of 7627 words, 8 runs each: 15.6 us against
 // 40 us for the LDS merge of a few workgroups; 2 x 10^6 words in 32 runs: 193 us against 39.
 template <int kG>
-__global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                                                                 int32_t* __restrict__ perm0, int32_t* __restrict__ perm1,
-                                                                 int BH0, SegGeom g, int run, int chunks_per_bh) {
-  const int total = gridDim.x;
-  int logical = blockIdx.x;                // a head's words on one XCD: their scattered stores meet in its L2
-  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+__device__ __forceinline__ void rank_runs(int logical, const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
+                                          int32_t* __restrict__ perm0, int32_t* __restrict__ perm1, int BH0, const SegGeom& g,
+                                          int run, int chunks_per_bh) {
   const int bh = logical / chunks_per_bh, i = (logical - bh * chunks_per_bh) * kSortThreads + threadIdx.x;
   if (i >= g.L) return;
   const int64_t hb = (int64_t)bh * g.L;
@@ -607,6 +625,25 @@ __global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t*
   if (perm_out) perm_out[hb + base + rank] = idx_of_word(v);
   else out[hb + base + rank] = v;
 }
+
+template <int kG>
+__global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
+                                                                 int32_t* __restrict__ perm0, int32_t* __restrict__ perm1,
+                                                                 int BH0, SegGeom g, int run, int chunks_per_bh) {
+  const int total = gridDim.x;
+  int logical = blockIdx.x;                // a head's words on one XCD: their scattered stores meet in its L2
+  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  rank_runs<kG>(logical, in, out, perm0, perm1, BH0, g, run, chunks_per_bh);
+}
+template <int kG>
+struct RankJob {
+  const uint64_t* in;
+  uint64_t* out;
+  int32_t *perm_q, *perm_k;                // null unless the last pass
+  int heads_q, run_len, chunks;
+  SegGeom g;
+  __device__ __forceinline__ void run(int block) const { rank_runs<kG>(block, in, out, perm_q, perm_k, heads_q, g, run_len, chunks); }
+};
 
 __global__ void iota_kernel(int32_t* perm, int L, int64_t total) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -742,6 +779,56 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   if (!single0) s = merge_tiles(buf1, buf0, BH0, BH0, g0, tile, few, perm0, nullptr, st);
   if (s == BASA_OK && !single1) s = merge_tiles(buf1 + words0, buf0 + words0, BH1, BH1, g1, tile, few, perm1, nullptr, st);
   return s;
+}
+
+template <int kG>
+static basa_status rank_many(const SeqJob* seq, int n, int run, int pass, hipStream_t st) {
+  Jobs<RankJob<kG>> jobs;
+  for (int i = 0; i < n; ++i) {
+    const int L = seq[i].q.L, rows = seq[i].q.heads + seq[i].k.heads;
+    if (run >= L) continue;                                // sorted by an earlier pass
+    const bool last = (int64_t)run * kG >= L;
+    uint64_t* buf[2] = {reinterpret_cast<uint64_t*>(seq[i].sort_ws),
+                        reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(seq[i].sort_ws) + align_up((size_t)rows * L * 8, 256))};
+    jobs.add(RankJob<kG>{buf[pass & 1], buf[(pass & 1) ^ 1], last ? seq[i].perm_q : nullptr, last ? seq[i].perm_k : nullptr,
+                         seq[i].q.heads, run, ceil_div(L, kSortThreads), geom_of(L, 0, kSmallTile)},
+             (int64_t)ceil_div(L, kSortThreads) * rows);
+  }
+  if (jobs.n == 0) return BASA_OK;
+  ProfScope prof(K_MERGE, st);
+  hipLaunchKernelGGL(many_kernel<RankJob<kG>>, dim3(jobs.first[jobs.n]), dim3(kSortThreads), 0, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("rank_runs");
+  return BASA_OK;
+}
+template <int kD>
+static basa_status sort_many(const SeqJob* seq, int n, hipStream_t st) {
+  int longest = 0;
+  {
+    Jobs<SmallSortJob<kD>> jobs;
+    for (int i = 0; i < n; ++i) {
+      const SegGeom g = geom_of(seq[i].q.L, 0, kSmallTile);
+      const bool single = g.tiles_per_seg == 1;
+      jobs.add(SmallSortJob<kD>{seq[i].q, seq[i].k, reinterpret_cast<uint64_t*>(seq[i].sort_ws), single ? seq[i].perm_q : nullptr,
+                                single ? seq[i].perm_k : nullptr, g},
+               (int64_t)g.tiles_per_seg * (seq[i].q.heads + seq[i].k.heads));
+      longest = std::max(longest, seq[i].q.L);
+    }
+    ProfScope prof(K_NORM_TILE_SORT, st);
+    hipLaunchKernelGGL(many_kernel<SmallSortJob<kD>>, dim3(jobs.first[n]), dim3(kSortThreads), 0, st, jobs);
+    BASA_HIP_CHECK_LAUNCH("norm_tile_sort");
+  }
+  // groups of eight runs (four if that is enough) until the longest sequence is one run
+  int pass = 0;
+  for (int64_t run = kSmallTile; run < longest; ++pass) {
+    const bool four = run * 4 >= longest;
+    const basa_status s = four ? rank_many<4>(seq, n, (int)run, pass, st) : rank_many<8>(seq, n, (int)run, pass, st);
+    if (s != BASA_OK) return s;
+    run *= four ? 4 : 8;
+  }
+  return BASA_OK;
+}
+basa_status launch_norm_sort_many(const SeqJob* seq, int n, hipStream_t st) {
+  return seq[0].q.d == 128 ? sort_many<128>(seq, n, st) : sort_many<64>(seq, n, st);
 }
 
 basa_status launch_norm_sort(const TensorView& x, int window, const SegList& segs, int32_t* perm, float* keys_out,

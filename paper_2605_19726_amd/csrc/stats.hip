@@ -44,7 +44,7 @@ __device__ __forceinline__ float chunk_elem(const uint4& r, int e) {
 // written at the end as 128-byte runs (in the [part][k/8][g][k%8] layout one block's features are
 // 16-byte pieces 16 KB apart, which cost a fifth of the kernel when every block wrote its own).
 template <bool kBf16, int kD, int kB>
-__global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob j1, int BH0, float beta, int per_wg) {
+__device__ __forceinline__ void block_stats(int bx, int by, const StatsJob& j0, const StatsJob& j1, int BH0, float beta, int per_wg) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;       // lanes per row
   constexpr int RPI = 256 / LPR;             // rows per iteration
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob 
   __shared__ float red[2][2][4][kD];         // [block parity][mean | centred squares][wave][column]
   __shared__ __attribute__((aligned(16))) uint16_t stage[3][3 * kD / 8][kGroup][8];   // [part][k/8][block][k%8]
 
-  const bool second = (int)blockIdx.y >= BH0;
+  const bool second = by >= BH0;
   const StatsJob& job = second ? j1 : j0;
   const TensorView& x = job.x;
   float* mean_out = job.mean_out;
@@ -62,10 +62,10 @@ __global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob 
   uint16_t* feat_out = job.feat_out;
   const int feat_is_query = job.feat_is_query;
   uint4* sorted_out = reinterpret_cast<uint4*>(job.sorted_out);
-  const int bh = second ? blockIdx.y - BH0 : blockIdx.y;
+  const int bh = second ? by - BH0 : by;
   const int L = x.L;
   const int N = (L + kB - 1) / kB;
-  const int g0 = blockIdx.x * per_wg;
+  const int g0 = bx * per_wg;
   const int nb = min(per_wg, N - g0);        // blocks of this workgroup that exist
   if (nb <= 0) return;                       // (the other tensor of the launch is the longer one)
   const int sub = threadIdx.x % LPR, rig = threadIdx.x / LPR;
@@ -268,7 +268,53 @@ __global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob 
   }
 }
 
+template <bool kBf16, int kD, int kB>
+__global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob j1, int BH0, float beta, int per_wg) {
+  block_stats<kBf16, kD, kB>(blockIdx.x, blockIdx.y, j0, j1, BH0, beta, per_wg);
+}
+template <int kD, int kB>
+struct FeatureJob {
+  StatsJob q, k;
+  int gx, per_wg;
+  float beta;
+  __device__ __forceinline__ void run(int block) const {
+    const int by = block / gx;
+    block_stats<true, kD, kB>(block - by * gx, by, q, k, q.x.heads, beta, per_wg);
+  }
+};
+
+// Blocks per workgroup: a workgroup takes its blocks one after the other, so calls of few blocks get as many
+// workgroups as there are (16 + 16 heads of 16 blocks: 11.0 us against 28.7 with 8 to a workgroup; 1920 blocks: 20.0
+// with 2, 29.0 with 8; 5120: 24.3 with 4, 28.3 with 8), large ones the full runs of features (8192: 57.5 with 8,
+// 63 with 2, 73 with 1).
+int blocks_per_wg(int64_t blocks) { return blocks <= 1024 ? 1 : blocks <= 2048 ? 2 : blocks <= 6144 ? 4 : kGroup; }
+
+template <int kD, int kB>
+basa_status features_many(const SeqJob* seq, int n, float beta, hipStream_t st) {
+  int64_t blocks = 0;
+  for (int i = 0; i < n; ++i) blocks += (int64_t)seq[i].q.heads * seq[i].Nq + (int64_t)seq[i].k.heads * seq[i].Nk;
+  const int per_wg = blocks_per_wg(blocks);
+  Jobs<FeatureJob<kD, kB>> jobs;
+  for (int i = 0; i < n; ++i) {
+    const SeqJob& s = seq[i];
+    const int gx = ceil_div(s.Nq, per_wg);
+    jobs.add(FeatureJob<kD, kB>{StatsJob{s.q, s.perm_q, nullptr, nullptr, reinterpret_cast<uint16_t*>(s.feat_q), 1, nullptr},
+                                StatsJob{s.k, s.perm_k, nullptr, nullptr, reinterpret_cast<uint16_t*>(s.feat_k), 0, nullptr},
+                                gx, per_wg, beta},
+             (int64_t)gx * (s.q.heads + s.k.heads));
+  }
+  ProfScope prof(K_STATS, st);
+  hipLaunchKernelGGL((many_kernel<FeatureJob<kD, kB>>), dim3(jobs.first[n]), dim3(256), 0, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("block_stats");
+  return BASA_OK;
+}
+
 }  // namespace
+
+basa_status launch_select_features_many(const SeqJob* seq, int n, int B, float beta, hipStream_t st) {
+  if (seq[0].q.d == 128) return B == 128 ? features_many<128, 128>(seq, n, beta, st) : features_many<128, 64>(seq, n, beta, st);
+  return B == 128 ? features_many<64, 128>(seq, n, beta, st) : features_many<64, 64>(seq, n, beta, st);
+}
 
 static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int B, float beta, hipStream_t st) {
   const TensorView& x = j0.x;
@@ -280,12 +326,8 @@ static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int 
     return s != BASA_OK ? s : block_stats_impl(*j1, nullptr, B, beta, st);
   }
   const int N = std::max(ceil_div(x.L, B), j1 ? ceil_div(j1->x.L, B) : 0);
-  // Blocks per workgroup: a workgroup takes its blocks one after the other, so calls of few blocks get as many
-  // workgroups as there are (16 + 16 heads of 16 blocks: 11.0 us against 28.7 with 8 to a workgroup; 1920 blocks: 20.0
-  // with 2, 29.0 with 8; 5120: 24.3 with 4, 28.3 with 8), large ones the full runs of features (8192: 57.5 with 8,
-  // 63 with 2, 73 with 1).
   const int64_t blocks = (int64_t)BH0 * ceil_div(x.L, B) + (int64_t)BH1 * (j1 ? ceil_div(j1->x.L, B) : 0);
-  const int per_wg = blocks <= 1024 ? 1 : blocks <= 2048 ? 2 : blocks <= 6144 ? 4 : kGroup;
+  const int per_wg = blocks_per_wg(blocks);
   dim3 grid(ceil_div(N, per_wg), BH0 + BH1);
   ProfScope prof(K_STATS, st);
   const bool bf = x.dtype == BASA_BF16;

@@ -206,3 +206,20 @@ def test_downsample_validation_without_a_launch(lib):
     assert lib.basa_block_mass_workspace_size(C.byref(fake_tensor(ptr=0)), C.byref(x)) == 0
     assert lib.basa_block_mass_workspace_size(C.byref(x), C.byref(fake_tensor(heads=3))) == 0
     assert lib.basa_block_mass_workspace_size(C.byref(x), C.byref(x)) > 0
+
+
+def test_packed_batch_validation(lib):
+    q, p = fake_tensor(heads=4, L=1000), bd.params(128, 0.5)
+    cu = lambda *x: (C.c_int32 * len(x))(*x)
+    size = lambda t, c, n, par=p: lib.basa_varlen_workspace_size(C.byref(t), C.byref(t), C.byref(t), c, n, C.byref(par))
+    assert size(q, cu(0, 500, 1000), 2) > 0
+    assert size(q, cu(0, 500, 500, 1000), 3) >= size(q, cu(0, 500, 1000), 2)
+    assert size(q, cu(0, 500, 1001), 2) == 0 and size(q, cu(0, 500, 400), 2) == 0 and size(q, cu(-1, 500), 1) == 0
+    assert size(fake_tensor(heads=4, L=1000, d=96), cu(0, 500, 1000), 2) == 0
+    assert size(q, cu(0, 500, 1000), 2, bd.params(128, 0.5, segments=[0, 100])) == 0
+    strides = (C.c_int64 * 3)(4 * 1000 * 128, 128, 4 * 128)
+    call = lambda out, ws, n: lib.basa_varlen_attn(C.byref(q), C.byref(q), C.byref(q), cu(0, 500, 1000), 2, C.byref(p), out, strides,
+                                                   ws, n, None)
+    assert call(None, 4096, 1 << 40) == 1 and call(8, 4096, 1 << 40) == 1          # no output, misaligned output
+    assert call(4096, None, 0) != 0 and b"workspace" in lib.basa_last_error()
+    assert call(4096, 4096, 1000) != 0 and b"workspace" in lib.basa_last_error()

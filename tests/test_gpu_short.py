@@ -432,3 +432,33 @@ def test_f32_three_part_products_leave_infinities_to_the_fp32_instruction(where,
         assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isinf(a), torch.isinf(b))
         fin = torch.isfinite(a) & torch.isfinite(b)
         assert torch.allclose(a[fin], b[fin], rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("dtype,d,block,hq,hk,lens,kw", [
+    (torch.bfloat16, 128, 128, 4, 2, [1024, 1, 1025, 129, 64, 2050], {}),
+    (torch.bfloat16, 64, 64, 4, 4, [63, 4096 + 1, 700, 65], dict(beta=0.0)),
+    (torch.bfloat16, 128, 64, 2, 1, [8192 + 100, 300, 9000], dict(mass_target=0.6, min_keep=2)),     # two ranking passes
+    (torch.bfloat16, 64, 128, 8, 2, [130 + 17 * i for i in range(15)], {}),                          # more than one launch holds
+    (torch.bfloat16, 128, 128, 32, 32, [200, 9000, 500], {}),                                        # one that goes by itself
+    (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(causal=True)),                                  # all by themselves
+    (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(sort=bd.SORT_K)),
+    (torch.float32, 64, 64, 2, 2, [400, 0, 300], {})])
+def test_packed_batch_against_one_call_per_sequence(dtype, d, block, hq, hk, lens, kw):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(sum(lens) + d)
+    T = sum(lens) + 3                                     # tokens behind the last sequence stay out of it
+    q, k, v = (torch.randn((T, h, d), generator=g, device=DEV).to(dtype) for h in (hq, hk, hk))
+    cu = np.cumsum([0] + lens).tolist()
+    out = bd.ba_att_varlen(q, k, v, cu, block, 0.5, **kw)
+    assert torch.equal(bd.ba_att_varlen(q, k, v, cu, block, 0.5, **kw)[:cu[-1]], out[:cu[-1]])
+    view = lambda x, a, b: x[a:b].permute(1, 0, 2).unsqueeze(0)
+    for a, b in zip(cu[:-1], cu[1:]):
+        if a == b:
+            continue
+        want, _ = bd.ba_att(view(q, a, b), view(k, a, b), view(v, a, b), block, 0.5, **kw)
+        got = view(out, a, b)
+        if dtype == torch.float32:
+            assert torch.equal(got, want)
+        else:                                             # (lists split or not, shapes of workgroup: bf16 rounding of out)
+            err = (got.float() - want.float()).norm() / want.float().norm()
+            assert err < 4e-3 and (got.float() - want.float()).abs().max() < 2e-2, (a, b, err)
