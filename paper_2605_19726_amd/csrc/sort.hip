@@ -127,33 +127,35 @@ __device__ __forceinline__ void sort_tile_in_lds(uint64_t* buf, int t) {
   __syncthreads();
 }
 
-// ---- the network of a small tile: 1024 words, 256 threads, 4 words per thread ------------------
-// Wave w sorts words 256 w .. 256 w + 255 by itself (index = 4 lane + register: two index bits in registers, six
+// ---- the network of a small tile: 1024 or 512 words, 256 threads, W = 4 or 2 words per thread ----
+// Wave w sorts words 64 W w .. 64 W (w + 1) - 1 by itself (index = W lane + register: the low index bits in registers, six
 // exchanged between lanes, no barrier); the four runs are then ranked against each other in LDS.  Returns in
 // rank[r] the place of v[r] in the tile (padding words, all alike, get places past the last real word).
 constexpr int kSmallTile = 1024;
-__device__ __forceinline__ void sort_256_in_wave(uint64_t (&v)[4], int lane) {
+template <int W>
+__device__ __forceinline__ void sort_in_wave(uint64_t (&v)[W], int lane) {
+  constexpr int kRegBits = W == 4 ? 2 : 1;
 #pragma unroll
-  for (int m = 1; m <= 8; ++m) {
-    const int k = 1 << m;              // k = 256: beyond the indices of a wave, everything ascending
+  for (int m = 1; m <= 6 + kRegBits; ++m) {
+    const int k = 1 << m;              // in the last step beyond the indices of a wave, everything ascending
 #pragma unroll
     for (int b = m - 1; b >= 0; --b) {
-      if (b < 2) {
+      if (b < kRegBits) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < W; ++r) {
           if (r & (1 << b)) continue;
           const int r2 = r | (1 << b);
-          const bool up = ((4 * lane + r) & k) == 0;
+          const bool up = ((W * lane + r) & k) == 0;
           const uint64_t a = v[r], c = v[r2];
           const bool swap = (a > c) == up;
           v[r] = swap ? c : a;
           v[r2] = swap ? a : c;
         }
       } else {
-        const bool up = ((4 * lane) & k) == 0, lower = (lane & (1 << (b - 2))) == 0;
+        const bool up = ((W * lane) & k) == 0, lower = (lane & (1 << (b - kRegBits))) == 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const uint64_t o = __shfl_xor((unsigned long long)v[r], 1 << (b - 2));
+        for (int r = 0; r < W; ++r) {
+          const uint64_t o = __shfl_xor((unsigned long long)v[r], 1 << (b - kRegBits));
           const bool take = (o < v[r]) == (lower == up);
           v[r] = take ? o : v[r];
         }
@@ -161,47 +163,50 @@ __device__ __forceinline__ void sort_256_in_wave(uint64_t (&v)[4], int lane) {
     }
   }
 }
-__device__ __forceinline__ void rank_small_tile(uint64_t (&v)[4], int (&rank)[4], uint64_t* buf, int t) {
+template <int W>
+__device__ __forceinline__ void rank_small_tile(uint64_t (&v)[W], int (&rank)[W], uint64_t* buf, int t) {
+  constexpr int kRun = 64 * W;
   const int lane = t & 63, wave = t >> 6;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) v[r] = buf[tile_slot(4 * t + r)];
-  sort_256_in_wave(v, lane);
+  for (int r = 0; r < W; ++r) v[r] = buf[tile_slot(W * t + r)];
+  sort_in_wave<W>(v, lane);
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    buf[tile_slot(4 * t + r)] = v[r];          // (each wave rewrites the words it read)
-    rank[r] = 4 * lane + r;
+  for (int r = 0; r < W; ++r) {
+    buf[tile_slot(W * t + r)] = v[r];          // (each wave rewrites the words it read)
+    rank[r] = W * lane + r;
   }
   __syncthreads();
-  // Words below v[r] in the other three runs: twelve binary searches side by side.  A position P in a run is kept as
+  // Words below v[r] in the other three runs: 3 W binary searches side by side.  A position P in a run is kept as
   // its slot P + P/16, which a step moves by a constant: every probe is one LDS read at an immediate offset, one
   // compare and one conditional add.
-  int pos[3][4];
+  int pos[3][W];
 #pragma unroll
   for (int j = 0; j < 3; ++j)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) pos[j][r] = tile_slot(((wave + 1 + j) & 3) * 256);
+    for (int r = 0; r < W; ++r) pos[j][r] = tile_slot(((wave + 1 + j) & 3) * kRun);
   auto probe = [&](auto step, auto move) {       // is word P + step - 1 below v[r]?  Then P moves on by `step`
     constexpr int kStep = decltype(step)::value, kMove = decltype(move)::value;
     constexpr int kOff = kStep >= 16 ? kMove - 2 : kStep - 1;
-    uint64_t w[3][4];
+    uint64_t w[3][W];
 #pragma unroll
     for (int j = 0; j < 3; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) w[j][r] = buf[pos[j][r] + kOff];
+      for (int r = 0; r < W; ++r) w[j][r] = buf[pos[j][r] + kOff];
 #pragma unroll
     for (int j = 0; j < 3; ++j)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) pos[j][r] = w[j][r] < v[r] ? pos[j][r] + kMove : pos[j][r];
+      for (int r = 0; r < W; ++r) pos[j][r] = w[j][r] < v[r] ? pos[j][r] + kMove : pos[j][r];
   };
 #define BASA_PROBE(S) probe(std::integral_constant<int, S>{}, std::integral_constant<int, S >= 16 ? S + S / 16 : S>{})
-  BASA_PROBE(128); BASA_PROBE(64); BASA_PROBE(32); BASA_PROBE(16); BASA_PROBE(8); BASA_PROBE(4); BASA_PROBE(2); BASA_PROBE(1);
+  if constexpr (W == 4) BASA_PROBE(128);
+  BASA_PROBE(64); BASA_PROBE(32); BASA_PROBE(16); BASA_PROBE(8); BASA_PROBE(4); BASA_PROBE(2); BASA_PROBE(1);
 #undef BASA_PROBE
-  // P <= 255 now; word P itself decides between P and P + 1
+  // P <= kRun - 1 now; word P itself decides between P and P + 1
 #pragma unroll
   for (int j = 0; j < 3; ++j) {
-    const int run0 = tile_slot(((wave + 1 + j) & 3) * 256);
+    const int run0 = tile_slot(((wave + 1 + j) & 3) * kRun);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < W; ++r) {
       const int slot = pos[j][r] - run0;         // P + P/16
       rank[r] += slot - slot / 17 + (buf[pos[j][r]] < v[r] ? 1 : 0);
     }
@@ -354,12 +359,13 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
   __syncthreads();
 
   // ---- phase 2: the words of the tile into order
-  if constexpr (kTileT == kSmallTile) {
-    uint64_t v[4];
-    int rank[4];
-    rank_small_tile(v, rank, buf, threadIdx.x);
+  if constexpr (kTileT <= kSmallTile) {
+    constexpr int W = kTileT / kSortThreads;
+    uint64_t v[W];
+    int rank[W];
+    rank_small_tile<W>(v, rank, buf, threadIdx.x);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
+    for (int r = 0; r < W; ++r) {
       if (v[r] == ~0ull) continue;             // padding
       if (perm_out) perm_out[hb + start + rank[r]] = idx_of_word(v[r]);
       else out[hb + start + rank[r]] = v[r];
@@ -752,7 +758,11 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + align_up((size_t)words * sizeof(uint64_t), 256));
   const TensorView& xb = x1 ? *x1 : x0;
   const bool bf16 = x0.dtype == BASA_BF16;
-  const int tile = few ? kSmallTile : kTile;
+  // Tiles of 512 where eight of them make a sequence and one ranking pass merges them either way: twice the workgroups read
+  // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
+  // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
+  const int longest = std::max(L0, L1), run = window > 0 ? std::min(window, longest) : longest;
+  const int tile = !few ? kTile : run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
   const SegGeom g0 = geom_of(L0, window, tile), g1 = geom_of(L1, window, tile);
   const bool single0 = g0.tiles_per_seg == 1, single1 = g1.tiles_per_seg == 1;
   {
@@ -763,7 +773,8 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
                      single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs)
 #define BASA_KEYS(BF, D)                          \
   do {                                            \
-    if (few) BASA_KEYS_T(BF, D, kSmallTile);      \
+    if (few && tile == 512) BASA_KEYS_T(BF, D, 512); \
+    else if (few) BASA_KEYS_T(BF, D, kSmallTile); \
     else BASA_KEYS_T(BF, D, kTile);               \
   } while (0)
   if (bf16 && x0.d == 128) BASA_KEYS(true, 128);

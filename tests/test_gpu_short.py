@@ -462,3 +462,17 @@ def test_packed_batch_against_one_call_per_sequence(dtype, d, block, hq, hk, len
         else:                                             # (lists split or not, shapes of workgroup: bf16 rounding of out)
             err = (got.float() - want.float()).norm() / want.float().norm()
             assert err < 4e-3 and (got.float() - want.float()).abs().max() < 2e-2, (a, b, err)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("L,window", [(1025, 0), (1536, 0), (2047, 0), (2049, 0), (3584 + 1, 0), (4096, 0), (4097, 0), (5000, 1152),
+                                      (5000, 4096), (3000, 512)])
+def test_sort_tiles_of_512_tokens(dtype, d, L, window):
+    Q, _, _ = _qkv(3, 1, L, 64, d, dtype, seed=L + d)
+    Q[0, 1] = Q[0, 1, :1]                                 # all keys alike: index order
+    Q[0, 2, ::7] = Q[0, 2, :1]
+    perm, keys = bd.basa_norm_sort(Q, 64, window=window, return_keys=True)
+    for a in range(0, L, window or L):
+        b = min(a + (window or L), L)
+        want = torch.sort(keys[0, :, a:b], dim=-1, stable=True).indices + a
+        assert torch.equal(perm[0, :, a:b].long(), want)
