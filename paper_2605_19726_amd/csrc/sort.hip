@@ -16,7 +16,8 @@ namespace basa {
 namespace {
 
 constexpr int kSortThreads = 256;
-constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB); kSmallTile for calls of few words
+constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB); kSmallTile for calls of fewer words
+constexpr int64_t kMidWords = 1 << 21;
 constexpr int kMergeItems = 8;       // outputs per thread in a merge pass
 constexpr int kMergeChunk = kSortThreads * kMergeItems;   // 2048 outputs per workgroup
 constexpr int kIdxBits = 27;
@@ -418,13 +419,28 @@ __device__ __forceinline__ int merge_path(const uint64_t* A, int na, const uint6
   return lo;
 }
 
+// The same on LDS, word i at slot i + i / kPer: the threads of a wave start kPer outputs apart, and without the pad their
+// reads and writes meet in a few banks (4 x 10^6 words: 18.4 -> 16.9 us a pass).
+template <int kPer>
+__device__ __forceinline__ int padded(int i) { return i + i / kPer; }
+template <int kPer>
+__device__ __forceinline__ int merge_path_lds(const uint64_t* buf, int a0, int na, int b0, int nb, int diag) {
+  int lo = max(0, diag - nb), hi = min(diag, na);
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (buf[padded<kPer>(a0 + mid)] < buf[padded<kPer>(b0 + diag - 1 - mid)]) lo = mid + 1; else hi = mid;
+  }
+  return lo;
+}
+
 __global__ __launch_bounds__(kSortThreads) void merge_pass_kernel(const uint64_t* __restrict__ in,
                                                                   uint64_t* __restrict__ out,
                                                                   int32_t* __restrict__ perm0,
                                                                   int32_t* __restrict__ perm1, int BH0,
                                                                   SegGeom g, int run,
                                                                   int chunks_per_pair, int pairs_per_seg) {
-  __shared__ uint64_t buf[kMergeChunk];
+  constexpr int kPer = kMergeItems;
+  __shared__ uint64_t buf[kMergeChunk + kMergeChunk / kPer];
   __shared__ int split[2];
   const int bh = blockIdx.y;
   int id = blockIdx.x;
@@ -464,41 +480,41 @@ __global__ __launch_bounds__(kSortThreads) void merge_pass_kernel(const uint64_t
 #pragma unroll
     for (int e = 0; e < kMergeItems; ++e) {
       const int i = e * kSortThreads + threadIdx.x;
-      if (i < n) buf[i] = w[e];
+      if (i < n) buf[padded<kPer>(i)] = w[e];
     }
   }
   __syncthreads();
 
   const int d0 = min(threadIdx.x * kMergeItems, n);
   const int d1 = min(d0 + kMergeItems, n);
-  int ia = merge_path(buf, ca, buf + ca, cb, d0);
+  int ia = merge_path_lds<kPer>(buf, 0, ca, ca, cb, d0);
   int ib = d0 - ia;
   // merge kMergeItems outputs into registers, then hand them back through LDS so that the
   // global stores of the workgroup are consecutive
   uint64_t res[kMergeItems];
 #pragma unroll
   for (int e = 0; e < kMergeItems; ++e) {
-    uint64_t va = ia < ca ? buf[ia] : ~0ull;
-    uint64_t vb = ib < cb ? buf[ca + ib] : ~0ull;
+    uint64_t va = ia < ca ? buf[padded<kPer>(ia)] : ~0ull;
+    uint64_t vb = ib < cb ? buf[padded<kPer>(ca + ib)] : ~0ull;
     if (va < vb) { res[e] = va; ++ia; } else { res[e] = vb; ++ib; }
   }
   __syncthreads();                       // everyone is done reading the two runs
 #pragma unroll
   for (int e = 0; e < kMergeItems; ++e)
-    if (d0 + e < d1) buf[d0 + e] = res[e];
+    if (d0 + e < d1) buf[padded<kPer>(d0 + e)] = res[e];
   __syncthreads();
   const int64_t obase = hb + a0 + diag0;
   if (perm_out) {
-    for (int i = threadIdx.x; i < n; i += kSortThreads) perm_out[obase + i] = idx_of_word(buf[i]);
+    for (int i = threadIdx.x; i < n; i += kSortThreads) perm_out[obase + i] = idx_of_word(buf[padded<kPer>(i)]);
   } else {
-    for (int i = threadIdx.x; i < n; i += kSortThreads) out[obase + i] = buf[i];
+    for (int i = threadIdx.x; i < n; i += kSortThreads) out[obase + i] = buf[padded<kPer>(i)];
   }
 }
 
 // ---------------------------------------------------------------------------------
-// The first two merge passes in one: four neighbouring sorted tiles (16384 words, 128 KB) are
-// brought into LDS, merged pairwise and then into one run, and written out once, so the words
-// cross the memory system one time less.  1024 threads, 16 words each: a thread finds the start
+// The first merge passes in one: 16384 words (128 KB), four neighbouring sorted tiles of 4096 or sixteen of 1024
+// (kRun0), are brought into LDS, merged pairwise until they are one run, and written out once, so the words
+// cross the memory system one time less (three times with the small tiles).  1024 threads, 16 words each: a thread finds the start
 // of its 16 consecutive outputs with a merge-path search in LDS, merges them into registers, and
 // the workgroup puts the registers back into LDS between the two levels.  Slots past the end of
 // the segment hold the all-ones word, which sorts last (no packed word has segment field 63).
@@ -506,6 +522,7 @@ __global__ __launch_bounds__(kSortThreads) void merge_pass_kernel(const uint64_t
 constexpr int kQuadThreads = 1024, kQuadItems = 16, kQuadWords = 4 * kTile;
 static_assert(kQuadThreads * kQuadItems == kQuadWords, "one word per thread and item");
 
+template <int kRun0>
 __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_t* __restrict__ in,
                                                                    uint64_t* __restrict__ out,
                                                                    int32_t* __restrict__ perm0,
@@ -553,9 +570,9 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
       request(nxt, v);
     }
     __syncthreads();
-    const int d0 = t * kQuadItems;               // this thread's outputs d0 .. d0 + 15 at both levels
+    const int d0 = t * kQuadItems;               // this thread's outputs d0 .. d0 + 15 at every level
 #pragma unroll
-    for (int run = kTile; run <= 2 * kTile; run *= 2) {
+    for (int run = kRun0; run <= 2 * kTile; run *= 2) {
       const int pb = d0 & ~(2 * run - 1);        // first word of the pair of runs these outputs belong to
       const uint64_t* A = quad + pb;
       const uint64_t* Bv = quad + pb + run;
@@ -707,20 +724,26 @@ static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, co
     }
     return BASA_OK;
   }
-  int run0 = kTile;
-  if (g.W > 2 * kTile) {
+  int run0 = tile;
+  if (g.W > 2 * tile) {
     // more than two tiles per segment: the first two passes in one launch
     const bool last = kQuadWords >= g.W;
     const int quads_per_seg = ceil_div(g.W, kQuadWords);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&merge_quads_kernel),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kQuadWords * 8);
-    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
-    ProfScope prof(K_MERGE, st);
     const int quads_total = BH * g.segs * quads_per_seg;
     // one quad per workgroup while there are compute units for all (64 quads: 21.7 us, two per workgroup 37)
     const int quad_wgs = quads_total <= 512 ? std::min(quads_total, 256) : ceil_div(quads_total, 2);
-    hipLaunchKernelGGL(merge_quads_kernel, dim3(quad_wgs), dim3(kQuadThreads), kQuadWords * 8, st,
-                       src, dst, last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, quads_per_seg, quads_total);
+#define BASA_QUADS(R)                                                                                            \
+  do {                                                                                                           \
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&merge_quads_kernel<R>),              \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kQuadWords * 8);        \
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");                                 \
+    ProfScope prof(K_MERGE, st);                                                                                 \
+    hipLaunchKernelGGL(merge_quads_kernel<R>, dim3(quad_wgs), dim3(kQuadThreads), kQuadWords * 8, st, src, dst,  \
+                       last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, quads_per_seg, quads_total);      \
+  } while (0)
+    if (tile == kTile) BASA_QUADS(kTile);
+    else BASA_QUADS(kSmallTile);
+#undef BASA_QUADS
     BASA_HIP_CHECK_LAUNCH("merge_quads_kernel");
     uint64_t* t = src; src = dst; dst = t;
     run0 = kQuadWords;
@@ -758,11 +781,14 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + align_up((size_t)words * sizeof(uint64_t), 256));
   const TensorView& xb = x1 ? *x1 : x0;
   const bool bf16 = x0.dtype == BASA_BF16;
+  // Up to kMidWords the tiles stay at 1024 and the quads start from those: 4096-token tiles are one or two workgroups to a
+  // compute unit there, whose bitonic networks nothing hides (selection: 32 + 32 heads, L = 8300: 135 -> 124 us; 32 + 8, L =
+  // 32000: 240 -> 215; 32 + 32, L = 16384: 165 -> 162, L = 32768: 326 -> 319, L = 65536: level).
   // Tiles of 512 where eight of them make a sequence and one ranking pass merges them either way: twice the workgroups read
   // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
   // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
   const int longest = std::max(L0, L1), run = window > 0 ? std::min(window, longest) : longest;
-  const int tile = !few ? kTile : run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
+  const int tile = !few ? (words <= kMidWords ? kSmallTile : kTile) : run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
   const SegGeom g0 = geom_of(L0, window, tile), g1 = geom_of(L1, window, tile);
   const bool single0 = g0.tiles_per_seg == 1, single1 = g1.tiles_per_seg == 1;
   {
@@ -774,7 +800,7 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
 #define BASA_KEYS(BF, D)                          \
   do {                                            \
     if (few && tile == 512) BASA_KEYS_T(BF, D, 512); \
-    else if (few) BASA_KEYS_T(BF, D, kSmallTile); \
+    else if (tile == kSmallTile) BASA_KEYS_T(BF, D, kSmallTile); \
     else BASA_KEYS_T(BF, D, kTile);               \
   } while (0)
   if (bf16 && x0.d == 128) BASA_KEYS(true, 128);

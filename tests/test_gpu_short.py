@@ -464,6 +464,19 @@ def test_packed_batch_against_one_call_per_sequence(dtype, d, block, hq, hk, len
             assert err < 4e-3 and (got.float() - want.float()).abs().max() < 2e-2, (a, b, err)
 
 
+@pytest.mark.parametrize("heads,L,window,segments", [(64, 8193, 0, None), (33, 16384 + 1, 0, None), (20, 32768 + 5000, 0, None),
+                                                     (400, 1500, 0, None), (40, 40000, 17408, None), (16, 50000, 0, [0, 3, 20000]),
+                                                     (41, 51150, 0, None)])
+def test_sort_of_middling_calls_from_tiles_of_1024(heads, L, window, segments):
+    Q, _, _ = _qkv(heads, 1, L, 64, 64, torch.bfloat16, seed=L)
+    Q[0, 1] = Q[0, 1, :1]
+    Q[0, 2, ::3] = Q[0, 2, :1]
+    perm, keys = bd.basa_norm_sort(Q, 64, window=window, segments=segments, return_keys=True)
+    bounds = segments + [L] if segments else list(range(0, L, window or L)) + [L]
+    for a, b in zip(bounds[:-1], bounds[1:]):
+        assert torch.equal(perm[0, :, a:b].long(), torch.sort(keys[0, :, a:b], dim=-1, stable=True).indices + a)
+
+
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
 @pytest.mark.parametrize("L,window", [(1025, 0), (1536, 0), (2047, 0), (2049, 0), (3584 + 1, 0), (4096, 0), (4097, 0), (5000, 1152),
                                       (5000, 4096), (3000, 512)])
