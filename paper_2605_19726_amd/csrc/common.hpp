@@ -53,6 +53,12 @@ struct ProfScope {
 
 // ---- stage launchers (each validates nothing: the C entry points do) -------------
 
+// Rows that the selection reads twice within one call, in the key pass and in the pooling pass: up to this many bytes they
+// are loaded through the caches, the second time from the 256 MB that all XCDs share; beyond it by streaming loads, which
+// leave the caches to what is written.  Streaming -> cached, both passes: 256 queries of 32768, 32 heads on 8 (84 MB):
+// 169 -> 165 us; 32 + 32 heads, L = 8300 (136 MB): 129.5 -> 124; 32 + 32 heads, L = 16384 (268 MB): level; L = 32768: 321 -> 351.
+constexpr int64_t kCachedRowBytes = 160 << 20;
+
 // Sort keys + segmented sort.  Writes perm[bh][L]; optional keys_out[bh][L].
 size_t sort_workspace_bytes(int BH, int L);
 constexpr int kMaxSortLen = 1 << 27;      // token indices take 27 bits of a packed sort word
@@ -217,6 +223,16 @@ basa_status launch_attn_many(const SeqJob* seq, int n, int B, const int64_t* out
 
 // ---- device helpers ------------------------------------------------------------
 #if defined(__HIPCC__)
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+// 16 bytes of a row, streaming or through the caches.  (Bit-cast into uint4, not held as the builtin's vector type: the
+// compiler rotates such vectors through several buffers as whole registers, copies that count as uses of loads still in
+// flight, and every batch is then waited for at the top of the loop.)
+template <bool kStream>
+__device__ __forceinline__ uint4 load_row_chunk(const char* row, int chunk) {
+  const u32x4_t* src = reinterpret_cast<const u32x4_t*>(row) + chunk;
+  return __builtin_bit_cast(uint4, kStream ? __builtin_nontemporal_load(src) : *src);
+}
+
 template <class Job, int kWavesPerSimd = 1>
 __global__ __launch_bounds__(256, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
   int i = 0;

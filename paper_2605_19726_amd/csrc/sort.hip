@@ -214,7 +214,7 @@ __device__ __forceinline__ void rank_small_tile(uint64_t (&v)[W], int (&rank)[W]
   }
 }
 
-template <bool kBf16, int kD, int kTileT>
+template <bool kBf16, int kD, int kTileT, bool kStream>
 __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView& x0, const TensorView& x1, int BH0,
                                                uint64_t* __restrict__ out, int32_t* __restrict__ perm0,
                                                int32_t* __restrict__ perm1, float* __restrict__ keys_out, const SegGeom& g0,
@@ -264,13 +264,9 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
 #pragma unroll
     for (int it = 0; it < kIters; ++it) {
       const int loc = live ? min(pass * kRowsPerPass + it * kRowsPerIter + rig, n - 1) : 0;
-      // (streaming loads: every row is read once here; with the hint the pass takes 0.416 instead of
-      //  0.431 ms at 128K, the rows no longer push the sort words being written out of the cache)
-      // (bit-cast into uint4, not held as the builtin's vector type: the compiler rotates such vectors
-      //  through the three buffers as whole registers, copies that count as uses of loads still in
-      //  flight, and every batch is then waited for at the top of the loop)
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      raw[it] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (int64_t)(start + loc) * x.stride_l * kElem) + sub_l));
+      // (streaming loads in large calls: the pass takes 0.416 instead of 0.431 ms at 128K, the rows no longer push
+      //  the sort words being written out of the cache)
+      raw[it] = load_row_chunk<kStream>(base + (int64_t)(start + loc) * x.stride_l * kElem, sub_l);
     }
   };
   auto keys_of_pass = [&](int pass, const uint4 (&cur)[kIters]) {
@@ -382,14 +378,14 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
   }
 }
 
-template <bool kBf16, int kD, int kTileT>
+template <bool kBf16, int kD, int kTileT, bool kStream>
 __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
                                                                       uint64_t* __restrict__ out,
                                                                       int32_t* __restrict__ perm0,
                                                                       int32_t* __restrict__ perm1,
                                                                       float* __restrict__ keys_out, SegGeom g0,
                                                                       SegGeom g1, SegList sl) {
-  norm_tile_sort<kBf16, kD, kTileT>(blockIdx.x, blockIdx.y, x0, x1, BH0, out, perm0, perm1, keys_out, g0, g1, sl);
+  norm_tile_sort<kBf16, kD, kTileT, kStream>(blockIdx.x, blockIdx.y, x0, x1, BH0, out, perm0, perm1, keys_out, g0, g1, sl);
 }
 template <int kD>
 struct SmallSortJob {
@@ -401,7 +397,7 @@ struct SmallSortJob {
     SegList whole;
     whole.n = 0;
     const int by = block / g.tiles_per_seg;
-    norm_tile_sort<true, kD, kSmallTile>(block - by * g.tiles_per_seg, by, q, k, q.heads, out, perm_q, perm_k, nullptr, g, g, whole);
+    norm_tile_sort<true, kD, kSmallTile, false>(block - by * g.tiles_per_seg, by, q, k, q.heads, out, perm_q, perm_k, nullptr, g, g, whole);
   }
 };
 
@@ -788,20 +784,22 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
   // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
   const int longest = std::max(L0, L1), run = window > 0 ? std::min(window, longest) : longest;
-  const int tile = !few ? (words <= kMidWords ? kSmallTile : kTile) : run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
+  const bool cached = words * x0.d * (bf16 ? 2 : 4) <= kCachedRowBytes;
+  const int tile = !few ? (words <= kMidWords ? kSmallTile : kTile) : cached && run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
   const SegGeom g0 = geom_of(L0, window, tile), g1 = geom_of(L1, window, tile);
   const bool single0 = g0.tiles_per_seg == 1, single1 = g1.tiles_per_seg == 1;
   {
   ProfScope prof(K_NORM_TILE_SORT, st);
   const dim3 grid(std::max(g0.segs * g0.tiles_per_seg, x1 ? g1.segs * g1.tiles_per_seg : 0), BH0 + BH1);
-#define BASA_KEYS_T(BF, D, T)                                                                            \
-  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
+#define BASA_KEYS_T(BF, D, T, S)                                                                            \
+  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T, S>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
                      single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs)
-#define BASA_KEYS(BF, D)                          \
-  do {                                            \
-    if (few && tile == 512) BASA_KEYS_T(BF, D, 512); \
-    else if (tile == kSmallTile) BASA_KEYS_T(BF, D, kSmallTile); \
-    else BASA_KEYS_T(BF, D, kTile);               \
+#define BASA_KEYS(BF, D)                                      \
+  do {                                                        \
+    if (tile == kTile) BASA_KEYS_T(BF, D, kTile, true);       \
+    else if (!cached) BASA_KEYS_T(BF, D, kSmallTile, true);   \
+    else if (tile == 512) BASA_KEYS_T(BF, D, 512, false);     \
+    else BASA_KEYS_T(BF, D, kSmallTile, false);               \
   } while (0)
   if (bf16 && x0.d == 128) BASA_KEYS(true, 128);
   else if (bf16 && x0.d == 64) BASA_KEYS(true, 64);

@@ -43,7 +43,7 @@ __device__ __forceinline__ float chunk_elem(const uint4& r, int e) {
 // over the four waves through LDS.  The features of its blocks are collected in LDS and
 // written at the end as 128-byte runs (in the [part][k/8][g][k%8] layout one block's features are
 // 16-byte pieces 16 KB apart, which cost a fifth of the kernel when every block wrote its own).
-template <bool kBf16, int kD, int kB>
+template <bool kBf16, int kD, int kB, bool kStream>
 __device__ __forceinline__ void block_stats(int bx, int by, const StatsJob& j0, const StatsJob& j1, int BH0, float beta, int per_wg) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;       // lanes per row
@@ -98,11 +98,7 @@ __device__ __forceinline__ void block_stats(int bx, int by, const StatsJob& j0, 
     for (int it = 0; it < ITERS; ++it) {
       // a malformed permutation entry falls back to the position itself
       const int row = (unsigned)rows[it] < (unsigned)L ? rows[it] : min(p0 + it * RPI, L - 1);
-      // (streaming loads, as in the key pass: every row is read once)
-      // (bit-cast into uint4, not held as the builtin's vector type: the compiler moves such vectors from
-      //  buffer to buffer as whole registers, copies that count as uses of loads still in flight)
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      raw[it] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (live ? row : 0) * row_bytes) + sub_l));
+      raw[it] = load_row_chunk<kStream>(base + (live ? row : 0) * row_bytes, sub_l);
     }
   };
 
@@ -268,9 +264,9 @@ __device__ __forceinline__ void block_stats(int bx, int by, const StatsJob& j0, 
   }
 }
 
-template <bool kBf16, int kD, int kB>
+template <bool kBf16, int kD, int kB, bool kStream>
 __global__ __launch_bounds__(256) void block_stats_kernel(StatsJob j0, StatsJob j1, int BH0, float beta, int per_wg) {
-  block_stats<kBf16, kD, kB>(blockIdx.x, blockIdx.y, j0, j1, BH0, beta, per_wg);
+  block_stats<kBf16, kD, kB, kStream>(blockIdx.x, blockIdx.y, j0, j1, BH0, beta, per_wg);
 }
 template <int kD, int kB>
 struct FeatureJob {
@@ -279,7 +275,7 @@ struct FeatureJob {
   float beta;
   __device__ __forceinline__ void run(int block) const {
     const int by = block / gx;
-    block_stats<true, kD, kB>(block - by * gx, by, q, k, q.x.heads, beta, per_wg);
+    block_stats<true, kD, kB, false>(block - by * gx, by, q, k, q.x.heads, beta, per_wg);
   }
 };
 
@@ -332,8 +328,12 @@ static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int 
   ProfScope prof(K_STATS, st);
   const bool bf = x.dtype == BASA_BF16;
   const StatsJob& jb = j1 ? *j1 : j0;
-#define BASA_STATS(BF, D, BB) \
-  hipLaunchKernelGGL((block_stats_kernel<BF, D, BB>), grid, dim3(256), 0, st, j0, jb, BH0, beta, per_wg)
+  const bool cached = ((int64_t)BH0 * x.L + (int64_t)BH1 * (j1 ? j1->x.L : 0)) * x.d * (bf ? 2 : 4) <= kCachedRowBytes;
+#define BASA_STATS(BF, D, BB)                                                                                               \
+  do {                                                                                                                      \
+    if (cached) hipLaunchKernelGGL((block_stats_kernel<BF, D, BB, false>), grid, dim3(256), 0, st, j0, jb, BH0, beta, per_wg); \
+    else hipLaunchKernelGGL((block_stats_kernel<BF, D, BB, true>), grid, dim3(256), 0, st, j0, jb, BH0, beta, per_wg);       \
+  } while (0)
   if (bf && x.d == 128 && B == 128) BASA_STATS(true, 128, 128);
   else if (bf && x.d == 128 && B == 64) BASA_STATS(true, 128, 64);
   else if (bf && x.d == 64 && B == 128) BASA_STATS(true, 64, 128);
