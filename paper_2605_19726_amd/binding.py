@@ -138,20 +138,20 @@ def _check(status: int):
                         lib.basa_last_error().decode())
 
 
+_DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def tensor_desc(x: torch.Tensor) -> BasaTensor:
     """Descriptor of a [batch, heads, L, d] tensor (no copy; d must be contiguous)."""
-    if x.dim() != 4:
+    shape, stride = x.shape, x.stride()
+    if len(shape) != 4:
         raise ValueError("expected a [batch, heads, L, d] tensor")
-    if x.stride(3) != 1:
+    if stride[3] != 1:
         raise ValueError("the head dimension must be contiguous")
-    if x.dtype == torch.float32:
-        dt = F32
-    elif x.dtype == torch.bfloat16:
-        dt = BF16
-    else:
+    dt = _DTYPES.get(x.dtype)
+    if dt is None:
         raise ValueError(f"unsupported dtype {x.dtype}")
-    return BasaTensor(x.data_ptr(), dt, x.shape[0], x.shape[1], x.shape[2], x.shape[3],
-                      x.stride(0), x.stride(1), x.stride(2))
+    return BasaTensor(x.data_ptr(), dt, *shape, *stride[:3])
 
 
 def params(block: int, sparsity: float = 0.0, beta: float = 1.0, sort: int = SORT_QK,
@@ -170,11 +170,11 @@ def params(block: int, sparsity: float = 0.0, beta: float = 1.0, sort: int = SOR
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()             # (the prototypes turn it into a pointer)
 
 
 def _stream(x: torch.Tensor):
-    return C.c_void_p(torch.cuda.current_stream(x.device).cuda_stream)
+    return torch.cuda.current_stream(x.device).cuda_stream
 
 
 def _ws(nbytes: int, device) -> torch.Tensor:
@@ -260,10 +260,14 @@ def basa_select(q: torch.Tensor, k: torch.Tensor, block: int, sparsity: float, b
                 want_mass: bool = True, want_scores: bool = False, ws=None, out: Selection = None,
                 mass_target: float = 0.0, min_keep: int = 0, segments=None, budget_total: int = 0,
                 causal: bool = False, select_path: int = 0):
-    lib = load()
-    qd, kd = tensor_desc(q), tensor_desc(k)
     p = params(block, sparsity, beta, sort, window, mass_target, min_keep, segments=segments,
                budget_total=budget_total, causal=causal, select_path=select_path)
+    return _select(load(), q, k, C.byref(tensor_desc(q)), C.byref(tensor_desc(k)), C.byref(p), block, sparsity, want_mask, want_mass,
+                   want_scores, ws, out)
+
+
+def _select(lib, q, k, qd, kd, p, block, sparsity, want_mask, want_mass, want_scores, ws, out):
+    """basa_select on descriptors that the caller has made (byref of them, qd, kd and p)."""
     b, hq, Lq, _ = q.shape
     hk, Lk = k.shape[1], k.shape[2]
     n_q, n_k = n_blocks(Lq, block), n_blocks(Lk, block)
@@ -283,8 +287,8 @@ def basa_select(q: torch.Tensor, k: torch.Tensor, block: int, sparsity: float, b
         s.scores = torch.empty((b, hq, n_q, n_k), dtype=torch.float32, device=dev) if want_scores else None
         s.kappa, s.n_q, s.n_k = kappa, n_q, n_k
     if ws is None:
-        ws = _ws(lib.basa_select_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), dev)
-    _check(lib.basa_select(C.byref(qd), C.byref(kd), C.byref(p), _ptr(s.mask_bits), _ptr(s.row_count),
+        ws = _ws(lib.basa_select_workspace_size(qd, kd, p), dev)
+    _check(lib.basa_select(qd, kd, p, _ptr(s.mask_bits), _ptr(s.row_count),
                            _ptr(s.row_cols), _ptr(s.perm_q), _ptr(s.perm_k), _ptr(s.row_mass),
                            _ptr(s.scores), _ptr(ws), ws.numel(), _stream(q)))
     return s
@@ -302,19 +306,25 @@ def _out_strides(out: torch.Tensor, q: torch.Tensor):
 def basa_sparse_attn(q, k, v, row_count, row_cols, block: int, perm_q=None, perm_k=None,
                      want_lse: bool = False, ws=None, out=None, attn_shape: int = 0, causal: bool = False):
     """out: optional [batch, heads_q, L_q, d] view to write into (strided views are passed as such)."""
-    lib = load()
-    qd, kd, vd = tensor_desc(q), tensor_desc(k), tensor_desc(v)
     p = params(block, attn_shape=attn_shape, causal=causal)
+    return _sparse_attn(load(), q, C.byref(tensor_desc(q)), C.byref(tensor_desc(k)), C.byref(tensor_desc(v)), C.byref(p), row_count,
+                        row_cols, perm_q, perm_k, want_lse, ws, out)
+
+
+def _sparse_attn(lib, q, qd, kd, vd, p, row_count, row_cols, perm_q, perm_k, want_lse, ws, out):
+    """basa_sparse_attn on descriptors that the caller has made (byref of them)."""
     b, hq, Lq, d = q.shape
     if out is None:
         out = torch.empty((b, hq, Lq, d), dtype=q.dtype, device=q.device)
-    ostr = _out_strides(out, q)
+        ostr = (C.c_int64 * 3)(hq * Lq * d, Lq * d, d)
+    else:
+        ostr = _out_strides(out, q)
     lse = torch.empty((b, hq, Lq), dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
-        ws = _ws(lib.basa_attn_best_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
+        ws = _ws(lib.basa_attn_best_workspace_size(qd, kd, p), q.device)
     stride = 0 if row_cols is None else int(row_cols.shape[-1])
-    _check(lib.basa_sparse_attn(C.byref(qd), C.byref(kd), C.byref(vd), _ptr(row_count), _ptr(row_cols),
-                                stride, _ptr(perm_q), _ptr(perm_k), C.byref(p), _ptr(out), ostr, _ptr(lse),
+    _check(lib.basa_sparse_attn(qd, kd, vd, _ptr(row_count), _ptr(row_cols),
+                                stride, _ptr(perm_q), _ptr(perm_k), p, _ptr(out), ostr, _ptr(lse),
                                 _ptr(ws), ws.numel(), _stream(q)))
     return (out, lse) if want_lse else out
 
@@ -339,10 +349,14 @@ def ba_att(q, k, v, block: int = 128, sparsity: float = 0.5, beta: float = 1.0, 
            window: int = 0, mass_target: float = 0.0, min_keep: int = 0, segments=None, out=None,
            causal: bool = False):
     """The whole operator (Alg. 1): basa_select, then basa_sparse_attn on its lists.  Returns (out, Selection)."""
-    sel = basa_select(q, k, block, sparsity, beta, sort, window, want_mask=False, want_mass=False,
-                      mass_target=mass_target, min_keep=min_keep, segments=segments, causal=causal)
-    o = basa_sparse_attn(q, k, v, sel.row_count, sel.row_cols, block, sel.perm_q, sel.perm_k, out=out, causal=causal)
-    return o, sel
+    # one set of descriptors and one workspace for both calls (the second starts when the first is through with it):
+    # one head, L = 1024, is bound by this function
+    lib = load()
+    p = params(block, sparsity, beta, sort, window, mass_target, min_keep, segments=segments, causal=causal)
+    qd, kd, vd, pr = C.byref(tensor_desc(q)), C.byref(tensor_desc(k)), C.byref(tensor_desc(v)), C.byref(p)
+    ws = _ws(max(lib.basa_select_workspace_size(qd, kd, pr), lib.basa_attn_best_workspace_size(qd, kd, pr)), q.device)
+    sel = _select(lib, q, k, qd, kd, pr, block, sparsity, False, False, False, ws, None)
+    return _sparse_attn(lib, q, qd, kd, vd, pr, sel.row_count, sel.row_cols, sel.perm_q, sel.perm_k, False, ws, out), sel
 
 
 def ba_att_varlen(q, k, v, cu_seqlens, block: int = 128, sparsity: float = 0.5, **kw):
