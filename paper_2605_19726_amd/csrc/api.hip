@@ -279,6 +279,7 @@ size_t carve_seq(SeqJob* s, const basa_tensor* q, const basa_tensor* k, int L, c
   s->row_count = reinterpret_cast<int32_t*>(take((size_t)q->heads * N * 4));
   s->row_cols = reinterpret_cast<int32_t*>(take((size_t)q->heads * N * kappa * 4));
   s->tiles = take(attn_many_tile_bytes(k->heads, L, q->d, B));
+  s->redo = reinterpret_cast<int32_t*>(take(attn_many_redo_bytes(q->heads, L, B)));
   return o;
 }
 // What one sequence needs by itself: its lists and permutations, then the workspaces of the two calls.

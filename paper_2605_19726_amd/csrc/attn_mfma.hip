@@ -1201,6 +1201,12 @@ struct AttnJob {
   MfmaArgs a;
   __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kSoloQueries, 32, false, true, false>(a, block); }
 };
+// The 512-query shape: the pass without running maxima, and the one with them for what that gave up on.
+template <int kB, int D, bool kFast>
+struct WideJob {
+  MfmaArgs a;
+  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kWideQueries, 64, false, kFast, false>(a, block); }
+};
 
 size_t sz_kv(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 2, 256); }
 size_t sz_kix(int BHkv, int Nk, int B) { return align_up((size_t)BHkv * (Nk * B / kTileKeys) * kIxStride * 4, 256); }
@@ -1400,35 +1406,66 @@ basa_status attn_many(const SeqJob* seq, int n, const int64_t* out_strides, hipS
     hipLaunchKernelGGL(many_kernel<TileJob<D>>, dim3(jobs.first[n]), dim3(256), 0, st, jobs);
     BASA_HIP_CHECK_LAUNCH("tile_kv");
   }
-  Jobs<AttnJob<kB, D>> jobs;
-  size_t lds = 0;
+  // Workgroups of 128 or of 512 queries (same bits): the time of all of them by the step times of plan_call, over the
+  // compute units, and the last ones to start, which find them unevenly full (the shortest: longest come first).  128 / 512,
+  // whole batch, keep 50 %: 6 sequences of 565 to 7627 tokens, 16 heads: 783 / 756 us; 9 of 45000 in all: 1612 / 1549; kept
+  // at 128: 10 of 6000, 8 heads: 82 / 107; 8 of 40000, 32 heads on 8, keep 25 %: 1628 / 1638; d = 64, where the narrow shape
+  // hides its softmax better, 6 of 40000: 1000 / 1012.
+  double solo_us = 0.0, wide_us = 0.0, tail_us = 0.0;
   for (int i = 0; i < n; ++i) {
     const SeqJob& s = seq[i];
-    MfmaArgs m = {};
-    m.q = s.q; m.Kt = s.tiles; m.Vt = s.tiles + sz_kv(s.k.heads, s.Nk, kB, D);
-    m.row_count = s.row_count; m.row_cols = s.row_cols; m.cols_stride = s.kappa;
-    m.perm_q = s.perm_q;
-    m.out = reinterpret_cast<__bf16*>(s.out);
-    m.out_sb = out_strides[0]; m.out_sh = out_strides[1]; m.out_sl = out_strides[2]; m.heads_q = s.q.heads;
-    m.Nq = s.Nq; m.Nk = s.Nk; m.Lq = s.q.L; m.Lk = s.k.L;
-    m.group = s.q.heads / s.k.heads;
-    m.wgs_per_head = ceil_div(s.Nq * kB, kSoloQueries);
-    m.total_wgs = s.q.heads * m.wgs_per_head;
-    m.scale_log2e = 1.4426950408889634f / sqrtf((float)D);
-    m.splits = 1;
-    jobs.add(AttnJob<kB, D>{m}, m.total_wgs);
-    lds = std::max(lds, lds_bytes<D>(kSoloQueries / 32 * 64, 32, s.Nk, false, true));
+    const double dead = 1.0 - (double)s.kappa / s.Nk, tiles = s.kappa * (kB / kTileKeys) * (1.0 + (kB == 64 ? 0.1 : 0.0) * dead);
+    const double scale = D == 128 ? 1.0 : 0.63, wide_tiles = std::min((double)s.Nk * (kB / kTileKeys), tiles * (1.0 + 0.3 * dead));
+    solo_us += s.q.heads * ceil_div(s.Nq * kB, kSoloQueries) * (tiles * 1.95 * scale + 10.0) / 2.0;
+    tail_us = wide_tiles * 2.95 * scale + 20.0;                              // (ends at the shortest sequence)
+    wide_us += s.q.heads * ceil_div(s.Nq * kB, kWideQueries) * tail_us;
   }
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&many_kernel<AttnJob<kB, D>, 2>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
-  ProfScope prof(K_ATTN, st);
-  hipLaunchKernelGGL((many_kernel<AttnJob<kB, D>, 2>), dim3(jobs.first[n]), dim3(256), lds, st, jobs);
-  BASA_HIP_CHECK_LAUNCH("attn_mfma");
+  const bool wide = D == 128 && wide_us / kCUs + tail_us < solo_us / kCUs;
+  auto launch = [&](auto job, int queries, int qpw, bool fast, int stages) -> basa_status {
+    typedef decltype(job) Job;
+    constexpr bool kSolo = std::is_same<Job, AttnJob<kB, D>>::value;
+    constexpr int kThreads = kSolo ? 256 : 512;
+    constexpr auto kernel = &many_kernel<Job, kSolo ? 2 : 1, kThreads>;
+    Jobs<Job> jobs;
+    size_t lds = 0;
+    for (int i = 0; i < n; ++i) {
+      const SeqJob& s = seq[i];
+      MfmaArgs m = {};
+      m.q = s.q; m.Kt = s.tiles; m.Vt = s.tiles + sz_kv(s.k.heads, s.Nk, kB, D);
+      m.row_count = s.row_count; m.row_cols = s.row_cols; m.cols_stride = s.kappa;
+      m.perm_q = s.perm_q;
+      m.out = reinterpret_cast<__bf16*>(s.out);
+      m.out_sb = out_strides[0]; m.out_sh = out_strides[1]; m.out_sl = out_strides[2]; m.heads_q = s.q.heads;
+      m.Nq = s.Nq; m.Nk = s.Nk; m.Lq = s.q.L; m.Lk = s.k.L;
+      m.group = s.q.heads / s.k.heads;
+      m.wgs_per_head = ceil_div(s.Nq * kB, queries);
+      m.total_wgs = s.q.heads * m.wgs_per_head;
+      m.scale_log2e = 1.4426950408889634f / sqrtf((float)D);
+      m.splits = 1;
+      m.stages = stages;
+      m.redo = kSolo ? nullptr : s.redo;
+      jobs.add(Job{m}, m.total_wgs);
+      lds = std::max(lds, lds_bytes<D>(kThreads, qpw, s.Nk, false, fast, stages));
+    }
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
+    ProfScope prof(K_ATTN, st);
+    hipLaunchKernelGGL(kernel, dim3(jobs.first[n]), dim3(kThreads), lds, st, jobs);
+    BASA_HIP_CHECK_LAUNCH("attn_mfma");
+    return BASA_OK;
+  };
+  if (!wide) return launch(AttnJob<kB, D>{}, kSoloQueries, 32, true, 0);
+  if constexpr (D == 128) {
+    int longest = 0;
+    for (int i = 0; i < n; ++i) longest = std::max(longest, seq[i].Nk);
+    const basa_status e = launch(WideJob<kB, D, true>{}, kWideQueries, 64, true, wide_stages<D>(longest));
+    return e != BASA_OK ? e : launch(WideJob<kB, D, false>{}, kWideQueries, 64, false, 2);
+  }
   return BASA_OK;
 }
 }  // namespace
 
+size_t attn_many_redo_bytes(int heads_q, int Lq, int B) { return (size_t)heads_q * ceil_div(ceil_div(Lq, B) * B, kWideQueries) * 4; }
 size_t attn_many_tile_bytes(int heads_kv, int Lk, int d, int B) { return 2 * sz_kv(heads_kv, ceil_div(Lk, B), B, d); }
 bool attn_many_takes(int Nk, int d) {
   // (the membership words of the key blocks live in the ring while the list is built; two workgroups per compute unit)

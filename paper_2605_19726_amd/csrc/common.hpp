@@ -210,6 +210,7 @@ struct SeqJob {
   float* scores;
   int32_t *perm_q, *perm_k, *row_count, *row_cols;
   char* tiles;               // K tiles, then V^T tiles
+  int32_t* redo;             // one word per 512 queries
   void* out;
 };
 // The stages for up to kMaxJobs sequences of bf16, sorted Q and K.
@@ -218,6 +219,7 @@ basa_status launch_select_features_many(const SeqJob* seq, int n, int B, float b
 basa_status launch_block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st);
 basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st);
 size_t attn_many_tile_bytes(int heads_kv, int Lk, int d, int B);
+size_t attn_many_redo_bytes(int heads_q, int Lq, int B);
 bool attn_many_takes(int Nk, int d);       // the list fits the kernel's LDS
 basa_status launch_attn_many(const SeqJob* seq, int n, int B, const int64_t* out_strides, hipStream_t st);
 
@@ -233,8 +235,8 @@ __device__ __forceinline__ uint4 load_row_chunk(const char* row, int chunk) {
   return __builtin_bit_cast(uint4, kStream ? __builtin_nontemporal_load(src) : *src);
 }
 
-template <class Job, int kWavesPerSimd = 1>
-__global__ __launch_bounds__(256, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
+template <class Job, int kWavesPerSimd = 1, int kThreads = 256>
+__global__ __launch_bounds__(kThreads, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
   int i = 0;
   while (i + 1 < jobs.n && (int)blockIdx.x >= jobs.first[i + 1]) ++i;
   const int b = blockIdx.x - jobs.first[i], per = (jobs.first[i + 1] - jobs.first[i]) >> 3;

@@ -440,6 +440,8 @@ def test_f32_three_part_products_leave_infinities_to_the_fp32_instruction(where,
     (torch.bfloat16, 128, 64, 2, 1, [8192 + 100, 300, 9000], dict(mass_target=0.6, min_keep=2)),     # two ranking passes
     (torch.bfloat16, 64, 128, 8, 2, [130 + 17 * i for i in range(15)], {}),                          # more than one launch holds
     (torch.bfloat16, 128, 128, 32, 32, [200, 9000, 500], {}),                                        # one that goes by itself
+    (torch.bfloat16, 128, 128, 16, 16, [565, 7627, 1977, 3390, 4802, 6215], {}),                     # 512 queries to a workgroup
+    (torch.bfloat16, 128, 64, 16, 4, [700, 7000, 4200, 6400, 5100, 300, 6900], {}),
     (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(causal=True)),                                  # all by themselves
     (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(sort=bd.SORT_K)),
     (torch.float32, 64, 64, 2, 2, [400, 0, 300], {})])
@@ -489,3 +491,19 @@ def test_sort_tiles_of_512_tokens(dtype, d, L, window):
         b = min(a + (window or L), L)
         want = torch.sort(keys[0, :, a:b], dim=-1, stable=True).indices + a
         assert torch.equal(perm[0, :, a:b].long(), want)
+
+
+def test_packed_batch_repeats_what_left_the_safe_range():
+    # 512 queries to a workgroup, scores near +-600 in one sequence: its workgroups go to the pass with running maxima
+    lens, h, d = [565, 7627, 1977, 3390, 4802, 6215], 16, 128
+    cu = np.cumsum([0] + lens).tolist()
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    q, k, v = (torch.randn((cu[-1], h, d), generator=g, device=DEV).to(torch.bfloat16) for _ in range(3))
+    q[cu[3]:cu[4]] *= 50
+    out = bd.ba_att_varlen(q, k, v, cu, 128, 0.5)
+    assert torch.isfinite(out.float()).all()
+    view = lambda x, a, b: x[a:b].permute(1, 0, 2).unsqueeze(0)
+    for a, b in zip(cu[:-1], cu[1:]):
+        want, _ = bd.ba_att(view(q, a, b), view(k, a, b), view(v, a, b), 128, 0.5)
+        assert (view(out, a, b).float() - want.float()).norm() < 4e-3 * want.float().norm()
