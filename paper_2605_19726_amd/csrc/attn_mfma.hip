@@ -771,15 +771,15 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   };
 
   // ---- union of the block lists of this workgroup's query blocks ------------------------
-  // Everything the prologue reads by one address is requested before the first barrier, which waits for it: the entries
-  // of perm_q, and of every list (its threads have one each) the count and the first entries.  One latency instead
-  // of one for perm_q and two for each list in turn.  8 heads, L = 2472, d = 64: 59.8 -> 59.4 us (whole operator); L = 16384,
-  // 32 heads, keep 10 %: 650 -> 647.
-  int q_raw[kNG];
-#pragma unroll
-  for (int r = 0; r < kNG; ++r) {
-    const int pos = min(position(r), a.Lq - 1);
-    q_raw[r] = a.perm_q ? a.perm_q[(int64_t)bhq * a.Lq + pos] : pos;
+  // What the prologue reads by one address is requested before the first barrier, which waits for it: of every list (its
+  // threads have one each) the count and the first entries, and the entry of perm_q.  One latency instead of two for each
+  // list in turn and one for perm_q: 8 heads, L = 2472, d = 64: 59.8 -> 59.2 us (whole operator); 32 heads, L = 16384, keep 10 %:
+  // 648 -> 641.  (With two query groups per wave perm_q waits until the union is there: two entries kept across it change
+  // the compiler's registers for the whole kernel, 2 % of it: dense, L = 16384, 3552 against 3473.)
+  int q_raw = 0;
+  if constexpr (kNG == 1) {
+    const int pos = min(position(0), a.Lq - 1);
+    q_raw = a.perm_q ? a.perm_q[(int64_t)bhq * a.Lq + pos] : pos;
   }
   constexpr int kPerList = kThreads / NQB;
   const int lg = tid / kPerList, l0 = tid % kPerList;
@@ -812,7 +812,11 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
       // the query of sorted position qpos, read from the caller's tensor; positions past L_q
       // (padding of the last block, or a query block that does not exist) read row 0 and are never stored
       const int qpos = position(r);
-      const int qrow = qpos >= a.Lq ? 0 : (unsigned)q_raw[r] < (unsigned)a.Lq ? q_raw[r] : qpos;     // (as perm_at)
+      int qrow = 0;
+      if (qpos < a.Lq) {
+        if constexpr (kNG == 1) qrow = (unsigned)q_raw < (unsigned)a.Lq ? q_raw : qpos;          // (as perm_at)
+        else qrow = perm_at(a.perm_q, (int64_t)bhq * a.Lq, qpos, a.Lq);
+      }
       if (kCausal && qpos < a.Lq) q_lim[r] = qrow + a.causal_off;
       const uint4* qp = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(a.q.ptr) +
                                                        (a.q.head_offset(bhq) + (int64_t)qrow * a.q.stride_l) * 2);
