@@ -331,7 +331,7 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
 
 // ---------------------------------------------------------------------------------------------
 // The same on the bf16 matrix instruction, for calls with enough work: every fp32 number is the exact sum of
-// three bf16 numbers (24 bits as 8 + 8 + 8, by truncation), products of two of those are exact in fp32, and the six part
+// three bf16 numbers (24 bits as 8 + 8 + 8, each part rounded to nearest), products of two of those are exact in fp32, and the six part
 // products above 2^-24 of a product are accumulated in fp32, the small ones first: 6 x 32 cycles per 32 x 32 x 16
 // against 8 x 64 of v_mfma_f32_32x32x2_f32.  The probabilities are cut up in registers, K and V once per call by
 // split_kv_kernel, which leaves the LDS image of every tile (two tiles of 32 keys, K and V^T, three parts: 96 KB at
