@@ -37,6 +37,7 @@
 #include <climits>
 #include <cmath>
 #include <type_traits>
+#include "attn_lds.hpp"
 #include "common.hpp"
 
 namespace basa {
@@ -48,11 +49,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kTileKeys = 64;
-constexpr int kIxStride = kTileKeys + 4;    // causal: ints per tile of the key-index array (64 indices and 4 bounds, key_index_tile)
-#ifndef BASA_ATTN_QR
-#define BASA_ATTN_QR 7
-#endif
 constexpr float kLazyTau = 8.0f;            // log2 of the largest exponentiated score kept
 // Running maximum (log2 units) of a query that has met no score above -inf yet: below every finite one (a float times
 // log2(e) / 8 at most), and itself finite, so that its scores of -inf exponentiate to 0 and rescaling it by itself is 1;
@@ -75,38 +71,6 @@ constexpr int kSharedQueries = 256, kSoloQueries = 128, kWideQueries = 512;
 #ifndef BASA_ATTN_DEFAULT_LISTS
 #define BASA_ATTN_DEFAULT_LISTS 3      // shape taken for block lists the overlap probe does not cover
 #endif
-
-// Sizes that follow from the head dimension D.
-template <int D>
-struct Geo {
-  static constexpr int kRowBytes = D * 2;                    // one row of Q or K
-  static constexpr int kChunksPerRow = kRowBytes / 16;       // 16-byte chunks per row: 16 or 8
-  static constexpr int kTileBytes = kTileKeys * kRowBytes;   // one K tile; a V^T tile (D rows of 128 B) is as large
-  static constexpr int kStageBytes = 2 * kTileBytes;         // K tile then V^T tile
-  static constexpr int kKSteps = D / 16;                     // MFMA k-steps of S^T = K Q^T
-  static constexpr int kDBlocks = D / 32;                    // 32-row blocks of O^T
-  static constexpr int kChunksPerTile = kTileBytes / 1024;   // 1 KB direct-to-LDS loads per K (or V^T) tile
-};
-// Ring stages of a workgroup: one of 512 threads has the compute unit to itself and walks tiles in
-// pairs (two slots of two); two workgroups of 256 threads share a compute unit and walk one by one.
-// With 64 queries per wave: two, or, where the waves walk in spans (wide_spans), up to four (wide_stages).
-// (Not with d = 64 or the causal mask, whose tiles are too short to hide the choice of the next one: 4527 -> 4721 us at
-//  32 heads, L = 32768, d = 64; 2116 -> 2206 causal, L = 16384.  Nor with running maxima, where the compiler then sends the
-//  accumulators through scratch.)
-constexpr bool wide_spans(int d, bool causal, bool fast) { return d == 128 && !causal && fast; }
-constexpr int stages_of(int threads, int qpw) { return threads == 512 && qpw == 32 ? 4 : 2; }
-// k-steps of Q^T a wave of 64 queries keeps in registers (the rest is parked in LDS): all for D = 64
-// (the causal variant of the 64-queries-per-wave kernel carries the two visibility limits and the
-//  key indices of the half-tile on top: one more k-step of Q^T is parked)
-// (the pass without running maxima needs no registers for them and keeps all of Q^T, 117.6-119.1 ms
-//  against 119.7-120.5 with one k-step parked; its causal variant does better with two parked as before:
-//  139-140 ms against 147 with one)
-#ifndef BASA_ATTN_QR_FAST
-#define BASA_ATTN_QR_FAST 8
-#endif
-constexpr int q_reg_steps(int d, int qpw, bool causal = false, bool fast = false) {
-  return (qpw == 64 && d == 128) ? (fast && !causal ? BASA_ATTN_QR_FAST : BASA_ATTN_QR - (causal ? 1 : 0)) : d / 16;
-}
 
 // ---------------------------------------------------------------------------------
 // Gather kernels
@@ -1228,28 +1192,11 @@ bool bitmaps_pay(size_t kv_bytes, double f, double entries) {
 }
 size_t sz_listed(int BHkv, int Nk) { return align_up((size_t)BHkv * kListedParts * ceil_div(Nk, 32) * 4, 256); }
 
-template <int D>
-size_t lds_bytes(int threads, int qpw, int Nk, bool causal = false, bool fast = false, int stages = 0) {
-  const size_t park = (size_t)(threads / 64) * (qpw / 32) * (D / 16 - q_reg_steps(D, qpw, causal, fast)) * 1024;
-  if (stages == 0) stages = stages_of(threads, qpw);
-  const size_t base = (size_t)stages * Geo<D>::kStageBytes + park + (size_t)Nk * 4 + (threads / 64) * 4;
-  return causal ? ((base + 15) & ~(size_t)15) + (size_t)stages * kIxStride * 4 : base;
-}
-// Ring stages of a 512-query workgroup that walks in spans and has its compute unit to itself: four, or what the list
-// leaves room for.
-constexpr size_t kLdsBytes = 160 * 1024;
-template <int D>
-int wide_stages(int Nk) {
-  int s = 4;
-  while (s > 2 && lds_bytes<D>(512, 64, Nk, false, true, s) > kLdsBytes) --s;
-  return s;
-}
-
 template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit>
 basa_status launch_main(MfmaArgs m, int BHq, hipStream_t st) {
   constexpr int kThreads = kWgQueries / kQPW * 64;
-  if (kQPW == 64) m.stages = wide_spans(D, kCausal, kFast) ? wide_stages<D>(m.Nk) : 2;
-  const size_t lds = lds_bytes<D>(kThreads, kQPW, m.Nk, kCausal, kFast, kQPW == 64 ? m.stages : 0);
+  m.stages = launch_stages<D>(kThreads, kQPW, m.Nk, kCausal, kFast);
+  const size_t lds = lds_bytes<D>(kThreads, kQPW, m.Nk, kCausal, kFast, m.stages);
   // while the union list is built, the per-key-block membership flags live in the ring area
   if ((size_t)m.Nk * 4 > (size_t)stages_of(kThreads, kQPW) * Geo<D>::kStageBytes) {
     set_error("attention: %d key blocks exceed the %zu this workgroup shape can list", m.Nk,
@@ -1500,18 +1447,14 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   const int Nq = ceil_div(a.q.L, B), Nk = ceil_div(a.k.L, B);
   if (BHq == 0 || Nq == 0) return BASA_OK;
   const int d = a.q.d;
-  // While a workgroup builds its union list, one membership word per key block lives in the ring
-  // area, whose smallest form is two stages: more key blocks than that cannot be listed.
   {
-    const size_t cap = (d == 128 ? (size_t)2 * Geo<128>::kStageBytes : (size_t)2 * Geo<64>::kStageBytes) / 4;
+    const size_t cap = d == 128 ? kMostBlocks<128> : kMostBlocks<64>;
     if ((size_t)Nk > cap) {
       set_error("attention: %d key blocks per head exceed the %zu this kernel can list (head dimension %d)", Nk, cap, d);
       return BASA_ERR_UNSUPPORTED;
     }
   }
-  // the largest LDS request among the shapes that may be launched
-  const size_t lds = d == 128 ? std::max(lds_bytes<128>(512, 32, Nk), lds_bytes<128>(512, 64, Nk))
-                              : std::max(lds_bytes<64>(512, 32, Nk), lds_bytes<64>(512, 64, Nk));
+  const size_t lds = d == 128 ? most_lds<128>(Nk) : most_lds<64>(Nk);
   {
     int dev = 0, max_lds = 0;
     hipError_t e = hipGetDevice(&dev);
