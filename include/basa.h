@@ -229,7 +229,8 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
  * bf16 tensors: bf16 MFMA with fp32 accumulation and fp32 softmax state (d = 64 or 128);
  * f32 tensors: inputs, accumulation and softmax state in fp32 throughout (given room, see
  * basa_attn_best_workspace_size, the products of large calls are formed on the bf16 matrix instruction from
- * numbers cut into three bf16 parts without loss).
+ * numbers cut into three bf16 parts without loss; queries that meet numbers of 2^86 or more in Q or K, infinities, or sums
+ * of values past 2^80 get theirs on the fp32 one).
  * A key whose score is -inf (and whose V row is finite) carries no weight; a query that has no other gets
  * a zero row and lse = -inf.
  * Repeating a call gives the same bits.  How far lists are split (f32 tensors; bf16 with attn_shape = 0), and which

@@ -1,6 +1,6 @@
 // Block-sparse attention for f32 tensors (Sec. 2; Eq. 1; Alg. 1 step 12): inputs, accumulation and softmax
 // state in fp32 throughout.  Two kernels: on the fp32 matrix instruction (small calls, the causal variant, workspaces
-// without room, and whatever holds infinities), and on the bf16 one with every number as the exact sum of three (below).
+// without room, and whatever holds infinities or huge numbers), and on the bf16 one with every number as the exact sum of three (below).
 //
 // The fp32 instruction.
 // Bound: the matrix cores.  v_mfma_f32_32x32x2_f32 does 4096 flop in 64 cycles (157 TFLOP/s over
@@ -342,9 +342,15 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
 // exponentiates and multiplies V^T P^T, so that the matrix cores have work while the vector unit does, and every LDS
 // buffer is refilled in the half in which nobody reads it.
 //
-// A part of an infinity or a NaN, or of a product that overflows, is NaN, and it reaches the sum or the row of
-// every query it touches: such a workgroup writes one word, and attn_f32_kernel, launched behind this one, computes its rows
-// instead (and returns at once elsewhere).
+// Parts of small numbers would be subnormal bf16 and lose bits (from 2^-110 down), so what the rows are made of is cut up in
+// larger units, V times 2^24 and the probabilities times 2^24: the parts of every fp32 number are exact then, and the rows are
+// scaled back at the end.  (Powers of two: ordinary inputs keep their bits.  V of 1e-36: 2.7e-5 off 64 bits without, 3.4e-7
+// with; rows that only probabilities of 2^-124 make up: 3.4e-4 -> 1.9e-6, as the fp32 instruction; time +0.3 %.)  In a number
+// of K or Q an error of 2^-126 matters only where the other factor is huge, and parts of numbers of 2^86 and more are NaN.
+//
+// A part of a huge number, an infinity or a NaN, or of a product or sum that overflows, is NaN or turns into it, and it reaches
+// the sum or the row of every query it touches: such a workgroup writes one word, and attn_f32_kernel, launched behind this
+// one, computes its rows instead (and returns at once elsewhere).
 //
 // Bound: power and the vector unit (290 instructions a tile next to 96 MFMAs; 1.16 PFLOP/s of part products with every
 // compute unit busy; without the tile loads 6 % faster).  8 heads, L = 4096, d = B = 128, 16 of 32 blocks: 276 us on
@@ -366,6 +372,9 @@ struct SplitGeo {
   static __device__ __forceinline__ int v_chunk(int row, int c) { return c ^ ((row >> 2) & 3); }
 };
 
+constexpr float kUnit = 16777216.f, kPerUnit = 1.f / kUnit;       // 2^24
+constexpr float kHuge = 7.7371252e25f;                            // 2^86
+
 // Two floats into their three parts, packed in pairs (low half: a).
 __device__ __forceinline__ void split_pair(float a, float b, uint32_t& w0, uint32_t& w1, uint32_t& w2) {
   auto pack = [](float x, float y) { return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)x, (__bf16)y}); };
@@ -380,6 +389,12 @@ __device__ __forceinline__ void split8(const floatx4& x, const floatx4& y, uintx
   split_pair(x[2], x[3], a, b, c); w[0][1] = a; w[1][1] = b; w[2][1] = c;
   split_pair(y[0], y[1], a, b, c); w[0][2] = a; w[1][2] = b; w[2][2] = c;
   split_pair(y[2], y[3], a, b, c); w[0][3] = a; w[1][3] = b; w[2][3] = c;
+}
+// Numbers of Q or K whose products the parts of small factors would not be exact enough for become NaN.
+__device__ __forceinline__ floatx4 not_huge(floatx4 x) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = fabsf(x[e]) < kHuge ? x[e] : __uint_as_float(0x7fc00000u);
+  return x;
 }
 
 // One 32-key tile of a KV head, blockIdx.z = 0 its K rows, 1 its V rows transposed; rows past the end are zeros.  Bound
@@ -417,7 +432,8 @@ __global__ __launch_bounds__(256) void split_kv_kernel(TensorView k, TensorView 
     const int id = it * 256 + t, r = id / CPR, c = id % CPR;
     if (tile * kTK + r >= x.L) lo[it] = hi[it] = floatx4{0.f, 0.f, 0.f, 0.f};
     uintx4 w[3];
-    split8(lo[it], hi[it], w);
+    if (is_v) split8(lo[it] * kUnit, hi[it] * kUnit, w);
+    else split8(not_huge(lo[it]), not_huge(hi[it]), w);
 #pragma unroll
     for (int part = 0; part < 3; ++part) {
       if (!is_v) *reinterpret_cast<uintx4*>(dst + part * G::kPart + r * G::kRow + 16 * G::k_chunk(r, c)) = w[part];
@@ -540,7 +556,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(SplitArgs p) {
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       uintx4 w[3];
-      split8(qp[4 * s + 2 * h], qp[4 * s + 2 * h + 1], w);
+      split8(not_huge(qp[4 * s + 2 * h]), not_huge(qp[4 * s + 2 * h + 1]), w);
 #pragma unroll
       for (int part = 0; part < 3; ++part) qf[part][s] = __builtin_bit_cast(bf16x8, w[part]);
     }
@@ -604,7 +620,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(SplitArgs p) {
         const float m_use = m_run == -INFINITY ? 0.f : m_run;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, -m_use));
+          sc[r] = __builtin_amdgcn_exp2f(fmaf(sc[r], c, -m_use)) * kUnit;
           l_run += sc[r];
         }
       }
@@ -702,6 +718,7 @@ __global__ __launch_bounds__(512) void attn_split_kernel(SplitArgs p) {
     for (int r = 0; r < 16; ++r) bad = fmaf(o[db][r], 0.f, bad);
   if (pos < Lq && bad != 0.f) p.redo[wgi] = 1;
   if (pos >= Lq) return;
+  l_tot *= kPerUnit;
   // register 4 r4 + e of block db: dimension 32 db + 8 r4 + 4 h + e
   if (p.splits > 1) {
     const int64_t prow = ((int64_t)split * (p.total / (p.splits * p.wgs_per_head)) + bhq) * Lq + pos;
@@ -711,11 +728,11 @@ __global__ __launch_bounds__(512) void attn_split_kernel(SplitArgs p) {
 #pragma unroll
       for (int r4 = 0; r4 < 4; ++r4)
         *reinterpret_cast<floatx4*>(po + 32 * db + 8 * r4 + 4 * h) =
-            floatx4{o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]};
+            floatx4{o[db][4 * r4], o[db][4 * r4 + 1], o[db][4 * r4 + 2], o[db][4 * r4 + 3]} * (kPerUnit * kPerUnit);
     if (h == 0) p.part_ml[prow] = make_float2(m_run, l_tot);
     return;
   }
-  const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;            // a row without any key: zeros
+  const float inv_l = l_tot > 0.f ? 1.0f / l_tot * (kPerUnit * kPerUnit) : 0.f;            // a row without any key: zeros
   float* op = reinterpret_cast<float*>(a.out) + a.out_offset(bhq, qrow);
 #pragma unroll
   for (int db = 0; db < DB; ++db)

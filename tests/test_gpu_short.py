@@ -434,6 +434,47 @@ def test_f32_three_part_products_leave_infinities_to_the_fp32_instruction(where,
         assert torch.allclose(a[fin], b[fin], rtol=1e-4, atol=1e-4)
 
 
+@pytest.mark.parametrize("where", ["v", "v_subnormal", "v_large", "k", "q", "probabilities"])
+@pytest.mark.parametrize("d,block", [(64, 64), (128, 128)])
+def test_f32_three_part_products_keep_the_bits_of_small_numbers(where, d, block):
+    # Parts of bf16 end at 2^-133: numbers whose 24 bits reach below that, as values, as keys or queries against large
+    # partners, and as probabilities that alone make up a column of the result.  Bound: that of the products above, an error
+    # of the fp32 instruction's by half again.
+    L, h = 4096, 8
+    Q, K, V = _qkv(h, h, L, L, d, torch.float32, seed=11)
+    cols = slice(None)
+    if where == "v":
+        V *= 1e-36
+    elif where == "v_subnormal":
+        V *= 1e-20
+        V *= 1e-19
+    elif where == "v_large":
+        V *= 1e30
+    elif where == "k":
+        Q, K = Q * 1e36, K * 1e-36
+    elif where == "q":
+        Q, K = Q * 1e-36, K * 1e36
+    else:                                                 # key 0 takes all but 2^-124 of every row; key j alone fills column j
+        Q *= 0.01
+        Q[..., 0] = 32.0
+        K[..., 0] = 0.0
+        K[..., 0, :] = 0.0
+        K[..., 0, 0] = 85.8 * d ** 0.5 / 32
+        V.zero_()
+        V[..., torch.arange(1, d), torch.arange(1, d)] = 1.0
+        V[..., 0, 0] = 1.0
+        cols = slice(1, None)
+    out = _three_part_call(Q, K, V, None, None, block, None, None)
+    plain = bd.basa_sparse_attn(Q, K, V, None, None, block, ws=torch.empty(256, dtype=torch.uint8, device=DEV))
+    for i in (0, 5):
+        q, k, v = (np64(x[0, i]) for x in (Q, K, V))
+        s = q @ k.T / d ** 0.5
+        w = np.exp(s - s.max(1, keepdims=True))
+        ref = ((w / w.sum(1, keepdims=True)) @ v)[:, cols]
+        err = lambda x: np.linalg.norm(np64(x[0, i])[:, cols] - ref) / np.linalg.norm(ref)
+        assert err(out) <= max(1.5 * err(plain), 3e-7), (err(out), err(plain))
+
+
 @pytest.mark.parametrize("dtype,d,block,hq,hk,lens,kw", [
     (torch.bfloat16, 128, 128, 4, 2, [1024, 1, 1025, 129, 64, 2050], {}),
     (torch.bfloat16, 64, 64, 4, 4, [63, 4096 + 1, 700, 65], dict(beta=0.0)),
