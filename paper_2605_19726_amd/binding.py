@@ -311,8 +311,8 @@ def basa_sparse_attn(q, k, v, row_count, row_cols, block: int, perm_q=None, perm
                         row_cols, perm_q, perm_k, want_lse, ws, out)
 
 
-def _sparse_attn(lib, q, qd, kd, vd, p, row_count, row_cols, perm_q, perm_k, want_lse, ws, out):
-    """basa_sparse_attn on descriptors that the caller has made (byref of them)."""
+def _sparse_attn(lib, q, qd, kd, vd, p, row_count, row_cols, perm_q, perm_k, want_lse, ws, out, ws_bytes=None):
+    """basa_sparse_attn on descriptors that the caller has made (byref of them); ws_bytes: how much of ws it gets."""
     b, hq, Lq, d = q.shape
     if out is None:
         out = torch.empty((b, hq, Lq, d), dtype=q.dtype, device=q.device)
@@ -325,7 +325,7 @@ def _sparse_attn(lib, q, qd, kd, vd, p, row_count, row_cols, perm_q, perm_k, wan
     stride = 0 if row_cols is None else int(row_cols.shape[-1])
     _check(lib.basa_sparse_attn(qd, kd, vd, _ptr(row_count), _ptr(row_cols),
                                 stride, _ptr(perm_q), _ptr(perm_k), p, _ptr(out), ostr, _ptr(lse),
-                                _ptr(ws), ws.numel(), _stream(q)))
+                                _ptr(ws), ws.numel() if ws_bytes is None else ws_bytes, _stream(q)))
     return (out, lse) if want_lse else out
 
 
@@ -350,13 +350,15 @@ def ba_att(q, k, v, block: int = 128, sparsity: float = 0.5, beta: float = 1.0, 
            causal: bool = False):
     """The whole operator (Alg. 1): basa_select, then basa_sparse_attn on its lists.  Returns (out, Selection)."""
     # one set of descriptors and one workspace for both calls (the second starts when the first is through with it):
-    # one head, L = 1024, is bound by this function
+    # one head, L = 1024, is bound by this function.  The second gets no more of it than it would ask for: how far lists are
+    # split goes by its size, and the bits are those of the two calls.
     lib = load()
     p = params(block, sparsity, beta, sort, window, mass_target, min_keep, segments=segments, causal=causal)
     qd, kd, vd, pr = C.byref(tensor_desc(q)), C.byref(tensor_desc(k)), C.byref(tensor_desc(v)), C.byref(p)
-    ws = _ws(max(lib.basa_select_workspace_size(qd, kd, pr), lib.basa_attn_best_workspace_size(qd, kd, pr)), q.device)
+    attn_bytes = lib.basa_attn_best_workspace_size(qd, kd, pr)
+    ws = _ws(max(lib.basa_select_workspace_size(qd, kd, pr), attn_bytes), q.device)
     sel = _select(lib, q, k, qd, kd, pr, block, sparsity, False, False, False, ws, None)
-    return _sparse_attn(lib, q, qd, kd, vd, pr, sel.row_count, sel.row_cols, sel.perm_q, sel.perm_k, False, ws, out), sel
+    return _sparse_attn(lib, q, qd, kd, vd, pr, sel.row_count, sel.row_cols, sel.perm_q, sel.perm_k, False, ws, out, attn_bytes), sel
 
 
 def ba_att_varlen(q, k, v, cu_seqlens, block: int = 128, sparsity: float = 0.5, **kw):

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from oracle import basa_oracle as o
 from paper_2605_19726_amd import binding as bd
@@ -223,3 +224,38 @@ def test_packed_batch_validation(lib):
     assert call(None, 4096, 1 << 40) == 1 and call(8, 4096, 1 << 40) == 1          # no output, misaligned output
     assert call(4096, None, 0) != 0 and b"workspace" in lib.basa_last_error()
     assert call(4096, 4096, 1000) != 0 and b"workspace" in lib.basa_last_error()
+
+
+class _Recorder:
+    """The library with the two calls of the operator replaced by ones that keep their workspace size."""
+
+    def __init__(self, lib):
+        self._lib, self.select, self.attn = lib, [], []
+
+    def __getattr__(self, name):
+        return getattr(self._lib, name)
+
+    def basa_select(self, *args):
+        self.select.append(args[-2])
+        return 0
+
+    def basa_sparse_attn(self, *args):
+        self.attn.append(args[-2])
+        return 0
+
+
+@pytest.mark.parametrize("dtype,hq,hk,Lq,Lk,d,block,causal", [
+    (torch.float32, 8, 8, 9000, 256, 64, 128, True), (torch.float32, 32, 8, 2472, 2472, 128, 64, True),
+    (torch.float32, 32, 32, 9000, 256, 64, 128, False), (torch.bfloat16, 4, 4, 9000, 256, 64, 64, False),
+    (torch.bfloat16, 16, 4, 20000, 300, 64, 128, False), (torch.float32, 1, 1, 1024, 1024, 64, 64, False)])
+def test_the_operator_gives_attention_the_workspace_of_the_two_calls(lib, monkeypatch, dtype, hq, hk, Lq, Lk, d, block, causal):
+    # how far lists are split goes by its size: with more room the bits would differ
+    rec = _Recorder(lib)
+    monkeypatch.setattr(bd, "_lib", rec)
+    monkeypatch.setattr(bd, "_stream", lambda x: None)
+    q, k, v = (torch.empty((1, h, L, d), dtype=dtype) for h, L in ((hq, Lq), (hk, Lk), (hk, Lk)))
+    _, sel = bd.ba_att(q, k, v, block, 0.5, causal=causal)
+    bd.basa_sparse_attn(q, k, v, sel.row_count, sel.row_cols, block, sel.perm_q, sel.perm_k, causal=causal)
+    p = bd.params(block, 0.5, causal=causal)
+    assert rec.select[0] >= bd.select_workspace_size(q, k, p)
+    assert rec.attn[0] == rec.attn[1], (rec.select, rec.attn)
