@@ -142,7 +142,8 @@ size_t basa_select_workspace_size(const basa_tensor* q, const basa_tensor* k, co
  * all, which costs time and never the call. */
 size_t basa_attn_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
 /* The same, and for f32 tensors the room with which large calls run fastest: K and V cut into bf16 parts (12
- * bytes per element of K, 1.5 times K and V) and the partial results that go with them. */
+ * bytes per element of K, 1.5 times K and V) and the partial results that go with them, if lists of some length would
+ * use it. */
 size_t basa_attn_best_workspace_size(const basa_tensor* q, const basa_tensor* k, const basa_params* p);
 /* Bytes of workspace basa_norm_sort needs for x. */
 size_t basa_sort_workspace_size(const basa_tensor* x, const basa_params* p);

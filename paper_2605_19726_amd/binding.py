@@ -181,6 +181,19 @@ def _ws(nbytes: int, device) -> torch.Tensor:
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
+def _attn_ws(lib, qd, kd, p, device, least: int = 0):
+    """(workspace, bytes of it for attention): the room with which large calls run fastest, or, where the device does not have
+    it, what basa_attn_workspace_size asks for; at least `least` bytes."""
+    nbytes = lib.basa_attn_best_workspace_size(qd, kd, p)
+    try:
+        return _ws(max(nbytes, least), device), nbytes
+    except torch.OutOfMemoryError:
+        fewer = lib.basa_attn_workspace_size(qd, kd, p)
+        if max(fewer, least) >= max(nbytes, least):
+            raise
+        return _ws(max(fewer, least), device), fewer
+
+
 def basa_version() -> str:
     return load().basa_version().decode()
 
@@ -321,7 +334,7 @@ def _sparse_attn(lib, q, qd, kd, vd, p, row_count, row_cols, perm_q, perm_k, wan
         ostr = _out_strides(out, q)
     lse = torch.empty((b, hq, Lq), dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
-        ws = _ws(lib.basa_attn_best_workspace_size(qd, kd, p), q.device)
+        ws, _ = _attn_ws(lib, qd, kd, p, q.device)
     stride = 0 if row_cols is None else int(row_cols.shape[-1])
     _check(lib.basa_sparse_attn(qd, kd, vd, _ptr(row_count), _ptr(row_cols),
                                 stride, _ptr(perm_q), _ptr(perm_k), p, _ptr(out), ostr, _ptr(lse),
@@ -339,7 +352,7 @@ def basa_dense_attn(q, k, v, block: int = 128, want_lse: bool = False, ws=None, 
     ostr = _out_strides(out, q)
     lse = torch.empty((b, hq, Lq), dtype=torch.float32, device=q.device) if want_lse else None
     if ws is None:
-        ws = _ws(lib.basa_attn_best_workspace_size(C.byref(qd), C.byref(kd), C.byref(p)), q.device)
+        ws, _ = _attn_ws(lib, C.byref(qd), C.byref(kd), C.byref(p), q.device)
     _check(lib.basa_dense_attn(C.byref(qd), C.byref(kd), C.byref(vd), C.byref(p), _ptr(out), ostr, _ptr(lse),
                                _ptr(ws), ws.numel(), _stream(q)))
     return (out, lse) if want_lse else out
@@ -355,8 +368,7 @@ def ba_att(q, k, v, block: int = 128, sparsity: float = 0.5, beta: float = 1.0, 
     lib = load()
     p = params(block, sparsity, beta, sort, window, mass_target, min_keep, segments=segments, causal=causal)
     qd, kd, vd, pr = C.byref(tensor_desc(q)), C.byref(tensor_desc(k)), C.byref(tensor_desc(v)), C.byref(p)
-    attn_bytes = lib.basa_attn_best_workspace_size(qd, kd, pr)
-    ws = _ws(max(lib.basa_select_workspace_size(qd, kd, pr), attn_bytes), q.device)
+    ws, attn_bytes = _attn_ws(lib, qd, kd, pr, q.device, lib.basa_select_workspace_size(qd, kd, pr))
     sel = _select(lib, q, k, qd, kd, pr, block, sparsity, False, False, False, ws, None)
     return _sparse_attn(lib, q, qd, kd, vd, pr, sel.row_count, sel.row_cols, sel.perm_q, sel.perm_k, False, ws, out, attn_bytes), sel
 
@@ -376,9 +388,13 @@ def ba_att_varlen(q, k, v, cu_seqlens, block: int = 128, sparsity: float = 0.5, 
         qv, ov = view(q, 0, T), view(out, 0, T)
         qd, kd, vd, p = tensor_desc(qv), tensor_desc(view(k, 0, T)), tensor_desc(view(v, 0, T)), _varlen_params(block, sparsity, **kw)
         args = C.byref(qd), C.byref(kd), C.byref(vd), (C.c_int32 * len(cu))(*cu), len(cu) - 1, C.byref(p)
-        ws = _ws(lib.basa_varlen_workspace_size(*args), q.device)
-        _check(lib.basa_varlen_attn(*args, _ptr(out), _out_strides(ov, qv), _ptr(ws), ws.numel(), _stream(q)))
-        return out
+        try:
+            ws = _ws(lib.basa_varlen_workspace_size(*args), q.device)
+        except torch.OutOfMemoryError:
+            ws = None                          # (one sequence after the other needs less)
+        if ws is not None:
+            _check(lib.basa_varlen_attn(*args, _ptr(out), _out_strides(ov, qv), _ptr(ws), ws.numel(), _stream(q)))
+            return out
     for a, b in seqs:
         ba_att(view(q, a, b), view(k, a, b), view(v, a, b), block, sparsity, out=view(out, a, b), **kw)
     return out

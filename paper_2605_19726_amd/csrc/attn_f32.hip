@@ -805,6 +805,30 @@ constexpr F32Shape shape_of(int d, int B) { return F32Shape{B / 32, d == 64 && B
 constexpr double kSplitStepUs[2] = {3.2, 5.4};
 size_t split_img_bytes(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 12, 256); }
 size_t split_redo_bytes(int BHq, int Nq, int B) { return align_up((size_t)BHq * ceil_div(Nq * B, 128) * 4, 256); }
+constexpr size_t split_ring_bytes(int d) { return (size_t)2 * 12 * kTK * d; }      // a K and a V^T tile for each of two slices
+size_t split_lds_bytes(int Nk, int d) { return split_ring_bytes(d) + (size_t)Nk * 4 + 8 * 4; }
+
+// The three-part kernel or the other, for lists of `tiles` tiles and a workspace: the three-part one where its estimate,
+// with the launches that go with it (9 us; 20 bytes per element of K and V at 5 TB/s), is the smaller one.  Attention call, fp32
+// instruction -> this: 8 heads, L = 4096, keep 50 %, d = B = 128: 278 -> 182 us, d = 64: 149 -> 104; L = 6000: 645 -> 405 (two
+// parts per list); 4 heads, L = 3001, keep 25 %: 69 -> 52; against, 2 heads, L = 1024: 30 / 31, L = 2048, B = 64: 40 / 47, d = B =
+// 64, L = 2000: 24 / 30 at its best number of parts.
+struct F32Plan { bool three_part; int splits; };
+F32Plan plan_f32(int BHq, int BHkv, int Lq, int Lk, int d, int B, int tiles, bool causal, size_t ws_bytes) {
+  const F32Shape f = shape_of(d, B);
+  const int Nq = ceil_div(Lq, B), Nk = ceil_div(Lk, B);
+  const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
+  const Splits plain = plan_splits((int64_t)BHq * ceil_div(Nq * B, 32 * f.QG), tiles, f.KS, f32_step_us(d, f.QG * f.KS), row_bytes,
+                                   ws_bytes);
+  const size_t img = split_img_bytes(BHkv, Nk, B, d), redo = split_redo_bytes(BHq, Nq, B);
+  // (the membership words of the key blocks live in the ring while the list is built)
+  if (causal || ws_bytes < img + redo || split_lds_bytes(Nk, d) > kLdsBytes || (size_t)Nk * 4 > split_ring_bytes(d))
+    return F32Plan{false, plain.splits};
+  const Splits three = plan_splits((int64_t)BHq * ceil_div(Nq * B, 128), B == 64 ? tiles + tiles / 12 : tiles, 2,
+                                   kSplitStepUs[d == 128], row_bytes, ws_bytes - img - redo);
+  const bool take = three.us + 9.0 + (double)img * 20.0 / 12.0 / 5e6 < plain.us;
+  return F32Plan{take, take ? three.splits : plain.splits};
+}
 
 template <int D, int B>
 basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
@@ -812,24 +836,18 @@ basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
   p.wgs_per_head = ceil_div(p.Nq * B, 32 * QG);
   const int work = BHq * p.wgs_per_head;                  // workgroups without splitting, one to a compute unit
   const int tiles = (p.a.row_cols ? std::min(p.a.cols_stride, p.Nk) : p.Nk) * (B / kTK);
-  const size_t row_bytes = (size_t)BHq * p.a.q.L * (D * 4 + 8);
-  Splits plan = plan_splits(work, tiles, KS, f32_step_us(D, QG * KS), row_bytes, p.a.ws_bytes);
-  // The three-part kernel where its estimate, with the launches that go with it (9 us; 20 bytes per element of K and V at 5
-  // TB/s), is the smaller one.  Attention call, fp32 instruction -> this: 8 heads, L = 4096, keep 50 %, d = B = 128: 278 -> 182 us,
-  // d = 64: 149 -> 104; L = 6000: 645 -> 405 (two parts per list); 4 heads, L = 3001, keep 25 %: 69 -> 52; against, 2 heads,
-  // L = 1024: 30 / 31, L = 2048, B = 64: 40 / 47, d = B = 64, L = 2000: 24 / 30 at its best number of parts.
   const int BHkv = p.a.k.batch * p.a.k.heads;
-  const size_t img = split_img_bytes(BHkv, p.Nk, B, D), redo = split_redo_bytes(BHq, p.Nq, B);
-  const size_t lds_s = 2 * SplitGeo<D>::kTile + (size_t)p.Nk * 4 + 8 * 4;
-  const bool fits = !p.a.causal && p.a.ws_bytes >= img + redo && lds_s <= kLdsBytes && (size_t)p.Nk * 4 <= 2 * SplitGeo<D>::kTile;
-  SplitArgs s;
-  s.wgs_per_head = ceil_div(p.Nq * B, 128);
-  const int work_s = BHq * s.wgs_per_head;
-  const Splits plan_s = plan_splits(work_s, B == 64 ? tiles + tiles / 12 : tiles, 2, kSplitStepUs[D == 128], row_bytes,
-                                    fits ? p.a.ws_bytes - img - redo : 0);
-  if (fits && plan_s.us + 9.0 + (double)img * 20.0 / 12.0 / 5e6 < plan.us) {
+  const F32Plan plan = plan_f32(BHq, BHkv, p.a.q.L, p.a.k.L, D, B, tiles, p.a.causal != 0, p.a.ws_bytes);
+  int splits = plan.splits;
+  if (plan.three_part) {
+    const size_t img = split_img_bytes(BHkv, p.Nk, B, D), redo = split_redo_bytes(BHq, p.Nq, B);
+    const size_t lds_s = split_lds_bytes(p.Nk, D);
+    static_assert(split_ring_bytes(D) == 2 * SplitGeo<D>::kTile, "a K and a V^T tile for each of two slices");
+    SplitArgs s;
+    s.wgs_per_head = ceil_div(p.Nq * B, 128);
+    const int work_s = BHq * s.wgs_per_head;
     s.a = p.a; s.Nq = p.Nq; s.Nk = p.Nk; s.group = p.group; s.scale_log2e = p.scale_log2e; s.lse_k = p.lse_k;
-    s.splits = plan_s.splits;
+    s.splits = plan.splits;
     s.total = work_s * s.splits;
     char* ws = reinterpret_cast<char*>(p.a.ws);
     s.img = ws;
@@ -856,9 +874,8 @@ basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
     }
     p.redo = s.redo;
     p.redo_wgs = s.wgs_per_head;
-    plan.splits = 1;                         // whole lists
+    splits = 1;                              // whole lists
   }
-  const int splits = plan.splits;
   p.splits = splits;
   p.total = work * splits;
   if (splits > 1) {
@@ -921,17 +938,23 @@ size_t attn_f32_workspace_bytes(int BHq, int Lq, int Lk, int d, int B) {
   }
   return align_up(splits * row_bytes, 256);
 }
-// With the tiles of the three-part kernel as well, and its partial rows.
+// With the tiles of the three-part kernel as well, and as many partial rows as lists of any length would have there, if lists
+// of some length go to that kernel at all.
 size_t attn_f32_best_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, int B, bool causal) {
   const size_t base = attn_f32_workspace_bytes(BHq, Lq, Lk, d, B);
   if (causal) return base;
-  const size_t img = split_img_bytes(BHkv, ceil_div(Lk, B), B, d) + split_redo_bytes(BHq, ceil_div(Lq, B), B);
-  const int64_t work = (int64_t)BHq * ceil_div(Lq, 128);
+  const int Nk = ceil_div(Lk, B);
+  const size_t img = split_img_bytes(BHkv, Nk, B, d) + split_redo_bytes(BHq, ceil_div(Lq, B), B);
   const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
-  size_t splits = 0;                                      // the most that lists of any length would be cut into
-  for (int n = 1; n <= ceil_div(Lk, B); n += std::max(1, n / 8))
+  const int64_t work = (int64_t)BHq * ceil_div(Lq, 128);
+  size_t splits = 0;            // (without what plan_f32 adds for two lists of 64: four heads, L = 3001, every block: 124 us, with
+                                //  the parts that it would then take 128)
+  for (int n = 1; n <= Nk; n += std::max(1, n / 8))
     splits = std::max<size_t>(splits, plan_splits(work, n * (B / kTK), 2, kSplitStepUs[d == 128], row_bytes, SIZE_MAX).splits);
-  return std::max(base, img + (splits > 1 ? align_up(splits * row_bytes, 256) : 0));
+  const size_t best = std::max(base, img + (splits > 1 ? align_up(splits * row_bytes, 256) : 0));
+  for (int n = Nk; n >= 1; n -= std::max(1, n / 9))
+    if (plan_f32(BHq, BHkv, Lq, Lk, d, B, n * (B / kTK), false, best).three_part) return best;
+  return base;
 }
 
 basa_status launch_attn_f32(const AttnArgs& a, hipStream_t st) {

@@ -259,3 +259,44 @@ def test_the_operator_gives_attention_the_workspace_of_the_two_calls(lib, monkey
     p = bd.params(block, 0.5, causal=causal)
     assert rec.select[0] >= bd.select_workspace_size(q, k, p)
     assert rec.attn[0] == rec.attn[1], (rec.select, rec.attn)
+
+
+@pytest.mark.parametrize("hq,hk,Lq,Lk,d,block,more", [
+    (1, 1, 1024, 1024, 64, 64, False), (32, 32, 256, 32768, 128, 128, False), (8, 8, 256, 20000, 64, 64, False),
+    (8, 8, 1, 8000, 128, 128, False), (8, 8, 4096, 4096, 128, 128, True), (8, 8, 4096, 4096, 64, 64, True),
+    (8, 8, 6000, 6000, 128, 128, True), (32, 32, 131072, 131072, 128, 128, True)])
+def test_the_larger_f32_workspace_is_asked_for_where_some_list_length_uses_it(lib, hq, hk, Lq, Lk, d, block, more):
+    q, k, p = fake_tensor(heads=hq, L=Lq, d=d, dtype=bd.F32), fake_tensor(heads=hk, L=Lk, d=d, dtype=bd.F32), bd.params(block)
+    base, best = (f(C.byref(q), C.byref(k), C.byref(p)) for f in (lib.basa_attn_workspace_size, lib.basa_attn_best_workspace_size))
+    assert best > base if more else best == base, (base, best)
+    if more:
+        assert best >= 12 * hk * Lk * d                   # K and V in three bf16 parts each
+
+
+def test_attention_takes_the_smaller_workspace_where_the_larger_one_is_not_to_be_had(lib, monkeypatch):
+    rec = _Recorder(lib)
+    rec.basa_varlen_attn = lambda *args: pytest.fail("its workspace was refused")
+    monkeypatch.setattr(bd, "_lib", rec)
+    monkeypatch.setattr(bd, "_stream", lambda x: None)
+    q, k, v = (torch.empty((1, 8, 4096, 128)) for _ in range(3))
+    qd, p = bd.tensor_desc(q), bd.params(128, 0.5)
+    base, best = (f(C.byref(qd), C.byref(qd), C.byref(p)) for f in (lib.basa_attn_workspace_size, lib.basa_attn_best_workspace_size))
+    select, real = bd.select_workspace_size(q, k, p), bd._ws
+
+    def short_of_memory(nbytes, device):
+        if nbytes >= best:
+            raise torch.OutOfMemoryError("no room")
+        return real(nbytes, device)
+
+    assert base < best and select < best
+    monkeypatch.setattr(bd, "_ws", short_of_memory)
+    bd.ba_att(q, k, v, 128, 0.5)
+    assert rec.select == [max(select, base)] and rec.attn == [base]
+    bd.basa_sparse_attn(q, k, v, None, None, 128)
+    assert rec.attn == [base, base]
+    packed = q[0].transpose(0, 1)
+    bd.ba_att_varlen(packed, packed, packed, [0, 4000, 4096], 128, 0.5)
+    assert len(rec.attn) == 4                             # one sequence after the other, each with what it needs
+    with pytest.raises(torch.OutOfMemoryError):           # bf16: there is no smaller one
+        best = 1 << 20
+        bd.ba_att(*(x.bfloat16() for x in (q, k, v)), 128, 0.5)
