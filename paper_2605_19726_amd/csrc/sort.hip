@@ -11,13 +11,12 @@
 #include <algorithm>
 #include <type_traits>
 #include "common.hpp"
+#include "sort_plan.hpp"
 
 namespace basa {
 namespace {
 
 constexpr int kSortThreads = 256;
-constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB); kSmallTile for calls of fewer words
-constexpr int64_t kMidWords = 1 << 21;
 constexpr int kMergeItems = 8;       // outputs per thread in a merge pass
 constexpr int kMergeChunk = kSortThreads * kMergeItems;   // 2048 outputs per workgroup
 constexpr int kIdxBits = 27;
@@ -132,7 +131,6 @@ __device__ __forceinline__ void sort_tile_in_lds(uint64_t* buf, int t) {
 // Wave w sorts words 64 W w .. 64 W (w + 1) - 1 by itself (index = W lane + register: the low index bits in registers, six
 // exchanged between lanes, no barrier); the four runs are then ranked against each other in LDS.  Returns in
 // rank[r] the place of v[r] in the tile (padding words, all alike, get places past the last real word).
-constexpr int kSmallTile = 1024;
 template <int W>
 __device__ __forceinline__ void sort_in_wave(uint64_t (&v)[W], int lane) {
   constexpr int kRegBits = W == 4 ? 2 : 1;
@@ -764,11 +762,10 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   const int BH0 = x0.batch * x0.heads, BH1 = x1 ? x1->batch * x1->heads : 0, L0 = x0.L, L1 = x1 ? x1->L : x0.L;
   const int64_t words0 = (int64_t)BH0 * L0, words = words0 + (int64_t)BH1 * L1;
   if (words == 0) return BASA_OK;
-  // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
-  // merges over the device; many words: tiles of 4096 and the merging kernels, which move each word once or
-  // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
-  // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
-  const bool few = words <= (1 << 19);
+  const bool cached = words * x0.d * (x0.dtype == BASA_BF16 ? 2 : 4) <= kCachedRowBytes;
+  const SortPlan plan = plan_sort(BH0, L0, BH1, L1, window, cached);
+  const bool few = plan.few;
+  const int tile = plan.tile;
   if (x1 && ((L0 != L1 && !few) || BH0 + BH1 > 65535)) {       // (65535: the grid's second dimension)
     const basa_status s = norm_sort_impl(x0, nullptr, window, segs, perm0, nullptr, keys_out, ws, st);
     return s != BASA_OK ? s : norm_sort_impl(*x1, nullptr, window, segs, perm1, nullptr, nullptr, ws, st);
@@ -777,15 +774,6 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + align_up((size_t)words * sizeof(uint64_t), 256));
   const TensorView& xb = x1 ? *x1 : x0;
   const bool bf16 = x0.dtype == BASA_BF16;
-  // Up to kMidWords the tiles stay at 1024 and the quads start from those: 4096-token tiles are one or two workgroups to a
-  // compute unit there, whose bitonic networks nothing hides (selection: 32 + 32 heads, L = 8300: 135 -> 124 us; 32 + 8, L =
-  // 32000: 240 -> 215; 32 + 32, L = 16384: 165 -> 162, L = 32768: 326 -> 319, L = 65536: level).
-  // Tiles of 512 where eight of them make a sequence and one ranking pass merges them either way: twice the workgroups read
-  // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
-  // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
-  const int longest = std::max(L0, L1), run = window > 0 ? std::min(window, longest) : longest;
-  const bool cached = words * x0.d * (bf16 ? 2 : 4) <= kCachedRowBytes;
-  const int tile = !few ? (words <= kMidWords ? kSmallTile : kTile) : cached && run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile;
   const SegGeom g0 = geom_of(L0, window, tile), g1 = geom_of(L1, window, tile);
   const bool single0 = g0.tiles_per_seg == 1, single1 = g1.tiles_per_seg == 1;
   {

@@ -1,0 +1,47 @@
+// Which tiles a norm sort starts from, by its sizes.  Plain C++ without the device: the rule is checked on the host.
+#pragma once
+#include <algorithm>
+#include <cstdint>
+
+namespace basa {
+
+constexpr int kTile = 4096;          // elements sorted per workgroup in LDS (32 KB); kSmallTile for calls of fewer words
+constexpr int kSmallTile = 1024;
+constexpr int64_t kMidWords = 1 << 21;
+
+struct SortPlan {
+  bool few;                          // runs are ranked against each other over the device instead of merged
+  int tile;
+};
+
+// One tensor, or two (rows1 > 0) through the same launches: rows of L tokens, sorted in runs of `window` tokens if that is not
+// 0.  cached: the rows are loaded through the caches.
+inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int window, bool cached) {
+  const int64_t words = rows0 * L0 + rows1 * L1;
+  const int longest = rows1 > 0 ? std::max(L0, L1) : L0, run = window > 0 ? std::min(window, longest) : longest;
+  // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
+  // merges over the device; many words: tiles of 4096 and the merging kernels, which move each word once or
+  // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
+  // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
+  if (words <= (1 << 19)) {
+    // Tiles of 512 where eight of them make a sequence and one ranking pass merges them either way: twice the workgroups read
+    // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
+    // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
+    return {true, cached && run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile};
+  }
+  // Up to kMidWords the tiles stay at 1024 and the quads (16384 words in LDS) start from those: 4096-token tiles are one or two
+  // workgroups to a compute unit there, whose bitonic networks nothing hides.  Whole sort, d = 128, large tiles -> small: 1.0
+  // million words in runs of 1024: 94 -> 54 us, 1500: 88 -> 75, 2048: 80 -> 63, 8300: 114 -> 102, 12000: 118 -> 100, 16384: 94 -> 90,
+  // 32768: 108 -> 105; 2.1 million words: 1500: 143 -> 131, 8300 and more: level.
+  if (words > kMidWords) return {false, kTile};
+  if (run <= 2 * kSmallTile || run > 2 * kTile) return {false, kSmallTile};
+  // Shorter runs leave much of a quad empty.  One large tile is the whole run: 3000 tokens 87 us against 143 and 129 / 266 (1.0 and
+  // 2.1 million words), 4096: 74 / 99 and 118 / 183.  Or two and a merge pass: small tiles only where the large ones are more than
+  // one to a compute unit, the quads are not, and the small ones at most five (large / small, 128 runs, then 132: 5000: 80 / 84,
+  // 102 / 84, 8192: 85 / 96, 108 / 104; 256 runs of 5000, then 260: 113 / 109, 144 / 150; 200 of 7000, then 230: 115 / 116, 120 / 129).
+  if (run <= kTile) return {false, kTile};
+  const int64_t runs = rows0 * ((L0 + run - 1) / run) + (rows1 > 0 ? rows1 * ((L1 + run - 1) / run) : 0);
+  return {false, runs > 128 && runs <= 256 && words <= 5 * 256 * kSmallTile ? kSmallTile : kTile};
+}
+
+}  // namespace basa
