@@ -762,8 +762,9 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   const int BH0 = x0.batch * x0.heads, BH1 = x1 ? x1->batch * x1->heads : 0, L0 = x0.L, L1 = x1 ? x1->L : x0.L;
   const int64_t words0 = (int64_t)BH0 * L0, words = words0 + (int64_t)BH1 * L1;
   if (words == 0) return BASA_OK;
-  const bool cached = words * x0.d * (x0.dtype == BASA_BF16 ? 2 : 4) <= kCachedRowBytes;
-  const SortPlan plan = plan_sort(BH0, L0, BH1, L1, window, cached);
+  const int token_bytes = x0.d * (x0.dtype == BASA_BF16 ? 2 : 4);
+  const bool cached = words * token_bytes <= kCachedRowBytes;
+  const SortPlan plan = plan_sort(BH0, L0, BH1, L1, window, token_bytes, cached);
   const bool few = plan.few;
   const int tile = plan.tile;
   if (x1 && ((L0 != L1 && !few) || BH0 + BH1 > 65535)) {       // (65535: the grid's second dimension)

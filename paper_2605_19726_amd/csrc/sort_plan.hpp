@@ -14,9 +14,9 @@ struct SortPlan {
   int tile;
 };
 
-// One tensor, or two (rows1 > 0) through the same launches: rows of L tokens, sorted in runs of `window` tokens if that is not
-// 0.  cached: the rows are loaded through the caches.
-inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int window, bool cached) {
+// One tensor, or two (rows1 > 0) through the same launches: rows of L tokens of `token_bytes` each, sorted in runs of `window`
+// tokens if that is not 0.  cached: the tokens are loaded through the caches.
+inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int window, int token_bytes, bool cached) {
   const int64_t words = rows0 * L0 + rows1 * L1;
   const int longest = rows1 > 0 ? std::max(L0, L1) : L0, run = window > 0 ? std::min(window, longest) : longest;
   // Few words: tiles of 1024 tokens, four times as many workgroups to read the rows, and ranking, which spreads the
@@ -24,10 +24,20 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
   // twice.  The line, rows x tokens (d = 128, tile pass + merges, small against large tiles): 16 x 8192 31 against 75 us,
   // 64 x 8192 61 / 78, 32 x 16384 69 / 88, 16 x 32768 93 / 102; 64 x 16384 116 / 96, 8 x 100000 196 / 135.
   if (words <= (1 << 19)) {
-    // Tiles of 512 where eight of them make a sequence and one ranking pass merges them either way: twice the workgroups read
-    // the rows and each sorts half as much.  1024 -> 512, whole operator: 8 heads, L = 2472, d = 64: 65.0 -> 60.4 us; fp32, 8
-    // heads, L = 4096: 232.8 -> 227.2; with more runs level (256 queries of 32768: 172.7 / 173.7).
-    return {true, cached && run > kSmallTile && run <= 8 * 512 ? 512 : kSmallTile};
+    if (!cached || run <= kSmallTile || run > 8 * 512) return {true, kSmallTile};
+    // Tiles of 512 where eight of them make a run and one ranking pass merges them either way: twice the workgroups read the
+    // rows and each sorts half as much, as long as there are no more of them than the compute units take at once.  Sort, tiles of
+    // 1024 -> 512, 256 bytes a token, runs of 4096: 16 rows 21.6 -> 17.8 us, 32: 22.4 -> 19.1, kept at 1024: 64: 27.7 / 32.1, 128:
+    // 44 / 52; longer where the second tile of 1024 is hardly used (runs of 1500: 20 rows 21.8 -> 16.8, 349: 48.4 -> 47.6) and with
+    // 128 bytes a token (runs of 4096, 64 rows: 21.3 / 21.4, 98: 31.4 / 33.6).
+    const bool short_tokens = token_bytes <= 128;
+    if (run <= 3 * 512 || (short_tokens && run <= 4 * 512)) return {true, 512};
+    auto tiles = [&](int64_t rows, int L) {
+      const int w = std::min(run, L);
+      return rows * ((L + w - 1) / w) * ((w + 511) / 512);
+    };
+    const int64_t count = tiles(rows0, L0) + (rows1 > 0 ? tiles(rows1, L1) : 0);
+    return {true, count <= (short_tokens ? 640 : run <= 4 * 512 ? 400 : 256) ? 512 : kSmallTile};
   }
   // Up to kMidWords the tiles stay at 1024 and the quads (16384 words in LDS) start from those: 4096-token tiles are one or two
   // workgroups to a compute unit there, whose bitonic networks nothing hides.  Whole sort, d = 128, large tiles -> small: 1.0

@@ -511,7 +511,7 @@ def test_packed_batch_against_one_call_per_sequence(dtype, d, block, hq, hk, len
                                                      (400, 1500, 0, None), (40, 40000, 17408, None), (16, 50000, 0, [0, 3, 20000]),
                                                      (41, 51150, 0, None), (130, 4097, 0, None), (132, 5000, 0, None), (300, 2049, 0, None),
                                                      (131, 4096, 0, None), (18, 40000, 5120, None), (64, 9000, 8192, None),
-                                                     (70, 9000, 2048, None)])
+                                                     (70, 9000, 2048, None), (128, 4096, 0, None), (101, 4001, 0, None)])
 def test_sort_of_middling_calls_from_tiles_of_1024(heads, L, window, segments):
     Q, _, _ = _qkv(heads, 1, L, 64, 64, torch.bfloat16, seed=L)
     Q[0, 1] = Q[0, 1, :1]

@@ -11,9 +11,9 @@ PROGRAM = r"""
 #include <cstdlib>
 #include "sort_plan.hpp"
 int main(int argc, char** argv) {
-  long v[6];
-  for (int i = 0; i < 6; ++i) v[i] = std::atol(argv[i + 1]);
-  const basa::SortPlan p = basa::plan_sort(v[0], (int)v[1], v[2], (int)v[3], (int)v[4], v[5] != 0);
+  long v[7];
+  for (int i = 0; i < 7; ++i) v[i] = std::atol(argv[i + 1]);
+  const basa::SortPlan p = basa::plan_sort(v[0], (int)v[1], v[2], (int)v[3], (int)v[4], (int)v[5], v[6] != 0);
   std::printf("%d %d\n", p.few ? 1 : 0, p.tile);
 }
 """
@@ -25,8 +25,8 @@ def plan(tmp_path_factory):
     (d / "p.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-std=c++17", "-I", build.CSRC, str(d / "p.cpp"), "-o", str(d / "p")], check=True)
 
-    def call(rows0, L0, rows1=0, L1=0, window=0, cached=True):
-        args = [str(int(x)) for x in (rows0, L0, rows1, L1, window, cached)]
+    def call(rows0, L0, rows1=0, L1=0, window=0, token_bytes=256, cached=True):
+        args = [str(int(x)) for x in (rows0, L0, rows1, L1, window, token_bytes, cached)]
         few, tile = subprocess.run([str(d / "p"), *args], check=True, capture_output=True, text=True).stdout.split()
         return few == "1", int(tile)
     return call
@@ -44,3 +44,17 @@ def test_middling_calls_start_from_the_tiles_that_fill_a_quad(plan, rows, L, win
     assert plan(rows, L, window=window, cached=False) == (False, tile)
     if rows % 2 == 0:
         assert plan(rows // 2, L, rows // 2, L, window=window) == (False, tile)
+
+
+# one head's rows are read by twice as many workgroups, which has to leave them at one to a compute unit (more where the second
+# large tile of a run is hardly used, and with short tokens)
+@pytest.mark.parametrize("rows,L,window,token_bytes,tile", [
+    (1, 1024, 0, 256, 1024), (1, 1025, 0, 256, 512), (1, 4096, 0, 256, 512), (1, 4097, 0, 256, 1024), (32, 4096, 0, 256, 512),
+    (33, 4096, 0, 256, 1024), (128, 4096, 0, 256, 1024), (42, 3000, 0, 256, 512), (44, 3000, 0, 512, 1024), (341, 1536, 0, 256, 512),
+    (100, 2048, 0, 256, 512), (101, 2048, 0, 256, 1024), (80, 4096, 0, 128, 512), (81, 4096, 0, 128, 1024), (256, 2048, 0, 128, 512),
+    (32, 8192, 4096, 256, 1024), (16, 8192, 4096, 256, 512), (8, 60000, 1024, 256, 1024)])
+def test_calls_of_few_words_start_from_512_tokens_while_the_device_has_room(plan, rows, L, window, token_bytes, tile):
+    assert plan(rows, L, window=window, token_bytes=token_bytes) == (True, tile)
+    assert plan(rows, L, window=window, token_bytes=token_bytes, cached=False) == (True, 1024)
+    if rows > 1:
+        assert plan(rows - 1, L, 1, L, window=window, token_bytes=token_bytes) == (True, tile)
