@@ -389,7 +389,8 @@ basa_status basa_norm_sort(const basa_tensor* x, const basa_params* p, int32_t* 
   SegList segs;
   if ((s = seg_list(p, x->L, &segs)) != BASA_OK) return s;
   if (x->L > kMaxSortLen) { set_error("sequences beyond %d tokens not supported", kMaxSortLen); return BASA_ERR_UNSUPPORTED; }
-  return launch_norm_sort(view_of(*x), p->window, segs, perm, keys_out, ws, reinterpret_cast<hipStream_t>(stream));
+  const TensorView xv = view_of(*x);
+  return launch_norm_sort(xv, p->window, segs, perm, keys_out, ws, rows_cached(xv), reinterpret_cast<hipStream_t>(stream));
 }
 
 basa_status basa_downsample(const basa_tensor* x, const int32_t* perm, const basa_params* p, float* mean,
@@ -440,23 +441,24 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
   void* featk = base + w.featk_off;
   float* sc = scores ? scores : reinterpret_cast<float*>(base + w.scores_off);
   const TensorView qv = view_of(*q), kv = view_of(*k);
+  const bool cached = rows_cached(qv, &kv);
 
   const bool sort_q = p->sort == BASA_SORT_Q || p->sort == BASA_SORT_QK;
   const bool sort_k = p->sort == BASA_SORT_K || p->sort == BASA_SORT_QK;
   if (sort_q && sort_k) {                   // Q and K share the launches
-    s = launch_norm_sort2(qv, kv, p->window, segs, perm_q, perm_k, sort_ws, st);
+    s = launch_norm_sort2(qv, kv, p->window, segs, perm_q, perm_k, sort_ws, cached, st);
     if (s != BASA_OK) return s;
   } else {
-    if (sort_q) s = launch_norm_sort(qv, p->window, segs, perm_q, nullptr, sort_ws, st);
+    if (sort_q) s = launch_norm_sort(qv, p->window, segs, perm_q, nullptr, sort_ws, cached, st);
     else s = launch_iota_perm(perm_q, BHq, q->L, st);
     if (s != BASA_OK) return s;
-    if (sort_k) s = launch_norm_sort(kv, p->window, segs, perm_k, nullptr, sort_ws, st);
+    if (sort_k) s = launch_norm_sort(kv, p->window, segs, perm_k, nullptr, sort_ws, cached, st);
     else s = launch_iota_perm(perm_k, BHk, k->L, st);
     if (s != BASA_OK) return s;
   }
   const int32_t* pq = sort_q ? perm_q : nullptr;
   const int32_t* pk = sort_k ? perm_k : nullptr;
-  if ((s = launch_select_features(qv, pq, featq, kv, pk, featk, B, p->beta, st)) != BASA_OK) return s;
+  if ((s = launch_select_features(qv, pq, featq, kv, pk, featk, B, p->beta, cached, st)) != BASA_OK) return s;
   const int kdim = (p->beta == 0.f) ? q->d : 3 * q->d;
   // fixed count per row, nobody asks for the map, no second pass over it: the map stays on chip
   const bool fusable = !scores && !p->causal && p->mass_target == 0.0 && p->budget_total == 0 &&
@@ -661,7 +663,8 @@ basa_status basa_norm_sort_static(const basa_tensor* x, const basa_params* p, in
   if ((s = static_scratch_of_current_device(&ptr)) != BASA_OK) return s;
   // nothing in the scratch has to start at zero: the tile pass writes every word the merges read
   t_prof_off = true;                       // the timing aid creates events; this call creates nothing
-  s = launch_norm_sort(view_of(*x), p->window, segs, perm, keys_out, ptr, reinterpret_cast<hipStream_t>(stream));
+  const TensorView xv = view_of(*x);
+  s = launch_norm_sort(xv, p->window, segs, perm, keys_out, ptr, rows_cached(xv), reinterpret_cast<hipStream_t>(stream));
   t_prof_off = false;
   return s;
 }

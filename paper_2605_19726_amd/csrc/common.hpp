@@ -55,9 +55,16 @@ struct ProfScope {
 
 // Rows that the selection reads twice within one call, in the key pass and in the pooling pass: up to this many bytes they
 // are loaded through the caches, the second time from the 256 MB that all XCDs share; beyond it by streaming loads, which
-// leave the caches to what is written.  Streaming -> cached, both passes: 256 queries of 32768, 32 heads on 8 (84 MB):
-// 169 -> 165 us; 32 + 32 heads, L = 8300 (136 MB): 129.5 -> 124; 32 + 32 heads, L = 16384 (268 MB): level; L = 32768: 321 -> 351.
+// leave the caches to what is written.  Selection, streaming -> cached, on other inputs every time and on inputs just written:
+// 256 queries of 32768, 32 heads on 8 (69 MB): 110 -> 102 and 103 -> 98 us; 16 + 16 heads, L = 4096: 61 -> 58 and 57 -> 53; 32 +
+// 32 heads, L = 8300 (136 MB): 142 -> 140 and 140 -> 136; 16 + 16 heads, L = 16384: level.  (Right after 512 MB of other writes,
+// which leave the caches full of lines to be written back: 106 -> 111, 140 -> 161.)  Both ways at 268 MB level, at 537 MB 321 / 351.
+// (One answer for all passes of a call, also where they take Q and K one after the other.)
 constexpr int64_t kCachedRowBytes = 160 << 20;
+inline bool rows_cached(const TensorView& x, const TensorView* y = nullptr) {
+  const int64_t rows = (int64_t)x.batch * x.heads * x.L + (y ? (int64_t)y->batch * y->heads * y->L : 0);
+  return rows * x.d * (x.dtype == BASA_BF16 ? 2 : 4) <= kCachedRowBytes;
+}
 
 // Sort keys + segmented sort.  Writes perm[bh][L]; optional keys_out[bh][L].
 size_t sort_workspace_bytes(int BH, int L);
@@ -69,10 +76,10 @@ struct SegList {
   int bound[BASA_MAX_SEGMENTS + 1];
 };
 basa_status launch_norm_sort(const TensorView& x, int window, const SegList& segs, int32_t* perm, float* keys_out,
-                             void* ws, hipStream_t st);
+                             void* ws, bool cached, hipStream_t st);
 // Two tensors of identical d and dtype through the same launches (ws sized for both at the larger L).
 basa_status launch_norm_sort2(const TensorView& q, const TensorView& k, int window, const SegList& segs, int32_t* perm_q,
-                              int32_t* perm_k, void* ws, hipStream_t st);
+                              int32_t* perm_k, void* ws, bool cached, hipStream_t st);
 basa_status launch_iota_perm(int32_t* perm, int BH, int L, hipStream_t st);
 
 // Block statistics.  Any of the outputs may be null.
@@ -92,7 +99,7 @@ basa_status launch_block_stats(const TensorView& x, const int32_t* perm, int B, 
 // Selection features of Q (query side) and K (key side), identical d / dtype, in one launch.
 basa_status launch_select_features(const TensorView& q, const int32_t* perm_q, void* feat_q,
                                    const TensorView& k, const int32_t* perm_k, void* feat_k, int B,
-                                   float beta, hipStream_t st);
+                                   float beta, bool cached, hipStream_t st);
 
 // Block logits: scores[BHq][Nq][Nk] = featQ . featK over `kdim` features.
 inline size_t feat_bytes_per_block(int d) { return (size_t)3 * 3 * d * 2; }

@@ -758,18 +758,16 @@ static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, co
 
 // Sort one tensor (x1 == nullptr) or two tensors of identical d and dtype in the same launches.
 static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, int window, const SegList& segs, int32_t* perm0,
-                                  int32_t* perm1, float* keys_out, void* ws, hipStream_t st) {
+                                  int32_t* perm1, float* keys_out, void* ws, bool cached, hipStream_t st) {
   const int BH0 = x0.batch * x0.heads, BH1 = x1 ? x1->batch * x1->heads : 0, L0 = x0.L, L1 = x1 ? x1->L : x0.L;
   const int64_t words0 = (int64_t)BH0 * L0, words = words0 + (int64_t)BH1 * L1;
   if (words == 0) return BASA_OK;
-  const int token_bytes = x0.d * (x0.dtype == BASA_BF16 ? 2 : 4);
-  const bool cached = words * token_bytes <= kCachedRowBytes;
-  const SortPlan plan = plan_sort(BH0, L0, BH1, L1, window, token_bytes, cached);
+  const SortPlan plan = plan_sort(BH0, L0, BH1, L1, window, x0.d * (x0.dtype == BASA_BF16 ? 2 : 4), cached);
   const bool few = plan.few;
   const int tile = plan.tile;
   if (x1 && ((L0 != L1 && !few) || BH0 + BH1 > 65535)) {       // (65535: the grid's second dimension)
-    const basa_status s = norm_sort_impl(x0, nullptr, window, segs, perm0, nullptr, keys_out, ws, st);
-    return s != BASA_OK ? s : norm_sort_impl(*x1, nullptr, window, segs, perm1, nullptr, nullptr, ws, st);
+    const basa_status s = norm_sort_impl(x0, nullptr, window, segs, perm0, nullptr, keys_out, ws, cached, st);
+    return s != BASA_OK ? s : norm_sort_impl(*x1, nullptr, window, segs, perm1, nullptr, nullptr, ws, cached, st);
   }
   uint64_t* buf0 = reinterpret_cast<uint64_t*>(ws);
   uint64_t* buf1 = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(ws) + align_up((size_t)words * sizeof(uint64_t), 256));
@@ -785,7 +783,8 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
                      single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs)
 #define BASA_KEYS(BF, D)                                      \
   do {                                                        \
-    if (tile == kTile) BASA_KEYS_T(BF, D, kTile, true);       \
+    if (tile == kTile && !cached) BASA_KEYS_T(BF, D, kTile, true); \
+    else if (tile == kTile) BASA_KEYS_T(BF, D, kTile, false); \
     else if (!cached) BASA_KEYS_T(BF, D, kSmallTile, true);   \
     else if (tile == 512) BASA_KEYS_T(BF, D, 512, false);     \
     else BASA_KEYS_T(BF, D, kSmallTile, false);               \
@@ -856,13 +855,13 @@ basa_status launch_norm_sort_many(const SeqJob* seq, int n, hipStream_t st) {
 }
 
 basa_status launch_norm_sort(const TensorView& x, int window, const SegList& segs, int32_t* perm, float* keys_out,
-                             void* ws, hipStream_t st) {
-  return norm_sort_impl(x, nullptr, window, segs, perm, nullptr, keys_out, ws, st);
+                             void* ws, bool cached, hipStream_t st) {
+  return norm_sort_impl(x, nullptr, window, segs, perm, nullptr, keys_out, ws, cached, st);
 }
 
 basa_status launch_norm_sort2(const TensorView& q, const TensorView& k, int window, const SegList& segs,
-                              int32_t* perm_q, int32_t* perm_k, void* ws, hipStream_t st) {
-  return norm_sort_impl(q, &k, window, segs, perm_q, perm_k, nullptr, ws, st);
+                              int32_t* perm_q, int32_t* perm_k, void* ws, bool cached, hipStream_t st) {
+  return norm_sort_impl(q, &k, window, segs, perm_q, perm_k, nullptr, ws, cached, st);
 }
 
 }  // namespace basa

@@ -312,14 +312,14 @@ basa_status launch_select_features_many(const SeqJob* seq, int n, int B, float b
   return B == 128 ? features_many<64, 128>(seq, n, beta, st) : features_many<64, 64>(seq, n, beta, st);
 }
 
-static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int B, float beta, hipStream_t st) {
+static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int B, float beta, bool cached, hipStream_t st) {
   const TensorView& x = j0.x;
   const int BH0 = x.batch * x.heads;
   const int BH1 = j1 ? j1->x.batch * j1->x.heads : 0;
   if (BH0 + BH1 == 0 || x.L == 0) return BASA_OK;
   if (j1 && BH0 + BH1 > 65535) {               // the grid's second dimension
-    const basa_status s = block_stats_impl(j0, nullptr, B, beta, st);
-    return s != BASA_OK ? s : block_stats_impl(*j1, nullptr, B, beta, st);
+    const basa_status s = block_stats_impl(j0, nullptr, B, beta, cached, st);
+    return s != BASA_OK ? s : block_stats_impl(*j1, nullptr, B, beta, cached, st);
   }
   const int N = std::max(ceil_div(x.L, B), j1 ? ceil_div(j1->x.L, B) : 0);
   const int64_t blocks = (int64_t)BH0 * ceil_div(x.L, B) + (int64_t)BH1 * (j1 ? ceil_div(j1->x.L, B) : 0);
@@ -328,7 +328,6 @@ static basa_status block_stats_impl(const StatsJob& j0, const StatsJob* j1, int 
   ProfScope prof(K_STATS, st);
   const bool bf = x.dtype == BASA_BF16;
   const StatsJob& jb = j1 ? *j1 : j0;
-  const bool cached = ((int64_t)BH0 * x.L + (int64_t)BH1 * (j1 ? j1->x.L : 0)) * x.d * (bf ? 2 : 4) <= kCachedRowBytes;
 #define BASA_STATS(BF, D, BB)                                                                                               \
   do {                                                                                                                      \
     if (cached) hipLaunchKernelGGL((block_stats_kernel<BF, D, BB, false>), grid, dim3(256), 0, st, j0, jb, BH0, beta, per_wg); \
@@ -351,15 +350,15 @@ basa_status launch_block_stats(const TensorView& x, const int32_t* perm, int B, 
                                float* var, void* feat, int feat_is_query, float beta, void* x_sorted,
                                hipStream_t st) {
   const StatsJob j{x, perm, mean, var, reinterpret_cast<uint16_t*>(feat), feat_is_query, x_sorted};
-  return block_stats_impl(j, nullptr, B, beta, st);
+  return block_stats_impl(j, nullptr, B, beta, rows_cached(x), st);
 }
 
 basa_status launch_select_features(const TensorView& q, const int32_t* perm_q, void* feat_q,
                                    const TensorView& k, const int32_t* perm_k, void* feat_k, int B,
-                                   float beta, hipStream_t st) {
+                                   float beta, bool cached, hipStream_t st) {
   const StatsJob jq{q, perm_q, nullptr, nullptr, reinterpret_cast<uint16_t*>(feat_q), 1, nullptr};
   const StatsJob jk{k, perm_k, nullptr, nullptr, reinterpret_cast<uint16_t*>(feat_k), 0, nullptr};
-  return block_stats_impl(jq, &jk, B, beta, st);
+  return block_stats_impl(jq, &jk, B, beta, cached, st);
 }
 
 }  // namespace basa

@@ -550,3 +550,24 @@ def test_packed_batch_repeats_what_left_the_safe_range():
     for a, b in zip(cu[:-1], cu[1:]):
         want, _ = bd.ba_att(view(q, a, b), view(k, a, b), view(v, a, b), 128, 0.5)
         assert (view(out, a, b).float() - want.float()).norm() < 4e-3 * want.float().norm()
+
+
+@pytest.mark.parametrize("hq,hk,Lq,Lk,d,sort,streams", [
+    (16, 16, 25000, 28000, 128, bd.SORT_QK, True),        # 102 and 115 MB, sorted one after the other
+    (16, 16, 15000, 20000, 128, bd.SORT_QK, False),       # 61 and 82 MB, likewise
+    (16, 4, 30000, 30000, 128, bd.SORT_Q, False), (16, 4, 40000, 40000, 128, bd.SORT_K, True),
+    (64, 64, 4096, 4096, 128, bd.SORT_QK, False), (75, 75, 4096, 4096, 128, bd.SORT_QK, False)])
+def test_both_passes_over_the_rows_load_them_the_same_way(hq, hk, Lq, Lk, d, sort, streams):
+    # one answer for a call: what the key pass leaves in the caches is there for the pooling pass, or neither pass goes by it
+    from torch.profiler import ProfilerActivity, profile
+    Q, K, _ = _qkv(hq, hk, Lq, Lk, d, torch.bfloat16)
+    bd.basa_select(Q, K, 128, 0.5, sort=sort)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        bd.basa_select(Q, K, 128, 0.5, sort=sort)
+        torch.cuda.synchronize()
+    names = [e.name for e in prof.events()]
+    passes = [m.group(2) == "true" for n in names for m in [re.search(r"(norm_tile_sort|block_stats)_kernel<[^>]*, (true|false)>", n)] if m]
+    if not passes:
+        pytest.skip("the profiler reports no kernels here")
+    assert len(passes) >= 2 and all(p == streams for p in passes), [n[:120] for n in names]
