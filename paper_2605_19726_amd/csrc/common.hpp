@@ -242,13 +242,19 @@ __device__ __forceinline__ uint4 load_row_chunk(const char* row, int chunk) {
   return __builtin_bit_cast(uint4, kStream ? __builtin_nontemporal_load(src) : *src);
 }
 
-template <class Job, int kWavesPerSimd = 1, int kThreads = 256>
-__global__ __launch_bounds__(kThreads, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
+// The job of a workgroup and which of its workgroups this is (null: none).
+template <class Job>
+__device__ __forceinline__ const Job* job_of(const Jobs<Job>& jobs, int* logical) {
   int i = 0;
   while (i + 1 < jobs.n && (int)blockIdx.x >= jobs.first[i + 1]) ++i;
   const int b = blockIdx.x - jobs.first[i], per = (jobs.first[i + 1] - jobs.first[i]) >> 3;
-  const int logical = (b & 7) * per + (b >> 3);
-  if (logical < jobs.blocks[i]) jobs.job[i].run(logical);
+  *logical = (b & 7) * per + (b >> 3);
+  return *logical < jobs.blocks[i] ? &jobs.job[i] : nullptr;
+}
+template <class Job, int kWavesPerSimd = 1, int kThreads = 256>
+__global__ __launch_bounds__(kThreads, kWavesPerSimd) void many_kernel(Jobs<Job> jobs) {
+  int logical;
+  if (const Job* job = job_of(jobs, &logical)) job->run(logical);
 }
 // Entry `pos` of a permutation of 0..L-1 (null = identity).  Permutations are device data the
 // host cannot check: a value that is no index falls back to `pos`, so that a malformed

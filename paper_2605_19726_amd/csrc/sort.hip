@@ -604,10 +604,32 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
 // ---------------------------------------------------------------------------------
 // Bound by the probes ((kG - 1) log2(run) per word, through L1); 32 rows of 7627 words, 8 runs each: 15.6 us against
 // 40 us for the LDS merge of a few workgroups; 2 x 10^6 words in 32 runs: 193 us against 39.
-template <int kG>
-__device__ __forceinline__ void rank_runs(int logical, const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                                          int32_t* __restrict__ perm0, int32_t* __restrict__ perm1, int BH0, const SegGeom& g,
-                                          int run, int chunks_per_bh) {
+struct RankArgs {
+  const uint64_t* in;
+  uint64_t* out;
+  int32_t *perm0, *perm1;                  // null unless the last pass
+  int BH0;
+  SegGeom g;
+  int run, chunks_per_bh;
+};
+__device__ __forceinline__ const RankArgs* job_of(const RankArgs& a, int* logical) {
+  const int total = gridDim.x;             // a head's words on one XCD: their scattered stores meet in its L2
+  *logical = (total & 7) == 0 ? (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  return &a;
+}
+// Src: the arguments of one problem or of several.  (The body stands in the kernel: as a function that is inlined into one kernel
+// for each, the loads of a step came out in three groups instead of two, 8 runs of 6500 words 6.4 -> 7.6 us.)
+template <int kG, class Src>
+__global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(Src src) {
+  int logical;
+  const RankArgs* args = job_of(src, &logical);
+  if (!args) return;
+  const uint64_t* __restrict__ in = args->in;
+  uint64_t* __restrict__ out = args->out;
+  int32_t* __restrict__ perm0 = args->perm0;
+  int32_t* __restrict__ perm1 = args->perm1;
+  const SegGeom g = args->g;
+  const int BH0 = args->BH0, run = args->run, chunks_per_bh = args->chunks_per_bh;
   const int bh = logical / chunks_per_bh, i = (logical - bh * chunks_per_bh) * kSortThreads + threadIdx.x;
   if (i >= g.L) return;
   const int64_t hb = (int64_t)bh * g.L;
@@ -642,25 +664,6 @@ __device__ __forceinline__ void rank_runs(int logical, const uint64_t* __restric
   if (perm_out) perm_out[hb + base + rank] = idx_of_word(v);
   else out[hb + base + rank] = v;
 }
-
-template <int kG>
-__global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(const uint64_t* __restrict__ in, uint64_t* __restrict__ out,
-                                                                 int32_t* __restrict__ perm0, int32_t* __restrict__ perm1,
-                                                                 int BH0, SegGeom g, int run, int chunks_per_bh) {
-  const int total = gridDim.x;
-  int logical = blockIdx.x;                // a head's words on one XCD: their scattered stores meet in its L2
-  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
-  rank_runs<kG>(logical, in, out, perm0, perm1, BH0, g, run, chunks_per_bh);
-}
-template <int kG>
-struct RankJob {
-  const uint64_t* in;
-  uint64_t* out;
-  int32_t *perm_q, *perm_k;                // null unless the last pass
-  int heads_q, run_len, chunks;
-  SegGeom g;
-  __device__ __forceinline__ void run(int block) const { rank_runs<kG>(block, in, out, perm_q, perm_k, heads_q, g, run_len, chunks); }
-};
 
 __global__ void iota_kernel(int32_t* perm, int L, int64_t total) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -705,9 +708,9 @@ static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, co
       while (G < 8 && (passes == 1 ? G : passes == 2 ? G * G : (int64_t)G * G * G) < runs) G *= 2;
       const bool last = run * G >= g.W;
       ProfScope prof(K_MERGE, st);
-#define BASA_RANK(N)                                                                                             \
-  hipLaunchKernelGGL(rank_runs_kernel<N>, dim3((unsigned)chunks * BH), dim3(kSortThreads), 0, st, src, dst,      \
-                     last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, (int)run, chunks)
+      const RankArgs args{src, dst, last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, (int)run, chunks};
+#define BASA_RANK(N) \
+  hipLaunchKernelGGL((rank_runs_kernel<N, RankArgs>), dim3((unsigned)chunks * BH), dim3(kSortThreads), 0, st, args)
       if (G == 2) BASA_RANK(2);
       else if (G == 4) BASA_RANK(4);
       else BASA_RANK(8);
@@ -806,20 +809,20 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
 
 template <int kG>
 static basa_status rank_many(const SeqJob* seq, int n, int run, int pass, hipStream_t st) {
-  Jobs<RankJob<kG>> jobs;
+  Jobs<RankArgs> jobs;
   for (int i = 0; i < n; ++i) {
     const int L = seq[i].q.L, rows = seq[i].q.heads + seq[i].k.heads;
     if (run >= L) continue;                                // sorted by an earlier pass
     const bool last = (int64_t)run * kG >= L;
     uint64_t* buf[2] = {reinterpret_cast<uint64_t*>(seq[i].sort_ws),
                         reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(seq[i].sort_ws) + align_up((size_t)rows * L * 8, 256))};
-    jobs.add(RankJob<kG>{buf[pass & 1], buf[(pass & 1) ^ 1], last ? seq[i].perm_q : nullptr, last ? seq[i].perm_k : nullptr,
-                         seq[i].q.heads, run, ceil_div(L, kSortThreads), geom_of(L, 0, kSmallTile)},
+    jobs.add(RankArgs{buf[pass & 1], buf[(pass & 1) ^ 1], last ? seq[i].perm_q : nullptr, last ? seq[i].perm_k : nullptr,
+                      seq[i].q.heads, geom_of(L, 0, kSmallTile), run, ceil_div(L, kSortThreads)},
              (int64_t)ceil_div(L, kSortThreads) * rows);
   }
   if (jobs.n == 0) return BASA_OK;
   ProfScope prof(K_MERGE, st);
-  hipLaunchKernelGGL(many_kernel<RankJob<kG>>, dim3(jobs.first[jobs.n]), dim3(kSortThreads), 0, st, jobs);
+  hipLaunchKernelGGL((rank_runs_kernel<kG, Jobs<RankArgs>>), dim3(jobs.first[jobs.n]), dim3(kSortThreads), 0, st, jobs);
   BASA_HIP_CHECK_LAUNCH("rank_runs");
   return BASA_OK;
 }
