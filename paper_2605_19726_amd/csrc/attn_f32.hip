@@ -70,11 +70,12 @@ struct F32Args {
   LseFactor lse_k;
   float* part_o;                            // splits > 1: [split][BHq][Lq][D], rows by sorted position
   float2* part_ml;                          //             [split][BHq][Lq] running maximum (log2), running sum
-  const int32_t* redo;                      // nullable, [BHq][redo_wgs]: the 128 queries whose rows are wanted (1)
+  const int32_t* redo;                      // kRedo: [BHq][redo_wgs]: the 128 queries whose rows are wanted (1)
   int redo_wgs;
 };
 
-template <int D, int QG, int KS, bool kCausal>
+// kRedo: only the workgroups that p.redo marks.
+template <int D, int QG, int KS, bool kCausal, bool kRedo>
 __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_kernel(F32Args p) {
   constexpr int CPR = D / 4;                // 16-byte chunks per row
   constexpr int DB = D / 32;                // output blocks of 32 dimensions
@@ -91,7 +92,9 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
   const int split = logical % p.splits;
   const int wgi = logical / p.splits;
   const int bhq = wgi / p.wgs_per_head, wg = wgi - bhq * p.wgs_per_head;
-  if (p.redo && p.redo[bhq * p.redo_wgs + wg * (32 * QG) / 128] == 0) return;
+  if constexpr (kRedo) {
+    if (p.redo[bhq * p.redo_wgs + wg * (32 * QG) / 128] == 0) return;
+  }
   const int bhk = bhq / p.group;
   const int lane = threadIdx.x & 63, li = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -885,15 +888,16 @@ basa_status launch_f32(F32Args p, int BHq, hipStream_t st) {
   const size_t lds = (size_t)KS * 2 * 2 * kTK * D * 4 + (p.a.causal ? KS * 2 * kTK * 4 : 0);
   {
     ProfScope prof(K_ATTN_F32, st);
-#define BASA_F32(C)                                                                                              \
+#define BASA_F32(C, R)                                                                                           \
   do {                                                                                                           \
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, QG, KS, C>),      \
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_f32_kernel<D, QG, KS, C, R>),   \
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);              \
     if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");                                 \
-    hipLaunchKernelGGL((attn_f32_kernel<D, QG, KS, C>), dim3(p.total), dim3(64 * QG * KS), lds, st, p);          \
+    hipLaunchKernelGGL((attn_f32_kernel<D, QG, KS, C, R>), dim3(p.total), dim3(64 * QG * KS), lds, st, p);       \
   } while (0)
-    if (p.a.causal) BASA_F32(true);
-    else BASA_F32(false);
+    if (p.a.causal) BASA_F32(true, false);
+    else if (p.redo) BASA_F32(false, true);
+    else BASA_F32(false, false);
 #undef BASA_F32
     BASA_HIP_CHECK_LAUNCH("attn_f32_kernel");
   }
