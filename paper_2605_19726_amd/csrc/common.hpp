@@ -232,16 +232,6 @@ basa_status launch_attn_many(const SeqJob* seq, int n, int B, const int64_t* out
 
 // ---- device helpers ------------------------------------------------------------
 #if defined(__HIPCC__)
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-// 16 bytes of a row, streaming or through the caches.  (Bit-cast into uint4, not held as the builtin's vector type: the
-// compiler rotates such vectors through several buffers as whole registers, copies that count as uses of loads still in
-// flight, and every batch is then waited for at the top of the loop.)
-template <bool kStream>
-__device__ __forceinline__ uint4 load_row_chunk(const char* row, int chunk) {
-  const u32x4_t* src = reinterpret_cast<const u32x4_t*>(row) + chunk;
-  return __builtin_bit_cast(uint4, kStream ? __builtin_nontemporal_load(src) : *src);
-}
-
 // The job of a workgroup and which of its workgroups this is (null: none).
 template <class Job>
 __device__ __forceinline__ const Job* job_of(const Jobs<Job>& jobs, int* logical) {

@@ -98,7 +98,10 @@ __device__ __forceinline__ void block_stats(int bx, int by, const StatsJob& j0, 
     for (int it = 0; it < ITERS; ++it) {
       // a malformed permutation entry falls back to the position itself
       const int row = (unsigned)rows[it] < (unsigned)L ? rows[it] : min(p0 + it * RPI, L - 1);
-      raw[it] = load_row_chunk<kStream>(base + (live ? row : 0) * row_bytes, sub_l);
+      // (as in the key pass)
+      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+      const u32x4* src = reinterpret_cast<const u32x4*>(base + (live ? row : 0) * row_bytes) + sub_l;
+      raw[it] = __builtin_bit_cast(uint4, kStream ? __builtin_nontemporal_load(src) : *src);
     }
   };
 
