@@ -3,6 +3,7 @@ store or atomic of the same wave, by a wait that empties lgkmcnt.  (One loop of 
 once lacked it: the compiler had dropped the LDS part of the wait that __syncthreads() asks for, and
 partial sums were read stale now and then.)  Runs on the CPU, on what the build keeps in _build/."""
 import os
+import re
 
 from paper_2605_19726_amd import build, lds_wait_audit as audit
 
@@ -20,6 +21,20 @@ def test_every_source_has_its_assembly_and_none_lacks_the_wait():
     names = {os.path.basename(f).split("-hip-")[0] + ".hip" for f in files}
     assert names == set(build.SOURCES), names
     assert audit.audit_files(files) == []
+
+
+def test_no_kernel_copies_its_arguments_to_scratch():
+    # (an array of them indexed through a pointer that the compiler loses sight of: 3 KB per thread; the spills there are, are small)
+    found = {}
+    for path in _asm_files():
+        kernel = None
+        for line in open(path):
+            m = re.match(r"\s*\.amdhsa_(kernel|private_segment_fixed_size) (\S+)", line)
+            if m and m.group(1) == "kernel":
+                kernel = m.group(2)
+            elif m and int(m.group(2)) > 64:
+                found[kernel] = int(m.group(2))
+    assert found == {}
 
 
 def test_the_audit_sees_a_missing_wait_across_a_loop_edge_and_accepts_the_repaired_form():
