@@ -27,9 +27,9 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
     if (!cached || run <= kSmallTile || run > 8 * 512) return {true, kSmallTile};
     // Tiles of 512 where eight of them make a run and one ranking pass merges them either way: twice the workgroups read the
     // rows and each sorts half as much, as long as there are no more of them than the compute units take at once.  Sort, tiles of
-    // 1024 -> 512, 256 bytes a token, runs of 4096: 16 rows 21.6 -> 17.8 us, 32: 22.4 -> 19.1, kept at 1024: 64: 27.7 / 32.1, 128:
-    // 44 / 52; longer where the second tile of 1024 is hardly used (runs of 1500: 20 rows 21.8 -> 16.8, 349: 48.4 -> 47.6) and with
-    // 128 bytes a token (runs of 4096, 64 rows: 21.3 / 21.4, 98: 31.4 / 33.6).
+    // 1024 -> 512, 256 bytes a token, runs of 4096: 16 rows 21.6 -> 16.8 us, 32: 22.0 -> 18.4, kept at 1024: 64: 27.6 / 31.4, 128:
+    // 44 / 51; longer where the second tile of 1024 is hardly used (runs of 1500: 20 rows 21.4 -> 16.0, 349: 47.5 -> 47.0) and with
+    // 128 bytes a token (runs of 4096, 64 rows: 21.1 / 21.2, kept at 1024: 98: 31.1 / 33.4).
     const bool short_tokens = token_bytes <= 128;
     if (run <= 3 * 512 || (short_tokens && run <= 4 * 512)) return {true, 512};
     auto tiles = [&](int64_t rows, int L) {
@@ -41,14 +41,15 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
   }
   // Up to kMidWords the tiles stay at 1024 and the quads (16384 words in LDS) start from those: 4096-token tiles are one or two
   // workgroups to a compute unit there, whose bitonic networks nothing hides.  Whole sort, d = 128, large tiles -> small: 1.0
-  // million words in runs of 1024: 94 -> 54 us, 1500: 88 -> 75, 2048: 80 -> 63, 8300: 114 -> 102, 12000: 118 -> 100, 16384: 94 -> 90,
-  // 32768: 108 -> 105; 2.1 million words: 1500: 143 -> 131, 8300 and more: level.
+  // million words in runs of 1024: 94 -> 52 us, 1500: 89 -> 75, 2048: 79 -> 60, 8300: 113 -> 99, 12000: 122 -> 97, 16384: 90 -> 88,
+  // 32768: 105 -> 102; 2.1 million words: 1500: 140 -> 129, 16384: 139 -> 137.  (From 0.53 to 2.1 million words, runs of 8300 to
+  // 65536, three types: 25 % faster to 6 % slower, the latter where the large tiles are just as many as the compute units.)
   if (words > kMidWords) return {false, kTile};
   if (run <= 2 * kSmallTile || run > 2 * kTile) return {false, kSmallTile};
-  // Shorter runs leave much of a quad empty.  One large tile is the whole run: 3000 tokens 87 us against 143 and 129 / 266 (1.0 and
-  // 2.1 million words), 4096: 74 / 99 and 118 / 183.  Or two and a merge pass: small tiles only where the large ones are more than
-  // one to a compute unit, the quads are not, and the small ones at most five (large / small, 128 runs, then 132: 5000: 80 / 84,
-  // 102 / 84, 8192: 85 / 96, 108 / 104; 256 runs of 5000, then 260: 113 / 109, 144 / 150; 200 of 7000, then 230: 115 / 116, 120 / 129).
+  // Shorter runs leave much of a quad empty.  One large tile is the whole run: 3000 tokens 86 us against 141 and 128 / 263 (1.0 and
+  // 2.1 million words), 4096: 70 / 96 and 118 / 181.  Or two and a merge pass: small tiles only where the large ones are more than
+  // one to a compute unit, the quads are not, and the small ones at most five (large / small, 128 runs, then 132: 5000: 74 / 82,
+  // 101 / 82, 8192: 81 / 93, 112 / 102; 256 runs of 5000, then 260: 113 / 107, 145 / 148; 200 of 7000, then 230: 115 / 115, 119 / 127).
   if (run <= kTile) return {false, kTile};
   const int64_t runs = rows0 * ((L0 + run - 1) / run) + (rows1 > 0 ? rows1 * ((L1 + run - 1) / run) : 0);
   return {false, runs > 128 && runs <= 256 && words <= 5 * 256 * kSmallTile ? kSmallTile : kTile};
