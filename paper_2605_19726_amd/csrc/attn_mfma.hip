@@ -1251,6 +1251,12 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36; not so the causal kernel, 8 heads, L = 2100: 94 and 59 in six), and a
 // whole list on the 128-query shape gives the same bits as on the 512-query one.
 constexpr int kCUs = 256, kMaxSplits = 32, kMinSplitTiles = 32;
+constexpr double kWideStepUs = 2.95, kCausalStepUs = 3.4, kSoloPairStepUs = 1.95, kSoloStepUs = 1.25;
+constexpr double kWideRoundUs = 20.0, kCausalRoundUs = 8.0, kSoloRoundUs = 10.0;
+constexpr double step_scale(int d) { return d == 128 ? 1.0 : 0.63; }
+// Blocks in the union of two lists of 64 queries and of the lists of 512, over one list, for lists that leave out `dead` of all.
+constexpr double union_of_pair(int B, double dead) { return 1.0 + (B == 64 ? 0.1 : 0.0) * dead; }
+constexpr double union_of_groups(int groups, double dead) { return 1.0 + 0.1 * (groups - 1) * dead; }
 struct Plan { bool solo; int splits; };
 // Up to six of 512 queries per compute unit, whole lists only: there a last round that is mostly empty decides, and the
 // 128-query shape has to be 5 % ahead by the estimate.  512-query -> chosen shape: 16 heads, L = 20000, keep 10 %
@@ -1259,7 +1265,7 @@ struct Plan { bool solo; int splits; };
 constexpr int kSmallRounds = 2, kPlannedRounds = 6;
 Plan plan_call(int BHq, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, bool small, size_t part_bytes) {
   const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
-  const double dead = 1.0 - (double)list_len / Nk, scale = d == 128 ? 1.0 : 0.63;
+  const double dead = 1.0 - (double)list_len / Nk, scale = step_scale(d);
   Plan best{false, 1};
   double best_cost = 0.0;
   for (int solo = 0; solo <= (causal ? 0 : 1); ++solo) {
@@ -1268,15 +1274,14 @@ Plan plan_call(int BHq, int Nq, int Nk, int Lq, int B, int d, int list_len, bool
     // blocks in the union of a workgroup's lists, measured (full method): the union over 512 queries is 1.14 times that
     // over 128 at 50 %, 1.22 at 75 %, 1.29 at 90 %; two lists of 64 queries make about 1.05 to 1.1
     const int groups = solo ? 1 : std::min(4, ceil_div(Nq * B, kSoloQueries));
-    const double uni = std::min((double)Nk, list_len * (1.0 + (B == 64 && Nq > 1 ? 0.1 : 0.0) * dead) *
-                                                (1.0 + 0.1 * (groups - 1) * dead));
+    const double uni = std::min((double)Nk, list_len * (Nq > 1 ? union_of_pair(B, dead) : 1.0) * union_of_groups(groups, dead));
     const bool may_split = small && (solo != 0) != causal && (causal || list_len * (B / kTileKeys) > kMinSplitTiles);
     for (int s = 1; s == 1 || (may_split && s <= kMaxSplits && uni >= s && s * row_bytes <= part_bytes); ++s) {
       const int64_t per_cu = (wgs * s + kCUs - 1) / kCUs;
       const double rounds = solo ? (double)((per_cu + 1) / 2) : (double)per_cu;
-      const double step_us = solo ? (double)(per_cu / 2) * 1.95 + (double)(per_cu % 2) * 1.25
-                                  : (double)per_cu * (causal ? 3.4 : 2.95);
-      const double round_us = solo ? 10.0 : causal ? 8.0 : 20.0;
+      const double step_us = solo ? (double)(per_cu / 2) * kSoloPairStepUs + (double)(per_cu % 2) * kSoloStepUs
+                                  : (double)per_cu * (causal ? kCausalStepUs : kWideStepUs);
+      const double round_us = solo ? kSoloRoundUs : causal ? kCausalRoundUs : kWideRoundUs;
       const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + round_us * rounds +
                           (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
       if ((!solo && s == 1) || cost < best_cost * (small ? 1.0 : 0.95)) { best_cost = cost; best = Plan{solo != 0, s}; }
@@ -1366,10 +1371,10 @@ basa_status attn_many(const SeqJob* seq, int n, const int64_t* out_strides, hipS
   double solo_us = 0.0, wide_us = 0.0, tail_us = 0.0;
   for (int i = 0; i < n; ++i) {
     const SeqJob& s = seq[i];
-    const double dead = 1.0 - (double)s.kappa / s.Nk, tiles = s.kappa * (kB / kTileKeys) * (1.0 + (kB == 64 ? 0.1 : 0.0) * dead);
-    const double scale = D == 128 ? 1.0 : 0.63, wide_tiles = std::min((double)s.Nk * (kB / kTileKeys), tiles * (1.0 + 0.3 * dead));
-    solo_us += s.q.heads * ceil_div(s.Nq * kB, kSoloQueries) * (tiles * 1.95 * scale + 10.0) / 2.0;
-    tail_us = wide_tiles * 2.95 * scale + 20.0;                              // (ends at the shortest sequence)
+    const double dead = 1.0 - (double)s.kappa / s.Nk, tiles = s.kappa * (kB / kTileKeys) * union_of_pair(kB, dead);
+    const double scale = step_scale(D), wide_tiles = std::min((double)s.Nk * (kB / kTileKeys), tiles * union_of_groups(4, dead));
+    solo_us += s.q.heads * ceil_div(s.Nq * kB, kSoloQueries) * (tiles * kSoloPairStepUs * scale + kSoloRoundUs) / 2.0;
+    tail_us = wide_tiles * kWideStepUs * scale + kWideRoundUs;               // (ends at the shortest sequence)
     wide_us += s.q.heads * ceil_div(s.Nq * kB, kWideQueries) * tail_us;
   }
   const bool wide = D == 128 && wide_us / kCUs + tail_us < solo_us / kCUs;
