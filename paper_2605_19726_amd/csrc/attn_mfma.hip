@@ -737,10 +737,10 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   // ---- union of the block lists of this workgroup's query blocks ------------------------
   // What the prologue reads by one address is requested before the first barrier, which waits for it: of every list (its
   // threads have one each) the count and the first entries, and the entry of perm_q.  One latency instead of two for each
-  // list in turn and one for perm_q: 8 heads, L = 2472, d = 64: 59.8 -> 59.2 us (whole operator); 32 heads, L = 16384, keep 10 %:
-  // 648 -> 641.  (With two query groups per wave perm_q waits until the union is there: two entries kept across it change
-  // the compiler's registers for the whole kernel: dense, L = 16384, 3494 against 3473; 32 heads, L = 131072, keep 50 %,
-  // 115.9 ms against 114.5; both in one run.)
+  // list in turn and one for perm_q (attention call, both in one run): 8 heads, L = 2472, d = 64: 28.2 -> 27.6 us; 32 heads, L =
+  // 16384, keep 10 %: 487 -> 480, 25 %: 1030 -> 1020; causal, blocks of 64, keep 50 %: 2209 -> 2190.  (With two query groups per
+  // wave perm_q waits until the union is there: two entries kept across it change the compiler's registers for the whole
+  // kernel: dense, L = 16384, 3494 against 3473; 32 heads, L = 131072, keep 50 %, 115.9 ms against 114.5; both in one run.)
   int q_raw = 0;
   if constexpr (kNG == 1) {
     const int pos = min(position(0), a.Lq - 1);
