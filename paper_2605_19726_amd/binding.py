@@ -376,8 +376,9 @@ def ba_att(q, k, v, block: int = 128, sparsity: float = 0.5, beta: float = 1.0, 
 def ba_att_varlen(q, k, v, cu_seqlens, block: int = 128, sparsity: float = 0.5, **kw):
     """Sequences of different lengths packed token-major: q [T, heads_q, d], k and v [T, heads_kv, d],
     cu_seqlens the host list [0, t_1, ..., T] of sequence boundaries.  Every sequence is its own
-    problem (its own sort, block map and kappa), read and written in place; short sequences share
-    their launches (basa_varlen_attn).  Returns the packed output [T, heads_q, d]."""
+    problem (its own sort, block map and kappa), read and written in place; short bf16 sequences share
+    their launches (basa_varlen_attn) and agree with ba_att on them alone within rounding, whose lists may
+    be split further.  Returns the packed output [T, heads_q, d]."""
     out = torch.empty_like(q)
     view = lambda x, a, b: x[a:b].permute(1, 0, 2).unsqueeze(0)          # [1, heads, L, d], no copy
     cu = [int(t) for t in cu_seqlens]

@@ -355,7 +355,7 @@ __global__ __launch_bounds__(64 * QG * KS, QG * KS == 8 ? 2 : 1) void attn_f32_k
 // the sum or the row of every query it touches: such a workgroup writes one word, and attn_f32_kernel, launched behind this
 // one, computes its rows instead (and returns at once elsewhere).
 //
-// Bound: power and the vector unit (290 instructions a tile next to 96 MFMAs; 1.16 PFLOP/s of part products with every
+// Bound: power and the vector unit (306 instructions a tile next to 96 MFMAs; 1.16 PFLOP/s of part products with every
 // compute unit busy; without the tile loads 6 % faster).  8 heads, L = 4096, d = B = 128, 16 of 32 blocks: 276 us on
 // the fp32 instruction -> 177 us + 13.5 us for the tiles; error against 64 bits 6.4e-7 -> 2.7e-7 (2-norm), largest 1.5e-5 ->
 // 0.8e-5 of the root mean square: the probabilities and the scores are rounded as before, their sums less often.

@@ -563,10 +563,14 @@ def test_both_passes_over_the_rows_load_them_the_same_way(hq, hk, Lq, Lk, d, sor
     Q, K, _ = _qkv(hq, hk, Lq, Lk, d, torch.bfloat16)
     bd.basa_select(Q, K, 128, 0.5, sort=sort)
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        bd.basa_select(Q, K, 128, 0.5, sort=sort)
-        torch.cuda.synchronize()
-    names = [e.name for e in prof.events()]
+    names = []
+    try:
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            bd.basa_select(Q, K, 128, 0.5, sort=sort)
+            torch.cuda.synchronize()
+        names = [e.name for e in prof.events()]
+    except RuntimeError as e:                             # (of the profiler: the calls above and below run without it)
+        pytest.skip(f"no profiler here: {e}")
     passes = [m.group(2) == "true" for n in names for m in [re.search(r"(norm_tile_sort|block_stats)_kernel<[^>]*, (true|false)>", n)] if m]
     if not passes:
         pytest.skip("the profiler reports no kernels here")
