@@ -816,6 +816,7 @@ size_t split_lds_bytes(int Nk, int d) { return split_ring_bytes(d) + (size_t)Nk 
 // instruction -> this: 8 heads, L = 4096, keep 50 %, d = B = 128: 278 -> 182 us, d = 64: 149 -> 104; L = 6000: 645 -> 405 (two
 // parts per list); 4 heads, L = 3001, keep 25 %: 69 -> 52; against, 2 heads, L = 1024: 30 / 31, L = 2048, B = 64: 40 / 47, d = B =
 // 64, L = 2000: 24 / 30 at its best number of parts.
+double three_part_fixed_us(size_t img) { return 9.0 + (double)img * 20.0 / 12.0 / 5e6; }
 struct F32Plan { bool three_part; int splits; };
 F32Plan plan_f32(int BHq, int BHkv, int Lq, int Lk, int d, int B, int tiles, bool causal, size_t ws_bytes) {
   const F32Shape f = shape_of(d, B);
@@ -829,7 +830,7 @@ F32Plan plan_f32(int BHq, int BHkv, int Lq, int Lk, int d, int B, int tiles, boo
     return F32Plan{false, plain.splits};
   const Splits three = plan_splits((int64_t)BHq * ceil_div(Nq * B, 128), B == 64 ? tiles + tiles / 12 : tiles, 2,
                                    kSplitStepUs[d == 128], row_bytes, ws_bytes - img - redo);
-  const bool take = three.us + 9.0 + (double)img * 20.0 / 12.0 / 5e6 < plain.us;
+  const bool take = three.us + three_part_fixed_us(img) < plain.us;
   return F32Plan{take, take ? three.splits : plain.splits};
 }
 
@@ -950,6 +951,11 @@ size_t attn_f32_best_workspace_bytes(int BHq, int BHkv, int Lq, int Lk, int d, i
   const int Nk = ceil_div(Lk, B);
   const size_t img = split_img_bytes(BHkv, Nk, B, d) + split_redo_bytes(BHq, ceil_div(Lq, B), B);
   const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
+  // (the other kernel with every block listed, already below what the three-part one takes with one tile: no length is for it)
+  const F32Shape f = shape_of(d, B);
+  if (plan_splits((int64_t)BHq * ceil_div(ceil_div(Lq, B) * B, 32 * f.QG), Nk * (B / kTK), f.KS, f32_step_us(d, f.QG * f.KS), row_bytes,
+                  base).us < three_part_fixed_us(split_img_bytes(BHkv, Nk, B, d)) + 8.0 + kSplitStepUs[d == 128])
+    return base;
   const int64_t work = (int64_t)BHq * ceil_div(Lq, 128);
   size_t splits = 0;            // (without what plan_f32 adds for two lists of 64: four heads, L = 3001, every block: 124 us, with
                                 //  the parts that it would then take 128)
