@@ -122,10 +122,12 @@ typedef struct {
                                 keeps the map on chip; possible when nobody needs the map in
                                 memory (fixed count per row, no `scores` output, no total budget,
                                 not causal, at most 1024 key blocks per row), else
-                                BASA_ERR_UNSUPPORTED.  0 = the library's choice: the faster of the
-                                two where both apply, which on MI355X is 1.  Logits, kept sets
-                                and lists are the same either way; row_mass may differ in its
-                                last bits (another order of summation)                          */
+                                BASA_ERR_UNSUPPORTED.  0 = the library's choice: the faster
+                                way, on MI355X 1, or for small calls of at most 128 key blocks
+                                per row one kernel that computes and selects as 1 does, the map in
+                                LDS.  Logits, kept sets and lists are the same on every path;
+                                row_mass of 2 may differ in its last bits (another order of
+                                summation)                                                      */
 } basa_params;
 #define BASA_MAX_SEGMENTS 63
 

@@ -469,11 +469,10 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
     return BASA_ERR_UNSUPPORTED;
   }
   // (the two-kernel path below is the faster one on this part, 0.21 against 0.30 ms at 128K, so the
-  //  library's own choice, select_path = 0, is that one)
+  //  library's own choice, select_path = 0, is that one, or for short rows of small calls the strips)
   if (fusable && p->select_path == 2)
     return launch_scores_select(featq, featk, BHq, q->heads / k->heads, Nq, Nk, kdim, 3 * q->d, kappa, mask_bits,
                                 row_count, row_cols, row_mass, st);
-  if ((s = launch_block_scores(featq, featk, sc, BHq, q->heads / k->heads, Nq, Nk, kdim, 3 * q->d, st)) != BASA_OK) return s;
   LiveBlocks live{nullptr, nullptr, Nq, q->heads / k->heads, k->L - q->L};
   if (p->causal) {
     int32_t* q_max = reinterpret_cast<int32_t*>(base + w.range_off);
@@ -482,6 +481,10 @@ basa_status basa_select(const basa_tensor* q, const basa_tensor* k, const basa_p
     if ((s = launch_block_index_range(perm_k, BHk, k->L, B, 0, k_min, st)) != BASA_OK) return s;
     live.q_max = q_max; live.k_min = k_min;
   }
+  if (p->select_path == 0 && !scores && p->budget_total == 0 && select_strip_rows(BHq, Nq, Nk) > 0)
+    return launch_select_strip(featq, featk, BHq, q->heads / k->heads, Nq, Nk, kdim, 3 * q->d, kappa, (float)p->mass_target,
+                               p->min_keep, live, mask_bits, row_count, row_cols, row_mass, st);
+  if ((s = launch_block_scores(featq, featk, sc, BHq, q->heads / k->heads, Nq, Nk, kdim, 3 * q->d, st)) != BASA_OK) return s;
   if ((s = launch_row_select(sc, BHq * Nq, Nk, kappa, (float)p->mass_target, p->min_keep, nullptr, live, mask_bits,
                              row_count, row_cols, row_mass, st)) != BASA_OK) return s;
   if (p->budget_total > 0) {
@@ -594,8 +597,7 @@ basa_status basa_varlen_attn(const basa_tensor* q, const basa_tensor* k, const b
     const int kdim = (p->beta == 0.f) ? q->d : 3 * q->d;
     if ((e = launch_norm_sort_many(job, n, st)) != BASA_OK) return e;
     if ((e = launch_select_features_many(job, n, p->block, p->beta, st)) != BASA_OK) return e;
-    if ((e = launch_block_scores_many(job, n, kdim, 3 * q->d, st)) != BASA_OK) return e;
-    if ((e = launch_row_select_many(job, n, (float)p->mass_target, p->min_keep, st)) != BASA_OK) return e;
+    if ((e = launch_map_select_many(job, n, kdim, 3 * q->d, (float)p->mass_target, p->min_keep, st)) != BASA_OK) return e;
     return launch_attn_many(job, n, p->block, out_strides, st);
   });
 }

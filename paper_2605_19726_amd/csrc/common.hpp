@@ -129,6 +129,12 @@ basa_status launch_row_select(const float* scores, int rows_total, int Nk, int k
                               float mass_target, int min_keep, const int32_t* keep_in, const LiveBlocks& live,
                               uint32_t* mask_bits, int32_t* row_count, int32_t* row_cols, float* row_mass,
                               hipStream_t st);
+// Both for short rows, in one launch, if no one needs the map afterwards (same logits, lists and masses): where
+// select_strip_rows is not 0, and that is the faster way.
+int select_strip_rows(int BHq, int Nq, int Nk);
+basa_status launch_select_strip(const void* featQ, const void* featK, int BHq, int group, int Nq, int Nk, int kdim_used,
+                                int feat_stride, int kappa, float mass_target, int min_keep, const LiveBlocks& live,
+                                uint32_t* mask_bits, int32_t* row_count, int32_t* row_cols, float* row_mass, hipStream_t st);
 // Per block of a permutation: out[bh][g] = max (want_max) or min of perm[bh][g*B .. min((g+1)*B, L)).
 basa_status launch_block_index_range(const int32_t* perm, int BH, int L, int B, int want_max, int32_t* out,
                                      hipStream_t st);
@@ -223,8 +229,8 @@ struct SeqJob {
 // The stages for up to kMaxJobs sequences of bf16, sorted Q and K.
 basa_status launch_norm_sort_many(const SeqJob* seq, int n, hipStream_t st);
 basa_status launch_select_features_many(const SeqJob* seq, int n, int B, float beta, hipStream_t st);
-basa_status launch_block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st);
-basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st);
+basa_status launch_map_select_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, float mass_target, int min_keep,
+                                   hipStream_t st);
 size_t attn_many_tile_bytes(int heads_kv, int Lk, int d, int B);
 size_t attn_many_redo_bytes(int heads_q, int Lq, int B);
 bool attn_many_takes(int Nk, int d);       // the list fits the kernel's LDS
@@ -250,6 +256,43 @@ __device__ __forceinline__ const Job* job_of(const Jobs<Job>& jobs, int* logical
   const int b = blockIdx.x - jobs.first[i], per = (jobs.first[i + 1] - jobs.first[i]) >> 3;
   *logical = (b & 7) * per + (b >> 3);
   return *logical < jobs.blocks[i] ? &jobs.job[i] : nullptr;
+}
+// The value of lane l ^ kOff, kOff < 16, by lane moves of the vector unit, which take a tenth of the time that an exchange through
+// the LDS does.
+template <int kOff>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  static_assert(kOff == 1 || kOff == 2 || kOff == 4 || kOff == 8, "within a row of 16 lanes");
+  constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kXor7 = 0x141, kRotate8 = 0x128;
+  int x = (int)v;
+  if constexpr (kOff == 1) x = __builtin_amdgcn_update_dpp(x, x, kXor1, 0xf, 0xf, false);
+  if constexpr (kOff == 2) x = __builtin_amdgcn_update_dpp(x, x, kXor2, 0xf, 0xf, false);
+  if constexpr (kOff == 4) {
+    x = __builtin_amdgcn_update_dpp(x, x, kXor7, 0xf, 0xf, false);
+    x = __builtin_amdgcn_update_dpp(x, x, kXor3, 0xf, 0xf, false);
+  }
+  if constexpr (kOff == 8) x = __builtin_amdgcn_update_dpp(x, x, kRotate8, 0xf, 0xf, false);
+  return (uint32_t)x;
+}
+// For kOff = 16 or 32: the value of the lane of the pair (l, l ^ kOff) with that bit clear, then of the one with it set.
+template <int kOff>
+__device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& lower, uint32_t& upper) {
+  static_assert(kOff == 16 || kOff == 32, "whole rows");
+  const auto p = kOff == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  lower = p[0];
+  upper = p[1];
+}
+// op over all lanes of the wave, in the order of a butterfly from the far lanes to the near ones; every lane gets the result.
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  uint32_t a, b;
+  lane_pair<32>(__float_as_uint(v), a, b);
+  v = op(__uint_as_float(a), __uint_as_float(b));
+  lane_pair<16>(__float_as_uint(v), a, b);
+  v = op(__uint_as_float(a), __uint_as_float(b));
+  v = op(v, __uint_as_float(lane_xor<8>(__float_as_uint(v))));
+  v = op(v, __uint_as_float(lane_xor<4>(__float_as_uint(v))));
+  v = op(v, __uint_as_float(lane_xor<2>(__float_as_uint(v))));
+  return op(v, __uint_as_float(lane_xor<1>(__float_as_uint(v))));
 }
 // Entry `pos` of a permutation of 0..L-1 (null = identity).  Permutations are device data the
 // host cannot check: a value that is no index falls back to `pos`, so that a malformed

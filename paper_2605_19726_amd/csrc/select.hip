@@ -165,23 +165,14 @@ __global__ __launch_bounds__(256, 2) void block_scores_kernel(const uint4* __res
 // 128 x 128: 46.4 -> 14.1; 32 heads, 2 x 256: 45.2 -> 11.1.
 // ---------------------------------------------------------------------------------
 constexpr int kSmallTile = 64;              // rows and columns of the map per workgroup
-__device__ __forceinline__ void block_scores_small(int logical, const uint4* __restrict__ featQ,
-                                                   const uint4* __restrict__ featK, float* __restrict__ scores, int group,
-                                                   int Nq, int Nk, int K, int S) {
-  constexpr int kDepth = 4;
-  const int tiles_x = (Nk + kSmallTile - 1) / kSmallTile, tiles_y = (Nq + kSmallTile - 1) / kSmallTile;
-  const int bhq = logical / (tiles_x * tiles_y);
-  const int rem = logical - bhq * (tiles_x * tiles_y);
-  const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
-  const int bhk = bhq / group;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int li = lane & 31, h = lane >> 5;
-  const int row_base = ty * kSmallTile + (wave >> 1) * 32, col_base = tx * kSmallTile + (wave & 1) * 32;
-  if (row_base >= Nq || col_base >= Nk) return;
+// The tile of a wave: lane (i, h) brings row `row` and column `col` (past the end the last one is read, its results are
+// not to be used) and ends with column `col` of the rows 8 (r / 4) + 4 h + r % 4 of the tile.
+template <int kDepth>
+__device__ __forceinline__ floatx16 tile_logits(const uint4* __restrict__ featQ, const uint4* __restrict__ featK, int bhq, int bhk,
+                                                int row, int col, int h, int Nq, int Nk, int K, int S) {
   const int n_steps = K >> 4, groups = S >> 3;
-  // (rows and columns past the end read the last one; their results are never stored)
-  const uint4* fq = featQ + ((int64_t)bhq * 3 * groups + h) * Nq + min(row_base + li, Nq - 1);
-  const uint4* fk = featK + ((int64_t)bhk * 3 * groups + h) * Nk + min(col_base + li, Nk - 1);
+  const uint4* fq = featQ + ((int64_t)bhq * 3 * groups + h) * Nq + min(row, Nq - 1);
+  const uint4* fk = featK + ((int64_t)bhk * 3 * groups + h) * Nk + min(col, Nk - 1);
   uint4 a[kDepth][3], b[kDepth][3];
   auto load = [&](int s, uint4 (&ra)[3], uint4 (&rb)[3]) {
     const int64_t st = 2 * min(s, n_steps - 1);
@@ -208,8 +199,22 @@ __device__ __forceinline__ void block_scores_small(int logical, const uint4* __r
       load(s0 + i + kDepth, a[i], b[i]);
     }
   }
-  float* out = scores + (int64_t)bhq * Nq * Nk;
+  return acc;
+}
+__device__ __forceinline__ void block_scores_small(int logical, const uint4* __restrict__ featQ,
+                                                   const uint4* __restrict__ featK, float* __restrict__ scores, int group,
+                                                   int Nq, int Nk, int K, int S) {
+  const int tiles_x = (Nk + kSmallTile - 1) / kSmallTile, tiles_y = (Nq + kSmallTile - 1) / kSmallTile;
+  const int bhq = logical / (tiles_x * tiles_y);
+  const int rem = logical - bhq * (tiles_x * tiles_y);
+  const int ty = rem / tiles_x, tx = rem - ty * tiles_x;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int li = lane & 31, h = lane >> 5;
+  const int row_base = ty * kSmallTile + (wave >> 1) * 32, col_base = tx * kSmallTile + (wave & 1) * 32;
+  if (row_base >= Nq || col_base >= Nk) return;
   const int col = col_base + li;
+  const floatx16 acc = tile_logits<4>(featQ, featK, bhq, bhq / group, row_base + li, col, h, Nq, Nk, K, S);
+  float* out = scores + (int64_t)bhq * Nq * Nk;
   if (col >= Nk) return;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -241,9 +246,10 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+  return wave_reduce(v, [](float a, float b) { return a + b; });
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 __device__ __forceinline__ float float_of_ordered(uint32_t u) {
@@ -254,16 +260,13 @@ __device__ __forceinline__ float float_of_ordered(uint32_t u) {
 // its largest m' that sum to at least mass_target, at least min_keep and at most kappa; the
 // count is found first (a second bisection, on "mass of the logits >= T"), then the same
 // top-count machinery runs with the row's own count.
+// One wave, one row: src holds its Nk logits, in memory or in LDS.
 template <int MAXI, bool kLive>
-__device__ __forceinline__ void row_select(int block, const float* __restrict__ scores, int rows_total, int Nk, int kappa,
-                                           float mass_target, int min_keep, const int32_t* __restrict__ keep_in,
-                                           const LiveBlocks& live, uint32_t* __restrict__ mask_bits,
-                                           int32_t* __restrict__ row_count, int32_t* __restrict__ row_cols,
-                                           float* __restrict__ row_mass) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = block * 4 + wave;
-  if (row >= rows_total) return;
-  const float* src = scores + (int64_t)row * Nk;
+__device__ __forceinline__ void select_row(int row, const float* __restrict__ src, int Nk, int kappa, float mass_target, int min_keep,
+                                           const int32_t* __restrict__ keep_in, const LiveBlocks& live,
+                                           uint32_t* __restrict__ mask_bits, int32_t* __restrict__ row_count,
+                                           int32_t* __restrict__ row_cols, float* __restrict__ row_mass) {
+  const int lane = threadIdx.x & 63;
   // causal variant: a key block is live for this row iff its smallest original key index does not
   // exceed the row's largest original query index (+ offset); dead blocks take no part below
   const int32_t* kmin = kLive ? live.k_min + (int64_t)(row / live.Nq / live.group) * Nk : nullptr;
@@ -304,8 +307,7 @@ __device__ __forceinline__ void row_select(int block, const float* __restrict__ 
     u[i] = in_row ? ordered_bits(e[i]) : 0u;        // 0 is below the image of every float
     mx = fmaxf(mx, e[i]);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  mx = wave_max(mx);
   float sum_all = 0.f;
 #pragma unroll
   for (int i = 0; i < MAXI; ++i) {
@@ -339,8 +341,7 @@ __device__ __forceinline__ void row_select(int block, const float* __restrict__ 
       e_eq = fmaxf(e_eq, (u[i] == T2) ? e[i] : 0.f);
     }
     m_gt = wave_sum(m_gt);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) e_eq = fmaxf(e_eq, __shfl_xor(e_eq, off));
+    e_eq = wave_max(e_eq);
     int r = n_eq;
     if (e_eq > 0.f) r = min(n_eq, max(1, (int)ceilf((need - m_gt) / e_eq)));
     keep = min(kLive ? min(kappa, n_live) : kappa, max(max(1, min_keep), n_gt + r));
@@ -395,6 +396,18 @@ __device__ __forceinline__ void row_select(int block, const float* __restrict__ 
 }
 
 template <int MAXI, bool kLive>
+__device__ __forceinline__ void row_select(int block, const float* __restrict__ scores, int rows_total, int Nk, int kappa,
+                                           float mass_target, int min_keep, const int32_t* __restrict__ keep_in,
+                                           const LiveBlocks& live, uint32_t* __restrict__ mask_bits,
+                                           int32_t* __restrict__ row_count, int32_t* __restrict__ row_cols,
+                                           float* __restrict__ row_mass) {
+  const int row = block * 4 + (threadIdx.x >> 6);
+  if (row >= rows_total) return;
+  select_row<MAXI, kLive>(row, scores + (int64_t)row * Nk, Nk, kappa, mass_target, min_keep, keep_in, live, mask_bits, row_count,
+                          row_cols, row_mass);
+}
+
+template <int MAXI, bool kLive>
 __global__ __launch_bounds__(256) void row_select_kernel(const float* __restrict__ scores,
                                                          int rows_total, int Nk, int kappa,
                                                          float mass_target, int min_keep,
@@ -417,6 +430,68 @@ struct RowSelectJob {
                             nullptr);
   }
 };
+
+// ---------------------------------------------------------------------------------
+// Map and selection of short rows (at most 128 blocks) in one launch, for calls that their launches bound: eight waves own
+// strip_rows rows of a head's map.  Up to four of them compute a 32 x 32 tile each, as block_scores_small does (same bits;
+// what lies past the strip is dropped), the logits meet in LDS, and a wave selects every eighth row.  A row is a serial chain
+// of some 300 instructions, so that more than one to a wave shows: strips of 8 rows while each has a compute unit to itself (two
+// of these workgroups do not fit one), of 16 as long as those do, though every strip computes 32 rows of the map.  Selection
+// without the sort, two launches -> strips of 8 / 16 / 32 rows: 1 head, 16 x 16 blocks, d = 64: 19.7 -> 17.1 us / 16.8 / 16.9; 8 heads,
+// 32 x 32, d = 128: 23.8 -> 19.7 / 21.1 / 23.7; 16 heads, 128 x 128, d = 128 (256 strips of 8): 48.4 -> 44.4 / 46.2 / 50.0; 32 heads,
+// 128 x 128 (512; 256 of 16): 73.6 -> 79.0 / 71.2 / 73.9; 64 heads, 80 x 80, d = 64 (320 of 16): 55.3, 64.5 / 61.3 / 56.4.
+// Rows of up to 256 blocks lose: 32 heads, 2 x 256: 14.2 us in two launches, 19.1 in one, whose workgroups read 590 KB each.
+// ---------------------------------------------------------------------------------
+constexpr int kStripDepth = 8;               // k-steps in flight
+constexpr int kStripCols = 128, kStripWaves = 8, kMostStrips = 256;
+struct StripArgs {
+  const uint4 *fq, *fk;
+  int group, Nq, Nk, K, S, kappa, min_keep, strip_rows;
+  float mass_target;
+  LiveBlocks live;
+  uint32_t* mask_bits;
+  int32_t *row_count, *row_cols;
+  float* row_mass;
+};
+template <int MAXI, bool kLive>
+__device__ __forceinline__ void select_strip(int logical, const StripArgs& a) {
+  __shared__ float map[32][64 * MAXI + 8];               // (+ 8: rows four apart are half the banks apart)
+  const int strips = (a.Nq + a.strip_rows - 1) / a.strip_rows;
+  const int bhq = logical / strips, row_base = (logical - bhq * strips) * a.strip_rows;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int li = lane & 31, h = lane >> 5, col = wave * 32 + li;
+  if (wave * 32 < a.Nk) {
+    const floatx16 acc = tile_logits<kStripDepth>(a.fq, a.fk, bhq, bhq / a.group, row_base + li, col, h, a.Nq, a.Nk, a.K, a.S);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) map[8 * (r >> 2) + 4 * h + (r & 3)][col] = acc[r];
+  }
+  __syncthreads();
+  const int rows = min(a.strip_rows, a.Nq - row_base);
+#pragma nounroll
+  for (int r = wave; r < rows; r += kStripWaves)
+    select_row<MAXI, kLive>(bhq * a.Nq + row_base + r, map[r], a.Nk, a.kappa, a.mass_target, a.min_keep, nullptr, a.live, a.mask_bits,
+                            a.row_count, a.row_cols, a.row_mass);
+}
+template <int MAXI, bool kLive>
+__global__ __launch_bounds__(64 * kStripWaves, 1) void select_strip_kernel(StripArgs a) {
+  const int total = gridDim.x;
+  int logical = blockIdx.x;                     // one XCD, one range of heads
+  if ((total & 7) == 0) logical = (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3);
+  select_strip<MAXI, kLive>(logical, a);
+}
+template <int MAXI>
+struct StripJob {
+  StripArgs a;
+  __device__ __forceinline__ void run(int block) const { select_strip<MAXI, false>(block, a); }
+};
+// Rows per strip, 0: not in strips.
+template <class CountOfRows>
+int rows_of_strip(int widest, CountOfRows&& strips_of) {
+  if (widest > kStripCols) return 0;
+  for (int rows = 8; rows <= 16; rows += 8)
+    if (strips_of(rows) <= kMostStrips) return rows;
+  return 0;
+}
 
 // ---------------------------------------------------------------------------------
 // Score map and fixed-count row selection in ONE kernel: the map never leaves the chip
@@ -776,7 +851,7 @@ basa_status launch_block_scores(const void* featQ, const void* featK, float* sco
   return BASA_OK;
 }
 
-basa_status launch_block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st) {
+static basa_status block_scores_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, hipStream_t st) {
   Jobs<ScoresJob> jobs;
   for (int i = 0; i < n; ++i) {
     const SeqJob& s = seq[i];
@@ -803,7 +878,7 @@ static basa_status select_many(const SeqJob* seq, int n, float mass_target, int 
   BASA_HIP_CHECK_LAUNCH("row_select");
   return BASA_OK;
 }
-basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st) {
+static basa_status row_select_many(const SeqJob* seq, int n, float mass_target, int min_keep, hipStream_t st) {
   int widest = 0;
   for (int i = 0; i < n; ++i) widest = std::max(widest, seq[i].Nk);
   if (widest <= 256) return select_many<4>(seq, n, mass_target, min_keep, st);
@@ -811,6 +886,67 @@ basa_status launch_row_select_many(const SeqJob* seq, int n, float mass_target, 
   if (widest <= 1024) return select_many<16>(seq, n, mass_target, min_keep, st);
   if (widest <= 2048) return select_many<32>(seq, n, mass_target, min_keep, st);
   return select_many<64>(seq, n, mass_target, min_keep, st);
+}
+
+int select_strip_rows(int BHq, int Nq, int Nk) {
+  return rows_of_strip(Nk, [&](int rows) { return (int64_t)BHq * ceil_div(Nq, rows); });
+}
+
+basa_status launch_select_strip(const void* featQ, const void* featK, int BHq, int group, int Nq, int Nk, int kdim_used,
+                                int feat_stride, int kappa, float mass_target, int min_keep, const LiveBlocks& live,
+                                uint32_t* mask_bits, int32_t* row_count, int32_t* row_cols, float* row_mass, hipStream_t st) {
+  if (BHq == 0 || Nq == 0 || Nk == 0) return BASA_OK;
+  const int strip_rows = select_strip_rows(BHq, Nq, Nk);
+  if (strip_rows == 0 || kdim_used % 16 != 0 || feat_stride % 8 != 0) {
+    set_error("selection in strips: %d rows of %d heads against %d blocks, contraction length %d", Nq, BHq, Nk, kdim_used);
+    return BASA_ERR_UNSUPPORTED;
+  }
+  const StripArgs a{reinterpret_cast<const uint4*>(featQ), reinterpret_cast<const uint4*>(featK), group, Nq, Nk, kdim_used, feat_stride,
+                    kappa, min_keep, strip_rows, mass_target, live, mask_bits, row_count, row_cols, row_mass};
+  const dim3 grid(ceil_div(Nq, strip_rows) * BHq), block(64 * kStripWaves);
+  ProfScope prof(K_SCORES_SELECT, st);
+#define BASA_STRIP(M)                                                                            \
+  do {                                                                                           \
+    if (live.q_max) hipLaunchKernelGGL((select_strip_kernel<M, true>), grid, block, 0, st, a);   \
+    else hipLaunchKernelGGL((select_strip_kernel<M, false>), grid, block, 0, st, a);             \
+  } while (0)
+  if (Nk <= 64) BASA_STRIP(1);
+  else BASA_STRIP(2);
+#undef BASA_STRIP
+  BASA_HIP_CHECK_LAUNCH("select_strip_kernel");
+  return BASA_OK;
+}
+
+template <int MAXI>
+static basa_status strips_many(const SeqJob* seq, int n, int strip_rows, int kdim_used, int feat_stride, float mass_target,
+                               int min_keep, hipStream_t st) {
+  Jobs<StripJob<MAXI>> jobs;
+  for (int i = 0; i < n; ++i) {
+    const SeqJob& s = seq[i];
+    jobs.add(StripJob<MAXI>{StripArgs{reinterpret_cast<const uint4*>(s.feat_q), reinterpret_cast<const uint4*>(s.feat_k),
+                                      s.q.heads / s.k.heads, s.Nq, s.Nk, kdim_used, feat_stride, s.kappa, min_keep, strip_rows,
+                                      mass_target, LiveBlocks{}, nullptr, s.row_count, s.row_cols, nullptr}},
+             (int64_t)ceil_div(s.Nq, strip_rows) * s.q.heads);
+  }
+  ProfScope prof(K_SCORES_SELECT, st);
+  hipLaunchKernelGGL((many_kernel<StripJob<MAXI>, 1, 64 * kStripWaves>), dim3(jobs.first[n]), dim3(64 * kStripWaves), 0, st, jobs);
+  BASA_HIP_CHECK_LAUNCH("select_strip");
+  return BASA_OK;
+}
+basa_status launch_map_select_many(const SeqJob* seq, int n, int kdim_used, int feat_stride, float mass_target, int min_keep,
+                                   hipStream_t st) {
+  int widest = 0;
+  for (int i = 0; i < n; ++i) widest = std::max(widest, seq[i].Nk);
+  const int strip_rows = rows_of_strip(widest, [&](int rows) {
+    int64_t strips = 0;
+    for (int i = 0; i < n; ++i) strips += (int64_t)ceil_div(seq[i].Nq, rows) * seq[i].q.heads;
+    return strips;
+  });
+  if (strip_rows > 0 && kdim_used % 16 == 0 && feat_stride % 8 == 0)
+    return widest <= 64 ? strips_many<1>(seq, n, strip_rows, kdim_used, feat_stride, mass_target, min_keep, st)
+                        : strips_many<2>(seq, n, strip_rows, kdim_used, feat_stride, mass_target, min_keep, st);
+  const basa_status s = block_scores_many(seq, n, kdim_used, feat_stride, st);
+  return s != BASA_OK ? s : row_select_many(seq, n, mass_target, min_keep, st);
 }
 
 bool scores_select_supported(int Nk, int kdim_used, int feat_stride) {

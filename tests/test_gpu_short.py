@@ -575,3 +575,17 @@ def test_both_passes_over_the_rows_load_them_the_same_way(hq, hk, Lq, Lk, d, sor
     if not passes:
         pytest.skip("the profiler reports no kernels here")
     assert len(passes) >= 2 and all(p == streams for p in passes), [n[:120] for n in names]
+
+
+@pytest.mark.parametrize("kw", [{}, dict(causal=True), dict(mass_target=0.6, min_keep=2), dict(beta=0.0)])
+@pytest.mark.parametrize("hq,hk,n_q,n_k,d", [(2, 1, 1, 1, 64), (3, 1, 9, 33, 64), (8, 2, 33, 64, 128), (2, 2, 40, 65, 128),
+                                             (2, 1, 7, 128, 64), (32, 8, 65, 65, 64), (32, 32, 128, 127, 128), (33, 11, 128, 40, 64)])
+def test_map_and_selection_in_one_launch_against_two(hq, hk, n_q, n_k, d, kw):
+    """Strips of 8 and 16 rows and calls on both sides of their line: the lists, bitmaps and masses of the two launches."""
+    Q, K, _ = _qkv(hq, hk, 64 * n_q - 5, 64 * n_k - 9, d, torch.bfloat16, seed=n_q + n_k)
+    one, two = (bd.basa_select(Q, K, 64, 0.6, select_path=path, **kw) for path in (0, 1))
+    torch.cuda.synchronize()
+    for name in ("row_count", "mask_bits", "row_mass"):
+        assert torch.equal(getattr(one, name), getattr(two, name)), name
+    listed = torch.arange(two.row_cols.shape[-1], device=DEV) < two.row_count[..., None]
+    assert torch.equal(torch.where(listed, one.row_cols, -1), torch.where(listed, two.row_cols, -1))
