@@ -519,9 +519,9 @@ __global__ __launch_bounds__(kSortThreads) void merge_pass_kernel(const uint64_t
 }
 
 // ---------------------------------------------------------------------------------
-// The first merge passes in one: 16384 words (128 KB), four neighbouring sorted tiles of 4096 or sixteen of 1024
-// (kRun0), are brought into LDS, merged pairwise until they are one run, and written out once, so the words
-// cross the memory system one time less (three times with the small tiles).  1024 threads, 16 words each: a thread finds the start
+// The first two merge passes in one: 16384 words (128 KB), four neighbouring sorted tiles of 4096, are brought
+// into LDS, merged pairwise until they are one run, and written out once, so the words cross the memory system
+// one time less.  1024 threads, 16 words each: a thread finds the start
 // of its 16 consecutive outputs with a merge-path search in LDS, merges them into registers, and
 // the workgroup puts the registers back into LDS between the two levels.  Slots past the end of
 // the segment hold the all-ones word, which sorts last (no packed word has segment field 63).
@@ -529,7 +529,6 @@ __global__ __launch_bounds__(kSortThreads) void merge_pass_kernel(const uint64_t
 constexpr int kQuadThreads = 1024, kQuadItems = 16, kQuadWords = 4 * kTile;
 static_assert(kQuadThreads * kQuadItems == kQuadWords, "one word per thread and item");
 
-template <int kRun0>
 __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_t* __restrict__ in,
                                                                    uint64_t* __restrict__ out,
                                                                    int32_t* __restrict__ perm0,
@@ -579,7 +578,7 @@ __global__ __launch_bounds__(kQuadThreads) void merge_quads_kernel(const uint64_
     __syncthreads();
     const int d0 = t * kQuadItems;               // this thread's outputs d0 .. d0 + 15 at every level
 #pragma unroll
-    for (int run = kRun0; run <= 2 * kTile; run *= 2) {
+    for (int run = kTile; run <= 2 * kTile; run *= 2) {
       const int pb = d0 & ~(2 * run - 1);        // first word of the pair of runs these outputs belong to
       const uint64_t* A = quad + pb;
       const uint64_t* Bv = quad + pb + run;
@@ -678,6 +677,254 @@ __global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(Src src) {
   else out[hb + base + rank] = v;
 }
 
+// ---------------------------------------------------------------------------------
+// Up to 32 neighbouring runs of 1024 words into one, the outputs cut into parts of about `part_samples` x 64 words so that the
+// whole device takes part.  Every 64th word of a run is a sample; a part holds the words between two values that have a
+// given number of samples below them, which is at most 63 words a run more than asked for.  A workgroup finds its two
+// values by bisection (a wave holds all 512 samples, a step is eight compares and as many ballots), counts the words below
+// them in each run with one load per run and value, brings its 32 pieces into LDS and merges them pairwise there.
+// Bound by the chain of its phases (6 us until the pieces are in LDS, 2.5 us for each of four or five levels of merges), which two or
+// three workgroups to a compute unit overlap.  64 rows of 16384: 22 us where a workgroup for every 16384 words, on a quarter of
+// the compute units, took 36; 64 rows of 32768: 42 for 50 in two launches.  Dealing the words of a part to bins by value instead of
+// merging measured no faster (the keys above a run's last sample fill a few bins), nor did probing three points at a time.
+// ---------------------------------------------------------------------------------
+constexpr int kCutRuns = 32, kCutStride = kSmallTile / 16, kCutThreads = 512, kCutLevels = 5;
+constexpr int kCutWords = kCutRuns * kSmallTile;          // of a group
+constexpr int kMaxPartSamples = 48;
+constexpr int kCutCap = kMaxPartSamples * kCutStride + kCutRuns * (kCutStride - 1);
+constexpr int kCutItems = 8;                              // outputs of a slot; a thread has slots t and (large parts) t + 512
+// (a pair of runs leaves part of its last slot unused)
+static_assert((2 * kCutThreads - kCutRuns / 2) * kCutItems >= kCutCap, "outputs of the largest part");
+struct CutArgs {
+  const uint64_t* in;
+  uint64_t* out;
+  int32_t *perm0, *perm1;                  // null unless the last pass
+  int BH0;
+  SegGeom g;
+  int groups_per_seg, parts, part_samples; // parts: of a whole group
+};
+__device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
+  __shared__ uint64_t buf[kCutCap];
+  __shared__ int below[2][kCutRuns], start_of[kCutRuns + 1], slot_of[kCutLevels][kCutRuns / 2 + 1];
+  __shared__ uint64_t cut[2];
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const SegGeom& g = a.g;
+  int id = logical;
+  const int part = id % a.parts; id /= a.parts;
+  const int group = id % a.groups_per_seg; id /= a.groups_per_seg;
+  const int seg = id % g.segs, bh = id / g.segs;
+  const int a0 = seg * g.W + group * kCutWords;
+  const int n_group = min(kCutWords, min((seg + 1) * g.W, g.L) - a0);
+  const int samples_per_part = a.part_samples, part_words = samples_per_part * kCutStride;
+  if (part * part_words >= n_group) return;
+  const bool last_part = (part + 1) * part_words >= n_group;
+  const uint64_t* __restrict__ in = a.in + (int64_t)bh * g.L + a0;
+
+  // ---- samples: register j of lane l is sample l % 16 of run 4 j + l / 16
+  uint64_t s[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int pos = (j * 64 + lane) * kCutStride;
+    const uint64_t w = in[min(pos, n_group - 1)];
+    s[j] = pos < n_group ? w : ~0ull;
+  }
+  auto samples_below = [&](uint64_t v) {
+    int c = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) c += __popcll(__builtin_amdgcn_ballot_w64(s[j] < v));
+    return c;
+  };
+  // ---- waves 0 and 1: the value with part * samples_per_part samples below it, and the one of the next part
+  if (wave < 2) {
+    const int want = (part + wave) * samples_per_part;
+    uint64_t v = wave == 0 ? 0ull : ~0ull;
+    if (wave == 0 ? part > 0 : !last_part) {
+      // Sample k = want / runs of every run: the smallest has at most `want` samples below it, and behind the largest there are
+      // more (of runs that have it: where the last run is short that is checked).  The words are distinct, so some value in between
+      // has exactly `want`.
+      const int runs = (n_group + kSmallTile - 1) / kSmallTile, k = want / runs;
+      uint64_t lo = ~0ull, hi = 0ull;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        lo = s[j] < lo ? s[j] : lo;
+        hi = s[j] != ~0ull && s[j] > hi ? s[j] : hi;
+      }
+#pragma unroll
+      for (int off = 16; off < 64; off <<= 1) {
+        const uint64_t x = __shfl_xor((unsigned long long)lo, off), y = __shfl_xor((unsigned long long)hi, off);
+        lo = x < lo ? x : lo;
+        hi = y > hi ? y : hi;
+      }
+      auto of_lane = [&](uint64_t x) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, k) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), k) << 32;
+      };
+      lo = of_lane(lo);
+      hi = of_lane(hi) + 1;
+      if (samples_below(hi) < want) hi = ~0ull;
+      // below(lo) <= want <= below(hi); mostly lo is it already, the runs being much alike
+      v = lo;
+      int c = samples_below(v);
+      while (c != want) {
+        if (c > want) hi = v; else lo = v;
+        v = lo + ((hi - lo) >> 1);
+        c = samples_below(v);
+        if (v == lo && c != want) break;       // (cannot be: distinct words)
+      }
+    }
+    if (lane == 0) cut[wave] = v;
+  }
+  __syncthreads();
+
+  // ---- wave w: the words of runs 4 w .. 4 w + 3 below the two values.  With c samples of a run below, they end among the
+  // 63 words behind the last of these.
+  {
+    uint64_t w[2][4];
+    int from[2][4];
+    uint64_t mine = s[0];
+#pragma unroll
+    for (int j = 1; j < 8; ++j) mine = wave == j ? s[j] : mine;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const uint64_t b = __builtin_amdgcn_ballot_w64(mine < cut[e]);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = __popc((uint32_t)(b >> (16 * r)) & 0xffffu);
+        from[e][r] = (c - 1) * kCutStride;       // (c = 0: negative, none)
+        const int pos = (4 * wave + r) * kSmallTile + max(from[e][r], 0) + lane;
+        w[e][r] = in[min(pos, n_group - 1)];
+        if (pos >= n_group) w[e][r] = ~0ull;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = __popcll(__builtin_amdgcn_ballot_w64(w[e][r] < cut[e]));
+        if (lane == 0) below[e][4 * wave + r] = from[e][r] < 0 ? 0 : from[e][r] + c;
+      }
+  }
+  __syncthreads();
+
+  // ---- where the pieces go: piece r at start_of[r]; every wave works out the same
+  const int lb = lane < kCutRuns ? below[0][lane] : 0, ub = lane < kCutRuns ? below[1][lane] : 0;
+  int sum = ub - lb, skip = lb;
+#pragma unroll
+  for (int off = 1; off < kCutRuns; off <<= 1) {
+    const int x = __shfl_up(sum, off);
+    if (lane >= off) sum += x;
+  }
+#pragma unroll
+  for (int off = 1; off < kCutRuns; off <<= 1) skip += __shfl_xor(skip, off);
+  const int base = __builtin_amdgcn_readfirstlane(skip);
+  const int n = __builtin_amdgcn_readlane(sum, kCutRuns - 1);
+  const int before = __shfl_up(sum, 1), ends = lane == 0 ? 0 : before;       // lane r: of the pieces before r (32: of all)
+  if (wave == 7 && lane <= kCutRuns) start_of[lane] = ends;
+  if (wave < kCutLevels) {
+    const int pairs = kCutRuns / 2 >> wave, q = min(lane, pairs);
+    const int len = __shfl(ends, min(q + 1, pairs) << (wave + 1)) - __shfl(ends, q << (wave + 1));
+    int x = (len + kCutItems - 1) / kCutItems;
+#pragma unroll
+    for (int off = 1; off < kCutRuns / 2; off <<= 1) {
+      const int y = __shfl_up(x, off);
+      if (lane >= off) x += y;
+    }
+    if (lane < pairs) slot_of[wave][lane + 1] = x;
+    if (lane == 0) slot_of[wave][0] = 0;
+  }
+  {
+    int to[5], from[4];
+#pragma unroll
+    for (int r = 0; r < 5; ++r) to[r] = __builtin_amdgcn_readlane(ends, 4 * wave + r);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) from[r] = (4 * wave + r) * kSmallTile + __builtin_amdgcn_readlane(lb, 4 * wave + r) - to[r];
+    for (int i0 = to[0] + lane; i0 - lane < to[4]; i0 += 8 * 64) {
+      uint64_t w[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = min(i0 + e * 64, to[4] - 1);
+        w[e] = in[i + (i >= to[3] ? from[3] : i >= to[2] ? from[2] : i >= to[1] ? from[1] : from[0])];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (i0 + e * 64 < to[4]) buf[i0 + e * 64] = w[e];
+    }
+  }
+  __syncthreads();
+
+  // ---- pairwise merges in LDS.  A slot's eight outputs start at a point of the merge path; they are the smaller ones of
+  // the next eight words of one run, ascending, and the next eight of the other, descending, a bitonic sequence that three
+  // steps put in order: all sixteen reads are in flight together, where merging word by word waits for each.
+  const int runs = (n_group + kSmallTile - 1) / kSmallTile;
+#pragma unroll 1
+  for (int level = 0; 1 << level < runs; ++level) {
+    const int* slots = slot_of[level];
+    const int used = __builtin_amdgcn_readfirstlane(slots[kCutRuns / 2 >> level]);
+    uint64_t res[2][kCutItems];
+    int to[2], count[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int slot = t + e * kCutThreads;
+      count[e] = 0;
+      if (e * kCutThreads + (t & ~63) >= used) continue;     // uniform over the wave
+      int q = 0;
+      for (int step = kCutRuns / 4 >> level; step > 0; step >>= 1)
+        if (slots[q + step] <= slot) q += step;
+      const int b0 = start_of[q << (level + 1)], mid = start_of[(2 * q + 1) << level], end = start_of[(q + 1) << (level + 1)];
+      const int d0 = min((slot - slots[q]) * kCutItems, end - b0);
+      const int x = merge_path(buf + b0, mid - b0, buf + mid, end - mid, d0);
+      const int ia = b0 + x, ib = mid + d0 - x;
+      uint64_t o[kCutItems];
+#pragma unroll
+      for (int i = 0; i < kCutItems; ++i) {
+        res[e][i] = buf[min(ia + i, kCutCap - 1)];
+        o[i] = buf[min(ib + i, kCutCap - 1)];
+      }
+#pragma unroll
+      for (int i = 0; i < kCutItems; ++i) {
+        if (ia + i >= mid) res[e][i] = ~0ull;
+        if (ib + i >= end) o[i] = ~0ull;
+      }
+#pragma unroll
+      for (int i = 0; i < kCutItems; ++i) res[e][i] = o[kCutItems - 1 - i] < res[e][i] ? o[kCutItems - 1 - i] : res[e][i];
+#pragma unroll
+      for (int step = kCutItems / 2; step > 0; step >>= 1)
+#pragma unroll
+        for (int i = 0; i < kCutItems; ++i) {
+          if (i & step) continue;
+          const uint64_t v = res[e][i], w = res[e][i + step];
+          const bool swap = w < v;
+          res[e][i] = swap ? w : v;
+          res[e][i + step] = swap ? v : w;
+        }
+      to[e] = b0 + d0;
+      count[e] = min(kCutItems, end - b0 - d0);
+    }
+    __syncthreads();                         // everyone is done reading the pieces
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int i = 0; i < kCutItems; ++i)
+        if (i < count[e]) buf[to[e] + i] = res[e][i];
+    __syncthreads();
+  }
+  int32_t* perm_out = bh < a.BH0 ? a.perm0 : (a.perm1 ? a.perm1 - (int64_t)a.BH0 * g.L : nullptr);
+  const int64_t obase = (int64_t)bh * g.L + a0 + base;
+  if (perm_out) {
+    for (int i = t; i < n; i += kCutThreads) perm_out[obase + i] = idx_of_word(buf[i]);
+  } else {
+    for (int i = t; i < n; i += kCutThreads) a.out[obase + i] = buf[i];
+  }
+}
+__global__ __launch_bounds__(kCutThreads) void cut_merge_kernel(CutArgs a) {
+  const int total = gridDim.x;             // a head's words on one XCD
+  cut_merge(a, (total & 7) == 0 ? (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3) : blockIdx.x);
+}
+struct CutJob {
+  CutArgs a;
+  __device__ __forceinline__ void run(int block) const { cut_merge(a, block); }
+};
+
 __global__ void iota_kernel(int32_t* perm, int L, int64_t total) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < total) perm[i] = (int32_t)(i % L);
@@ -706,16 +953,40 @@ static SegGeom geom_of(int L, int window, int tile) {
   return g;
 }
 
+// Is a call's first merge the one that is cut by sampling?  Few words: from 3 x 2^17 on, where ranking takes two passes (sort,
+// ranking / cut: 8 rows of 32768: 39.5 / 40.1 us, 10: 51.6 / 49.1, 16: 66.4 / 53.3, 24 of 16384: 48.0 / 47.8, 32: 56.2 / 51.3).  More: wherever
+// runs have more than two tiles (quads of 16384 words in LDS and merge passes / cut: 64 rows of 32768 149 / 142, 32: 101 / 84, 64 of
+// 16384: 87 / 77, 64 of 8200: 78 / 62, 8 of 100000: 128 / 100).
+static bool cut_pays(int run, int64_t words, bool few) {
+  return few ? run > 8 * kSmallTile && words >= 3 << 17 : run > 2 * kSmallTile;
+}
+// Parts of 2048 words, of 3072 where those would be more than three to a compute unit (64 rows of 32768: 148 / 143 us; 40: 103 / 97,
+// 32: 83.5 / 84.6, 48 of 16384: 66 / 69).
+static CutArgs cut_args(const uint64_t* src, uint64_t* dst, int32_t* perm0, int32_t* perm1, int BH0, const SegGeom& g, int64_t words) {
+  const int samples = words <= (int64_t)3 * 256 * 32 * kCutStride ? 32 : kMaxPartSamples;
+  return CutArgs{src, dst, perm0, perm1, BH0, g, ceil_div(g.W, kCutWords), ceil_div(std::min(g.W, kCutWords), samples * kCutStride), samples};
+}
+
 // Sorted tiles in src merged into whole segments: BH rows (the first BH0 go to perm0, the rest to perm1).
 static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, const SegGeom& g, int tile, bool few,
                                int32_t* perm0, int32_t* perm1, hipStream_t st) {
   const int L = g.L;
+  int64_t sorted = tile;                       // words of a run
+  if (tile == kSmallTile && cut_pays(g.W, (int64_t)BH * L, few)) {
+    const bool last = g.W <= kCutWords;
+    const CutArgs args = cut_args(src, dst, last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, (int64_t)BH * L);
+    ProfScope prof(K_MERGE, st);
+    hipLaunchKernelGGL(cut_merge_kernel, dim3((unsigned)(BH * g.segs * args.groups_per_seg * args.parts)), dim3(kCutThreads), 0, st, args);
+    BASA_HIP_CHECK_LAUNCH("cut_merge_kernel");
+    uint64_t* t = src; src = dst; dst = t;
+    sorted = kCutWords;
+  }
   if (few) {
     // as few passes as groups of up to eight runs allow, each with the smallest group that keeps to that number
     const int chunks = ceil_div(L, kSortThreads);
     int passes = 0;
-    for (int64_t r = 1; r < ceil_div(g.W, tile); r *= 8) ++passes;
-    for (int64_t run = tile; run < g.W; --passes) {
+    for (int64_t r = 1; r < (g.W + sorted - 1) / sorted; r *= 8) ++passes;
+    for (int64_t run = sorted; run < g.W; --passes) {
       const int64_t runs = (g.W + run - 1) / run;
       int G = 2;
       while (G < 8 && (passes == 1 ? G : passes == 2 ? G * G : (int64_t)G * G * G) < runs) G *= 2;
@@ -734,26 +1005,20 @@ static basa_status merge_tiles(uint64_t* src, uint64_t* dst, int BH, int BH0, co
     }
     return BASA_OK;
   }
-  int run0 = tile;
-  if (g.W > 2 * tile) {
+  int run0 = (int)sorted;
+  if (sorted == kTile && g.W > 2 * kTile) {
     // more than two tiles per segment: the first two passes in one launch
     const bool last = kQuadWords >= g.W;
     const int quads_per_seg = ceil_div(g.W, kQuadWords);
     const int quads_total = BH * g.segs * quads_per_seg;
     // one quad per workgroup while there are compute units for all (64 quads: 21.7 us, two per workgroup 37)
     const int quad_wgs = quads_total <= 512 ? std::min(quads_total, 256) : ceil_div(quads_total, 2);
-#define BASA_QUADS(R)                                                                                            \
-  do {                                                                                                           \
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&merge_quads_kernel<R>),              \
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, kQuadWords * 8);        \
-    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");                                 \
-    ProfScope prof(K_MERGE, st);                                                                                 \
-    hipLaunchKernelGGL(merge_quads_kernel<R>, dim3(quad_wgs), dim3(kQuadThreads), kQuadWords * 8, st, src, dst,  \
-                       last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, quads_per_seg, quads_total);      \
-  } while (0)
-    if (tile == kTile) BASA_QUADS(kTile);
-    else BASA_QUADS(kSmallTile);
-#undef BASA_QUADS
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&merge_quads_kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, kQuadWords * 8);
+    if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
+    ProfScope prof(K_MERGE, st);
+    hipLaunchKernelGGL(merge_quads_kernel, dim3(quad_wgs), dim3(kQuadThreads), kQuadWords * 8, st, src, dst,
+                       last ? perm0 : nullptr, last ? perm1 : nullptr, BH0, g, quads_per_seg, quads_total);
     BASA_HIP_CHECK_LAUNCH("merge_quads_kernel");
     uint64_t* t = src; src = dst; dst = t;
     run0 = kQuadWords;
@@ -859,6 +1124,23 @@ static basa_status sort_many(const SeqJob* seq, int n, hipStream_t st) {
     ProfScope prof(K_NORM_TILE_SORT, st);
     hipLaunchKernelGGL(many_kernel<SmallSortJob<kD>>, dim3(jobs.first[n]), dim3(kSortThreads), 0, st, jobs);
     BASA_HIP_CHECK_LAUNCH("norm_tile_sort");
+  }
+  // (longer sequences than a group of the cut merge do not come here)
+  int64_t words = 0;
+  for (int i = 0; i < n; ++i) words += seq[i].q.L > kSmallTile ? (int64_t)seq[i].q.L * (seq[i].q.heads + seq[i].k.heads) : 0;
+  if (words >= 3 << 17 && longest <= kCutWords) {
+    Jobs<CutJob> jobs;
+    for (int i = 0; i < n; ++i) {
+      const int L = seq[i].q.L, rows = seq[i].q.heads + seq[i].k.heads;
+      if (L <= kSmallTile) continue;
+      uint64_t* src = reinterpret_cast<uint64_t*>(seq[i].sort_ws);
+      const CutArgs a = cut_args(src, nullptr, seq[i].perm_q, seq[i].perm_k, seq[i].q.heads, geom_of(L, 0, kSmallTile), words);
+      jobs.add(CutJob{a}, (int64_t)a.parts * rows);
+    }
+    ProfScope prof(K_MERGE, st);
+    hipLaunchKernelGGL((many_kernel<CutJob, 1, kCutThreads>), dim3(jobs.first[jobs.n]), dim3(kCutThreads), 0, st, jobs);
+    BASA_HIP_CHECK_LAUNCH("cut_merge");
+    return BASA_OK;
   }
   // groups of eight runs (four if that is enough) until the longest sequence is one run
   int pass = 0;

@@ -39,14 +39,15 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
     const int64_t count = tiles(rows0, L0) + (rows1 > 0 ? tiles(rows1, L1) : 0);
     return {true, count <= (short_tokens ? 640 : run <= 4 * 512 ? 400 : 256) ? 512 : kSmallTile};
   }
-  // Up to kMidWords the tiles stay at 1024 and the quads (16384 words in LDS) start from those: 4096-token tiles are one or two
-  // workgroups to a compute unit there, whose bitonic networks nothing hides.  Whole sort, d = 128, large tiles -> small: 1.0
+  // Up to kMidWords the tiles stay at 1024: 4096-token tiles are one or two workgroups to a compute unit there, whose bitonic networks
+  // nothing hides.  The figures below are of merges of sixteen tiles in one workgroup's LDS; the merge cut by samples that took their
+  // place (sort.hip) is 3 to 25 % faster on the small side of each.  Whole sort, d = 128, large tiles -> small: 1.0
   // million words in runs of 1024: 94 -> 52 us, 1500: 89 -> 75, 2048: 79 -> 60, 8300: 113 -> 99, 12000: 122 -> 97, 16384: 90 -> 88,
   // 32768: 105 -> 102; 2.1 million words: 1500: 140 -> 129, 16384: 139 -> 137.  (From 0.53 to 2.1 million words, runs of 8300 to
   // 65536, three types: 25 % faster to 6 % slower, the latter where the large tiles are just as many as the compute units.)
   if (words > kMidWords) return {false, kTile};
   if (run <= 2 * kSmallTile || run > 2 * kTile) return {false, kSmallTile};
-  // Shorter runs leave much of a quad empty.  One large tile is the whole run: 3000 tokens 86 us against 141 and 128 / 263 (1.0 and
+  // Shorter runs left much of the room for sixteen tiles empty.  One large tile is the whole run: 3000 tokens 86 us against 141 and 128 / 263 (1.0 and
   // 2.1 million words), 4096: 70 / 96 and 118 / 181.  Or two and a merge pass: small tiles only where the large ones are more than
   // one to a compute unit, the quads are not, and the small ones at most five (large / small, 128 runs, then 132: 5000: 74 / 82,
   // 101 / 82, 8192: 81 / 93, 112 / 102; 256 runs of 5000, then 260: 113 / 107, 145 / 148; 200 of 7000, then 230: 115 / 115, 119 / 127).

@@ -536,6 +536,25 @@ def test_sort_tiles_of_512_tokens(dtype, d, L, window):
         assert torch.equal(perm[0, :, a:b].long(), want)
 
 
+@pytest.mark.parametrize("heads,L", [(64, 8193), (16, 32768), (30, 32769), (41, 32767), (260, 2113), (6, 70000), (12, 33000)])
+@pytest.mark.parametrize("kind", ["spread", "few values", "ascending", "descending", "far outliers"])
+def test_merge_cut_by_samples(heads, L, kind):
+    """Parts whose bounds fall on few distinct keys, on runs that do not overlap at all, and far apart."""
+    x, _, _ = _qkv(heads, 1, L, 64, 64, torch.bfloat16, seed=L)
+    ramp = torch.linspace(0.01, 3.0, L, device=DEV)[None, None, :, None]
+    if kind == "few values":
+        x = x[:, :, :1].expand(-1, -1, L, -1).contiguous()
+        x[:, :, ::3] *= 2
+        x[:, :, L // 2:L // 2 + 3000] = 0
+    elif kind in ("ascending", "descending"):
+        x = ((ramp if kind == "ascending" else ramp.flip(2)) * torch.ones_like(x)).to(x.dtype)
+    elif kind == "far outliers":
+        x[:, :, ::50] *= 1000
+        x[:, :, 5::1000] = float("inf")
+    perm, keys = bd.basa_norm_sort(x, 64, return_keys=True)
+    assert torch.equal(perm[0].long(), torch.sort(keys[0], dim=-1, stable=True).indices)
+
+
 def test_packed_batch_repeats_what_left_the_safe_range():
     # 512 queries to a workgroup, scores near +-600 in one sequence: its workgroups go to the pass with running maxima
     lens, h, d = [565, 7627, 1977, 3390, 4802, 6215], 16, 128
