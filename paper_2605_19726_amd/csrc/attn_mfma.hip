@@ -1104,11 +1104,32 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   const int h_e = (tid_e >> 5) & 1;
   const int pos_e = wg * kQueriesPerWg + (tid_e >> 6) * kQPW + (tid_e & 31);
   int qpos_e[2];
-  if constexpr (kByIndex) {
-    __syncthreads();                           // (the positions are worked out in the ring, which others may still read)
-    positions_by_index(tid_e, qpos_e);
-  }
-  int unsafe = 0;                // kFast: some row of this lane has a sum outside the safe range
+  // Whether some row's sum left the safe range is settled before the rows are stored: the vote waits for all that the
+  // workgroup has in flight, and behind the stores that was their way to memory, with every compute unit writing at once.
+  if constexpr (kFast && !kRetry) {
+    int unsafe = 0;
+#pragma unroll
+    for (int r = 0; r < kNG; ++r) {
+      const float l_part = l_of(st, r), l_tot = l_part + __shfl_xor(l_part, 32);
+      // (causal: a query that sees no key of its list has the sum 0 and is done; there are one or two such queries
+      //  per head, and repeating their workgroups took 1210 us after the 8579 of this pass at 32 heads, L = 32768)
+      if ((kCausal ? q_lim[r] >= wk_min : pos_e + 32 * r < a.Lq) && sum_is_unsafe(l_tot)) unsafe = 1;
+    }
+    const int any = __syncthreads_or(unsafe);
+    if (tid_e == 0) a.redo[logical] = any;
+  } else {
+    __syncthreads();
+  }                                            // (the ring, which others may still read, is used below)
+  if constexpr (kByIndex) positions_by_index(tid_e, qpos_e);
+  // A lane holds four neighbouring dimensions of its query at a time: stored from there, an instruction touches 32 rows for 16
+  // bytes each (10.4 us of a workgroup's 125 at 32 heads, L = 16384, keep 10 %).  The rows of a group of queries therefore go through
+  // LDS, in the wave's own part of the ring (chunk c of row r at c ^ (r & (chunks per row - 1))), and are written as whole rows.
+  const int wave_e = __builtin_amdgcn_readfirstlane(tid_e >> 6), lane_e = tid_e & 63;
+  char* const area = smem + wave_e * 32 * G::kRowBytes;
+  char* const mine_e = area + (lane_e & 31) * G::kRowBytes;
+  const int swz_e = lane_e & (G::kChunksPerRow - 1);
+  constexpr int kRowsPerStore = 64 / G::kChunksPerRow;
+  const int sub_e = lane_e % G::kChunksPerRow, row_e = lane_e / G::kChunksPerRow;
 #pragma unroll
   for (int r = 0; r < kNG; ++r) {
     const float l_part = l_of(st, r), m_fin = m_of(st, r);
@@ -1116,28 +1137,32 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;    // a query block without any valid key block: zeros
     int pos = pos_e + 32 * r;
     if constexpr (kByIndex) pos = qpos_e[r];
-    // (causal: a query that sees no key of its list has the sum 0 and is done; there are one or two such queries
-    //  per head, and repeating their workgroups took 1210 us after the 8579 of this pass at 32 heads, L = 32768)
-    if (kFast && !kRetry && pos < a.Lq && (!kCausal || q_lim[r] >= wk_min) && sum_is_unsafe(l_tot)) unsafe = 1;
     const int h = h_e;
     if constexpr (kSplit) {
-      if (pos < a.Lq) {
-        const int64_t prow = ((int64_t)split * (a.total_wgs / (a.splits * a.wgs_per_head)) + bhq) * a.Lq + pos;
-        float* po = a.part_o + prow * D;
+      const int64_t row0 = ((int64_t)split * (a.total_wgs / (a.splits * a.wgs_per_head)) + bhq) * a.Lq;
+      const int to = pos < a.Lq ? pos : -1;
+      if (to >= 0 && h == 0) a.part_ml[row0 + pos] = make_float2(m_fin, l_tot);
+      // (fp32: half a row at a time)
 #pragma unroll
-        for (int db = 0; db < G::kDBlocks; ++db)
+      for (int half = 0; half < 2; ++half) {
+#pragma unroll
+        for (int db = 0; db < G::kDBlocks / 2; ++db)
 #pragma unroll
           for (int r4 = 0; r4 < 4; ++r4) {
             floatx4 t;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) t[e] = o_of(st, r, db)[4 * r4 + e];
-            *reinterpret_cast<floatx4*>(po + 32 * db + 8 * r4 + 4 * h) = t;
+            for (int e = 0; e < 4; ++e) t[e] = o_of(st, r, half * (G::kDBlocks / 2) + db)[4 * r4 + e];
+            *reinterpret_cast<floatx4*>(mine_e + (((8 * db + 2 * r4 + h) ^ swz_e) << 4)) = t;
           }
-        if (h == 0) a.part_ml[prow] = make_float2(m_fin, l_tot);
+#pragma unroll
+        for (int i = 0; i < 32 / kRowsPerStore; ++i) {
+          const int row = i * kRowsPerStore + row_e, at = __shfl(to, row);
+          const floatx4 t = *reinterpret_cast<const floatx4*>(area + row * G::kRowBytes + ((sub_e ^ (row & (G::kChunksPerRow - 1))) << 4));
+          if (at >= 0) *reinterpret_cast<floatx4*>(a.part_o + (row0 + at) * D + half * (D / 2) + 4 * sub_e) = t;
+        }
       }
-    } else if (pos < a.Lq) {
-      const int orow = perm_at(a.perm_q, (int64_t)bhq * a.Lq, pos, a.Lq);
-      __bf16* op = a.out + out_off(a, bhq, orow);
+    } else {
+      const int orow = pos < a.Lq ? perm_at(a.perm_q, (int64_t)bhq * a.Lq, pos, a.Lq) : -1;
 #pragma unroll
       for (int db = 0; db < G::kDBlocks; ++db)
 #pragma unroll
@@ -1145,15 +1170,18 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
           bf16x4 pk;
 #pragma unroll
           for (int e = 0; e < 4; ++e) pk[e] = (__bf16)(o_of(st, r, db)[4 * r4 + e] * inv_l);
-          *reinterpret_cast<bf16x4*>(op + 32 * db + 8 * r4 + 4 * h) = pk;
+          *reinterpret_cast<bf16x4*>(mine_e + (((4 * db + r4) ^ swz_e) << 4) + 8 * h) = pk;
         }
-      if (a.lse && h == 0)
+      __bf16* const out_head = a.out + out_off(a, bhq, 0);
+#pragma unroll
+      for (int i = 0; i < 32 / kRowsPerStore; ++i) {
+        const int row = i * kRowsPerStore + row_e, at = __shfl(orow, row);
+        const bf16x8 t = *reinterpret_cast<const bf16x8*>(area + row * G::kRowBytes + ((sub_e ^ (row & (G::kChunksPerRow - 1))) << 4));
+        if (at >= 0) *reinterpret_cast<bf16x8*>(out_head + (int64_t)at * a.out_sl + 8 * sub_e) = t;
+      }
+      if (a.lse && h == 0 && orow >= 0)
         a.lse[(int64_t)bhq * a.Lq + orow] = (m_fin + __log2f(l_tot)) * 0.6931471805599453f;
     }
-  }
-  if constexpr (kFast && !kRetry) {
-    const int any = __syncthreads_or(unsafe);
-    if (threadIdx.x == 0) a.redo[logical] = any;
   }
 }
 
