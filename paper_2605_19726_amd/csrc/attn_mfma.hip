@@ -1132,7 +1132,9 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   const int sub_e = lane_e % G::kChunksPerRow, row_e = lane_e / G::kChunksPerRow;
 #pragma unroll
   for (int r = 0; r < kNG; ++r) {
-    const float l_part = l_of(st, r), m_fin = m_of(st, r);
+    float l_part = l_of(st, r);
+    const float m_fin = m_of(st, r);
+    asm volatile("" : "+v"(l_part));             // (its exchange stays behind the barrier, which would have to wait for it)
     const float l_tot = l_part + __shfl_xor(l_part, 32);
     const float inv_l = l_tot > 0.f ? 1.0f / l_tot : 0.f;    // a query block without any valid key block: zeros
     int pos = pos_e + 32 * r;
