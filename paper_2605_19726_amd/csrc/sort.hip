@@ -417,7 +417,8 @@ struct SmallSortJob {
 // One workgroup produces kMergeChunk consecutive outputs of one pair, located with a
 // merge-path search on the pair's two runs.
 // ---------------------------------------------------------------------------------
-__device__ __forceinline__ int merge_path(const uint64_t* A, int na, const uint64_t* Bv, int nb, int diag) {
+template <class T>
+__device__ __forceinline__ int merge_path(const T* A, int na, const T* Bv, int nb, int diag) {
   int lo = max(0, diag - nb), hi = min(diag, na);
   while (lo < hi) {
     int mid = (lo + hi) >> 1;
@@ -429,9 +430,9 @@ __device__ __forceinline__ int merge_path(const uint64_t* A, int na, const uint6
 // The same on LDS, word i at slot i + i / kPer: the threads of a wave start kPer outputs apart, and without the pad their
 // reads and writes meet in a few banks (4 x 10^6 words: 18.4 -> 16.9 us a pass).
 template <int kPer>
-__device__ __forceinline__ int padded(int i) { return i + i / kPer; }
-template <int kPer>
-__device__ __forceinline__ int merge_path_lds(const uint64_t* buf, int a0, int na, int b0, int nb, int diag) {
+__host__ __device__ constexpr __forceinline__ int padded(int i) { return i + i / kPer; }
+template <int kPer, class T>
+__device__ __forceinline__ int merge_path_lds(const T* buf, int a0, int na, int b0, int nb, int diag) {
   int lo = max(0, diag - nb), hi = min(diag, na);
   while (lo < hi) {
     const int mid = (lo + hi) >> 1;
@@ -695,6 +696,29 @@ constexpr int kCutCap = kMaxPartSamples * kCutStride + kCutRuns * (kCutStride - 
 constexpr int kCutItems = 8;                              // outputs of a slot; a thread has slots t and (large parts) t + 512
 // (a pair of runs leaves part of its last slot unused)
 static_assert((2 * kCutThreads - kCutRuns / 2) * kCutItems >= kCutCap, "outputs of the largest part");
+// In LDS a word is [0][segment : 6][key : 31][index : 26], which as a double is positive and finite and orders as before: the vector
+// unit has a minimum and a maximum of doubles, but none of 64-bit integers (whole sort, with the padding of the slots: 64 rows of 32768 142 -> 138 us, 32: 82.9 -> 80.8, 64 of 16384: 76.8 -> 75.4).
+constexpr int kCutIdxBits = kIdxBits - 1;
+__device__ __forceinline__ double to_double(uint64_t w) {
+  constexpr uint64_t kIdx = (1ull << kCutIdxBits) - 1;
+  return __longlong_as_double((long long)((w >> 1 & ~kIdx) | (w & kIdx)));
+}
+__device__ __forceinline__ int32_t idx_of_double(double x) { return (int32_t)((uint32_t)__double_as_longlong(x) & ((1u << kCutIdxBits) - 1u)); }
+__device__ __forceinline__ uint64_t to_word(double x) {
+  const uint64_t w = (uint64_t)__double_as_longlong(x);
+  return (w >> kCutIdxBits << kIdxBits) | (w & ((1ull << kCutIdxBits) - 1));
+}
+// (written out: the library's minimum first quiets NaNs, which there are none of, with another instruction for each operand)
+__device__ __forceinline__ double min_of(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double max_of(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 struct CutArgs {
   const uint64_t* in;
   uint64_t* out;
@@ -704,11 +728,12 @@ struct CutArgs {
   int groups_per_seg, parts, part_samples; // parts: of a whole group
 };
 __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
-  __shared__ uint64_t buf[kCutCap];
+  __shared__ double buf[padded<kCutItems>(kCutCap + kCutItems)];      // (a slot reads eight words on, past the last piece too)
   __shared__ int below[2][kCutRuns], start_of[kCutRuns + 1], slot_of[kCutLevels][kCutRuns / 2 + 1];
   __shared__ uint64_t cut[2];
   const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const SegGeom& g = a.g;
+  auto at = [](int i) { return padded<kCutItems>(i); };      // (a slot's words in banks of their own)
   int id = logical;
   const int part = id % a.parts; id /= a.parts;
   const int group = id % a.groups_per_seg; id /= a.groups_per_seg;
@@ -847,7 +872,7 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (i0 + e * 64 < to[4]) buf[i0 + e * 64] = w[e];
+        if (i0 + e * 64 < to[4]) buf[at(i0 + e * 64)] = to_double(w[e]);
     }
   }
   __syncthreads();
@@ -860,7 +885,7 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
   for (int level = 0; 1 << level < runs; ++level) {
     const int* slots = slot_of[level];
     const int used = __builtin_amdgcn_readfirstlane(slots[kCutRuns / 2 >> level]);
-    uint64_t res[2][kCutItems];
+    double res[2][kCutItems];
     int to[2], count[2];
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
@@ -872,30 +897,31 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
         if (slots[q + step] <= slot) q += step;
       const int b0 = start_of[q << (level + 1)], mid = start_of[(2 * q + 1) << level], end = start_of[(q + 1) << (level + 1)];
       const int d0 = min((slot - slots[q]) * kCutItems, end - b0);
-      const int x = merge_path(buf + b0, mid - b0, buf + mid, end - mid, d0);
+      const int x = merge_path_lds<kCutItems>(buf, b0, mid - b0, mid, end - mid, d0);
       const int ia = b0 + x, ib = mid + d0 - x;
-      uint64_t o[kCutItems];
+      double o[kCutItems];
 #pragma unroll
       for (int i = 0; i < kCutItems; ++i) {
-        res[e][i] = buf[min(ia + i, kCutCap - 1)];
-        o[i] = buf[min(ib + i, kCutCap - 1)];
+        res[e][i] = buf[at(ia + i)];
+        o[i] = buf[at(ib + i)];
+      }
+      if (__builtin_amdgcn_ballot_w64(ia + kCutItems > mid || ib + kCutItems > end) != 0) {
+#pragma unroll
+        for (int i = 0; i < kCutItems; ++i) {
+          if (ia + i >= mid) res[e][i] = INFINITY;
+          if (ib + i >= end) o[i] = INFINITY;
+        }
       }
 #pragma unroll
-      for (int i = 0; i < kCutItems; ++i) {
-        if (ia + i >= mid) res[e][i] = ~0ull;
-        if (ib + i >= end) o[i] = ~0ull;
-      }
-#pragma unroll
-      for (int i = 0; i < kCutItems; ++i) res[e][i] = o[kCutItems - 1 - i] < res[e][i] ? o[kCutItems - 1 - i] : res[e][i];
+      for (int i = 0; i < kCutItems; ++i) res[e][i] = min_of(res[e][i], o[kCutItems - 1 - i]);
 #pragma unroll
       for (int step = kCutItems / 2; step > 0; step >>= 1)
 #pragma unroll
         for (int i = 0; i < kCutItems; ++i) {
           if (i & step) continue;
-          const uint64_t v = res[e][i], w = res[e][i + step];
-          const bool swap = w < v;
-          res[e][i] = swap ? w : v;
-          res[e][i + step] = swap ? v : w;
+          const double v = res[e][i], w = res[e][i + step];
+          res[e][i] = min_of(v, w);
+          res[e][i + step] = max_of(v, w);
         }
       to[e] = b0 + d0;
       count[e] = min(kCutItems, end - b0 - d0);
@@ -905,15 +931,15 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
     for (int e = 0; e < 2; ++e)
 #pragma unroll
       for (int i = 0; i < kCutItems; ++i)
-        if (i < count[e]) buf[to[e] + i] = res[e][i];
+        if (i < count[e]) buf[at(to[e] + i)] = res[e][i];
     __syncthreads();
   }
   int32_t* perm_out = bh < a.BH0 ? a.perm0 : (a.perm1 ? a.perm1 - (int64_t)a.BH0 * g.L : nullptr);
   const int64_t obase = (int64_t)bh * g.L + a0 + base;
   if (perm_out) {
-    for (int i = t; i < n; i += kCutThreads) perm_out[obase + i] = idx_of_word(buf[i]);
+    for (int i = t; i < n; i += kCutThreads) perm_out[obase + i] = idx_of_double(buf[at(i)]);
   } else {
-    for (int i = t; i < n; i += kCutThreads) a.out[obase + i] = buf[i];
+    for (int i = t; i < n; i += kCutThreads) a.out[obase + i] = to_word(buf[at(i)]);
   }
 }
 __global__ __launch_bounds__(kCutThreads) void cut_merge_kernel(CutArgs a) {
