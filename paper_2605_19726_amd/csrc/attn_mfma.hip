@@ -48,6 +48,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef short short4v __attribute__((ext_vector_type(4)));
 
 constexpr float kLazyTau = 8.0f;            // log2 of the largest exponentiated score kept
 // Running maximum (log2 units) of a query that has met no score above -inf yet: below every finite one (a float times
@@ -307,6 +308,12 @@ struct MfmaArgs {
   float2* part_ml;           //   [split][BHq][Lq] running maximum (log2), running sum
 };
 
+// kGather: where the rows of the tiles are read from, in the order of perm_k (nullable).
+struct RowSource {
+  TensorView k, v;
+  const int32_t* perm_k;
+};
+
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
 
@@ -329,14 +336,39 @@ struct WaveState {
 // -inf), so no NaN canonicalisation is emitted and this becomes one v_max3_f32.
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
+// LDS byte address of a pointer into the workgroup's shared memory, and a 16-byte fragment read at one.
+typedef const __attribute__((address_space(3))) char* lds_cptr_t;
+typedef const __attribute__((address_space(3))) bf16x8* lds_frag_ptr_t;
+__device__ __forceinline__ uint32_t lds_addr(const char* p) { return (uint32_t)(uintptr_t)(lds_cptr_t)p; }
+__device__ __forceinline__ bf16x8 lds_frag(uint32_t addr) { return *(lds_frag_ptr_t)(uintptr_t)addr; }
+typedef __attribute__((address_space(3))) short4v* lds_quad_ptr_t;
+__device__ __forceinline__ bf16x4 lds_transposed(uint32_t addr) {
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_quad_ptr_t)(uintptr_t)addr));
+}
+__device__ const uint4 kZeroRow[16] = {};         // the row of a key that does not exist
+
 // One 64-key tile: S^T, softmax, O^T update, reading the LDS stage at `stage`.  kMasked:
 // keys at tile positions >= nvalid do not exist (ragged end of the sequence) and get -inf.
 // kFast: no maximum is taken, the arithmetic of process_tile2's kFast form step by step (same bits).
-template <bool kMasked, int D, bool kFast>
+// kGather: V as it stands in memory, one row of D values per key; vaddr0 is then row 4h + (lane / 4) % 4, chunk 2 (lane / 16 % 2) +
+// lane % 4 / 2, half lane % 2 of it, where chunk c of row r sits at c ^ 4 (r & 3) (D = 64: c ^ 4 (r / 2 & 1)).
+template <bool kMasked, int D, bool kFast, bool kGather>
 __device__ __forceinline__ void process_tile(WaveState<D>& st, const bf16x8 (&qf)[Geo<D>::kKSteps], const char* stage,
                                              int kaddr0, int vaddr0, float c, int nvalid, int h) {
   const char* ks = stage;
   const char* vs = stage + Geo<D>::kTileBytes;
+  // V^T of 16 keys (group g of the tile) and 32 dimensions: a lane's dimension, its eight keys in operand-slot order.  From rows
+  // of V the transposing read gives lane i of 16 column i of the four rows that the 16 lanes address.
+  auto vt_frag = [&](int g, int db) -> bf16x8 {
+    if constexpr (kGather) {
+      const uint32_t at = lds_addr(vs) + ((uint32_t)vaddr0 ^ (uint32_t)(db << 6)) + g * 16 * Geo<D>::kRowBytes;
+      const bf16x4 lo = lds_transposed(at), hi = lds_transposed(at + 8 * Geo<D>::kRowBytes);
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      // chunk 2g+h of d-row li at position (2g+h) ^ ((li>>1)&7)
+      return *reinterpret_cast<const bf16x8*>(vs + (vaddr0 ^ (g << 5)) + db * 32 * 128);
+    }
+  };
 
   // ---- S^T = K Q^T : two 32-key row blocks
   floatx16 s0 = {0}, s1 = {0};
@@ -387,10 +419,9 @@ __device__ __forceinline__ void process_tile(WaveState<D>& st, const bf16x8 (&qf
       st.lt = la;
 #pragma unroll
       for (int g = 0; g < 2; ++g) {
-        const int va = vaddr0 ^ ((2 * half + g) << 5);
 #pragma unroll
         for (int db = 0; db < Geo<D>::kDBlocks; ++db) {
-          const bf16x8 vv = *reinterpret_cast<const bf16x8*>(vs + va + db * 32 * 128);
+          const bf16x8 vv = vt_frag(2 * half + g, db);
           st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, pb[g], st.o[db], 0, 0, 0);
         }
       }
@@ -435,20 +466,13 @@ __device__ __forceinline__ void process_tile(WaveState<D>& st, const bf16x8 (&qf
   // ---- O^T += V^T P^T
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
-    const int va = vaddr0 ^ (g << 5);     // chunk 2g+h of d-row li at position (2g+h) ^ ((li>>1)&7)
 #pragma unroll
     for (int db = 0; db < Geo<D>::kDBlocks; ++db) {
-      const bf16x8 vv = *reinterpret_cast<const bf16x8*>(vs + va + db * 32 * 128);
+      const bf16x8 vv = vt_frag(g, db);
       st.o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vv, pb[g], st.o[db], 0, 0, 0);
     }
   }
 }
-
-// LDS byte address of a pointer into the workgroup's shared memory, and a 16-byte fragment read at one.
-typedef const __attribute__((address_space(3))) char* lds_cptr_t;
-typedef const __attribute__((address_space(3))) bf16x8* lds_frag_ptr_t;
-__device__ __forceinline__ uint32_t lds_addr(const char* p) { return (uint32_t)(uintptr_t)(lds_cptr_t)p; }
-__device__ __forceinline__ bf16x8 lds_frag(uint32_t addr) { return *(lds_frag_ptr_t)(uintptr_t)addr; }
 
 // Two query groups per wave (64 queries): the same arithmetic per query, but every K and V^T
 // fragment read from LDS feeds two MFMAs (one per group), and the 64-key tile is walked as two
@@ -653,10 +677,13 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
 // left out, 7209 without the masks that mask nothing.
 // kSplit: a.splits workgroups share the query blocks and take equal runs of the union list each; their rows
 // stay unnormalised and attn_combine_kernel adds them up.
-template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit>
-__device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
+// kGather (128-query shape): no tiles are laid out beforehand; the rows of K and V are fetched straight from the caller's
+// tensors (the source address of a lane of a direct-to-LDS load is free), and V^T fragments come from rows of V.
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit, bool kGather = false>
+__device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const RowSource* src = nullptr) {
   using G = Geo<D>;
   static_assert(!kCausal || (kQPW == 64 && kWgQueries == kWideQueries), "the causal path is built on the 512-query shape");
+  static_assert(!kGather || (kQPW == 32 && kWgQueries == kSoloQueries), "rows are gathered by the 128-query shape");
   static_assert(!kFast || !kSplit, "the safe range of a row's sum is tested on the whole sum");
   static_assert(!kFast || (kQPW == 64 && kWgQueries == kWideQueries) || (kQPW == 32 && kWgQueries == kSoloQueries),
                 "the pass without running maxima is built on the 512-query and the 128-query shape");
@@ -860,7 +887,52 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   };
   // direct-to-LDS copy of tile `tile` into ring stage `stage`: 32 chunks of 1 KB, chunk
   // j*kWaves+wave by this wave (16 K chunks, then 16 V chunks)
+  // kGather: this lane's rows of a tile (those of its K chunks, and of its V chunks again), requested a tile ahead
+  constexpr int kRowsPerLane = kLoadsPerWave / 2, kRowsPerLoad = 64 / G::kChunksPerRow;
+  int rows[kGather ? kRowsPerLane : 1];
+  auto pos_of = [&](int tile, int j) { return tile * kTileKeys + (j * kWaves + wave) * kRowsPerLoad + lane / G::kChunksPerRow; };
+  auto request_rows = [&](int tile) {
+    if constexpr (kGather) {
+      if (src->perm_k) {
+        const int32_t* pm = src->perm_k + (int64_t)bhk * a.Lk;
+#pragma unroll
+        for (int j = 0; j < kRowsPerLane; ++j) rows[j] = pm[(uint32_t)min(pos_of(tile, j), a.Lk - 1)];
+      } else {
+#pragma unroll
+        for (int j = 0; j < kRowsPerLane; ++j) rows[j] = min(pos_of(tile, j), a.Lk - 1);
+      }
+    }
+  };
+  auto issue_rows = [&](int tile, int stage) {             // the rows of `tile` have been requested
+    const char* kh = reinterpret_cast<const char*>(src->k.ptr) + src->k.head_offset(bhk) * 2;
+    const char* vh = reinterpret_cast<const char*>(src->v.ptr) + src->v.head_offset(bhk) * 2;
+    const uint32_t k_row = (uint32_t)src->k.stride_l * 2, v_row = (uint32_t)src->v.stride_l * 2;
+    // (the places of a lane's chunks are the same in every tile and for every j)
+    const int chunk = lane % G::kChunksPerRow, r = wave * kRowsPerLoad + lane / G::kChunksPerRow;
+    const uint32_t kc = (uint32_t)(chunk ^ (r & (G::kChunksPerRow - 1))) * 16, vc = (uint32_t)(chunk ^ (D == 128 ? 4 * (r & 3) : 4 * (r >> 1 & 1))) * 16;
+    char* dst = smem + stage * kStageBytes + wave * 1024;
+    uint32_t at[kRowsPerLane];
+#pragma unroll
+    for (int j = 0; j < kRowsPerLane; ++j) {
+      const int got = rows[kGather ? j : 0];
+      at[j] = (unsigned)got < (unsigned)a.Lk ? got : min(pos_of(tile, j), a.Lk - 1);     // (as perm_at)
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)(kh + (__umul24(at[j], k_row) + kc)), (lds_ptr_t)(dst + j * kWaves * 1024), 16, 0, 0);
+    }
+    if ((tile + 1) * kTileKeys <= a.Lk) {                  // uniform
+#pragma unroll
+      for (int j = 0; j < kRowsPerLane; ++j)
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(vh + (__umul24(at[j], v_row) + vc)), (lds_ptr_t)(dst + kTileBytes + j * kWaves * 1024), 16, 0, 0);
+    } else {
+      // (keys that do not exist: their probability is 0, which an infinity would not survive)
+#pragma unroll
+      for (int j = 0; j < kRowsPerLane; ++j) {
+        const char* from = pos_of(tile, j) < a.Lk ? vh + (__umul24(at[j], v_row) + vc) : reinterpret_cast<const char*>(kZeroRow);
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)from, (lds_ptr_t)(dst + kTileBytes + j * kWaves * 1024), 16, 0, 0);
+      }
+    }
+  };
   auto issue_tile = [&](int tile, int stage) {
+    if constexpr (kGather) { issue_rows(tile, stage); return; }
     // (kept in registers the lane offset becomes three 64-bit addresses, and Q^T fragments go to scratch for them)
     const int lane_i = kSpans || kCausal ? fresh_lane() : lane;
     const char* kp = Kh + (int64_t)tile * kTileBytes;      // wave-uniform bases
@@ -887,7 +959,9 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
 
   // prologue: the first tile (SHARED: the first pair; past the end: the last tile again, never read)
   auto issue_first = [&]() {
+    request_rows(tile_of(0));
     issue_tile(tile_of(0), 0);
+    request_rows(tile_of(1));
     if (kStages == 4) issue_tile(tile_of(1), 1);
   };
   issue_first();
@@ -897,7 +971,10 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   // position (2s+h) ^ (li & 15).  V^T: d-row li (+32 db), chunk 2g+h at (2g+h) ^ ((li>>1)&7).
   // (step s / group g are folded in by xor with s<<5 / g<<5 at the point of use)
   const int kaddr = li * G::kRowBytes + ((h ^ (li & (G::kChunksPerRow - 1))) << 4);
-  const int vaddr = li * 128 + ((h ^ ((li >> 1) & 7)) << 4);
+  const int vquad = lane >> 2 & 3;
+  const int vaddr = kGather ? (4 * h + vquad) * G::kRowBytes +
+                                  (((2 * (lane >> 4 & 1) + (lane >> 1 & 1)) ^ (D == 128 ? 4 * vquad : 4 * (vquad >> 1))) << 4) + 8 * (lane & 1)
+                            : li * 128 + ((h ^ ((li >> 1) & 7)) << 4);
 
   typename StateOf<D, kNG>::type st;
   init_state<D>(st, kFast);
@@ -929,7 +1006,7 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   };
   auto tile = [&](auto masked, int stage_no, int nvalid, auto fast) {
     const char* stage = smem + stage_no * kStageBytes;
-    if constexpr (kNG == 1) process_tile<decltype(masked)::value, D, decltype(fast)::value>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
+    if constexpr (kNG == 1) process_tile<decltype(masked)::value, D, decltype(fast)::value, kGather>(st, qf[0], stage, kaddr, vaddr, c, nvalid, h);
     else {
       // the lane half is needed by the masking code only (ragged tile, causal mask): taken from the
       // lane number there, it does not occupy a register through the main loop
@@ -1076,6 +1153,7 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
         const uint32_t raw_n = seq[(t + 1) / TPB];
         const uint32_t e_nxt = (uint32_t)__builtin_amdgcn_readfirstlane((int)raw_n);
         issue_tile((int)(e_nxt & 0xffffffu) * TPB + ((t + 1) % TPB), (t + 1) & 1);
+        request_rows(tile_of(t + 2));
         if (e_cur & my_bit) tile(kFull, t & 1, kTileKeys, fast);
         e_cur = e_nxt;
       }
@@ -1187,13 +1265,18 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical) {
   }
 }
 
+// XCD-aware order: consecutive workgroup ids go round-robin over the 8 XCDs; give each
+// XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
+__device__ __forceinline__ int xcd_order(int total) {
+  return (total & 7) == 0 ? (blockIdx.x & 7) * (total >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+}
 template <int kB, int D, int kWgQueries, int kQPW, bool kCausal = false, bool kFast = false, bool kSplit = false>
 __global__ __launch_bounds__(kWgQueries / kQPW * 64, kWgQueries / kQPW == 8 ? 1 : 2) void attn_mfma_kernel(MfmaArgs a) {
-  // XCD-aware order: consecutive workgroup ids go round-robin over the 8 XCDs; give each
-  // XCD a contiguous range of (head, query blocks) so that its L2 sees one head at a time.
-  int logical = blockIdx.x;
-  if ((a.total_wgs & 7) == 0) logical = (blockIdx.x & 7) * (a.total_wgs >> 3) + (blockIdx.x >> 3);
-  attn_mfma<kB, D, kWgQueries, kQPW, kCausal, kFast, kSplit>(a, logical);
+  attn_mfma<kB, D, kWgQueries, kQPW, kCausal, kFast, kSplit>(a, xcd_order(a.total_wgs));
+}
+template <int kB, int D, bool kFast, bool kSplit>
+__global__ __launch_bounds__(kSoloQueries / 32 * 64, 2) void attn_rows_kernel(MfmaArgs a, RowSource src) {
+  attn_mfma<kB, D, kSoloQueries, 32, false, kFast, kSplit, true>(a, xcd_order(a.total_wgs), &src);
 }
 template <int kB, int D>
 struct AttnJob {
@@ -1250,6 +1333,24 @@ basa_status launch_shape(const MfmaArgs& m, int B, int d, int BHq, hipStream_t s
   return B == 128 ? launch_main<128, 64, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st)
                   : launch_main<64, 64, kWgQueries, kQPW, kCausal, kFast, kSplit>(m, BHq, st);
 }
+// The 128-query shape on rows of K and V (whole lists without running maxima, or split ones).
+template <int kB, int D, bool kFast, bool kSplit>
+basa_status launch_rows_of(MfmaArgs m, const RowSource& src, int BHq, hipStream_t st) {
+  m.wgs_per_head = ceil_div(m.Nq * kB, kSoloQueries);
+  m.total_wgs = BHq * m.wgs_per_head * (kSplit ? m.splits : 1);
+  const size_t lds = lds_bytes<D>(kSoloQueries * 2, 32, m.Nk, false, kFast);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_rows_kernel<kB, D, kFast, kSplit>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return hip_fail(e, "hipFuncSetAttribute(dynamic LDS)");
+  hipLaunchKernelGGL((attn_rows_kernel<kB, D, kFast, kSplit>), dim3(m.total_wgs), dim3(kSoloQueries * 2), lds, st, m, src);
+  BASA_HIP_CHECK_LAUNCH("attn_rows_kernel");
+  return BASA_OK;
+}
+template <bool kFast, bool kSplit>
+basa_status launch_rows(const MfmaArgs& m, const RowSource& src, int B, int d, int BHq, hipStream_t st) {
+  if (d == 128) return B == 128 ? launch_rows_of<128, 128, kFast, kSplit>(m, src, BHq, st) : launch_rows_of<64, 128, kFast, kSplit>(m, src, BHq, st);
+  return B == 128 ? launch_rows_of<128, 64, kFast, kSplit>(m, src, BHq, st) : launch_rows_of<64, 64, kFast, kSplit>(m, src, BHq, st);
+}
 // The 512-query shape in two passes: without running maxima, then, for the workgroups whose row sums
 // left the safe range (none on ordinary inputs: that launch returns at once), with them.
 template <bool kCausal>
@@ -1287,7 +1388,7 @@ constexpr double step_scale(int d) { return d == 128 ? 1.0 : 0.63; }
 // Blocks in the union of two lists of 64 queries and of the lists of 512, over one list, for lists that leave out `dead` of all.
 constexpr double union_of_pair(int B, double dead) { return 1.0 + (B == 64 ? 0.1 : 0.0) * dead; }
 constexpr double union_of_groups(int groups, double dead) { return 1.0 + 0.1 * (groups - 1) * dead; }
-struct Plan { bool solo; int splits; };
+struct Plan { bool solo; int splits; double us; };
 // Up to six of 512 queries per compute unit, whole lists only: there a last round that is mostly empty decides, and the
 // 128-query shape has to be 5 % ahead by the estimate.  512-query -> chosen shape: 16 heads, L = 20000, keep 10 %
 // (2.5 rounds): 388 -> 338 us; 24 heads, L = 12500, B = 64, keep 25 %: 644 -> 547; 32 heads, L = 9000, B = d = 64, keep
@@ -1296,8 +1397,7 @@ constexpr int kSmallRounds = 2, kPlannedRounds = 6;
 Plan plan_call(int BHq, int Nq, int Nk, int Lq, int B, int d, int list_len, bool causal, bool small, size_t part_bytes) {
   const size_t row_bytes = (size_t)BHq * Lq * (d * 4 + 8);
   const double dead = 1.0 - (double)list_len / Nk, scale = step_scale(d);
-  Plan best{false, 1};
-  double best_cost = 0.0;
+  Plan best{false, 1, 0.0};
   for (int solo = 0; solo <= (causal ? 0 : 1); ++solo) {
     const int queries = solo ? kSoloQueries : kWideQueries;
     const int64_t wgs = (int64_t)BHq * ceil_div(Nq * B, queries);
@@ -1314,7 +1414,7 @@ Plan plan_call(int BHq, int Nq, int Nk, int Lq, int B, int d, int list_len, bool
       const double round_us = solo ? kSoloRoundUs : causal ? kCausalRoundUs : kWideRoundUs;
       const double cost = std::ceil(uni / s) * (B / kTileKeys) * step_us * scale + round_us * rounds +
                           (s > 1 ? 4.0 + (double)(s * row_bytes) / 2e6 : 0.0);
-      if ((!solo && s == 1) || cost < best_cost * (small ? 1.0 : 0.95)) { best_cost = cost; best = Plan{solo != 0, s}; }
+      if ((!solo && s == 1) || cost < best.us * (small ? 1.0 : 0.95)) best = Plan{solo != 0, s, cost};
     }
   }
   return best;
@@ -1324,6 +1424,17 @@ size_t part_bytes_of(int BHq, int Lq, int Nk, int B, int d, bool causal) {
   if (!causal && Nk * (B / kTileKeys) <= kMinSplitTiles) return 0;
   const int64_t splits = std::min<int64_t>(std::min(kMaxSplits, Nk), 8 * kCUs / ((int64_t)BHq * ceil_div(Lq, kSoloQueries)));
   return splits < 2 ? 0 : (size_t)splits * BHq * Lq * (d * 4 + 8);
+}
+
+// Does the 128-query shape read the rows of K and V itself?  Its loop is 9 % slower for it (addresses, twice the reads of V^T, and
+// the loads of the next tile are waited for in mid-tile); laying out the tiles takes a launch and four times kv_bytes.  Attention call,
+// tiles -> rows: 256 queries of 32768, keep 25 %, 32 heads on 8: 73.3 -> 56.7 us, 32 on 32: 108 -> 59.5; 32 of 100000, keep 10 %: 67 -> 44;
+// 8 heads, L = 4000, keep 10 %: 22.1 -> 16.8, L = 2472, keep 50 %: 35.2 -> 32.1 (d = 64: 25.4 -> 25.2), L = 8000: 145.5 -> 141.5; 2 heads, L = 600,
+// d = 64: 14.6 -> 11.5; kept at tiles: 8 heads on 2, L = 8000: 137.9 / 140.0; 32 on 8, L = 4000: 124.4 / 125.0.
+bool rows_pay(size_t kv_bytes, double attention_us) { return 4.0 + 4.0 * (double)kv_bytes / 5.6e6 > 0.09 * attention_us; }
+// The kernel forms a row's offset from the head's first as a product of two 24-bit numbers, in 32 bits.
+bool offsets_fit(const TensorView& x) {
+  return x.stride_l * 2 < 1 << 24 && x.L < 1 << 24 && (int64_t)x.L * x.stride_l * 2 < (int64_t)1 << 32;
 }
 
 // How much the lists of the query blocks that would share a 512-query workgroup have in common, on
@@ -1507,7 +1618,37 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   int32_t* redo = reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256 + sz_kix(BHkv, Nk, B));
 
   int32_t* kix = a.causal ? reinterpret_cast<int32_t*>(ws + 2 * sz_kv(BHkv, Nk, B, d) + 256) : nullptr;
-  {
+  MfmaArgs m;
+  m.q = a.q; m.Kt = reinterpret_cast<const char*>(Kt); m.Vt = reinterpret_cast<const char*>(Vt);
+  m.row_count = a.row_count; m.row_cols = a.row_cols; m.cols_stride = a.cols_stride;
+  m.perm_q = a.perm_q;
+  m.out = reinterpret_cast<__bf16*>(a.out); m.lse = a.lse;
+  m.out_sb = a.out_sb; m.out_sh = a.out_sh; m.out_sl = a.out_sl; m.heads_q = a.q.heads;
+  m.Nq = Nq; m.Nk = Nk; m.Lq = a.q.L; m.Lk = a.k.L;
+  m.group = a.q.heads / a.k.heads;
+  m.wgs_per_head = 0; m.total_wgs = 0;
+  m.scale_log2e = 1.4426950408889634f / sqrtf((float)d);
+  m.probe = nullptr; m.run_if_solo = 0; m.redo = nullptr;
+  m.kix = kix; m.causal_off = a.causal_off;
+  const int gsz = kWideQueries / B;
+  Plan plan{false, 1, 0.0};
+  m.stages = 0; m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
+  const int64_t rows = (int64_t)BHq * Nq * B;
+  const bool small = rows < (int64_t)kSmallRounds * kCUs * kWideQueries;
+  if (a.variant == 0 && rows < (int64_t)kPlannedRounds * kCUs * kWideQueries) {
+    const size_t base = attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B);
+    plan = plan_call(BHq, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0, small,
+                     a.ws_bytes - base);
+    if (plan.splits > 1) {
+      m.splits = plan.splits;
+      m.part_o = reinterpret_cast<float*>(ws + base);
+      m.part_ml = reinterpret_cast<float2*>(m.part_o + (size_t)plan.splits * BHq * a.q.L * d);
+    }
+  }
+  const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
+  const bool solo_only = plan.solo && (small || !can_probe);
+  const bool from_rows = solo_only && rows_pay(sz_kv(BHkv, Nk, B, d), plan.us) && offsets_fit(a.k) && offsets_fit(a.v);
+  if (!from_rows) {
     ProfScope prof(K_GATHER, st);
     const dim3 grid(Nk * B / kTileKeys, BHkv, 2);
     const int by_index = a.causal && B == 128 && a.perm_k;
@@ -1529,34 +1670,6 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
                                     listed, parts, B / kTileKeys);
     BASA_HIP_CHECK_LAUNCH("tile_kv_kernel");
   }
-
-  MfmaArgs m;
-  m.q = a.q; m.Kt = reinterpret_cast<const char*>(Kt); m.Vt = reinterpret_cast<const char*>(Vt);
-  m.row_count = a.row_count; m.row_cols = a.row_cols; m.cols_stride = a.cols_stride;
-  m.perm_q = a.perm_q;
-  m.out = reinterpret_cast<__bf16*>(a.out); m.lse = a.lse;
-  m.out_sb = a.out_sb; m.out_sh = a.out_sh; m.out_sl = a.out_sl; m.heads_q = a.q.heads;
-  m.Nq = Nq; m.Nk = Nk; m.Lq = a.q.L; m.Lk = a.k.L;
-  m.group = a.q.heads / a.k.heads;
-  m.wgs_per_head = 0; m.total_wgs = 0;
-  m.scale_log2e = 1.4426950408889634f / sqrtf((float)d);
-  m.probe = nullptr; m.run_if_solo = 0; m.redo = nullptr;
-  m.kix = kix; m.causal_off = a.causal_off;
-  const int gsz = kWideQueries / B;
-  Plan plan{false, 1};
-  m.stages = 0; m.splits = 1; m.part_o = nullptr; m.part_ml = nullptr;
-  const int64_t rows = (int64_t)BHq * Nq * B;
-  const bool small = rows < (int64_t)kSmallRounds * kCUs * kWideQueries;
-  if (a.variant == 0 && rows < (int64_t)kPlannedRounds * kCUs * kWideQueries) {
-    const size_t base = attn_mfma_workspace_bytes(BHq, BHkv, a.q.L, a.k.L, d, B);
-    plan = plan_call(BHq, Nq, Nk, a.q.L, B, d, a.row_cols ? std::min(a.cols_stride, Nk) : Nk, a.causal != 0, small,
-                     a.ws_bytes - base);
-    if (plan.splits > 1) {
-      m.splits = plan.splits;
-      m.part_o = reinterpret_cast<float*>(ws + base);
-      m.part_ml = reinterpret_cast<float2*>(m.part_o + (size_t)plan.splits * BHq * a.q.L * d);
-    }
-  }
   if (a.causal) {
     if (plan.splits > 1) {
       ProfScope prof(K_ATTN, st);
@@ -1568,11 +1681,13 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
     }
     return launch_attn_combine(a, m.part_o, m.part_ml, m.splits, st);
   }
-  const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
-  if (plan.solo && (small || !can_probe)) {
+  if (solo_only) {
     {
       ProfScope prof(K_ATTN, st);
-      const basa_status s = plan.splits == 1 ? launch_shape<kSoloQueries, 32, false, true>(m, B, d, BHq, st)
+      const RowSource src{a.k, a.v, a.perm_k};
+      const basa_status s = from_rows ? (plan.splits == 1 ? launch_rows<true, false>(m, src, B, d, BHq, st)
+                                                          : launch_rows<false, true>(m, src, B, d, BHq, st))
+                            : plan.splits == 1 ? launch_shape<kSoloQueries, 32, false, true>(m, B, d, BHq, st)
                                              : launch_shape<kSoloQueries, 32, false, false, true>(m, B, d, BHq, st);
       if (s != BASA_OK || plan.splits == 1) return s;
     }

@@ -536,6 +536,38 @@ def test_sort_tiles_of_512_tokens(dtype, d, L, window):
         assert torch.equal(perm[0, :, a:b].long(), want)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("block", [64, 128])
+@pytest.mark.parametrize("Lq,Lk", [(3, 64), (100, 65), (1, 127), (257, 1000), (64, 2049), (300, 6017), (40, 20000)])
+@pytest.mark.parametrize("form", ["plain", "token-major", "no order", "broken order", "infinite last key"])
+def test_attention_on_rows_of_k_and_v(d, block, Lq, Lk, form):
+    """The 128-query shape without tiles, which calls of few queries take, against the 512-query one, which always lays them out:
+    whole lists give the same bits, split ones (more than 32 tiles) the same within the rounding of bf16 outputs."""
+    Q, K, V = _qkv(4, 2, Lq, Lk, d, torch.bfloat16, seed=Lk + d)
+    if form == "token-major":
+        K, V = (torch.cat([x.permute(0, 2, 1, 3), x.permute(0, 2, 1, 3)], 2).contiguous()[:, :, 1:3].permute(0, 2, 1, 3) for x in (K, V))
+    n_q, n_k = -(-Lq // block), -(-Lk // block)
+    cnt, cols, _, _ = _lists(4, n_q, n_k, Lk, n_k)
+    pq, pk = _perm(4, Lq, 1), _perm(2, Lk, 50)
+    if form == "no order":
+        pq, pk = None, None
+    elif form == "broken order":
+        pk[0, 0, ::7] = Lk + 3
+        pk[0, 1, 5::11] = -1
+    elif form == "infinite last key":
+        V[0, 0, int(pk[0, 0, Lk - 1])] = float("inf")
+    rows, lse = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True)
+    tiles, lse_t = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, attn_shape=3)
+    if n_k * (block // 64) <= 32:
+        assert torch.equal(rows.view(torch.int16), tiles.view(torch.int16)) and torch.equal(lse, lse_t)
+        return
+    fin = torch.isfinite(tiles.float())
+    assert torch.equal(fin, torch.isfinite(rows.float()))
+    diff = (rows.float() - tiles.float())[fin].abs()
+    assert diff.max() <= 2.0 ** -7 * tiles.float()[fin].abs().max()      # a last place of the largest, rounded twice
+    torch.testing.assert_close(lse, lse_t, rtol=0, atol=4e-3)             # (sums of probabilities rounded to 8 bits)
+
+
 @pytest.mark.parametrize("heads,L", [(64, 8193), (16, 32768), (30, 32769), (41, 32767), (260, 2113), (6, 70000), (12, 33000)])
 @pytest.mark.parametrize("kind", ["spread", "few values", "ascending", "descending", "far outliers"])
 def test_merge_cut_by_samples(heads, L, kind):
