@@ -756,17 +756,35 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const flo
   if (row >= rows) return;
   const int sub = threadIdx.x % LPR;
   const int Lq = a.q.L, bhq = (int)(row / Lq), pos = (int)(row - (int64_t)bhq * Lq);
-  float m = -INFINITY, l = 0.f;
-  for (int s = 0; s < splits; ++s) m = fmaxf(m, part_ml[s * rows + row].x);
-  floatx4 o = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < splits; ++s) {
-    const float2 ml = part_ml[s * rows + row];
-    if (ml.y == 0.f) continue;                           // nothing was seen there (and perhaps nothing written); not so a NaN
-    const float f = __builtin_amdgcn_exp2f(ml.x - m);
-    const floatx4 t = *reinterpret_cast<const floatx4*>(part_o + (s * rows + row) * D + 4 * sub);
-    l = fmaf(ml.y, f, l);
+  // The parts of eight workgroups are requested at once (past the last: the last again); one after the other their latencies were the
+  // kernel.
+  constexpr int kAtOnce = 8;
+  float2 ml[kAtOnce];
+  floatx4 t[kAtOnce];
+  auto request = [&](int s0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = fmaf(t[e], f, o[e]);
+    for (int j = 0; j < kAtOnce; ++j) {
+      const int64_t at = min(s0 + j, splits - 1) * rows + row;
+      ml[j] = part_ml[at];
+      t[j] = *reinterpret_cast<const floatx4*>(part_o + at * D + 4 * sub);
+    }
+  };
+  request(0);
+  float m = -INFINITY, l = 0.f;
+#pragma unroll
+  for (int j = 0; j < kAtOnce; ++j) m = fmaxf(m, ml[j].x);
+  for (int s = kAtOnce; s < splits; ++s) m = fmaxf(m, part_ml[s * rows + row].x);
+  floatx4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < splits; s0 += kAtOnce) {
+    if (s0 > 0) request(s0);
+#pragma unroll
+    for (int j = 0; j < kAtOnce; ++j) {
+      if (s0 + j >= splits || ml[j].y == 0.f) continue;    // nothing was seen there (and perhaps nothing written); not so a NaN
+      const float f = __builtin_amdgcn_exp2f(ml[j].x - m);
+      l = fmaf(ml[j].y, f, l);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = fmaf(t[j][e], f, o[e]);
+    }
   }
   const float inv_l = l > 0.f ? 1.0f / l : 0.f;
   const int qrow = perm_at(a.perm_q, (int64_t)bhq * Lq, pos, Lq);
