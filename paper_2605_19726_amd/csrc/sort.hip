@@ -127,13 +127,13 @@ __device__ __forceinline__ void sort_tile_in_lds(uint64_t* buf, int t) {
   __syncthreads();
 }
 
-// ---- the network of a small tile: 1024 or 512 words, 256 threads, W = 4 or 2 words per thread ----
+// ---- the network of a small tile: 1024 or 512 words, 256 or 512 threads, W = 4, 2 or 1 words per thread ----
 // Wave w sorts words 64 W w .. 64 W (w + 1) - 1 by itself (index = W lane + register: the low index bits in registers, six
-// exchanged between lanes, no barrier); the four runs are then ranked against each other in LDS.  Returns in
+// exchanged between lanes, no barrier); the runs of the waves are then ranked against each other in LDS.  Returns in
 // rank[r] the place of v[r] in the tile (padding words, all alike, get places past the last real word).
 template <int W>
 __device__ __forceinline__ void sort_in_wave(uint64_t (&v)[W], int lane) {
-  constexpr int kRegBits = W == 4 ? 2 : 1;
+  constexpr int kRegBits = W == 4 ? 2 : W == 2 ? 1 : 0;
 #pragma unroll
   for (int m = 1; m <= 6 + kRegBits; ++m) {
     const int k = 1 << m;              // in the last step beyond the indices of a wave, everything ascending
@@ -162,9 +162,9 @@ __device__ __forceinline__ void sort_in_wave(uint64_t (&v)[W], int lane) {
     }
   }
 }
-template <int W>
+template <int W, int kWaves>
 __device__ __forceinline__ void rank_small_tile(uint64_t (&v)[W], int (&rank)[W], uint64_t* buf, int t) {
-  constexpr int kRun = 64 * W;
+  constexpr int kRun = 64 * W, kOthers = kWaves - 1;
   const int lane = t & 63, wave = t >> 6;
 #pragma unroll
   for (int r = 0; r < W; ++r) v[r] = buf[tile_slot(W * t + r)];
@@ -175,35 +175,36 @@ __device__ __forceinline__ void rank_small_tile(uint64_t (&v)[W], int (&rank)[W]
     rank[r] = W * lane + r;
   }
   __syncthreads();
-  // Words below v[r] in the other three runs: 3 W binary searches side by side.  A position P in a run is kept as
+  // Words below v[r] in the runs of the other waves: a binary search in each, side by side.  A position P in a run is kept as
   // its slot P + P/16, which a step moves by a constant: every probe is one LDS read at an immediate offset, one
   // compare and one conditional add.
-  int pos[3][W];
+  int pos[kOthers][W];
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
+  for (int j = 0; j < kOthers; ++j)
 #pragma unroll
-    for (int r = 0; r < W; ++r) pos[j][r] = tile_slot(((wave + 1 + j) & 3) * kRun);
+    for (int r = 0; r < W; ++r) pos[j][r] = tile_slot(((wave + 1 + j) & kOthers) * kRun);
   auto probe = [&](auto step, auto move) {       // is word P + step - 1 below v[r]?  Then P moves on by `step`
     constexpr int kStep = decltype(step)::value, kMove = decltype(move)::value;
     constexpr int kOff = kStep >= 16 ? kMove - 2 : kStep - 1;
-    uint64_t w[3][W];
+    uint64_t w[kOthers][W];
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < kOthers; ++j)
 #pragma unroll
       for (int r = 0; r < W; ++r) w[j][r] = buf[pos[j][r] + kOff];
 #pragma unroll
-    for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < kOthers; ++j)
 #pragma unroll
       for (int r = 0; r < W; ++r) pos[j][r] = w[j][r] < v[r] ? pos[j][r] + kMove : pos[j][r];
   };
 #define BASA_PROBE(S) probe(std::integral_constant<int, S>{}, std::integral_constant<int, S >= 16 ? S + S / 16 : S>{})
   if constexpr (W == 4) BASA_PROBE(128);
-  BASA_PROBE(64); BASA_PROBE(32); BASA_PROBE(16); BASA_PROBE(8); BASA_PROBE(4); BASA_PROBE(2); BASA_PROBE(1);
+  if constexpr (W >= 2) BASA_PROBE(64);
+  BASA_PROBE(32); BASA_PROBE(16); BASA_PROBE(8); BASA_PROBE(4); BASA_PROBE(2); BASA_PROBE(1);
 #undef BASA_PROBE
   // P <= kRun - 1 now; word P itself decides between P and P + 1
 #pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const int run0 = tile_slot(((wave + 1 + j) & 3) * kRun);
+  for (int j = 0; j < kOthers; ++j) {
+    const int run0 = tile_slot(((wave + 1 + j) & kOthers) * kRun);
 #pragma unroll
     for (int r = 0; r < W; ++r) {
       const int slot = pos[j][r] - run0;         // P + P/16
@@ -212,14 +213,14 @@ __device__ __forceinline__ void rank_small_tile(uint64_t (&v)[W], int (&rank)[W]
   }
 }
 
-template <bool kBf16, int kD, int kTileT, bool kStream>
+template <bool kBf16, int kD, int kTileT, bool kStream, int kThreads = kSortThreads>
 __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView& x0, const TensorView& x1, int BH0,
                                                uint64_t* __restrict__ out, int32_t* __restrict__ perm0,
                                                int32_t* __restrict__ perm1, float* __restrict__ keys_out, const SegGeom& g0,
                                                const SegGeom& g1, const SegList& sl) {
   constexpr int kElem = kBf16 ? 2 : 4;
   constexpr int LPR = kD * kElem / 16;          // lanes per row: 8, 16 or 32
-  constexpr int kRowsPerIter = kSortThreads / LPR;
+  constexpr int kRowsPerIter = kThreads / LPR;
   constexpr int kIters = 8;
   constexpr int kRowsPerPass = kRowsPerIter * kIters;
   static_assert(kTileT % kRowsPerPass == 0, "a tile is a whole number of passes");
@@ -345,7 +346,7 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
     //  was found missing on this path by lds_wait_audit, so it is spelt out)
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __syncthreads();
-    for (int i = threadIdx.x; i < n; i += kSortThreads) {
+    for (int i = threadIdx.x; i < n; i += kThreads) {
       int sg = seg_lo;
       for (int j = seg_lo + 1; j < sl.n; ++j) sg += (start + i >= sl.bound[j]) ? 1 : 0;
       if (sg != seg_lo) {
@@ -354,16 +355,16 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
       }
     }
   }
-  for (int i = n + threadIdx.x; i < kTileT; i += kSortThreads) buf[tile_slot(i)] = ~0ull;
+  for (int i = n + threadIdx.x; i < kTileT; i += kThreads) buf[tile_slot(i)] = ~0ull;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __syncthreads();
 
   // ---- phase 2: the words of the tile into order
   if constexpr (kTileT <= kSmallTile) {
-    constexpr int W = kTileT / kSortThreads;
+    constexpr int W = kTileT / kThreads;
     uint64_t v[W];
     int rank[W];
-    rank_small_tile<W>(v, rank, buf, threadIdx.x);
+    rank_small_tile<W, kThreads / 64>(v, rank, buf, threadIdx.x);
 #pragma unroll
     for (int r = 0; r < W; ++r) {
       if (v[r] == ~0ull) continue;             // padding
@@ -374,15 +375,15 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
   }
   sort_tile_in_lds(buf, threadIdx.x);
   if (perm_out) {
-    for (int i = threadIdx.x; i < n; i += kSortThreads) perm_out[hb + start + i] = idx_of_word(buf[tile_slot(i)]);
+    for (int i = threadIdx.x; i < n; i += kThreads) perm_out[hb + start + i] = idx_of_word(buf[tile_slot(i)]);
   } else {
     // (streaming stores, like the loads of the rows: another 3 % of this kernel)
-    for (int i = threadIdx.x; i < n; i += kSortThreads) __builtin_nontemporal_store(buf[tile_slot(i)], &out[hb + start + i]);
+    for (int i = threadIdx.x; i < n; i += kThreads) __builtin_nontemporal_store(buf[tile_slot(i)], &out[hb + start + i]);
   }
 }
 
-template <bool kBf16, int kD, int kTileT, bool kStream>
-__global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
+template <bool kBf16, int kD, int kTileT, bool kStream, int kThreads = kSortThreads>
+__global__ __launch_bounds__(kThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
                                                                       uint64_t* __restrict__ out,
                                                                       int32_t* __restrict__ perm0,
                                                                       int32_t* __restrict__ perm1,
@@ -396,7 +397,7 @@ __global__ __launch_bounds__(kSortThreads) void norm_tile_sort_kernel(TensorView
     bx = i - by * per_row;
     by += second ? BH0 : 0;
   }
-  norm_tile_sort<kBf16, kD, kTileT, kStream>(bx, by, x0, x1, BH0, out, perm0, perm1, keys_out, g0, g1, sl);
+  norm_tile_sort<kBf16, kD, kTileT, kStream, kThreads>(bx, by, x0, x1, BH0, out, perm0, perm1, keys_out, g0, g1, sl);
 }
 template <int kD>
 struct SmallSortJob {
@@ -1088,17 +1089,25 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   // compute units get two real ones is then a matter of their timing: 256 queries of 32768, 32 heads on 8: 34 to 42 us, 24 in one row.
   const int per0 = g0.segs * g0.tiles_per_seg, per1 = g1.segs * g1.tiles_per_seg;
   const int tiles1 = x1 && L0 != L1 ? BH1 * per1 : 0;
+  // Eight waves to a tile instead of four where the tiles leave compute units idle: twice the rows in flight in each, half the words
+  // to a lane.  Sort, four -> eight waves: 2 fp32 rows of 1024, d = 64: 12.9 -> 11.7 us, 64 of 512: 13.8 -> 11.2; tiles of 512: 40 of 2000:
+  // 15.3 -> 12.2, 16 of 2472: 15.9 -> 12.7; level at 160 tiles of 1024 and kept at four beyond 128: 192: 27.5 / 28.1, 256: 39.8 / 43.3;
+  // fp32, d = 128, 128 tiles of 512: the whole operator 213.8 / 215.6.
+  const int tiles = per0 * BH0 + per1 * BH1, token_bytes = x0.d * (bf16 ? 2 : 4);
+  const bool eight = tile == kSmallTile ? tiles <= 128 : tiles * token_bytes <= 48 * 1024;
   const dim3 grid = tiles1 > 0 ? dim3(BH0 * per0 + tiles1) : dim3(per0, BH0 + BH1);
-#define BASA_KEYS_T(BF, D, T, S)                                                                            \
-  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T, S>), grid, dim3(kSortThreads), 0, st, x0, xb, BH0, buf1, \
+#define BASA_KEYS_T(BF, D, T, S, N)                                                                            \
+  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T, S, N>), grid, dim3(N), 0, st, x0, xb, BH0, buf1, \
                      single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs, tiles1)
-#define BASA_KEYS(BF, D)                                      \
-  do {                                                        \
-    if (tile == kTile && !cached) BASA_KEYS_T(BF, D, kTile, true); \
-    else if (tile == kTile) BASA_KEYS_T(BF, D, kTile, false); \
-    else if (!cached) BASA_KEYS_T(BF, D, kSmallTile, true);   \
-    else if (tile == 512) BASA_KEYS_T(BF, D, 512, false);     \
-    else BASA_KEYS_T(BF, D, kSmallTile, false);               \
+#define BASA_KEYS(BF, D)                                                                   \
+  do {                                                                                     \
+    if (tile == kTile && !cached) BASA_KEYS_T(BF, D, kTile, true, kSortThreads);           \
+    else if (tile == kTile) BASA_KEYS_T(BF, D, kTile, false, kSortThreads);                \
+    else if (!cached) BASA_KEYS_T(BF, D, kSmallTile, true, kSortThreads);                  \
+    else if (tile == 512 && eight) BASA_KEYS_T(BF, D, 512, false, 2 * kSortThreads);       \
+    else if (tile == 512) BASA_KEYS_T(BF, D, 512, false, kSortThreads);                    \
+    else if (eight) BASA_KEYS_T(BF, D, kSmallTile, false, 2 * kSortThreads);               \
+    else BASA_KEYS_T(BF, D, kSmallTile, false, kSortThreads);                              \
   } while (0)
   if (bf16 && x0.d == 128) BASA_KEYS(true, 128);
   else if (bf16 && x0.d == 64) BASA_KEYS(true, 64);

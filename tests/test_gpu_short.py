@@ -568,6 +568,15 @@ def test_attention_on_rows_of_k_and_v(d, block, Lq, Lk, form):
     torch.testing.assert_close(lse, lse_t, rtol=0, atol=4e-3)             # (sums of probabilities rounded to 8 bits)
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
+@pytest.mark.parametrize("heads,L", [(128, 900), (129, 900), (16, 8000), (32, 4096), (33, 4096), (64, 2047), (65, 2047), (1, 1), (3, 5000)])
+def test_sort_on_both_sides_of_eight_waves_to_a_tile(dtype, d, heads, L):
+    x, _, _ = _qkv(heads, 1, L, 64, d, dtype, seed=L + d)
+    x[0, heads // 2] = x[0, heads // 2, :1]
+    perm, keys = bd.basa_norm_sort(x, 64, return_keys=True)
+    assert torch.equal(perm[0].long(), torch.sort(keys[0], dim=-1, stable=True).indices)
+
+
 @pytest.mark.parametrize("heads,L", [(64, 8193), (16, 32768), (30, 32769), (41, 32767), (260, 2113), (6, 70000), (12, 33000)])
 @pytest.mark.parametrize("kind", ["spread", "few values", "ascending", "descending", "far outliers"])
 def test_merge_cut_by_samples(heads, L, kind):
