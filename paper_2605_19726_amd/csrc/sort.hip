@@ -382,7 +382,7 @@ __device__ __forceinline__ void norm_tile_sort(int bx, int by, const TensorView&
   }
 }
 
-template <bool kBf16, int kD, int kTileT, bool kStream, int kThreads = kSortThreads>
+template <bool kBf16, int kD, int kTileT, int kThreads, bool kStream>
 __global__ __launch_bounds__(kThreads) void norm_tile_sort_kernel(TensorView x0, TensorView x1, int BH0,
                                                                       uint64_t* __restrict__ out,
                                                                       int32_t* __restrict__ perm0,
@@ -1097,7 +1097,7 @@ static basa_status norm_sort_impl(const TensorView& x0, const TensorView* x1, in
   const bool eight = tile == kSmallTile ? tiles <= 128 : tiles * token_bytes <= 48 * 1024;
   const dim3 grid = tiles1 > 0 ? dim3(BH0 * per0 + tiles1) : dim3(per0, BH0 + BH1);
 #define BASA_KEYS_T(BF, D, T, S, N)                                                                            \
-  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T, S, N>), grid, dim3(N), 0, st, x0, xb, BH0, buf1, \
+  hipLaunchKernelGGL((norm_tile_sort_kernel<BF, D, T, N, S>), grid, dim3(N), 0, st, x0, xb, BH0, buf1, \
                      single0 ? perm0 : nullptr, single1 ? perm1 : nullptr, keys_out, g0, g1, segs, tiles1)
 #define BASA_KEYS(BF, D)                                                                   \
   do {                                                                                     \
