@@ -1075,9 +1075,11 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const 
     uint32_t lo = 0, issued = 1, slot = 0, issue_slot = 1, stage_no = 0;
     uint32_t e0 = entry_at(1), e1 = entry_at(2);       // of the next two tiles to request
     uint32_t win = listed_by(entry_at(0), 0), mine = win >> grp & 0x01010101u;
-    // (The loop starts 56 bytes into a line of 64: at 0, 20 and 56 bytes, in turn on one card, dense, L = 16384: 3397 / 3424 / 3390 us,
-    //  128K, keep 50 %: 111.5 / 112.2 / 111.1 ms, video 75K: 24985 / 25140 / 24850 us.)
-    asm volatile(".p2align 6\n\ts_nop 0\n\ts_nop 0");             // (twelve instructions follow in front of it)
+    // (Where the loop starts in a line of 64 bytes; twelve instructions stand between this and it.  Blocks of 128 at 0, 20 and 56 bytes,
+    //  in turn on one card: dense, L = 16384: 3397 / 3424 / 3390 us, 128K, keep 50 %: 111.5 / 112.2 / 111.1 ms, video 75K: 24985 / 25140 /
+    //  24850 us.  Blocks of 64, 24 heads, L = 32100, at 20 and 56: 5789 / 5834 us, a tenth of a percent apart at other sizes.)
+    if constexpr (kB == 128) asm volatile(".p2align 6\n\t.rept 2\n\ts_nop 0\n\t.endr");
+    else asm volatile(".p2align 6\n\t.rept 9\n\ts_nop 0\n\t.endr");
 #pragma nounroll
     while (lo < last || issued <= last) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
