@@ -690,9 +690,10 @@ __global__ __launch_bounds__(kSortThreads) void rank_runs_kernel(Src src) {
 // the compute units, took 36; 64 rows of 32768: 42 for 50 in two launches.  Dealing the words of a part to bins by value instead of
 // merging measured no faster (the keys above a run's last sample fill a few bins), nor did probing three points at a time.
 // ---------------------------------------------------------------------------------
-constexpr int kCutRuns = 32, kCutStride = kSmallTile / 16, kCutThreads = 512, kCutLevels = 5;
+constexpr int kCutThreads = 512, kCutLevels = 5;
 constexpr int kCutWords = kCutRuns * kSmallTile;          // of a group
-constexpr int kMaxPartSamples = 48;
+constexpr int kPartSamples = 32, kMaxPartSamples = 48;
+static_assert(kPartSamples % 16 == 0 && kMaxPartSamples % 16 == 0, "cut_bracket");
 constexpr int kCutCap = kMaxPartSamples * kCutStride + kCutRuns * (kCutStride - 1);
 constexpr int kCutItems = 8;                              // outputs of a slot; a thread has slots t and (large parts) t + 512
 // (a pair of runs leaves part of its last slot unused)
@@ -765,10 +766,7 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
     const int want = (part + wave) * samples_per_part;
     uint64_t v = wave == 0 ? 0ull : ~0ull;
     if (wave == 0 ? part > 0 : !last_part) {
-      // Sample k = want / runs of every run: the smallest has at most `want` samples below it, and behind the largest there are
-      // more (of runs that have it: where the last run is short that is checked).  The words are distinct, so some value in between
-      // has exactly `want`.
-      const int runs = (n_group + kSmallTile - 1) / kSmallTile, k = want / runs;
+      const CutBracket at_sample = cut_bracket(want, n_group);
       uint64_t lo = ~0ull, hi = 0ull;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -781,22 +779,11 @@ __device__ __forceinline__ void cut_merge(const CutArgs& a, int logical) {
         lo = x < lo ? x : lo;
         hi = y > hi ? y : hi;
       }
-      auto of_lane = [&](uint64_t x) {
-        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, k) |
-               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), k) << 32;
+      auto of_lane = [&](uint64_t x, int l) {
+        return (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, l) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), l) << 32;
       };
-      lo = of_lane(lo);
-      hi = of_lane(hi) + 1;
-      if (samples_below(hi) < want) hi = ~0ull;
-      // below(lo) <= want <= below(hi); mostly lo is it already, the runs being much alike
-      v = lo;
-      int c = samples_below(v);
-      while (c != want) {
-        if (c > want) hi = v; else lo = v;
-        v = lo + ((hi - lo) >> 1);
-        c = samples_below(v);
-        if (v == lo && c != want) break;       // (cannot be: distinct words)
-      }
+      v = cut_value(of_lane(lo, at_sample.lowest), of_lane(hi, at_sample.highest) + 1, want, samples_below);
     }
     if (lane == 0) cut[wave] = v;
   }
@@ -990,7 +977,7 @@ static bool cut_pays(int run, int64_t words, bool few) {
 // Parts of 2048 words, of 3072 where those would be more than three to a compute unit (64 rows of 32768: 148 / 143 us; 40: 103 / 97,
 // 32: 83.5 / 84.6, 48 of 16384: 66 / 69).
 static CutArgs cut_args(const uint64_t* src, uint64_t* dst, int32_t* perm0, int32_t* perm1, int BH0, const SegGeom& g, int64_t words) {
-  const int samples = words <= (int64_t)3 * 256 * 32 * kCutStride ? 32 : kMaxPartSamples;
+  const int samples = words <= (int64_t)3 * 256 * kPartSamples * kCutStride ? kPartSamples : kMaxPartSamples;
   return CutArgs{src, dst, perm0, perm1, BH0, g, ceil_div(g.W, kCutWords), ceil_div(std::min(g.W, kCutWords), samples * kCutStride), samples};
 }
 

@@ -1,4 +1,5 @@
-// Which tiles a norm sort starts from, by its sizes.  Plain C++ without the device: the rule is checked on the host.
+// Which tiles a norm sort starts from, by its sizes, and where its merge cuts their runs.  Plain C++ without the device: checked on
+// the host.
 #pragma once
 #include <algorithm>
 #include <cstdint>
@@ -54,6 +55,33 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
   if (run <= kTile) return {false, kTile};
   const int64_t runs = rows0 * ((L0 + run - 1) / run) + (rows1 > 0 ? rows1 * ((L1 + run - 1) / run) : 0);
   return {false, runs > 128 && runs <= 256 && words <= 5 * 256 * kSmallTile ? kSmallTile : kTile};
+}
+
+// The merge that is cut by samples (sort.hip): up to kCutRuns neighbouring runs of kSmallTile words, every kCutStride-th word of a
+// run a sample.
+constexpr int kCutRuns = 32, kCutStride = kSmallTile / 16;
+// A value with exactly `want` of the samples of `words` words below it lies between two that are known by their numbers in the runs.
+// Sample `lowest`: the smallest of the runs' has at most `want` below it.  Sample `highest`: behind the largest there are at least
+// `want`, those of the whole runs alone (the last run may be short and lack it).  For want > 0, a multiple of 16, kCutStride * want <
+// words: then there are two runs or more, and `highest` is at most 15.  (With sample `lowest` at both ends, a short last run that lacks
+// it left the upper end one value short, or at the largest of all values: 40 steps of 0.2 us in place of 6.  Whole sort, 64-bit words,
+// 196 rows of 5354: 89.3 -> 81.9 us, 26 of 30222: 83.6 -> 77.9.)
+struct CutBracket { int lowest, highest; };
+constexpr CutBracket cut_bracket(int want, int words) {
+  return {want / ((words + kSmallTile - 1) / kSmallTile), (want - 1) / (words / kSmallTile)};
+}
+// That value: below(lo) <= want <= below(hi), and below() grows by at most one with each step of its argument, the words being distinct.
+template <class Below>
+constexpr uint64_t cut_value(uint64_t lo, uint64_t hi, int want, Below&& below) {
+  if (below(lo) == want) return lo;        // mostly: the runs are much alike
+  if (below(hi) == want) return hi;        // (no value between the two need have it)
+  while (hi - lo > 1) {                    // below(lo) < want < below(hi)
+    const uint64_t v = lo + ((hi - lo) >> 1);
+    const int c = below(v);
+    if (c == want) return v;
+    if (c > want) hi = v; else lo = v;
+  }
+  return lo;                               // (cannot be)
 }
 
 }  // namespace basa

@@ -1,5 +1,5 @@
-"""Tiles that a norm sort starts from, on both sides of the lines that were measured.  On the CPU: the rule stands in a header
-of plain C++, compiled here with the host compiler."""
+"""Tiles that a norm sort starts from, on both sides of the lines that were measured, and the values at which its merge cuts their
+runs.  On the CPU: the rules stand in a header of plain C++, compiled here with the host compiler."""
 import subprocess
 
 import pytest
@@ -58,3 +58,78 @@ def test_calls_of_few_words_start_from_512_tokens_while_the_device_has_room(plan
     assert plan(rows, L, window=window, token_bytes=token_bytes, cached=False) == (True, 1024)
     if rows > 1:
         assert plan(rows - 1, L, 1, L, window=window, token_bytes=token_bytes) == (True, tile)
+
+
+CUTS = r"""
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+#include "sort_plan.hpp"
+using namespace basa;
+// A group of `n` words in sorted runs of 1024, cut into parts of `samples` samples: every cut has exactly as many samples below it as
+// asked for, in the steps of a search between two neighbouring samples, and no part exceeds what the kernel has room for.
+int main(int argc, char** argv) {
+  const int n = std::atoi(argv[1]), samples = std::atoi(argv[2]), kind = std::atoi(argv[3]);
+  std::mt19937_64 rng(n + 7 * samples + kind);
+  std::vector<uint64_t> w(n);
+  for (int i = 0; i < n; ++i) {
+    uint64_t key = 0x3f000000u + (rng() & 0xffffff);                     // 0: spread
+    if (kind == 1) key = i >= n / 1024 * 1024 ? 0 : key;                 // short last run: zeros (padding tokens)
+    if (kind == 2) key = i >= n / 1024 * 1024 ? 0x7f800000u : key;       // ... infinities
+    if (kind == 3) key = 0x3f000000u;                                    // all alike
+    if (kind == 4) key = 0x3f000000u + i;                                // ascending
+    if (kind == 5) key = 0x3f000000u + n - i;                            // descending
+    if (kind == 6) key = 0x3f000000u + i % 1024;                         // every run alike
+    if (kind == 7) key = i >= n / 1024 * 1024 ? 0 : 0x3f000000u + i % 1024;
+    w[i] = key << 27 | (uint64_t)i;
+  }
+  std::vector<uint64_t> all;
+  const int runs = (n + kSmallTile - 1) / kSmallTile;
+  for (int r = 0; r < runs; ++r) {
+    std::sort(w.begin() + r * kSmallTile, w.begin() + std::min(n, (r + 1) * kSmallTile));
+    for (int i = r * kSmallTile; i < std::min(n, (r + 1) * kSmallTile); i += kCutStride) all.push_back(w[i]);
+  }
+  int worst = 0;
+  size_t words_before = 0;
+  for (int want = samples; want * kCutStride < n; want += samples) {
+    const CutBracket at = cut_bracket(want, n);
+    if (at.highest > 15 || at.lowest > 15) return std::printf("sample %d, %d of a run\n", at.lowest, at.highest), 1;
+    uint64_t lo = ~0ull, hi = 0;
+    for (int r = 0; r < runs; ++r) {
+      auto sample = [&](int k) { return r * kSmallTile + k * kCutStride; };
+      if (sample(at.lowest) < n) lo = std::min(lo, w[sample(at.lowest)]);
+      if (sample(at.highest) < n) hi = std::max(hi, w[sample(at.highest)] + 1);
+    }
+    int calls = 0;
+    auto below = [&](uint64_t v) { ++calls; return (int)std::count_if(all.begin(), all.end(), [&](uint64_t s) { return s < v; }); };
+    const uint64_t v = cut_value(lo, hi, want, below);
+    worst = std::max(worst, calls);
+    if (below(v) != want) return std::printf("%d samples below the cut for %d\n", below(v), want), 1;
+    const size_t words = std::count_if(w.begin(), w.end(), [&](uint64_t x) { return x < v; });
+    if (words - words_before > (size_t)(samples * kCutStride + kCutRuns * (kCutStride - 1))) return std::printf("a part of %zu\n", words - words_before), 1;
+    words_before = words;
+  }
+  std::printf("%d\n", worst);
+  return n - words_before > (size_t)(samples * kCutStride + kCutRuns * (kCutStride - 1));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def cuts(tmp_path_factory):
+    d = tmp_path_factory.mktemp("cuts")
+    (d / "c.cpp").write_text(CUTS)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", build.CSRC, str(d / "c.cpp"), "-o", str(d / "c")], check=True)
+    return str(d / "c")
+
+
+@pytest.mark.parametrize("kind", range(8))
+@pytest.mark.parametrize("samples", [32, 48])
+def test_merge_cuts_have_the_samples_asked_for_below_them(cuts, samples, kind):
+    # a last run of no, one, hardly any, half and almost all its words, behind two to thirty-one whole ones
+    for n in [2049, 2112, 2648, 2688, 3071, 3072, 3073, 4600, 8193, 8300, 16384, 20000, 22331, 31745, 32767, 32768]:
+        r = subprocess.run([cuts, str(n), str(samples), str(kind)], capture_output=True, text=True)
+        assert r.returncode == 0, (n, r.stdout)
+        assert int(r.stdout) <= 2 + 57, n                # two ends and the bits of key and index below a common segment
