@@ -746,8 +746,9 @@ __global__ __launch_bounds__(512) void attn_split_kernel(SplitArgs p) {
   if (a.lse && h == 0) a.lse[(int64_t)bhq * Lq + qrow] = lse_of(m_run, l_tot, p.lse_k);
 }
 
-// Adds up the partial results of the workgroups that shared a query's list: D/4 lanes per query.
-template <bool kBf16, int D>
+// Adds up the partial results of the workgroups that shared a query's list: D/4 lanes per query.  The parts of kAtOnce workgroups are
+// requested at once (past the last: the last again); one after the other their latencies were the kernel.
+template <bool kBf16, int D, int kAtOnce>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const float* __restrict__ part_o,
                                                            const float2* __restrict__ part_ml, int splits, int64_t rows,
                                                            LseFactor lse_k) {
@@ -756,9 +757,6 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a, const flo
   if (row >= rows) return;
   const int sub = threadIdx.x % LPR;
   const int Lq = a.q.L, bhq = (int)(row / Lq), pos = (int)(row - (int64_t)bhq * Lq);
-  // The parts of eight workgroups are requested at once (past the last: the last again); one after the other their latencies were the
-  // kernel.
-  constexpr int kAtOnce = 8;
   float2 ml[kAtOnce];
   floatx4 t[kAtOnce];
   auto request = [&](int s0) {
@@ -930,14 +928,24 @@ basa_status launch_attn_combine(const AttnArgs& a, const float* part_o, const fl
   const int rpw = 256 / (a.q.d / 4);
   const dim3 grid((unsigned)((rows + rpw - 1) / rpw));
   ProfScope prof(K_ATTN_COMBINE, st);
-#define BASA_COMB(BF, D) hipLaunchKernelGGL((attn_combine_kernel<BF, D>), grid, dim3(256), 0, st, a, part_o, part_ml, splits, rows, \
-                                               lse_factor(D))
+  // Eight at once for two parts are six requests too many, which shows where there are many rows.  Combining pass, one part after the
+  // other / eight at once / this rule: bf16, d = 128, two parts of 2 heads, L = 6500: 5.8 / 7.0 / 5.3 us, d = 64, 4 heads, L = 18350: 12.6 / 13.6 / 10.5; fp32, d =
+  // 128, 2 heads, L = 6500: 6.3 / 7.6 / 5.9.
+#define BASA_COMB_N(BF, D, N) \
+  hipLaunchKernelGGL((attn_combine_kernel<BF, D, N>), grid, dim3(256), 0, st, a, part_o, part_ml, splits, rows, lse_factor(D))
+#define BASA_COMB(BF, D)                          \
+  do {                                            \
+    if (splits <= 2) BASA_COMB_N(BF, D, 2);       \
+    else if (splits <= 4) BASA_COMB_N(BF, D, 4);  \
+    else BASA_COMB_N(BF, D, 8);                   \
+  } while (0)
   const bool bf = a.q.dtype == BASA_BF16;
   if (bf && a.q.d == 128) BASA_COMB(true, 128);
   else if (bf) BASA_COMB(true, 64);
   else if (a.q.d == 128) BASA_COMB(false, 128);
   else BASA_COMB(false, 64);
 #undef BASA_COMB
+#undef BASA_COMB_N
   BASA_HIP_CHECK_LAUNCH("attn_combine_kernel");
   return BASA_OK;
 }

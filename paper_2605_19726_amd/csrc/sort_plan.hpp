@@ -64,7 +64,7 @@ constexpr int kCutRuns = 32, kCutStride = kSmallTile / 16;
 // Sample `lowest`: the smallest of the runs' has at most `want` below it.  Sample `highest`: behind the largest there are at least
 // `want`, those of the whole runs alone (the last run may be short and lack it).  For want > 0, a multiple of 16, kCutStride * want <
 // words: then there are two runs or more, and `highest` is at most 15.  (With sample `lowest` at both ends, a short last run that lacks
-// it left the upper end one value short, or at the largest of all values: 40 steps of 0.2 us in place of 6.  Whole sort, 64-bit words,
+// it left the upper end one value short, or at the largest of all values: 40 steps of 0.2 us in place of 6.  Whole sort,
 // 196 rows of 5354: 89.3 -> 81.9 us, 26 of 30222: 83.6 -> 77.9.)
 struct CutBracket { int lowest, highest; };
 constexpr CutBracket cut_bracket(int want, int words) {

@@ -311,6 +311,27 @@ def test_split_lists_with_several_batch_entries_and_less_workspace(dtype, d, blo
                 np.testing.assert_allclose(have[fin], ref_lse[fin], rtol=0, atol=2e-2 if dtype == torch.bfloat16 else 1e-4)
 
 
+@pytest.mark.parametrize("dtype,d", [(torch.bfloat16, 64), (torch.bfloat16, 128), (torch.float32, 64), (torch.float32, 128)])
+@pytest.mark.parametrize("parts", [1, 2, 3, 4, 5, 8, 9, 17])
+def test_adding_up_any_number_of_parts(parts, dtype, d):
+    """Room for so many partial rows, lists long enough for all of them: the rows of the whole lists.  bf16: within the rounding of the
+    outputs and of the probabilities, fp32: sixteen units of the last place of the values that a row averages."""
+    h, Lq, Lk = 2, 70, 20000
+    Q, K, V = _qkv(h, 1, Lq, Lk, d, dtype, seed=parts)
+    n_k = -(-Lk // 64)
+    cnt, cols, _, _ = _lists(h, -(-Lq // 64), n_k, 3, n_k)
+    call = lambda n: bd.basa_sparse_attn(Q, K, V, cnt, cols, 64, want_lse=True, ws=torch.full((n,), 0xFF, dtype=torch.uint8, device=DEV))
+    least = 256
+    if dtype == torch.bfloat16:
+        with pytest.raises(bd.BasaError, match="too small: need") as e:
+            call(256)
+        least = int(re.search(r"need (\d+) bytes", str(e.value)).group(1))
+    (whole, lse), (out, lse_p) = call(least), call(least + parts * h * Lq * (4 * d + 8))
+    bf = dtype == torch.bfloat16
+    assert (out.float() - whole.float()).abs().max() <= (2.0 ** -7 * whole.float().abs().max() if bf else 2.0 ** -20 * V.abs().mean())
+    torch.testing.assert_close(lse_p, lse, rtol=0, atol=4e-3 if bf else 1e-5)
+
+
 @pytest.mark.parametrize("dtype,d,windows", [(torch.bfloat16, 128, (12416, 40960, 16384, 0)), (torch.float32, 64, (12416, 0))])
 def test_norm_sort_of_many_words_with_runs_of_three_to_eighteen_tiles(dtype, d, windows):
     """Past 2^19 words: tiles of 4096, and the kernel that merges four of them in LDS (a ragged quad that is also the last
