@@ -38,6 +38,7 @@
 #include <cmath>
 #include <type_traits>
 #include "attn_lds.hpp"
+#include "attn_rows.hpp"
 #include "common.hpp"
 
 namespace basa {
@@ -1431,17 +1432,6 @@ size_t part_bytes_of(int BHq, int Lq, int Nk, int B, int d, bool causal) {
   return splits < 2 ? 0 : (size_t)splits * BHq * Lq * (d * 4 + 8);
 }
 
-// Does the 128-query shape read the rows of K and V itself?  Its loop is 9 % slower for it (addresses, twice the reads of V^T, and
-// the loads of the next tile are waited for in mid-tile); laying out the tiles takes a launch and four times kv_bytes.  Attention call,
-// tiles -> rows: 256 queries of 32768, keep 25 %, 32 heads on 8: 73.3 -> 56.7 us, 32 on 32: 108 -> 59.5; 32 of 100000, keep 10 %: 67 -> 44;
-// 8 heads, L = 4000, keep 10 %: 22.1 -> 16.8, L = 2472, keep 50 %: 35.2 -> 32.1 (d = 64: 25.4 -> 25.2), L = 8000: 145.5 -> 141.5; 2 heads, L = 600,
-// d = 64: 14.6 -> 11.5; kept at tiles: 8 heads on 2, L = 8000: 137.9 / 140.0; 32 on 8, L = 4000: 124.4 / 125.0.
-bool rows_pay(size_t kv_bytes, double attention_us) { return 4.0 + 4.0 * (double)kv_bytes / 5.6e6 > 0.09 * attention_us; }
-// The kernel forms a row's offset from the head's first as a product of two 24-bit numbers, in 32 bits.
-bool offsets_fit(const TensorView& x) {
-  return x.stride_l * 2 < 1 << 24 && x.L < 1 << 24 && (int64_t)x.L * x.stride_l * 2 < (int64_t)1 << 32;
-}
-
 // How much the lists of the query blocks that would share a 512-query workgroup have in common, on
 // every kProbeStride-th such group of gsz = 512 / B neighbouring blocks: probe[0] += blocks in the
 // union of the group's lists (what a 512-query workgroup walks), probe[1] += the same for each of
@@ -1652,7 +1642,9 @@ basa_status launch_attn_mfma(const AttnArgs& a, hipStream_t st) {
   }
   const bool can_probe = a.row_cols != nullptr && Nq >= 2 * gsz && (int64_t)BHq * Nq * B >= 2048 * 128;
   const bool solo_only = plan.solo && (small || !can_probe);
-  const bool from_rows = solo_only && rows_pay(sz_kv(BHkv, Nk, B, d), plan.us) && offsets_fit(a.k) && offsets_fit(a.v);
+  const bool d64_alone = d == 64 && plan.splits == 1 && (int64_t)BHq * ceil_div(Nq * B, kSoloQueries) <= kCUs;
+  const bool from_rows = solo_only && rows_pay(sz_kv(BHkv, Nk, B, d), plan.us, d64_alone) && offsets_fit(a.k.L, a.k.stride_l) &&
+                         offsets_fit(a.v.L, a.v.stride_l);
   if (!from_rows) {
     ProfScope prof(K_GATHER, st);
     const dim3 grid(Nk * B / kTileKeys, BHkv, 2);
