@@ -975,9 +975,12 @@ static bool cut_pays(int run, int64_t words, bool few) {
   return few ? run > 8 * kSmallTile && words >= 3 << 17 : run > 2 * kSmallTile;
 }
 // Parts of 2048 words, of 3072 where those would be more than three to a compute unit (64 rows of 32768: 148 / 143 us; 40: 103 / 97,
-// 32: 83.5 / 84.6, 48 of 16384: 66 / 69).
+// 32: 83.5 / 84.6, 48 of 16384: 66 / 69).  Runs of up to 4096 words (packed batches) in one part of 3072 or two of 2048: a second part of
+// what is left takes as long as the first.  Merge, by the line of the others / this: 32 heads on 8, 12 sequences of 2078 to
+// 2296: 33.8 / 18.0 us, 32 on 32, 8 of 2066 to 2273: 34.0 / 17.8, 12 of 3130 to 3394: 50.8 / 38.3, 8 of 3120 to 4048: 43.7 / 31.9.
 static CutArgs cut_args(const uint64_t* src, uint64_t* dst, int32_t* perm0, int32_t* perm1, int BH0, const SegGeom& g, int64_t words) {
-  const int samples = words <= (int64_t)3 * 256 * kPartSamples * kCutStride ? kPartSamples : kMaxPartSamples;
+  const bool large = g.W > 2 * kPartSamples * kCutStride ? words > (int64_t)3 * 256 * kPartSamples * kCutStride : g.W <= kMaxPartSamples * kCutStride;
+  const int samples = large ? kMaxPartSamples : kPartSamples;
   return CutArgs{src, dst, perm0, perm1, BH0, g, ceil_div(g.W, kCutWords), ceil_div(std::min(g.W, kCutWords), samples * kCutStride), samples};
 }
 
@@ -1147,10 +1150,14 @@ static basa_status sort_many(const SeqJob* seq, int n, hipStream_t st) {
     hipLaunchKernelGGL(many_kernel<SmallSortJob<kD>>, dim3(jobs.first[n]), dim3(kSortThreads), 0, st, jobs);
     BASA_HIP_CHECK_LAUNCH("norm_tile_sort");
   }
-  // (longer sequences than a group of the cut merge do not come here)
+  // Cut by samples, or ranked: from 3 x 2^17 words on, where ranking takes two passes or a pass of eight runs; of four runs, three or four
+  // of which are used, from 3 x 2^18 on; sequences longer than a group are ranked.  Merge, rank / cut: 16 heads on 16, 4 of 3928 to 4054
+  // tokens (0.51 million words): 11.8 / 15.7 us; 32 on 8, 8 of 2113 to 2289 (0.72): 16.4 / 17.2; 32 on 32, 6 of 2141 to 2188 (0.83): 18.2 / 17.4, 8 of
+  // 2066 to 2273 (1.11): 23.0 / 18.0; two used: 32 on 32, 6 of 1217 to 2035 (0.60): 14.5 / 11.9; eight: 32 on 8, 2 of 5341 to 5813 (0.45): 20.0 / 17.6.
   int64_t words = 0;
   for (int i = 0; i < n; ++i) words += seq[i].q.L > kSmallTile ? (int64_t)seq[i].q.L * (seq[i].q.heads + seq[i].k.heads) : 0;
-  if (words >= 3 << 17 && longest <= kCutWords) {
+  const bool four_used = longest > 2 * kSmallTile && longest <= 4 * kSmallTile;
+  if (words >= (four_used ? 3 << 18 : 3 << 17) && longest <= kCutWords) {
     Jobs<CutJob> jobs;
     for (int i = 0; i < n; ++i) {
       const int L = seq[i].q.L, rows = seq[i].q.heads + seq[i].k.heads;

@@ -504,6 +504,9 @@ def test_f32_three_part_products_keep_the_bits_of_small_numbers(where, d, block)
     (torch.bfloat16, 128, 128, 32, 32, [200, 9000, 500], {}),                                        # one that goes by itself
     (torch.bfloat16, 128, 128, 16, 16, [565, 7627, 1977, 3390, 4802, 6215], {}),                     # 512 queries to a workgroup
     (torch.bfloat16, 128, 64, 16, 4, [700, 7000, 4200, 6400, 5100, 300, 6900], {}),
+    (torch.bfloat16, 64, 128, 32, 32, [3072, 2049, 4096, 3070], {}),                                 # words: one ranking pass
+    (torch.bfloat16, 64, 128, 32, 32, [3072, 2049, 4096, 3073], {}),                                 # ... a cut merge, one part and two
+    (torch.bfloat16, 64, 128, 32, 32, [4096, 3073, 2048, 1025, 4096, 3072, 4000, 3500], {}),         # ... of a large call
     (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(causal=True)),                                  # all by themselves
     (torch.bfloat16, 128, 64, 2, 2, [400, 300], dict(sort=bd.SORT_K)),
     (torch.float32, 64, 64, 2, 2, [400, 0, 300], {})])
