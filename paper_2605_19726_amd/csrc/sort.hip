@@ -976,8 +976,8 @@ static bool cut_pays(int run, int64_t words, bool few) {
 }
 // Parts of 2048 words, of 3072 where those would be more than three to a compute unit (64 rows of 32768: 148 / 143 us; 40: 103 / 97,
 // 32: 83.5 / 84.6, 48 of 16384: 66 / 69).  Runs of up to 4096 words (packed batches) in one part of 3072 or two of 2048: a second part of
-// what is left takes as long as the first.  Merge, by the line of the others / this: 32 heads on 8, 12 sequences of 2078 to
-// 2296: 33.8 / 18.0 us, 32 on 32, 8 of 2066 to 2273: 34.0 / 17.8, 12 of 3130 to 3394: 50.8 / 38.3, 8 of 3120 to 4048: 43.7 / 31.9.
+// what is left takes as long as the first.  Merge, by the line of the others / this: 32 heads on 8, 11 sequences of 2065 to
+// 2246: 29.1 / 17.9 us, 32 on 32, 11 of 2060 to 2273: 35.6 / 20.6, 11 of 2738 to 3370: 40.7 / 36.1, 9 of 3921 to 4089: 43.0 / 35.0.
 static CutArgs cut_args(const uint64_t* src, uint64_t* dst, int32_t* perm0, int32_t* perm1, int BH0, const SegGeom& g, int64_t words) {
   const bool large = g.W > 2 * kPartSamples * kCutStride ? words > (int64_t)3 * 256 * kPartSamples * kCutStride : g.W <= kMaxPartSamples * kCutStride;
   const int samples = large ? kMaxPartSamples : kPartSamples;
