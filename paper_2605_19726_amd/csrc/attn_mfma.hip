@@ -680,7 +680,8 @@ __device__ __forceinline__ int64_t out_off(const MfmaArgs& a, int bhq, int row) 
 // stay unnormalised and attn_combine_kernel adds them up.
 // kGather (128-query shape): no tiles are laid out beforehand; the rows of K and V are fetched straight from the caller's
 // tensors (the source address of a lane of a direct-to-LDS load is free), and V^T fragments come from rows of V.
-template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit, bool kGather = false>
+// kPacked: among the jobs of a packed batch (that changes where the compiler puts the loop, see there).
+template <int kB, int D, int kWgQueries, int kQPW, bool kCausal, bool kFast, bool kSplit, bool kGather = false, bool kPacked = false>
 __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const RowSource* src = nullptr) {
   using G = Geo<D>;
   static_assert(!kCausal || (kQPW == 64 && kWgQueries == kWideQueries), "the causal path is built on the 512-query shape");
@@ -1076,11 +1077,13 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const 
     uint32_t lo = 0, issued = 1, slot = 0, issue_slot = 1, stage_no = 0;
     uint32_t e0 = entry_at(1), e1 = entry_at(2);       // of the next two tiles to request
     uint32_t win = listed_by(entry_at(0), 0), mine = win >> grp & 0x01010101u;
-    // (Where the loop starts in a line of 64 bytes; twelve instructions stand between this and it.  Blocks of 128 at 0, 20 and 56 bytes,
-    //  in turn on one card: dense, L = 16384: 3397 / 3424 / 3390 us, 128K, keep 50 %: 111.5 / 112.2 / 111.1 ms, video 75K: 24985 / 25140 /
-    //  24850 us.  Blocks of 64, 24 heads, L = 32100, at 20 and 56: 5789 / 5834 us, a tenth of a percent apart at other sizes.)
-    if constexpr (kB == 128) asm volatile(".p2align 6\n\t.rept 2\n\ts_nop 0\n\t.endr");
-    else asm volatile(".p2align 6\n\t.rept 9\n\ts_nop 0\n\t.endr");
+    // Where the loop starts in a line of 64 bytes: at 56, blocks of 64 at 20.  What the compiler puts between this and the loop (some 400
+    // bytes) decides how many instructions that takes; a test reads the offsets of the four forms from the code object, and fails where
+    // that has moved them.  At 56 / 0 / 20 / 36, in turn on one card, three times: blocks of 128: dense, L = 16384: 3586 / 3595 / 3623 / 3619
+    // us, 128K, keep 50 %: 117.8 / 118.0 / 118.7 / 118.7 ms, video 75K: 25845 / 25936 / 26113 / 26085 us, a packed batch of six: 721 / 722 / 726 /
+    // 726; of 64: 32 heads, L = 50000, keep 25 %: 10902 / 10891 / 10815 / 10832, L = 32768: 8205 / 8186 / 8126 / 8165, the batch: 737 / 737 / 733 / 733.
+    constexpr int kNops = (kB == 128 ? 2 : 9) - (kPacked ? 1 : 0);
+    asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(kNops));
 #pragma nounroll
     while (lo < last || issued <= last) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1287,13 +1290,13 @@ __global__ __launch_bounds__(kSoloQueries / 32 * 64, 2) void attn_rows_kernel(Mf
 template <int kB, int D>
 struct AttnJob {
   MfmaArgs a;
-  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kSoloQueries, 32, false, true, false>(a, block); }
+  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kSoloQueries, 32, false, true, false, false, true>(a, block); }
 };
 // The 512-query shape: the pass without running maxima, and the one with them for what that gave up on.
 template <int kB, int D, bool kFast>
 struct WideJob {
   MfmaArgs a;
-  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kWideQueries, 64, false, kFast, false>(a, block); }
+  __device__ __forceinline__ void run(int block) const { attn_mfma<kB, D, kWideQueries, 64, false, kFast, false, false, true>(a, block); }
 };
 
 size_t sz_kv(int BHkv, int Nk, int B, int d) { return align_up((size_t)BHkv * Nk * B * d * 2, 256); }
