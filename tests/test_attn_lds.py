@@ -38,7 +38,8 @@ def _static():
         if m:
             one = re.search(r"attn_mfma_kernelILi\d+ELi\d+ELi(\d+)ELi\d+ELb\dELb(\d)", m.group(1))
             many = re.search(r"(Attn|Wide)JobILi\d+ELi\d+E(?:Lb(\d))?", m.group(1))
-            kernel = (int(one.group(1)), one.group(2) == "1") if one else \
+            rows = re.search(r"attn_rows_kernelILi\d+ELi\d+ELb(\d)", m.group(1))
+            kernel = (int(one.group(1)), one.group(2) == "1") if one else (128, rows.group(1) == "1") if rows else \
                      (512 if many.group(1) == "Wide" else 128, many.group(2) != "0") if many else None
         m = re.match(r"\s*\.amdhsa_group_segment_fixed_size (\d+)", line)
         if m and kernel:

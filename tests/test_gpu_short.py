@@ -560,9 +560,20 @@ def test_sort_tiles_of_512_tokens(dtype, d, L, window):
         assert torch.equal(perm[0, :, a:b].long(), want)
 
 
+def _tiles_laid_out(call):
+    """What the call returns, and whether tiles of K and V were laid out for it."""
+    bd.basa_profile_enable(True)
+    try:
+        out = call()
+        torch.cuda.synchronize()
+        return out, bd.basa_profile_read().get("gather_kernels", (0.0, 0))[1] > 0
+    finally:
+        bd.basa_profile_enable(False)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("block", [64, 128])
-@pytest.mark.parametrize("Lq,Lk", [(3, 64), (100, 65), (1, 127), (257, 1000), (64, 2049), (300, 6017), (40, 20000)])
+@pytest.mark.parametrize("Lq,Lk", [(3, 64), (100, 65), (1, 127), (257, 600), (64, 2049), (300, 6017), (40, 20000)])
 @pytest.mark.parametrize("form", ["plain", "token-major", "no order", "broken order", "infinite last key"])
 def test_attention_on_rows_of_k_and_v(d, block, Lq, Lk, form):
     """The 128-query shape without tiles, which calls of few queries take, against the 512-query one, which always lays them out:
@@ -580,8 +591,10 @@ def test_attention_on_rows_of_k_and_v(d, block, Lq, Lk, form):
         pk[0, 1, 5::11] = -1
     elif form == "infinite last key":
         V[0, 0, int(pk[0, 0, Lk - 1])] = float("inf")
-    rows, lse = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True)
-    tiles, lse_t = bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, attn_shape=3)
+    (rows, lse), laid_out = _tiles_laid_out(lambda: bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True))
+    assert not laid_out
+    (tiles, lse_t), laid_out = _tiles_laid_out(lambda: bd.basa_sparse_attn(Q, K, V, cnt, cols, block, pq, pk, want_lse=True, attn_shape=3))
+    assert laid_out
     if n_k * (block // 64) <= 32:
         assert torch.equal(rows.view(torch.int16), tiles.view(torch.int16)) and torch.equal(lse, lse_t)
         return
@@ -590,6 +603,24 @@ def test_attention_on_rows_of_k_and_v(d, block, Lq, Lk, form):
     diff = (rows.float() - tiles.float())[fin].abs()
     assert diff.max() <= 2.0 ** -7 * tiles.float()[fin].abs().max()      # a last place of the largest, rounded twice
     torch.testing.assert_close(lse, lse_t, rtol=0, atol=4e-3)             # (sums of probabilities rounded to 8 bits)
+
+
+@pytest.mark.parametrize("stride,Lk,laid_out", [(2 ** 23 - 8, 256, False), (2 ** 23, 70, True), (2 ** 15, 2 ** 16, True), (2 ** 15 - 8, 2 ** 16, False)])
+def test_rows_of_k_and_v_at_the_limits_of_their_offsets(stride, Lk, laid_out):
+    """Tokens so far apart that the last one's offset takes all 32 bits, or more, where the call has to go by tiles."""
+    far = torch.empty(stride * Lk, dtype=torch.bfloat16, device=DEV)
+    Q, K0, V0 = _qkv(2, 2, 50, Lk, 64, torch.bfloat16, seed=Lk)
+    K, V = (far.as_strided((1, 2, Lk, 64), (0, 64, stride, 1), 128 * i) for i in range(2))
+    K.copy_(K0)
+    V.copy_(V0)
+    n_k = -(-Lk // 64)
+    cnt, cols, _, _ = _lists(2, 1, n_k, Lk, n_k)
+    pk = _perm(2, Lk, 9)
+    call = lambda k, v: bd.basa_sparse_attn(Q, k, v, cnt, cols, 64, None, pk)
+    want, near = _tiles_laid_out(lambda: call(K0, V0))
+    got, apart = _tiles_laid_out(lambda: call(K, V))
+    assert not near and apart == laid_out and torch.isfinite(want.float()).all()
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
 
 
 @pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 128), (torch.bfloat16, 64), (torch.bfloat16, 128)])
@@ -601,11 +632,14 @@ def test_sort_on_both_sides_of_eight_waves_to_a_tile(dtype, d, heads, L):
     assert torch.equal(perm[0].long(), torch.sort(keys[0], dim=-1, stable=True).indices)
 
 
-@pytest.mark.parametrize("heads,L", [(64, 8193), (16, 32768), (30, 32769), (41, 32767), (260, 2113), (6, 70000), (12, 33000)])
-@pytest.mark.parametrize("kind", ["spread", "few values", "ascending", "descending", "far outliers"])
+# (from (64, 32768) on parts of 48 samples, before them of 32)
+@pytest.mark.parametrize("heads,L", [(64, 8193), (16, 32768), (30, 32769), (41, 32767), (132, 5000), (6, 70000), (12, 33000), (64, 32768),
+                                     (50, 35456), (80, 22500)])
+@pytest.mark.parametrize("kind", ["spread", "few values", "ascending", "descending", "far outliers", "runs alike", "smallest last"])
 def test_merge_cut_by_samples(heads, L, kind):
-    """Parts whose bounds fall on few distinct keys, on runs that do not overlap at all, and far apart."""
-    x, _, _ = _qkv(heads, 1, L, 64, 64, torch.bfloat16, seed=L)
+    """Parts whose bounds fall on few distinct keys, on runs that do not overlap at all, and far apart; the largest parts (runs that hold
+    the same 1024 keys: 4206 words of 22500, in more slots than there are threads); a short last run below all others."""
+    x, _, _ = _qkv(heads, 1, L, 64, 64, torch.float32 if kind == "runs alike" else torch.bfloat16, seed=L)
     ramp = torch.linspace(0.01, 3.0, L, device=DEV)[None, None, :, None]
     if kind == "few values":
         x = x[:, :, :1].expand(-1, -1, L, -1).contiguous()
@@ -613,6 +647,10 @@ def test_merge_cut_by_samples(heads, L, kind):
         x[:, :, L // 2:L // 2 + 3000] = 0
     elif kind in ("ascending", "descending"):
         x = ((ramp if kind == "ascending" else ramp.flip(2)) * torch.ones_like(x)).to(x.dtype)
+    elif kind == "runs alike":
+        x = (1.0 + torch.arange(L, device=DEV) % 1024)[None, None, :, None] * torch.ones_like(x)
+    elif kind == "smallest last":
+        x[:, :, L // 1024 * 1024:] = 0
     elif kind == "far outliers":
         x[:, :, ::50] *= 1000
         x[:, :, 5::1000] = float("inf")

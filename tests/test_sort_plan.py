@@ -32,14 +32,14 @@ def plan(tmp_path_factory):
     return call
 
 
-# runs that leave most of a quad of 16384 words empty: one tile of 4096, or two and a merge pass, is the whole run
+# runs of 2049 to 8192 tokens: one tile of 4096, or two and a merge pass, is the whole run, but for 129 to 256 of the longer ones
 @pytest.mark.parametrize("rows,L,window,tile", [
     (1024, 1024, 0, 1024), (699, 1500, 0, 1024), (300, 2048, 0, 1024), (300, 2049, 0, 4096), (350, 3000, 0, 4096), (256, 4096, 0, 4096),
     (512, 4096, 0, 4096), (128, 5000, 0, 4096), (130, 5000, 0, 1024), (256, 5000, 0, 1024), (258, 5000, 0, 4096), (128, 8192, 0, 4096),
     (130, 8192, 0, 1024), (160, 8192, 0, 1024), (162, 8192, 0, 4096), (64, 8193, 0, 1024), (96, 8300, 0, 1024), (64, 32768, 0, 1024),
     (65, 32768, 0, 4096), (32, 32768, 1024, 1024), (32, 32768, 2048, 1024), (32, 32768, 4096, 4096), (32, 32768, 8192, 4096),
     (34, 32768, 8192, 1024), (32, 32768, 16384, 1024), (600, 1000, 4096, 1024)])
-def test_middling_calls_start_from_the_tiles_that_fill_a_quad(plan, rows, L, window, tile):
+def test_middling_calls_start_from_the_tiles_of_their_run_length(plan, rows, L, window, tile):
     assert plan(rows, L, window=window) == (False, tile)
     assert plan(rows, L, window=window, cached=False) == (False, tile)
     if rows % 2 == 0:
