@@ -12,7 +12,9 @@
 //        tile (d major); the 8 keys of a chunk are in MFMA operand-slot order (below);
 //        chunk c of d-row r sits at chunk position c ^ ((r >> 1) & 7)
 // The swizzles make every ds_read_b128 of 16 consecutive lanes hit 16 distinct 16-byte
-// bank groups.
+// bank groups.  Calls of few queries have no such copy (attn_rows.hpp): the 128-query shape fetches the rows of K and V
+// from the caller's tensors, through perm_k, into the same K image and an image of V by rows, from which a
+// transposing LDS read takes V^T.
 //
 // Main kernel: a workgroup owns 512, 256 or 128 consecutive sorted queries, i.e. 4, 2 or 1 query blocks of 128
 // (twice as many of 64); a wave owns 64 queries in the first shape, which large calls run on, and 32 in the
@@ -887,8 +889,6 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const 
   auto entry_of = [&](int t) -> uint32_t {
     return (uint32_t)__builtin_amdgcn_readfirstlane((int)seq[t / TPB]);
   };
-  // direct-to-LDS copy of tile `tile` into ring stage `stage`: 32 chunks of 1 KB, chunk
-  // j*kWaves+wave by this wave (16 K chunks, then 16 V chunks)
   // kGather: this lane's rows of a tile (those of its K chunks, and of its V chunks again), requested a tile ahead
   constexpr int kRowsPerLane = kLoadsPerWave / 2, kRowsPerLoad = 64 / G::kChunksPerRow;
   int rows[kGather ? kRowsPerLane : 1];
@@ -933,6 +933,8 @@ __device__ __forceinline__ void attn_mfma(const MfmaArgs& a, int logical, const 
       }
     }
   };
+  // direct-to-LDS copy of tile `tile` into ring stage `stage`: 32 chunks of 1 KB, chunk
+  // j*kWaves+wave by this wave (16 K chunks, then 16 V chunks)
   auto issue_tile = [&](int tile, int stage) {
     if constexpr (kGather) { issue_rows(tile, stage); return; }
     // (kept in registers the lane offset becomes three 64-bit addresses, and Q^T fragments go to scratch for them)
@@ -1382,14 +1384,17 @@ basa_status launch_wide(MfmaArgs m, int B, int d, int BHq, int32_t* redo, bool t
 // One step of a 64-key tile, measured at D = 128: 2.95 us for a workgroup of 512 queries (causal: 3.4), 1.95 us for
 // two of 128 that share a compute unit, 1.25 us for one alone; 0.63 of that at D = 64; 20 us of prologue and epilogue per
 // round of workgroups of 512 queries (25 us of lists of one block, where nothing overlaps them), 10 us of 128, 4 us for the
-// combining pass, and the partial rows at 2 TB/s written and read.
+// combining pass, and the partial rows at 2 TB/s written and read.  (From before the epilogue wrote whole rows, 5 us less for 512
+// queries, and before the combining pass requested its parts together.)
 // Attention call (tiling of K and V included), one workgroup of 512 queries per list -> this rule:
 // 256 queries against 32K keys, 32 heads on 8, keep 25 %: 351 -> 98 us (128 queries, 8 workgroups per list);
 // 8 heads, L = 2472, d = 64: 63 -> 28 us; 16 heads, L = 1977: 81 -> 36 us; dense, 8 heads, L = 12000, d = 128: 560 us,
 // unchanged (the 128-query shape would take 624).
-// Lists of up to 32 tiles stay whole: splitting them never paid (16 heads, L = 1977, 16 tiles: 39 us whole, 47 in two;
-// 8 heads, L = 2472, d = 64, 20 tiles: 31 and 36; not so the causal kernel, 8 heads, L = 2100: 94 and 59 in six), and a
-// whole list on the 128-query shape gives the same bits as on the 512-query one.
+// Lists of up to 32 tiles stay whole, and a whole list on the 128-query shape gives the same bits as on the 512-query one.  Splitting
+// them did not pay with the combining pass of the time (16 heads, L = 1977, 16 tiles: 39 us whole, 47 in two; 8 heads, L =
+// 2472, d = 64, 20 tiles: 31 and 36; not so the causal kernel, 8 heads, L = 2100: 94 and 59 in six).  With the present one it does
+// where few workgroups are there (whole / split, keep 50 %, d = 128: 1 head, L = 2472: 31.0 / 18.9, 4: 31.2 / 29.3, 8: level; 8 heads, 300
+// queries of 4000: 46.4 / 20.8; 1 head, L = 600, d = 64: 12.5 / 13.4): this line is older than that.
 constexpr int kCUs = 256, kMaxSplits = 32, kMinSplitTiles = 32;
 constexpr double kWideStepUs = 2.95, kCausalStepUs = 3.4, kSoloPairStepUs = 1.95, kSoloStepUs = 1.25;
 constexpr double kWideRoundUs = 20.0, kCausalRoundUs = 8.0, kSoloRoundUs = 10.0;

@@ -41,17 +41,17 @@ inline SortPlan plan_sort(int64_t rows0, int L0, int64_t rows1, int L1, int wind
     return {true, count <= (short_tokens ? 640 : run <= 4 * 512 ? 400 : 256) ? 512 : kSmallTile};
   }
   // Up to kMidWords the tiles stay at 1024: 4096-token tiles are one or two workgroups to a compute unit there, whose bitonic networks
-  // nothing hides.  The figures below are of merges of sixteen tiles in one workgroup's LDS; the merge cut by samples that took their
-  // place (sort.hip) is 3 to 25 % faster on the small side of each.  Whole sort, d = 128, large tiles -> small: 1.0
-  // million words in runs of 1024: 94 -> 52 us, 1500: 89 -> 75, 2048: 79 -> 60, 8300: 113 -> 99, 12000: 122 -> 97, 16384: 90 -> 88,
-  // 32768: 105 -> 102; 2.1 million words: 1500: 140 -> 129, 16384: 139 -> 137.  (From 0.53 to 2.1 million words, runs of 8300 to
-  // 65536, three types: 25 % faster to 6 % slower, the latter where the large tiles are just as many as the compute units.)
+  // nothing hides.  Whole sort, d = 128, large tiles / small: 1.0 million words in runs of 1024: 92 / 50 us, 1500: 87 / 72, 2048: 79 / 59,
+  // 8300: 114 / 81, 12000: 88 / 73, 16384: 90 / 75, 32768: 104 / 81; 2.0 million: 2048: 128 / 108, 8300: 139 / 136, 16384: 139 / 129, 32768:
+  // 154 / 137.  The line is older than the merge cut by samples (sort.hip), which the small tiles have here from runs of 2049 on: beyond it,
+  // kept at large tiles, 2.1 million words in runs of 32768: 187 / 148, 2.5: 191 / 174, 3.0: 197 / 202, 4.0: 249 / 260, 16384: 229 / 249, 2.4
+  // in runs of 8300: 199 / 165.
   if (words > kMidWords) return {false, kTile};
   if (run <= 2 * kSmallTile || run > 2 * kTile) return {false, kSmallTile};
-  // Shorter runs left much of the room for sixteen tiles empty.  One large tile is the whole run: 3000 tokens 86 us against 141 and 128 / 263 (1.0 and
-  // 2.1 million words), 4096: 70 / 96 and 118 / 181.  Or two and a merge pass: small tiles only where the large ones are more than
-  // one to a compute unit, the quads are not, and the small ones at most five (large / small, 128 runs, then 132: 5000: 74 / 82,
-  // 101 / 82, 8192: 81 / 93, 112 / 102; 256 runs of 5000, then 260: 113 / 107, 145 / 148; 200 of 7000, then 230: 115 / 115, 119 / 127).
+  // Runs of 2049 to 8192 tokens.  One large tile is the whole run: 3000 tokens, 1.0 and 2.0 million words: 86 / 78 and 127 / 128, 4096: 70 / 70 and
+  // 117 / 128.  Or two are, and a merge pass: small tiles for 129 to 256 runs, where the large ones are more than one to a compute unit and
+  // the small ones at most five (132 of 5000: 101 / 61, 256: 112 / 86, 132 of 8192: 112 / 82, 160: 114 / 86).  These lines too are older than the
+  // present merge; kept at large tiles: 128 of 5000: 74 / 59, 260: 144 / 101, 128 of 8192: 81 / 73, 162: 114 / 93, 200 of 7000: 115 / 104.
   if (run <= kTile) return {false, kTile};
   const int64_t runs = rows0 * ((L0 + run - 1) / run) + (rows1 > 0 ? rows1 * ((L1 + run - 1) / run) : 0);
   return {false, runs > 128 && runs <= 256 && words <= 5 * 256 * kSmallTile ? kSmallTile : kTile};
